@@ -23,6 +23,17 @@ static const uint32_t kResNW = 8;
 static uint32_t res_bn(int ks) { return ks <= 2 ? 256 : ks <= 8 ? 128 : 64; }
 static const uint32_t kStBM = ST_BM, kStBN = ST_BN, kStG = 8, kStNW = ST_NW;
 
+static int resident_occupancy(int dtype, int metric, int variant)
+{
+    const bool l2 = metric == MET_L2;
+    switch (dtype) {
+    case DT_F16: return l2 ? resident_occupancy_f16_l2(variant) : resident_occupancy_f16_ip(variant);
+    case DT_BF16:
+        return l2 ? resident_occupancy_bf16_l2(variant) : resident_occupancy_bf16_ip(variant);
+    default: return l2 ? resident_occupancy_i8_l2(variant) : resident_occupancy_i8_ip(variant);
+    }
+}
+
 bool plan_join(int dtype, int metric, uint32_t n_p, uint32_t n_q, uint32_t row_bytes, int num_cus,
                Plan *plan)
 {
@@ -46,9 +57,7 @@ bool plan_join(int dtype, int metric, uint32_t n_p, uint32_t n_q, uint32_t row_b
         // are powers of two so that, with workgroups dealt round-robin to the
         // 8 XCDs, each XCD's workgroups sweep the same Q range (shared in that
         // XCD's L2).
-        const int occ = dtype == DT_I8    ? resident_occupancy_i8(metric, variant)
-                        : dtype == DT_F16 ? resident_occupancy_f16(metric, variant)
-                                          : resident_occupancy_bf16(metric, variant);
+        const int occ = resident_occupancy(dtype, metric, variant);
         uint64_t qsplit = 1;
         while (n_pb * qsplit < 2ull * (uint64_t)occ * (uint64_t)num_cus && qsplit * 2 <= n_qt &&
                qsplit < 64)
@@ -85,10 +94,19 @@ bool plan_join(int dtype, int metric, uint32_t n_p, uint32_t n_q, uint32_t row_b
 hipError_t launch_join(const Plan &plan, int dtype, int metric, int mode, const JoinArgs &args,
                        hipStream_t stream)
 {
+    if (metric != MET_IP && metric != MET_L2)
+        return hipErrorInvalidValue;
+    const bool l2 = metric == MET_L2;
     switch (dtype) {
-    case DT_F16: return launch_join_f16(plan, metric, mode, args, stream);
-    case DT_BF16: return launch_join_bf16(plan, metric, mode, args, stream);
-    case DT_I8: return launch_join_i8(plan, metric, mode, args, stream);
+    case DT_F16:
+        return l2 ? launch_join_f16_l2(plan, mode, args, stream)
+                  : launch_join_f16_ip(plan, mode, args, stream);
+    case DT_BF16:
+        return l2 ? launch_join_bf16_l2(plan, mode, args, stream)
+                  : launch_join_bf16_ip(plan, mode, args, stream);
+    case DT_I8:
+        return l2 ? launch_join_i8_l2(plan, mode, args, stream)
+                  : launch_join_i8_ip(plan, mode, args, stream);
     }
     return hipErrorInvalidValue;
 }

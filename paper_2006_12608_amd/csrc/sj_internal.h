@@ -149,13 +149,17 @@ hipError_t launch_scan(const uint32_t *counts, uint64_t n, unsigned long long *o
                        unsigned long long *partials, unsigned long long *total,
                        hipStream_t stream);
 
-// Per-dtype launchers (one translation unit per element type).
-hipError_t launch_join_f16(const Plan &, int metric, int mode, const JoinArgs &, hipStream_t);
-hipError_t launch_join_bf16(const Plan &, int metric, int mode, const JoinArgs &, hipStream_t);
-hipError_t launch_join_i8(const Plan &, int metric, int mode, const JoinArgs &, hipStream_t);
-// Workgroups of a resident-kernel variant that one CU holds at once.
-int resident_occupancy_f16(int metric, int variant);
-int resident_occupancy_bf16(int metric, int variant);
-int resident_occupancy_i8(int metric, int variant);
+// Launchers and occupancy (workgroups of a resident-kernel variant that one CU
+// holds at once) per element type and metric, one translation unit each.
+#define SJ_JOIN_DECL(NAME)                                                            \
+    hipError_t launch_join_##NAME(const Plan &, int mode, const JoinArgs &, hipStream_t); \
+    int resident_occupancy_##NAME(int variant);
+SJ_JOIN_DECL(f16_ip)
+SJ_JOIN_DECL(f16_l2)
+SJ_JOIN_DECL(bf16_ip)
+SJ_JOIN_DECL(bf16_l2)
+SJ_JOIN_DECL(i8_ip)
+SJ_JOIN_DECL(i8_l2)
+#undef SJ_JOIN_DECL
 
 }  // namespace sjk

@@ -1206,111 +1206,67 @@ int resident_occupancy_v()
     return n < 1 ? 1 : n;
 }
 
-template <int DT>
-int resident_occupancy_dtype(int metric, int variant)
+template <int DT, int MET>
+int resident_occupancy_unit(int variant)
 {
-    static int cache[2][4];   // written with the same value by any racing caller
-    int &c = cache[metric == MET_L2][variant & 3];
+    static int cache[4];   // written with the same value by any racing caller
+    int &c = cache[variant & 3];
     if (c == 0) {
-        const bool l2 = metric == MET_L2;
         switch (variant) {
-        case 0: c = l2 ? resident_occupancy_v<DT, MET_L2, 0>() : resident_occupancy_v<DT, MET_IP, 0>(); break;
-        case 1: c = l2 ? resident_occupancy_v<DT, MET_L2, 1>() : resident_occupancy_v<DT, MET_IP, 1>(); break;
-        case 2: c = l2 ? resident_occupancy_v<DT, MET_L2, 2>() : resident_occupancy_v<DT, MET_IP, 2>(); break;
-        default: c = l2 ? resident_occupancy_v<DT, MET_L2, 3>() : resident_occupancy_v<DT, MET_IP, 3>(); break;
+        case 0: c = resident_occupancy_v<DT, MET, 0>(); break;
+        case 1: c = resident_occupancy_v<DT, MET, 1>(); break;
+        case 2: c = resident_occupancy_v<DT, MET, 2>(); break;
+        default: c = resident_occupancy_v<DT, MET, 3>(); break;
         }
     }
     return c;
 }
 
+// MODE_RECORD belongs to the resident kernel, MODE_MASK to the K-streamed one.
 template <int DT, int MET, int MODE>
 hipError_t launch_mode(const Plan &p, const JoinArgs &g, hipStream_t st)
 {
     if (p.family == FAM_STREAMED) {
-        hipLaunchKernelGGL((join_streamed<DT, MET, MODE>), dim3(p.grid), dim3(ST_NW * 64), 0, st,
-                           g);
-        return hipGetLastError();
-    }
-    switch (p.variant) {
-    case 0: return launch_resident_v<DT, MET, MODE, 0>(p, g, st);
-    case 1: return launch_resident_v<DT, MET, MODE, 1>(p, g, st);
-    case 2: return launch_resident_v<DT, MET, MODE, 2>(p, g, st);
-    case 3: return launch_resident_v<DT, MET, MODE, 3>(p, g, st);
-    default: return hipErrorInvalidValue;
-    }
-}
-
-template <int DT>
-hipError_t launch_dtype(const Plan &p, int metric, int mode, const JoinArgs &g, hipStream_t st)
-{
-    if (mode == MODE_RECORD) {
-        // resident kernel only
-        if (p.family != FAM_RESIDENT || (metric != MET_IP && metric != MET_L2))
-            return hipErrorInvalidValue;
-        const bool l2 = metric == MET_L2;
-        switch (p.variant) {
-        case 0: return l2 ? launch_resident_v<DT, MET_L2, MODE_RECORD, 0>(p, g, st)
-                          : launch_resident_v<DT, MET_IP, MODE_RECORD, 0>(p, g, st);
-        case 1: return l2 ? launch_resident_v<DT, MET_L2, MODE_RECORD, 1>(p, g, st)
-                          : launch_resident_v<DT, MET_IP, MODE_RECORD, 1>(p, g, st);
-        case 2: return l2 ? launch_resident_v<DT, MET_L2, MODE_RECORD, 2>(p, g, st)
-                          : launch_resident_v<DT, MET_IP, MODE_RECORD, 2>(p, g, st);
-        case 3: return l2 ? launch_resident_v<DT, MET_L2, MODE_RECORD, 3>(p, g, st)
-                          : launch_resident_v<DT, MET_IP, MODE_RECORD, 3>(p, g, st);
-        default: return hipErrorInvalidValue;
-        }
-    }
-    if (mode == MODE_TRI) {
-        if (metric != MET_IP && metric != MET_L2)
-            return hipErrorInvalidValue;
-        const bool l2 = metric == MET_L2;
-        if (p.family == FAM_STREAMED) {
-            if (l2)
-                hipLaunchKernelGGL((join_streamed<DT, MET_L2, MODE_TRI>), dim3(p.grid),
-                                   dim3(ST_NW * 64), 0, st, g);
-            else
-                hipLaunchKernelGGL((join_streamed<DT, MET_IP, MODE_TRI>), dim3(p.grid),
-                                   dim3(ST_NW * 64), 0, st, g);
+        if constexpr (MODE != MODE_RECORD) {
+            hipLaunchKernelGGL((join_streamed<DT, MET, MODE>), dim3(p.grid), dim3(ST_NW * 64), 0,
+                               st, g);
             return hipGetLastError();
         }
+    } else if constexpr (MODE != MODE_MASK) {
         switch (p.variant) {
-        case 0: return l2 ? launch_resident_v<DT, MET_L2, MODE_TRI, 0>(p, g, st)
-                          : launch_resident_v<DT, MET_IP, MODE_TRI, 0>(p, g, st);
-        case 1: return l2 ? launch_resident_v<DT, MET_L2, MODE_TRI, 1>(p, g, st)
-                          : launch_resident_v<DT, MET_IP, MODE_TRI, 1>(p, g, st);
-        case 2: return l2 ? launch_resident_v<DT, MET_L2, MODE_TRI, 2>(p, g, st)
-                          : launch_resident_v<DT, MET_IP, MODE_TRI, 2>(p, g, st);
-        case 3: return l2 ? launch_resident_v<DT, MET_L2, MODE_TRI, 3>(p, g, st)
-                          : launch_resident_v<DT, MET_IP, MODE_TRI, 3>(p, g, st);
-        default: return hipErrorInvalidValue;
-        }
-    }
-    if (mode == MODE_MASK) {
-        // K-streamed kernel only
-        if (p.family != FAM_STREAMED || (metric != MET_IP && metric != MET_L2))
-            return hipErrorInvalidValue;
-        if (metric == MET_IP)
-            hipLaunchKernelGGL((join_streamed<DT, MET_IP, MODE_MASK>), dim3(p.grid),
-                               dim3(ST_NW * 64), 0, st, g);
-        else
-            hipLaunchKernelGGL((join_streamed<DT, MET_L2, MODE_MASK>), dim3(p.grid),
-                               dim3(ST_NW * 64), 0, st, g);
-        return hipGetLastError();
-    }
-    if (metric == MET_IP) {
-        switch (mode) {
-        case MODE_SINGLE: return launch_mode<DT, MET_IP, MODE_SINGLE>(p, g, st);
-        case MODE_COUNT: return launch_mode<DT, MET_IP, MODE_COUNT>(p, g, st);
-        case MODE_EMIT: return launch_mode<DT, MET_IP, MODE_EMIT>(p, g, st);
-        }
-    } else if (metric == MET_L2) {
-        switch (mode) {
-        case MODE_SINGLE: return launch_mode<DT, MET_L2, MODE_SINGLE>(p, g, st);
-        case MODE_COUNT: return launch_mode<DT, MET_L2, MODE_COUNT>(p, g, st);
-        case MODE_EMIT: return launch_mode<DT, MET_L2, MODE_EMIT>(p, g, st);
+        case 0: return launch_resident_v<DT, MET, MODE, 0>(p, g, st);
+        case 1: return launch_resident_v<DT, MET, MODE, 1>(p, g, st);
+        case 2: return launch_resident_v<DT, MET, MODE, 2>(p, g, st);
+        case 3: return launch_resident_v<DT, MET, MODE, 3>(p, g, st);
         }
     }
     return hipErrorInvalidValue;
 }
+
+template <int DT, int MET>
+hipError_t launch_unit(const Plan &p, int mode, const JoinArgs &g, hipStream_t st)
+{
+    switch (mode) {
+    case MODE_SINGLE: return launch_mode<DT, MET, MODE_SINGLE>(p, g, st);
+    case MODE_COUNT: return launch_mode<DT, MET, MODE_COUNT>(p, g, st);
+    case MODE_EMIT: return launch_mode<DT, MET, MODE_EMIT>(p, g, st);
+    case MODE_MASK: return launch_mode<DT, MET, MODE_MASK>(p, g, st);
+    case MODE_RECORD: return launch_mode<DT, MET, MODE_RECORD>(p, g, st);
+    case MODE_TRI: return launch_mode<DT, MET, MODE_TRI>(p, g, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+// The launcher and the occupancy query of one (element type, metric): one
+// translation unit each, so that they compile in parallel.
+#define SJ_JOIN_UNIT(NAME, DT, MET)                                                               \
+    hipError_t launch_join_##NAME(const Plan &p, int mode, const JoinArgs &g, hipStream_t st)     \
+    {                                                                                             \
+        return launch_unit<DT, MET>(p, mode, g, st);                                              \
+    }                                                                                             \
+    int resident_occupancy_##NAME(int variant)                                                    \
+    {                                                                                             \
+        return resident_occupancy_unit<DT, MET>(variant);                                         \
+    }
 
 }  // namespace sjk
