@@ -173,15 +173,17 @@ int sj_normalize(sj_ctx *ctx, int dtype, const void *X, uint32_t n, uint32_t d, 
 /* Section 4's Hamming ip-distance: every (i, j) whose bit rows P_i and Q_j
  * differ in at most r of their d coordinates.  P (n_p rows) and Q (n_q rows)
  * are device bit rows of ceil(d / 8) bytes each, coordinate m in bit m % 8 of
- * byte m / 8 (bits past d are ignored).  As the paper does, the rows are
- * mapped to f(x) = (x, 1 - x) and g(y) = (1 - y, y) (int8 rows of 2 d values
- * in device memory the context owns, (n_p + n_q) * 2 d bytes rounded up to 16
- * per row), so that f(x).g(y) is the Hamming distance, and the pairs come from
- * the int8 matrix-core join of f(P) with -g(Q) at threshold -r
- * (f(x).(-g(y)) >= -r).  With P == Q and n_p == n_q the single pass computes
- * the upper triangle only and mirrors its pairs.  Limits: d <= 16384.
- * Outputs, flags (SJ_FLAG_TWO_PASS, SJ_FLAG_TIMING, SJ_FLAG_RECOMPUTE) and
- * errors as sj_join_ip; d = 0 gives every pair when r >= 0. */
+ * byte m / 8 (bits past d are ignored).  The rows are mapped to codes in
+ * {+1, -1}^d (4-bit floats in device memory the context owns, (n_p + n_q) d / 2
+ * bytes rounded up to 16 per row, n_q's part absent when P == Q and n_p ==
+ * n_q): f(x).f(y) = d - 2 Hamming(x, y), the affine form of the paper's
+ * f(x) = (x, 1 - x), g(y) = (1 - y, y) with one product per coordinate, and the
+ * pairs come from the 4-bit matrix-core join at threshold d - 2 floor(r)
+ * (exact: sums of at most 16384 values +-1 in fp32).  With P == Q and n_p == n_q
+ * the single pass computes the upper triangle only and mirrors its pairs.
+ * Limits: d <= 16384.  Outputs, flags (SJ_FLAG_TWO_PASS, SJ_FLAG_TIMING,
+ * SJ_FLAG_RECOMPUTE) and errors as sj_join_ip; d = 0 gives every pair when
+ * r >= 0. */
 int sj_join_hamming(sj_ctx *ctx, const void *P, uint32_t n_p, const void *Q, uint32_t n_q,
                     uint32_t d, double r, uint32_t *pairs, uint64_t cap, uint64_t *n_out,
                     unsigned flags);

@@ -20,8 +20,9 @@ BUILD_DIR = os.path.join(HERE, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 SOURCES = ["sj_join_f16_ip.hip", "sj_join_f16_l2.hip", "sj_join_bf16_ip.hip",
-           "sj_join_bf16_l2.hip", "sj_join_i8_ip.hip", "sj_join_i8_l2.hip", "sj_lsh.hip",
-           "sj_api.cpp", "sj_aux.hip", "sj_lsh_api.cpp", "sj_jl_api.cpp", "sj_jl.hip", "sj_front.hip", "sj_sort.hip"]
+           "sj_join_bf16_l2.hip", "sj_join_i8_ip.hip", "sj_join_i8_l2.hip",
+           "sj_join_fp4_ip.hip", "sj_lsh.hip", "sj_api.cpp", "sj_aux.hip", "sj_lsh_api.cpp", "sj_jl_api.cpp",
+           "sj_jl.hip", "sj_front.hip", "sj_sort.hip"]
 PEAK_SOURCE = os.path.join("peak", "mfma_peak.hip")
 PEAK_OUT = os.path.join(HERE, "libsj_peak.so")
 # Packed-fp32 instructions are kept out of the generated code (they are not

@@ -46,7 +46,8 @@ int hip_fail(hipError_t e, const char *what)
     return fail(SJ_E_HIP, "%s: %s", what, hipGetErrorString(e));
 }
 
-size_t esize(int dtype) { return dtype == SJ_I8 ? 1 : 2; }
+// (4-bit rows are counted in bytes)
+size_t esize(int dtype) { return dtype == SJ_I8 || dtype == sjk::DT_FP4 ? 1 : 2; }
 
 int check_device_ptr(const sj_ctx *c, const void *p, size_t bytes, const char *name)
 {
@@ -172,10 +173,8 @@ struct Request {
     uint32_t *pairs;
     uint64_t cap;
     bool two_pass, count_only, timing, recompute;
-    // the score matrix is symmetric although P and Q are different buffers
-    // (the Hamming front end's f(x) and -g(x)): a single pass computes the
-    // upper triangle only and mirrors its pairs, as for P == Q
-    bool symmetric = false;
+    // rows are the Hamming front end's 4-bit codes (d counts their bytes)
+    bool fp4 = false;
 };
 
 // Largest match-bit buffer the two-pass mode keeps (bytes); beyond it, or
@@ -228,7 +227,7 @@ int run(sj_ctx *c, const Request &rq, uint64_t *n_out, const Fixed *fx = nullptr
     if (!n_out)
         return fail(SJ_E_INVAL, "result pointer is NULL");
     *n_out = 0;
-    if (rq.dtype != SJ_F16 && rq.dtype != SJ_BF16 && rq.dtype != SJ_I8)
+    if (rq.dtype != SJ_F16 && rq.dtype != SJ_BF16 && rq.dtype != SJ_I8 && !rq.fp4)
         return fail(SJ_E_INVAL, "unknown dtype %d", rq.dtype);
     if (rq.metric != SJ_IP && rq.metric != SJ_L2)
         return fail(SJ_E_INVAL, "unknown metric %d", rq.metric);
@@ -413,8 +412,7 @@ int run(sj_ctx *c, const Request &rq, uint64_t *n_out, const Fixed *fx = nullptr
     bool emit_from_bits = false;
     if (!blocks) {
         // a self-join computes the upper triangle only and mirrors its pairs
-        const bool tri = (self || rq.symmetric) && rq.n_p == rq.n_q;
-        const int mode = tri ? sjk::MODE_TRI : sjk::MODE_SINGLE;
+        const int mode = self ? sjk::MODE_TRI : sjk::MODE_SINGLE;
         SJ_HIP(sjk::launch_join(plan, rq.dtype, rq.metric, mode, g, s));
         if (rq.timing)
             SJ_HIP(hipEventRecord(c->ev[2], s));
@@ -644,19 +642,24 @@ int sj_join_hamming(sj_ctx *ctx, const void *P, uint32_t n_p, const void *Q, uin
                (flags & SJ_FLAG_RECOMPUTE) != 0};
     if (n_p == 0 || n_q == 0 || d == 0)
         return run(ctx, rq, n_out);   // no pairs, or every distance 0 (d = 0)
-    // f(x) and -g(y) as int8 rows of 2 d values, padded with zeros to 16 bytes
-    const uint32_t rb = (uint32_t)((2 * (size_t)d + 15) & ~(size_t)15);
-    const size_t bp = align_up((size_t)n_p * rb), bq = align_up((size_t)n_q * rb);
+    // +-1 codes, two per byte, rows padded with zeros to 16 bytes:
+    // Hamming(x, y) <= r <=> <f(x), f(y)> >= d - 2 floor(r)
+    const bool self = P == Q && n_p == n_q;
+    const uint32_t rb = (uint32_t)((((size_t)d + 1) / 2 + 15) & ~(size_t)15);
+    const size_t bp = align_up((size_t)n_p * rb), bq = self ? 0 : align_up((size_t)n_q * rb);
     if ((st = grow_front(ctx, bp + bq)) != SJ_OK)
         return st;
     uint8_t *f = (uint8_t *)ctx->front;
     SJ_HIP(hipSetDevice(ctx->device));
-    SJ_HIP(sjk::launch_unpack_hamming((const uint8_t *)P, n_p, d, rb, 0, f, ctx->stream));
-    SJ_HIP(sjk::launch_unpack_hamming((const uint8_t *)Q, n_q, d, rb, 1, f + bp, ctx->stream));
+    SJ_HIP(sjk::launch_unpack_hamming((const uint8_t *)P, n_p, d, rb, f, ctx->stream));
+    if (!self)
+        SJ_HIP(sjk::launch_unpack_hamming((const uint8_t *)Q, n_q, d, rb, f + bp, ctx->stream));
     rq.P = f;
-    rq.Q = f + bp;
+    rq.Q = self ? f : f + bp;
+    rq.dtype = sjk::DT_FP4;
+    rq.fp4 = true;
     rq.d = rb;
-    rq.symmetric = P == Q && n_p == n_q;
+    rq.thr = (double)d - 2.0 * std::floor(r);
     return run(ctx, rq, n_out);
 }
 

@@ -13,7 +13,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // ------------------------------------------------------------------ planning
 // Resident-P limits: 32-byte k-steps of the largest variant (16 for 2-byte
-// elements, 8 for int8, i.e. d <= 256 either way); workgroup of 8 waves over
+// elements, 8 for int8, i.e. d <= 256 either way; 16 for 4-bit ones, d <= 1024); workgroup of 8 waves over
 // 32 * WMB rows each (WMB = 4 for int8 rows of at most 64 bytes, else 2); Q
 // tiles of 256 rows for rows of at most 64 bytes, 128 up to 256 bytes and 64
 // for the longest rows.  Must agree with sj_join_kernels.h.
@@ -30,6 +30,7 @@ static int resident_occupancy(int dtype, int metric, int variant)
     case DT_F16: return l2 ? resident_occupancy_f16_l2(variant) : resident_occupancy_f16_ip(variant);
     case DT_BF16:
         return l2 ? resident_occupancy_bf16_l2(variant) : resident_occupancy_bf16_ip(variant);
+    case DT_FP4: return resident_occupancy_fp4_ip(variant);
     default: return l2 ? resident_occupancy_i8_l2(variant) : resident_occupancy_i8_ip(variant);
     }
 }
@@ -107,6 +108,8 @@ hipError_t launch_join(const Plan &plan, int dtype, int metric, int mode, const 
     case DT_I8:
         return l2 ? launch_join_i8_l2(plan, mode, args, stream)
                   : launch_join_i8_ip(plan, mode, args, stream);
+    case DT_FP4:
+        return l2 ? hipErrorInvalidValue : launch_join_fp4_ip(plan, mode, args, stream);
     }
     return hipErrorInvalidValue;
 }

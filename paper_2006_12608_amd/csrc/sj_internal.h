@@ -7,7 +7,9 @@
 
 namespace sjk {
 
-enum { DT_F16 = 1, DT_BF16 = 2, DT_I8 = 3 };
+// DT_FP4: rows of 4-bit floats (two per byte), made by the Hamming front end
+// only; the kernels count its rows in bytes like every other type's.
+enum { DT_F16 = 1, DT_BF16 = 2, DT_I8 = 3, DT_FP4 = 4 };
 enum { MET_IP = 0, MET_L2 = 1 };
 
 // What the fused epilogue does with the matches it finds.
@@ -132,12 +134,12 @@ hipError_t launch_repack(const uint8_t *src, uint32_t n, uint32_t src_bytes, uin
 hipError_t launch_normalize(int dtype, const void *X, uint32_t n, uint32_t d, double *norm,
                             void *Y, hipStream_t stream);
 
-// Section 4's Hamming front end: bit rows (ceil(d / 8) bytes, coordinate m in
-// bit m % 8 of byte m / 8) to int8 rows of out_bytes bytes (a multiple of 16,
-// at least 2 d): side 0 writes f(x) = (x, 1 - x), side 1 writes -g(y) =
-// (y - 1, -y), zero past 2 d; <f(x), -g(y)> = -Hamming(x, y).
+// Hamming front end: bit rows (ceil(d / 8) bytes, coordinate m in bit m % 8 of
+// byte m / 8) to rows of 4-bit floats of out_bytes bytes (a multiple of 16, at
+// least d / 2): coordinate m is +1 or -1 (bit 0 or 1) in nibble m, nibbles past
+// d are 0, so that the inner product of two rows is d - 2 Hamming(x, y).
 hipError_t launch_unpack_hamming(const uint8_t *bits, uint32_t n, uint32_t d, uint32_t out_bytes,
-                                 int side, uint8_t *out, hipStream_t stream);
+                                 uint8_t *out, hipStream_t stream);
 
 // Zeroes n 64-bit words on `stream` (one small kernel, no memset node).
 hipError_t launch_zero_u64(unsigned long long *p, uint32_t n, hipStream_t stream);
@@ -160,6 +162,7 @@ SJ_JOIN_DECL(bf16_ip)
 SJ_JOIN_DECL(bf16_l2)
 SJ_JOIN_DECL(i8_ip)
 SJ_JOIN_DECL(i8_l2)
+SJ_JOIN_DECL(fp4_ip)
 #undef SJ_JOIN_DECL
 
 }  // namespace sjk

@@ -7,7 +7,7 @@ sides take in the same precision); the cosine join (SJ_FLAG_COSINE) against
 the oracle's inner-product join of the oracle's normalised rows, identical
 outside the boundary band 1e-3 |s| (the normalised rows are real-valued).
 
-Hamming (f(x) = (x, 1 - x), g(y) = (1 - y, y) on {0, 1}^d): sj_join_hamming's
+Hamming (codes in {+1, -1}^d, f(x).f(y) = d - 2 Hamming): sj_join_hamming's
 pairs against the oracle's Hamming join on the same bit rows, exactly (integer
 scores), across the resident and K-streamed kernels, both modes, ragged
 shapes, garbage in the padding bits, the self-join, ties at r and the edges.
@@ -163,6 +163,31 @@ def test_hamming_join(d, n_p, n_q, two_pass):
                                          cap=None if two_pass else n_p * n_q))
         want = oracle.hamming_join(P, Q, d, r)
         assert np.array_equal(keys(g), keys(want)), (d, r, g.shape[0], len(want))
+
+
+@pytest.mark.parametrize("d", [31, 33, 127, 128, 129, 255, 513, 1023, 1024, 1025, 2100])
+def test_hamming_code_lengths(d):
+    """Row lengths around the 4-bit kernels' limits (16-byte rows: 32 bits; the
+    resident variants end at 128, 256, 512 and 1024 bits, the K-streamed kernel
+    takes the rest), every mode, thresholds at and beyond the possible
+    distances; all sums are whole numbers below 2^24, so the sets are equal."""
+    import paper_2006_12608_amd as sj
+    rng = np.random.default_rng(7300 + d)
+    P, _ = _bits(rng, 283, d)
+    Q, _ = _bits(rng, 531, d)
+    Q[7:17] = P[0:10]
+    Pd, Qd = _bits_device(P), _bits_device(Q)
+    for r in (-0.5, 0.0, d / 2 - 1, d / 2 + 0.25, float(d), float("inf")):
+        say("hamming code length", d, r)
+        want = keys(oracle.hamming_join(P, Q, d, min(r, 1e9)))
+        for kw in (dict(two_pass=True), dict(two_pass=False, cap=283 * 531)):
+            assert np.array_equal(keys(sorted_pairs(sj.join_hamming(Pd, Qd, d, r, **kw))), want)
+        st, n = sj.sj_join_hamming(sj.context(), Pd.data_ptr(), 283, Qd.data_ptr(), 531, d, r,
+                                   None, 0, sj.SJ_FLAG_TWO_PASS | sj.SJ_FLAG_RECOMPUTE)
+        assert n == len(want) and st == (sj.SJ_E_OVERFLOW if n else sj.SJ_OK)
+    say("hamming code length, self-join", d)
+    g = sorted_pairs(sj.join_hamming(Pd, Pd, d, d / 2, two_pass=False, cap=283 * 283))
+    assert np.array_equal(keys(g), keys(oracle.hamming_join(P, P.copy(), d, d / 2)))
 
 
 def test_hamming_self_join_and_larger():
