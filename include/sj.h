@@ -166,8 +166,7 @@ int sj_count(sj_ctx *ctx, int metric, int dtype, const void *P, uint32_t n_p, co
  * of the squares of the exactly decoded elements, summed in double in
  * ascending k; each x_k / ||x|| is one double division, rounded to the
  * nearest output value, ties to even.  A row whose norm is 0 is written as
- * zeros.  Device scratch: n doubles.  Errors as sj_join_ip (16-bit rows must
- * be 2-byte aligned). */
+ * zeros.  Errors as sj_join_ip (16-bit rows must be 2-byte aligned). */
 int sj_normalize(sj_ctx *ctx, int dtype, const void *X, uint32_t n, uint32_t d, void *Y);
 
 /* Section 4's Hamming ip-distance: every (i, j) whose bit rows P_i and Q_j

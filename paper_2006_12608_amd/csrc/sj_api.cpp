@@ -506,15 +506,13 @@ int cosine_join(sj_ctx *c, Request rq, uint64_t *n_out)
     const bool self = rq.P == rq.Q && rq.n_p == rq.n_q;
     const size_t bp = align_up((size_t)rq.n_p * rq.d * 2);
     const size_t bq = self ? 0 : align_up((size_t)rq.n_q * rq.d * 2);
-    const size_t bn = (size_t)(rq.n_p > rq.n_q ? rq.n_p : rq.n_q) * sizeof(double);
-    if ((st = grow_front(c, bp + bq + bn)) != SJ_OK)
+    if ((st = grow_front(c, bp + bq)) != SJ_OK)
         return st;
     uint8_t *f = (uint8_t *)c->front;
-    double *norm = (double *)(f + bp + bq);
     SJ_HIP(hipSetDevice(c->device));
-    SJ_HIP(sjk::launch_normalize(rq.dtype, rq.P, rq.n_p, rq.d, norm, f, c->stream));
+    SJ_HIP(sjk::launch_normalize(rq.dtype, rq.P, rq.n_p, rq.d, f, c->stream));
     if (!self)
-        SJ_HIP(sjk::launch_normalize(rq.dtype, rq.Q, rq.n_q, rq.d, norm, f + bp, c->stream));
+        SJ_HIP(sjk::launch_normalize(rq.dtype, rq.Q, rq.n_q, rq.d, f + bp, c->stream));
     rq.P = f;
     rq.Q = self ? f : f + bp;
     rq.dtype = rq.dtype == SJ_BF16 ? SJ_BF16 : SJ_F16;
@@ -607,10 +605,8 @@ int sj_normalize(sj_ctx *ctx, int dtype, const void *X, uint32_t n, uint32_t d, 
     ctx->stats = sj_stats{};
     if (n == 0 || d == 0)
         return SJ_OK;
-    if ((st = grow_scratch(ctx, (size_t)n * sizeof(double))) != SJ_OK)
-        return st;
     SJ_HIP(hipSetDevice(ctx->device));
-    SJ_HIP(sjk::launch_normalize(dtype, X, n, d, (double *)ctx->scratch, Y, ctx->stream));
+    SJ_HIP(sjk::launch_normalize(dtype, X, n, d, Y, ctx->stream));
     SJ_HIP(hipStreamSynchronize(ctx->stream));
     return SJ_OK;
 }

@@ -130,9 +130,9 @@ hipError_t launch_repack(const uint8_t *src, uint32_t n, uint32_t src_bytes, uin
 // Section 4's cosine front end: Y (n x d, 16-bit) = every row of X (n x d of
 // dtype, row-major) divided by its Euclidean norm (double, ascending k) and
 // rounded to the nearest binary16 (fp16 and int8 inputs) or bfloat16 (bf16
-// inputs), ties to even; zero rows give zeros.  `norm` is n doubles of scratch.
-hipError_t launch_normalize(int dtype, const void *X, uint32_t n, uint32_t d, double *norm,
-                            void *Y, hipStream_t stream);
+// inputs), ties to even; zero rows give zeros.
+hipError_t launch_normalize(int dtype, const void *X, uint32_t n, uint32_t d, void *Y,
+                            hipStream_t stream);
 
 // Hamming front end: bit rows (ceil(d / 8) bytes, coordinate m in bit m % 8 of
 // byte m / 8) to rows of 4-bit floats of out_bytes bytes (a multiple of 16, at

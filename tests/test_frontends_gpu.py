@@ -68,6 +68,36 @@ def test_normalize_bit_exact(dtype, d, n, kind):
     assert bad.size == 0, f"{bad.shape[0]} values differ, first {bad[:3].tolist()}"
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "i8"])
+@pytest.mark.parametrize("d", [3, 8, 15, 16, 32, 33, 40, 64, 72, 1000])
+def test_normalize_chunks_and_alignment(dtype, d):
+    """Row lengths around the 16-byte chunks and the four lanes that share a
+    row, row counts around the 64 rows of a workgroup, rows at odd addresses,
+    and values spread over many binades in one row (subnormal results, results
+    whose fp32 rounding is a midpoint): bit for bit, both sides round the same
+    double quotient."""
+    import torch
+    import paper_2006_12608_amd as sj
+    rng = np.random.default_rng(5200 + d)
+    for n, off in ((1, 0), (64, 0), (65, 1), (700, 0)):
+        X = _rows(rng, dtype, n, d, "wide")
+        if dtype != "i8":
+            v = rng.standard_normal((n, d)) * np.exp2(rng.integers(-14, 10, size=(n, d)))
+            X[n // 2:] = workloads.encode(v, dtype)[n // 2:]
+        say("normalize chunks", dtype, n, d, off)
+        flat = to_device(X.reshape(1, -1), dtype).view(-1)
+        buf = torch.zeros(n * d + 8, dtype=flat.dtype, device="cuda")
+        buf[off:off + n * d] = flat
+        Y = torch.full((n * d + 8,), 7, dtype=torch.int16, device="cuda")
+        st = sj.sj_normalize(sj.context(), {"f16": 1, "bf16": 2, "i8": 3}[dtype],
+                             buf[off:].data_ptr(), n, d, Y[off:].data_ptr())
+        assert st == sj.SJ_OK
+        want = oracle.normalize(dtype, X).view(np.uint16).reshape(-1)
+        got = Y[off:off + n * d].cpu().numpy().view(np.uint16)
+        assert np.array_equal(got, want), np.argwhere(got != want)[:3].tolist()
+        assert torch.all(Y[:off] == 7) and torch.all(Y[off + n * d:] == 7)
+
+
 def _cos_case(dtype, n_p, n_q, d, seed, q=0.995):
     rng = np.random.default_rng(seed)
     P = _rows(rng, dtype, n_p, d, "unit")
