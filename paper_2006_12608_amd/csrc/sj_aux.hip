@@ -54,14 +54,15 @@ bool plan_join(int dtype, int metric, uint32_t n_p, uint32_t n_q, uint32_t row_b
         const uint64_t bn = res_bn(ks);
         const uint64_t n_qt = (n_q + bn - 1) / bn;
         // Enough workgroups to fill every CU twice (with exactly one round,
-        // one late workgroup start stretches the whole kernel); splits of Q
-        // are powers of two so that, with workgroups dealt round-robin to the
-        // 8 XCDs, each XCD's workgroups sweep the same Q range (shared in that
-        // XCD's L2).
+        // one late workgroup start stretches the whole kernel), down to one Q
+        // tile each: a few hundred query rows against 262144 rows would
+        // otherwise leave most CUs without a workgroup (256 x 262144 x 256 fp16:
+        // 139 us with at most 64 splits, 43 us with 512).  Splits of Q are powers
+        // of two so that, with workgroups dealt round-robin to the 8 XCDs, each
+        // XCD's workgroups sweep the same Q range (shared in that XCD's L2).
         const int occ = resident_occupancy(dtype, metric, variant);
         uint64_t qsplit = 1;
-        while (n_pb * qsplit < 2ull * (uint64_t)occ * (uint64_t)num_cus && qsplit * 2 <= n_qt &&
-               qsplit < 64)
+        while (n_pb * qsplit < 2ull * (uint64_t)occ * (uint64_t)num_cus && qsplit * 2 <= n_qt)
             qsplit *= 2;
         plan->family = FAM_RESIDENT;
         plan->variant = variant;

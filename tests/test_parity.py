@@ -245,6 +245,30 @@ def test_streamed_dense_output(dtype, d):
         run_case(w, two_pass=two_pass)
 
 
+@pytest.mark.parametrize("dtype,d,metric", [("f16", 256, "ip"), ("bf16", 100, "l2"),
+                                             ("i8", 64, "l2"), ("i8", 16, "ip")])
+@pytest.mark.parametrize("n_p", [1, 64, 65, 200, 513, 1100])
+def test_few_rows_against_many(dtype, d, metric, n_p):
+    """Few rows of P against many of Q: one Q tile per workgroup and waves
+    without rows (which only load tiles), all modes, integer inputs: the
+    oracle's set, and count-then-emit's order whichever second pass runs."""
+    import paper_2006_12608_amd as sj
+    w = workloads.random_case(60 + n_p + d, n_p, 9001, d, dtype, lo=-3, hi=3, metric=metric)
+    x, y = values(dtype, w.P).astype(np.int64), values(dtype, w.Q).astype(np.int64)
+    s = x @ y.T
+    if metric == "l2":
+        s = (x * x).sum(1)[:, None] + (y * y).sum(1)[None, :] - 2 * s
+    w.threshold = float(np.quantile(s, 0.99 if metric == "ip" else 0.01, method="nearest"))
+    _, g, _ = run_case(w)
+    _, h, _ = run_case(w, two_pass=True)
+    assert np.array_equal(g, h)
+    Pd, Qd = to_device(w.P, dtype), to_device(w.Q, dtype)
+    f = sj.join_ip if metric == "ip" else sj.join_l2
+    a, b = f(Pd, Qd, w.threshold), f(Pd, Qd, w.threshold, recompute=True)
+    assert np.array_equal(a.cpu().numpy(), b.cpu().numpy())
+    assert sj.count(Pd, Qd, w.threshold, metric) == g.shape[0]
+
+
 @pytest.mark.parametrize("dtype,d,metric", [("bf16", 300, "ip"), ("f16", 520, "l2"),
                                              ("i8", 700, "ip"), ("i8", 530, "l2"),
                                              ("bf16", 128, "ip"), ("f16", 256, "l2"),
