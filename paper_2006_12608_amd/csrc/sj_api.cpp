@@ -254,9 +254,14 @@ int run(sj_ctx *c, const Request &rq, uint64_t *n_out, const Fixed *fx = nullptr
     if (rq.n_p == 0 || rq.n_q == 0)
         return SJ_OK;
 
+    // a self-join's single pass computes the upper triangle only and mirrors its
+    // pairs
+    const bool self = rq.P == rq.Q && rq.n_p == rq.n_q;
+    const bool blocks = rq.two_pass || rq.count_only;
+    const bool tri = self && !blocks;
     sjk::Plan plan;
     if (!sjk::plan_join(rq.dtype, rq.metric, rq.n_p, rq.n_q,
-                        (uint32_t)(row_bytes == 0 ? 16 : (row_bytes + 15) & ~(size_t)15),
+                        (uint32_t)(row_bytes == 0 ? 16 : (row_bytes + 15) & ~(size_t)15), tri,
                         c->num_cus, &plan))
         return fail(SJ_E_UNSUPPORTED, "shape %u x %u x %u is too large for one launch", rq.n_p,
                     rq.n_q, rq.d);
@@ -267,9 +272,7 @@ int run(sj_ctx *c, const Request &rq, uint64_t *n_out, const Fixed *fx = nullptr
     const bool aligned = row_bytes > 0 && row_bytes % 16 == 0 && ((uintptr_t)rq.P % 16) == 0 &&
                          ((uintptr_t)rq.Q % 16) == 0;
     const size_t krow = row_bytes == 0 ? 16 : (row_bytes + 15) & ~(size_t)15;
-    const bool self = rq.P == rq.Q && rq.n_p == rq.n_q;
     const bool l2 = rq.metric == SJ_L2;
-    const bool blocks = rq.two_pass || rq.count_only;
     // Count-then-emit with the K-streamed kernel keeps the first pass's match
     // bits (one per result) when they fit, so the second pass does not repeat
     // the product.
@@ -376,7 +379,6 @@ int run(sj_ctx *c, const Request &rq, uint64_t *n_out, const Fixed *fx = nullptr
                                               align_up((size_t)rec_cap * plan.grid *
                                                        sizeof(sjk::MatchRecord)))
                                : nullptr;
-    g.rec_max = d_small + 2;
     g.qsplit = plan.qsplit;
 
     hipStream_t s = c->stream;
@@ -384,41 +386,32 @@ int run(sj_ctx *c, const Request &rq, uint64_t *n_out, const Fixed *fx = nullptr
     if (fx) {
         // the fixed region keeps the previous call's contents: clear the
         // counters (the count pass writes every block count itself)
-        SJ_HIP(sjk::launch_zero_u64(d_small, 4, s));
-    } else {
-        if (!blocks)
-            SJ_HIP(hipMemsetAsync(c->d_small, 0, sizeof(unsigned long long), s));
-        if (use_records)
-            SJ_HIP(hipMemsetAsync(c->d_small + 2, 0, sizeof(unsigned long long), s));
+        SJ_HIP(sjk::launch_zero_u64(d_small, 2, s));
+    } else if (!blocks) {
+        if (!c->counter_clear)
+            SJ_HIP(sjk::launch_zero_u64(d_small, 1, s));
+        c->counter_clear = false;   // until it is published
     }
     if (rq.timing)
         SJ_HIP(hipEventRecord(c->ev[0], s));
-    if (!aligned) {
-        SJ_HIP(sjk::launch_repack((const uint8_t *)rq.P, rq.n_p, (uint32_t)row_bytes,
-                                  scr + off_rp, (uint32_t)krow, s));
-        if (!self)
-            SJ_HIP(sjk::launch_repack((const uint8_t *)rq.Q, rq.n_q, (uint32_t)row_bytes,
-                                      scr + off_rq, (uint32_t)krow, s));
-    }
-    if (l2) {
-        SJ_HIP(sjk::launch_norms(rq.dtype, g.P, rq.n_p, g.row_bytes, scr + off_np, s));
-        if (!self)
-            SJ_HIP(sjk::launch_norms(rq.dtype, g.Q, rq.n_q, g.row_bytes, scr + off_nq, s));
-    }
+    SJ_HIP(sjk::launch_prep(rq.dtype, rq.P, rq.n_p, rq.Q, self ? 0u : rq.n_q,
+                            aligned ? (uint32_t)krow : (uint32_t)row_bytes, (uint32_t)krow,
+                            aligned ? nullptr : scr + off_rp, aligned ? nullptr : scr + off_rq,
+                            l2 ? scr + off_np : nullptr, l2 ? scr + off_nq : nullptr, s));
     if (rq.timing)
         SJ_HIP(hipEventRecord(c->ev[1], s));
 
     uint64_t total = 0;
     bool emit_from_bits = false;
     if (!blocks) {
-        // a self-join computes the upper triangle only and mirrors its pairs
-        const int mode = self ? sjk::MODE_TRI : sjk::MODE_SINGLE;
-        SJ_HIP(sjk::launch_join(plan, rq.dtype, rq.metric, mode, g, s));
+        SJ_HIP(sjk::launch_join(plan, rq.dtype, rq.metric,
+                                tri ? sjk::MODE_TRI : sjk::MODE_SINGLE, g, s));
         if (rq.timing)
             SJ_HIP(hipEventRecord(c->ev[2], s));
-        SJ_HIP(hipMemcpyAsync(c->h_small, d_small, sizeof(unsigned long long),
-                              hipMemcpyDeviceToHost, s));
+        SJ_HIP(sjk::launch_publish(d_small, c->h_small, s));
         SJ_HIP(hipStreamSynchronize(s));
+        if (!fx)
+            c->counter_clear = true;
         total = c->h_small[0];
         if (rq.timing) {
             c->stats.ms_norms = l2 ? elapsed_ms(c->ev[0], c->ev[1]) : 0.0;
@@ -434,14 +427,13 @@ int run(sj_ctx *c, const Request &rq, uint64_t *n_out, const Fixed *fx = nullptr
             SJ_HIP(hipEventRecord(c->ev[2], s));
         SJ_HIP(sjk::launch_scan(g.block_counts, plan.n_blocks,
                                 (unsigned long long *)(scr + off_offs),
-                                (unsigned long long *)(scr + off_part), d_small + 1, s));
+                                (unsigned long long *)(scr + off_part), d_small + 1, s,
+                                c->h_small, g.rec_counts, use_records ? plan.grid : 0u));
         if (rq.timing)
             SJ_HIP(hipEventRecord(c->ev[3], s));
-        SJ_HIP(hipMemcpyAsync(c->h_small + 1, d_small + 1, 2 * sizeof(unsigned long long),
-                              hipMemcpyDeviceToHost, s));
         SJ_HIP(hipStreamSynchronize(s));
-        total = c->h_small[1];
-        if (use_records && c->h_small[2] > rec_cap)
+        total = c->h_small[0];
+        if (use_records && c->h_small[1] > rec_cap)
             use_records = false;   // some blocks have no record: recompute
         if (rq.timing) {
             c->stats.ms_norms = l2 ? elapsed_ms(c->ev[0], c->ev[1]) : 0.0;

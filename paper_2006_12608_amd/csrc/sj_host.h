@@ -15,9 +15,11 @@ struct sj_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
     int num_cus = 256;
-    unsigned long long *d_small = nullptr;  // [0] match counter, [1] scan total,
-                                            // [2] largest per-workgroup record count
-    unsigned long long *h_small = nullptr;  // pinned host copy of d_small
+    unsigned long long *d_small = nullptr;  // [0] match counter, [1] scan total
+    bool counter_clear = false;             // d_small[0] is 0 for the next call on the stream
+    unsigned long long *h_small = nullptr;  // pinned: [0] match count or scan total, [1]
+                                            // largest per-workgroup record count (the kernels
+                                            // write them)
     void *scratch = nullptr;
     size_t scratch_bytes = 0;
     void *front = nullptr;        // rows made by the front ends (normalised or

@@ -82,7 +82,6 @@ struct JoinArgs {
     MatchRecord *records;        // MODE_RECORD: rec_cap records per workgroup, by workgroup
     uint32_t rec_cap;
     uint32_t *rec_counts;        // MODE_RECORD: records found per workgroup (may pass rec_cap)
-    unsigned long long *rec_max; // MODE_RECORD: largest of rec_counts (atomic max)
     uint32_t qsplit;             // FAM_RESIDENT: Q ranges per P block
 };
 
@@ -93,13 +92,14 @@ struct Plan {
     int variant;                 // index into the family's instantiation table
     uint32_t grid, block;
     uint32_t qsplit;
+    bool small;                  // FAM_RESIDENT: the small geometry (sj_join_kernels.h)
     uint64_t n_blocks;           // number of output blocks (entries of block_counts)
     uint64_t wg_blocks32;        // FAM_RESIDENT: most 32x32 result blocks of one workgroup
 };
 
-// Chooses the kernel for (dtype, metric, shape) on a GPU with `num_cus` CUs.
-// Returns false when the shape is unsupported.
-bool plan_join(int dtype, int metric, uint32_t n_p, uint32_t n_q, uint32_t row_bytes,
+// Chooses the kernel for (dtype, metric, shape) on a GPU with `num_cus` CUs
+// (tri: for MODE_TRI).  Returns false when the shape is unsupported.
+bool plan_join(int dtype, int metric, uint32_t n_p, uint32_t n_q, uint32_t row_bytes, bool tri,
                int num_cus, Plan *plan);
 
 hipError_t launch_join(const Plan &plan, int dtype, int metric, int mode, const JoinArgs &args,
@@ -117,15 +117,15 @@ hipError_t launch_emit_masks(const Plan &plan, const JoinArgs &g, hipStream_t st
 // position, in the order of a MODE_EMIT pass.
 hipError_t launch_emit_records(const JoinArgs &g, uint32_t n_wg, hipStream_t stream);
 
-// Squared row norms: out[i] = sum_k X[i][k]^2 (int32 for int8, fp32 otherwise).
-// Rows as in JoinArgs (16-byte aligned, row_bytes a multiple of 16).
-hipError_t launch_norms(int dtype, const uint8_t *X, uint32_t n, uint32_t row_bytes, void *out,
-                        hipStream_t stream);
-
-// Copies n rows of src_bytes bytes (any alignment) into rows of dst_bytes
-// bytes (dst_bytes >= src_bytes, a multiple of 16), zero-filling the tail.
-hipError_t launch_repack(const uint8_t *src, uint32_t n, uint32_t src_bytes, uint8_t *dst,
-                         uint32_t dst_bytes, hipStream_t stream);
+// The rows of both operands as the kernels read them, in one launch: copies of
+// rows of src_bytes bytes (any alignment) in rows of row_bytes bytes (a multiple
+// of 16, zero-filled tail) when copy_p / copy_q are not null, and squared row
+// norms (int32 for int8, fp32 otherwise) when norm_p / norm_q are not null (both
+// or neither operand; without copies src_bytes == row_bytes, rows 16-byte
+// aligned).  n_q = 0 when Q is P.
+hipError_t launch_prep(int dtype, const void *P, uint32_t n_p, const void *Q, uint32_t n_q,
+                       uint32_t src_bytes, uint32_t row_bytes, uint8_t *copy_p, uint8_t *copy_q,
+                       void *norm_p, void *norm_q, hipStream_t stream);
 
 // Section 4's cosine front end: Y (n x d, 16-bit) = every row of X (n x d of
 // dtype, row-major) divided by its Euclidean norm (double, ascending k) and
@@ -144,12 +144,19 @@ hipError_t launch_unpack_hamming(const uint8_t *bits, uint32_t n, uint32_t d, ui
 // Zeroes n 64-bit words on `stream` (one small kernel, no memset node).
 hipError_t launch_zero_u64(unsigned long long *p, uint32_t n, hipStream_t stream);
 
+// Writes *counter to host[0] (pinned host memory) and clears it.
+hipError_t launch_publish(unsigned long long *counter, unsigned long long *host,
+                          hipStream_t stream);
+
 // Exclusive scan of n uint32 counts into n uint64 offsets; *total receives the
-// sum.  `partials` needs scan_partials_size(n) elements of scratch.
+// sum.  `partials` needs scan_partials_size(n) elements of scratch.  With `host`
+// (pinned host memory) the sum also goes to host[0] and the largest of the
+// n_max values at `max_of` (may be none) to host[1].
 uint64_t scan_partials_size(uint64_t n);
 hipError_t launch_scan(const uint32_t *counts, uint64_t n, unsigned long long *offsets,
                        unsigned long long *partials, unsigned long long *total,
-                       hipStream_t stream);
+                       hipStream_t stream, unsigned long long *host = nullptr,
+                       const uint32_t *max_of = nullptr, uint32_t n_max = 0);
 
 // Launchers and occupancy (workgroups of a resident-kernel variant that one CU
 // holds at once) per element type and metric, one translation unit each.

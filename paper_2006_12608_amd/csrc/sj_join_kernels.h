@@ -626,6 +626,7 @@ __global__ void __launch_bounds__(NW * 64) join_resident(JoinArgs g)
     // Sub-tile pipeline (two accumulator sets); at 16 k-steps only the inner
     // product fits a second set in 256 VGPRs (the L2 epilogue needs more).
     constexpr bool PIPE = KS <= 8 || MET == MET_IP;
+    static_assert(SUBS % 2 == 0, "the sets alternate over the sub-tiles of a tile");
 
     // Two distinct LDS buffers (not one array indexed at run time): the tile
     // loop is unrolled by two so every access names its buffer statically, which
@@ -939,11 +940,8 @@ __global__ void __launch_bounds__(NW * 64) join_resident(JoinArgs g)
         flush_workgroup_out<NW>(wo, wave, lane, g);
     if constexpr (MODE == MODE_RECORD) {
         __syncthreads();
-        if (tid == 0) {
-            const uint32_t n = s_nrec;
-            g.rec_counts[blockIdx.x] = n;
-            atomicMax(g.rec_max, (unsigned long long)n);
-        }
+        if (tid == 0)
+            g.rec_counts[blockIdx.x] = s_nrec;
     }
 }
 
@@ -1224,17 +1222,35 @@ constexpr int res_bn()
     return KS <= 2 ? 256 : KS <= 8 ? 128 : 64;
 }
 
+// The small geometry (Plan::small): two waves and Q tiles of 64 rows, for joins
+// whose ordinary tiles would leave CUs without a workgroup.  A wave owns the
+// same rows of P as in the ordinary one, so count-then-emit's order (by wave
+// row block, then column) is the same.
+constexpr int SMALL_NW = 2, SMALL_BN = 64;
+
+template <int DT, int MET, int MODE, int V, bool SMALL>
+struct ResidentKernel {
+    static constexpr int KS = ResidentCfg<DT>::KS[V];
+    static constexpr int NW = SMALL ? SMALL_NW : RES_NW;
+    static constexpr auto fn = &join_resident<DT, MET, MODE, KS, res_wmb<DT, KS>(), NW,
+                                              SMALL ? SMALL_BN : res_bn<KS>()>;
+};
+
 template <int DT, int MET, int MODE, int V>
 hipError_t launch_resident_v(const Plan &p, const JoinArgs &g, hipStream_t st)
 {
-    constexpr int KS = ResidentCfg<DT>::KS[V];
-    constexpr int WMB = res_wmb<DT, KS>();
-    constexpr int BN = res_bn<KS>();
+    if constexpr (MODE != MODE_TRI) {
+        if (p.small) {
+            typedef ResidentKernel<DT, MET, MODE, V, true> K;
+            hipLaunchKernelGGL(K::fn, dim3(p.grid), dim3(K::NW * 64), 0, st, g);
+            return hipGetLastError();
+        }
+    }
+    typedef ResidentKernel<DT, MET, MODE, V, false> K;
     // the self-join triangle pairs the blocks of P rows (see join_resident)
     const uint32_t grid =
         MODE == MODE_TRI ? (p.grid / p.qsplit + 1) / 2 * p.qsplit : p.grid;
-    hipLaunchKernelGGL((join_resident<DT, MET, MODE, KS, WMB, RES_NW, BN>), dim3(grid),
-                       dim3(RES_NW * 64), 0, st, g);
+    hipLaunchKernelGGL(K::fn, dim3(grid), dim3(K::NW * 64), 0, st, g);
     return hipGetLastError();
 }
 
@@ -1242,13 +1258,10 @@ hipError_t launch_resident_v(const Plan &p, const JoinArgs &g, hipStream_t st)
 template <int DT, int MET, int V>
 int resident_occupancy_v()
 {
-    constexpr int KS = ResidentCfg<DT>::KS[V];
-    constexpr int WMB = res_wmb<DT, KS>();
-    constexpr int BN = res_bn<KS>();
+    typedef ResidentKernel<DT, MET, MODE_SINGLE, V, false> K;
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &n, reinterpret_cast<const void *>(&join_resident<DT, MET, MODE_SINGLE, KS, WMB, RES_NW, BN>),
-            RES_NW * 64, 0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(K::fn),
+                                                     K::NW * 64, 0) != hipSuccess)
         n = 1;
     return n < 1 ? 1 : n;
 }

@@ -156,20 +156,14 @@ extern "C" int sj_join_lsh(sj_ctx *c, int metric, int dtype, const void *P, uint
     sjl::Rows rq{aligned ? (const uint8_t *)Q : scr + off_rq, n_q, (uint32_t)krow};
     unsigned long long *cnt = (unsigned long long *)(scr + off_cnt);
     SJ_HIP(hipMemsetAsync(cnt, 0, 8 * 8, s));
-    SJ_HIP(hipMemsetAsync(c->d_small, 0, sizeof(unsigned long long), s));
+    if (!c->counter_clear)
+        SJ_HIP(sjk::launch_zero_u64(c->d_small, 1, s));
+    c->counter_clear = false;   // until it is published
     SJ_HIP(hipEventRecord(c->ev[0], s));
-    if (!aligned) {
-        SJ_HIP(sjk::launch_repack((const uint8_t *)P, n_p, (uint32_t)row_bytes, scr + off_rp,
-                                  (uint32_t)krow, s));
-        if (!self)
-            SJ_HIP(sjk::launch_repack((const uint8_t *)Q, n_q, (uint32_t)row_bytes,
-                                      scr + off_rq, (uint32_t)krow, s));
-    }
-    if (l2) {
-        SJ_HIP(sjk::launch_norms(dtype, rp.X, n_p, rp.row_bytes, scr + off_np, s));
-        if (!self)
-            SJ_HIP(sjk::launch_norms(dtype, rq.X, n_q, rq.row_bytes, scr + off_nq, s));
-    }
+    SJ_HIP(sjk::launch_prep(dtype, P, n_p, Q, self ? 0u : n_q,
+                            aligned ? (uint32_t)krow : (uint32_t)row_bytes, (uint32_t)krow,
+                            aligned ? nullptr : scr + off_rp, aligned ? nullptr : scr + off_rq,
+                            l2 ? scr + off_np : nullptr, l2 ? scr + off_nq : nullptr, s));
     uint64_t *keys_p = (uint64_t *)(scr + off_kp), *keys_q = (uint64_t *)(scr + off_kq);
     SJ_HIP(sjl::launch_widen(dtype, A, L * k, d, scr + off_aw, s));
     if (fast) {
@@ -273,8 +267,9 @@ extern "C" int sj_join_lsh(sj_ctx *c, int metric, int dtype, const void *P, uint
     g.counter = c->d_small;
     SJ_HIP(sjl::launch_join(dtype, metric, g, c->num_cus, s));
     SJ_HIP(hipEventRecord(c->ev[3], s));
-    SJ_HIP(hipMemcpyAsync(c->h_small, c->d_small, 8, hipMemcpyDeviceToHost, s));
+    SJ_HIP(sjk::launch_publish(c->d_small, c->h_small, s));
     SJ_HIP(hipStreamSynchronize(s));
+    c->counter_clear = true;
     const uint64_t total = c->h_small[0];
     c->stats.total = total;
     c->stats.ms_norms = elapsed_ms(c->ev[0], c->ev[1]);

@@ -269,6 +269,35 @@ def test_few_rows_against_many(dtype, d, metric, n_p):
     assert sj.count(Pd, Qd, w.threshold, metric) == g.shape[0]
 
 
+@pytest.mark.parametrize("dtype,d", [("f16", 20), ("f16", 64), ("bf16", 128), ("bf16", 200),
+                                     ("i8", 30), ("i8", 64), ("i8", 128), ("i8", 250)])
+@pytest.mark.parametrize("metric", ["ip", "l2"])
+def test_ordinary_tiles_all_modes(dtype, d, metric):
+    """Every resident variant at a size that takes the ordinary tiles (more
+    than one for every second CU; smaller joins take the small geometry),
+    ragged in both directions, in every mode: the oracle's set, and the same
+    array from both second passes of count-then-emit."""
+    import paper_2006_12608_amd as sj
+    n_p, n_q = 8209, 9001
+    w = workloads.random_case(71 + d, n_p, n_q, d, dtype, lo=-3, hi=3, metric=metric)
+    rows = np.sort(np.random.default_rng(d).choice(n_p, 500, replace=False))
+    x, y = values(dtype, w.P[rows]).astype(np.int64), values(dtype, w.Q).astype(np.int64)
+    s = x @ y.T
+    if metric == "l2":
+        s = (x * x).sum(1)[:, None] + (y * y).sum(1)[None, :] - 2 * s
+    w.threshold = float(np.quantile(s, 0.998 if metric == "ip" else 0.002, method="nearest"))
+    _, g, _ = run_case(w, rows=rows)
+    Pd, Qd = to_device(w.P, dtype), to_device(w.Q, dtype)
+    f = sj.join_ip if metric == "ip" else sj.join_l2
+    a, b = f(Pd, Qd, w.threshold), f(Pd, Qd, w.threshold, recompute=True)
+    assert np.array_equal(a.cpu().numpy(), b.cpu().numpy())
+    h = sorted_pairs(a)
+    assert np.array_equal(g, h[np.isin(h[:, 0], rows)])
+    one = sorted_pairs(f(Pd, Qd, w.threshold, two_pass=False))
+    assert np.array_equal(one, h)
+    assert sj.count(Pd, Qd, w.threshold, metric) == h.shape[0]
+
+
 @pytest.mark.parametrize("dtype,d,metric", [("bf16", 300, "ip"), ("f16", 520, "l2"),
                                              ("i8", 700, "ip"), ("i8", 530, "l2"),
                                              ("bf16", 128, "ip"), ("f16", 256, "l2"),
