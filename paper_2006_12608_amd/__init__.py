@@ -42,6 +42,11 @@ class sj_stats(ctypes.Structure):
                 ("emit_from_bits", ctypes.c_uint32), ("lsh_rows", ctypes.c_uint64)]
 
 
+# allocation of an output half-way through a call, once its size is known
+# (csrc/sj_sized.h): (user, number of pairs) -> device pointer
+_ALLOC = ctypes.CFUNCTYPE(ctypes.c_void_p, ctypes.c_void_p, ctypes.c_uint64)
+
+
 def _load():
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"{LIB_PATH} is missing: build it with "
@@ -70,6 +75,13 @@ def _load():
                                 ctypes.c_int32, vp, u64, ctypes.POINTER(u64),
                                 ctypes.POINTER(u64)]
     lib.sj_join_lsh.restype = i32
+    lib.sji_join_sized.argtypes = [vp, i32, i32, vp, u32, vp, u32, u32, dbl, _ALLOC, vp,
+                                   ctypes.POINTER(u64), ctypes.c_uint]
+    lib.sji_join_sized.restype = i32
+    lib.sji_lsh_sized.argtypes = [vp, i32, i32, vp, u32, vp, u32, u32, dbl, u32, u32, vp, vp,
+                                  ctypes.c_int32, _ALLOC, vp, ctypes.POINTER(u64),
+                                  ctypes.POINTER(u64)]
+    lib.sji_lsh_sized.restype = i32
     lib.sj_lsh_sort.argtypes = [vp, vp, u32, u32, u32, vp]
     lib.sj_lsh_sort.restype = i32
     lib.sj_lsh_collision.argtypes = [ctypes.c_int32, dbl, dbl]
@@ -252,6 +264,38 @@ def count(P, Q, threshold: float, metric: str = "ip", ctx=None) -> int:
     return n
 
 
+def _own_output(call, device):
+    """Runs call(alloc) -> status, which sizes its output itself and asks for
+    it half-way (the product, or the hashing and sorting, runs once).  Returns
+    the pairs."""
+    import torch
+    out, failed = None, None
+
+    def alloc(_, n):
+        nonlocal out, failed
+        try:
+            out = torch.empty((n, 2), dtype=torch.int32, device=device)
+            return out.data_ptr()
+        except BaseException as e:      # nothing may pass through the C call
+            failed = e
+            return None
+    st = call(_ALLOC(alloc))
+    if failed is not None:
+        raise failed
+    if st != SJ_OK:
+        raise SjError(st, sj_last_error(), 0 if out is None else out.shape[0])
+    return torch.empty((1, 2), dtype=torch.int32, device=device)[:0] if out is None else out
+
+
+def _join_sized(kind, ctx, dtype, P, Q, d, thr, flags):
+    """A join without a capacity: count-then-emit into an output of the size
+    that the count gives (kind 0: inner product, 1: L2, 2: Hamming)."""
+    n = ctypes.c_uint64(0)
+    return _own_output(lambda alloc: lib.sji_join_sized(
+        ctx, kind, dtype, P.data_ptr(), P.shape[0], Q.data_ptr(), Q.shape[0], d, float(thr), alloc,
+        None, ctypes.byref(n), flags), P.device)
+
+
 def _sized_call(call, flags, cap, out, device):
     """Runs call(pairs_ptr, cap, flags) -> (status, n); with neither a
     capacity nor an output buffer, a first count-then-emit call with no room
@@ -277,17 +321,21 @@ def _join(metric, P, Q, thr, cap, two_pass, timing, ctx, out, recompute=False, c
     import torch
     _check_pair(P, Q)
     ctx = ctx or context(P.device.index)
+    unsized = cap is None and out is None
     if two_pass is None:
         # no capacity given: count-then-emit sizes the output exactly
-        two_pass = cap is None and out is None
+        two_pass = unsized
     flags = ((SJ_FLAG_TWO_PASS if two_pass else 0) | (SJ_FLAG_TIMING if timing else 0)
              | (SJ_FLAG_RECOMPUTE if recompute else 0) | (SJ_FLAG_COSINE if cosine else 0))
+    if unsized and two_pass:
+        return _join_sized(0 if metric == "ip" else 1, ctx, dtype_code(P), P, Q, P.shape[1], thr,
+                           flags)
     if cosine:
         def call(ptr, c, f):
             return sj_join_ip(ctx, dtype_code(P), P.data_ptr(), P.shape[0], Q.data_ptr(),
                               Q.shape[0], P.shape[1], thr, ptr, c, f)
         return _sized_call(call, flags, cap, out, P.device)
-    if cap is None and out is None:
+    if unsized:
         cap = count(P, Q, thr, metric, ctx)
     if out is None:
         out = torch.empty((max(int(cap), 1), 2), dtype=torch.int32, device=P.device)
@@ -306,9 +354,9 @@ def join_ip(P, Q, s: float, cap: int | None = None, two_pass: bool | None = None
             timing: bool = False, ctx=None, out=None, recompute: bool = False,
             cosine: bool = False):
     """All (i, j) with <P_i, Q_j> >= s as an (n, 2) int32 tensor of uint32
-    indices.  With cap=None (and no `out`) the output is sized by sj_count and
-    filled by count-then-emit (deterministic order) unless two_pass=False asks
-    for the single pass; with a capacity the single pass runs unless
+    indices.  With cap=None (and no `out`) the output is sized by the counting
+    pass of count-then-emit (deterministic order) unless two_pass=False asks
+    for the single pass (sized by sj_count); with a capacity the single pass runs unless
     two_pass=True.  recompute makes the second pass of count-then-emit repeat
     the product even where the first pass's match bits would be kept.
     cosine=True normalises the rows in the library first (SJ_FLAG_COSINE)."""
@@ -353,6 +401,8 @@ def join_hamming(P, Q, d: int, r: float, cap: int | None = None, two_pass: bool 
     if two_pass is None:
         two_pass = cap is None and out is None
     flags = (SJ_FLAG_TWO_PASS if two_pass else 0) | (SJ_FLAG_TIMING if timing else 0)
+    if cap is None and out is None and two_pass:
+        return _join_sized(2, ctx, 0, P, Q, d, r, flags)
 
     def call(ptr, c, f):
         return sj_join_hamming(ctx, P.data_ptr(), P.shape[0], Q.data_ptr(), Q.shape[0], d, r,
@@ -366,7 +416,7 @@ def join_lsh(P, Q, thr: float, metric: str = "ip", *, L: int, k: int, A, B=None,
     of L tables (k concatenated random projections each: signs when w == 0,
     quantised with offsets B when w > 0) and pass the exact test of `metric`.
     A is an (L*k, d) int8 device tensor, B an (L*k,) int32 device tensor (or
-    None for sign hashes).  With cap=None a first call sizes the output.
+    None for sign hashes).  With cap=None the library sizes the output.
     Returns (pairs as an (n, 2) int32 tensor of uint32 indices, number of pair
     evaluations made)."""
     import torch
@@ -382,12 +432,13 @@ def join_lsh(P, Q, thr: float, metric: str = "ip", *, L: int, k: int, A, B=None,
     args = (ctx, m, dtype_code(P), P.data_ptr(), P.shape[0], Q.data_ptr(), Q.shape[0],
             P.shape[1], thr, L, k, A.data_ptr() if A.numel() else None,
             None if B is None else B.data_ptr(), w)
+    if out is None and cap is None:
+        n, nc = ctypes.c_uint64(0), ctypes.c_uint64(0)
+        pairs = _own_output(lambda alloc: lib.sji_lsh_sized(
+            *args[:8], float(thr), *args[9:], alloc, None, ctypes.byref(n), ctypes.byref(nc)),
+            P.device)
+        return pairs, nc.value
     if out is None:
-        if cap is None:
-            st, n, _ = sj_join_lsh(*args, None, 0)
-            if st not in (SJ_OK, SJ_E_OVERFLOW):
-                raise SjError(st, sj_last_error(), n)
-            cap = n
         out = torch.empty((max(int(cap), 1), 2), dtype=torch.int32, device=P.device)
         cap = int(cap)
     else:

@@ -16,6 +16,7 @@
 
 #include "sj_host.h"
 #include "sj_internal.h"
+#include "sj_sized.h"
 
 // Device scratch of sj_join_noalloc, for callers that cannot allocate: the
 // match counter and scan total (first 256 bytes), then the row norms,
@@ -175,6 +176,9 @@ struct Request {
     bool two_pass, count_only, timing, recompute;
     // rows are the Hamming front end's 4-bit codes (d counts their bytes)
     bool fp4 = false;
+    // count-then-emit into memory allocated once the count is known (pairs and
+    // cap are then not used)
+    const Sized *sized = nullptr;
 };
 
 // Largest match-bit buffer the two-pass mode keeps (bytes); beyond it, or
@@ -440,7 +444,19 @@ int run(sj_ctx *c, const Request &rq, uint64_t *n_out, const Fixed *fx = nullptr
             c->stats.ms_count = elapsed_ms(c->ev[1], c->ev[2]);
             c->stats.ms_scan = elapsed_ms(c->ev[2], c->ev[3]);
         }
-        if (!rq.count_only && total <= rq.cap && total > 0) {
+        if (rq.sized && total > 0) {
+            g.pairs = (uint32_t *)rq.sized->alloc(rq.sized->user, total);
+            g.cap = total;
+            if (!g.pairs)
+                return fail(SJ_E_NOMEM, "no room for %llu pairs", (unsigned long long)total);
+            if (total > (uint64_t)SIZE_MAX / 8)
+                return fail(SJ_E_INVAL, "too many pairs");
+            if ((st = check_device_ptr(c, g.pairs, (size_t)total * 8, "pairs")) != SJ_OK)
+                return st;
+            if ((uintptr_t)g.pairs % 8 != 0)
+                return fail(SJ_E_INVAL, "pairs must be 8-byte aligned");
+        }
+        if (!rq.count_only && total <= g.cap && total > 0) {
             if (rq.timing)
                 SJ_HIP(hipEventRecord(c->ev[4], s));
             if (use_masks)
@@ -462,9 +478,9 @@ int run(sj_ctx *c, const Request &rq, uint64_t *n_out, const Fixed *fx = nullptr
     c->stats.emit_from_bits = emit_from_bits ? 1u : 0u;
     c->stats.timed = rq.timing ? 1u : 0u;
     *n_out = total;
-    if (!rq.count_only && total > rq.cap)
+    if (!rq.count_only && total > g.cap)
         return fail(SJ_E_OVERFLOW, "%llu matches exceed the capacity of %llu pairs",
-                    (unsigned long long)total, (unsigned long long)rq.cap);
+                    (unsigned long long)total, (unsigned long long)g.cap);
     return SJ_OK;
 }
 
@@ -508,6 +524,55 @@ int cosine_join(sj_ctx *c, Request rq, uint64_t *n_out)
     rq.P = f;
     rq.Q = self ? f : f + bp;
     rq.dtype = rq.dtype == SJ_BF16 ? SJ_BF16 : SJ_F16;
+    return run(c, rq, n_out);
+}
+
+// Section 4's Hamming ip-distance (rq.thr is the radius): bit rows as 4-bit +-1
+// codes in the front-end buffer, then their inner-product join.
+int hamming_join(sj_ctx *c, Request rq, unsigned flags, uint64_t *n_out)
+{
+    if (!c)
+        return fail(SJ_E_INVAL, "context is NULL");
+    if (!n_out)
+        return fail(SJ_E_INVAL, "result pointer is NULL");
+    *n_out = 0;
+    const void *P = rq.P, *Q = rq.Q;
+    const uint32_t n_p = rq.n_p, n_q = rq.n_q, d = rq.d;
+    const double r = rq.thr;
+    if (std::isnan(r))
+        return fail(SJ_E_INVAL, "radius is NaN");
+    if (flags & ~(unsigned)(SJ_FLAG_TWO_PASS | SJ_FLAG_TIMING | SJ_FLAG_RECOMPUTE))
+        return fail(SJ_E_INVAL, "unknown flags 0x%x", flags);
+    if (d > 16384)
+        return fail(SJ_E_UNSUPPORTED, "d = %u bits is above the limit of 16384", d);
+    const size_t in_row = (d + 7) / 8;
+    int st;
+    if ((st = check_device_ptr(c, P, (size_t)n_p * in_row, "P")) != SJ_OK)
+        return st;
+    if ((st = check_device_ptr(c, Q, (size_t)n_q * in_row, "Q")) != SJ_OK)
+        return st;
+    rq.d = 0;
+    rq.thr = -r;
+    if (n_p == 0 || n_q == 0 || d == 0)
+        return run(c, rq, n_out);   // no pairs, or every distance 0 (d = 0)
+    // +-1 codes, two per byte, rows padded with zeros to 16 bytes:
+    // Hamming(x, y) <= r <=> <f(x), f(y)> >= d - 2 floor(r)
+    const bool self = P == Q && n_p == n_q;
+    const uint32_t rb = (uint32_t)((((size_t)d + 1) / 2 + 15) & ~(size_t)15);
+    const size_t bp = align_up((size_t)n_p * rb), bq = self ? 0 : align_up((size_t)n_q * rb);
+    if ((st = grow_front(c, bp + bq)) != SJ_OK)
+        return st;
+    uint8_t *f = (uint8_t *)c->front;
+    SJ_HIP(hipSetDevice(c->device));
+    SJ_HIP(sjk::launch_unpack_hamming((const uint8_t *)P, n_p, d, rb, f, c->stream));
+    if (!self)
+        SJ_HIP(sjk::launch_unpack_hamming((const uint8_t *)Q, n_q, d, rb, f + bp, c->stream));
+    rq.P = f;
+    rq.Q = self ? f : f + bp;
+    rq.dtype = sjk::DT_FP4;
+    rq.fp4 = true;
+    rq.d = rb;
+    rq.thr = (double)d - 2.0 * std::floor(r);
     return run(c, rq, n_out);
 }
 
@@ -608,47 +673,11 @@ int sj_join_hamming(sj_ctx *ctx, const void *P, uint32_t n_p, const void *Q, uin
                     unsigned flags)
 {
     g_err.clear();
-    if (!ctx)
-        return fail(SJ_E_INVAL, "context is NULL");
-    if (!n_out)
-        return fail(SJ_E_INVAL, "result pointer is NULL");
-    *n_out = 0;
-    if (std::isnan(r))
-        return fail(SJ_E_INVAL, "radius is NaN");
-    if (flags & ~(unsigned)(SJ_FLAG_TWO_PASS | SJ_FLAG_TIMING | SJ_FLAG_RECOMPUTE))
-        return fail(SJ_E_INVAL, "unknown flags 0x%x", flags);
-    if (d > 16384)
-        return fail(SJ_E_UNSUPPORTED, "d = %u bits is above the limit of 16384", d);
-    const size_t in_row = (d + 7) / 8;
-    int st;
-    if ((st = check_device_ptr(ctx, P, (size_t)n_p * in_row, "P")) != SJ_OK)
-        return st;
-    if ((st = check_device_ptr(ctx, Q, (size_t)n_q * in_row, "Q")) != SJ_OK)
-        return st;
-    Request rq{SJ_IP, SJ_I8, P, Q, n_p, n_q, 0, -r, pairs, cap,
-               (flags & SJ_FLAG_TWO_PASS) != 0, false, (flags & SJ_FLAG_TIMING) != 0,
-               (flags & SJ_FLAG_RECOMPUTE) != 0};
-    if (n_p == 0 || n_q == 0 || d == 0)
-        return run(ctx, rq, n_out);   // no pairs, or every distance 0 (d = 0)
-    // +-1 codes, two per byte, rows padded with zeros to 16 bytes:
-    // Hamming(x, y) <= r <=> <f(x), f(y)> >= d - 2 floor(r)
-    const bool self = P == Q && n_p == n_q;
-    const uint32_t rb = (uint32_t)((((size_t)d + 1) / 2 + 15) & ~(size_t)15);
-    const size_t bp = align_up((size_t)n_p * rb), bq = self ? 0 : align_up((size_t)n_q * rb);
-    if ((st = grow_front(ctx, bp + bq)) != SJ_OK)
-        return st;
-    uint8_t *f = (uint8_t *)ctx->front;
-    SJ_HIP(hipSetDevice(ctx->device));
-    SJ_HIP(sjk::launch_unpack_hamming((const uint8_t *)P, n_p, d, rb, f, ctx->stream));
-    if (!self)
-        SJ_HIP(sjk::launch_unpack_hamming((const uint8_t *)Q, n_q, d, rb, f + bp, ctx->stream));
-    rq.P = f;
-    rq.Q = self ? f : f + bp;
-    rq.dtype = sjk::DT_FP4;
-    rq.fp4 = true;
-    rq.d = rb;
-    rq.thr = (double)d - 2.0 * std::floor(r);
-    return run(ctx, rq, n_out);
+    return hamming_join(ctx, Request{SJ_IP, SJ_I8, P, Q, n_p, n_q, d, r, pairs, cap,
+                                     (flags & SJ_FLAG_TWO_PASS) != 0, false,
+                                     (flags & SJ_FLAG_TIMING) != 0,
+                                     (flags & SJ_FLAG_RECOMPUTE) != 0},
+                        flags, n_out);
 }
 
 int sj_join_l2(sj_ctx *ctx, int dtype, const void *P, uint32_t n_p, const void *Q, uint32_t n_q,
@@ -662,6 +691,30 @@ int sj_join_l2(sj_ctx *ctx, int dtype, const void *P, uint32_t n_p, const void *
     Request rq{SJ_L2, dtype, P, Q, n_p, n_q, d, r2, pairs, cap,
                (flags & SJ_FLAG_TWO_PASS) != 0, false, (flags & SJ_FLAG_TIMING) != 0,
                (flags & SJ_FLAG_RECOMPUTE) != 0};
+    return run(ctx, rq, n_out);
+}
+
+int sji_join_sized(sj_ctx *ctx, int kind, int dtype, const void *P, uint32_t n_p, const void *Q,
+                   uint32_t n_q, uint32_t d, double thr, sj_alloc_fn alloc, void *user,
+                   uint64_t *n_out, unsigned flags)
+{
+    g_err.clear();
+    if (!alloc)
+        return fail(SJ_E_INVAL, "no allocation function");
+    if (kind < 0 || kind > 2)
+        return fail(SJ_E_INVAL, "unknown join %d", kind);
+    const unsigned taken = SJ_FLAG_TWO_PASS | SJ_FLAG_TIMING | SJ_FLAG_RECOMPUTE |
+                           (kind == 0 ? (unsigned)SJ_FLAG_COSINE : 0u);
+    if (flags & ~taken)
+        return fail(SJ_E_INVAL, "flags 0x%x: not taken by this join", flags);
+    const Sized sized{alloc, user};
+    Request rq{kind == 1 ? SJ_L2 : SJ_IP, kind == 2 ? SJ_I8 : dtype, P, Q, n_p, n_q, d, thr, nullptr, 0, true, false,
+               (flags & SJ_FLAG_TIMING) != 0, (flags & SJ_FLAG_RECOMPUTE) != 0};
+    rq.sized = &sized;
+    if (kind == 2)
+        return hamming_join(ctx, rq, flags, n_out);
+    if (flags & SJ_FLAG_COSINE)
+        return cosine_join(ctx, rq, n_out);
     return run(ctx, rq, n_out);
 }
 

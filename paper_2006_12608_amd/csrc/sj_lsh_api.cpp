@@ -12,6 +12,7 @@
 #include "sj_host.h"
 #include "sj_internal.h"
 #include "sj_lsh.h"
+#include "sj_sized.h"
 
 using namespace sjh;
 
@@ -21,12 +22,14 @@ namespace {
 const uint64_t kMaxTableRows = (uint64_t)1 << 32;
 const uint32_t kMaxTables = 256;
 
-}  // namespace
+// Pairs a call that sizes its own output keeps room for in its scratch (32
+// MiB), so that the bucket join runs once for outputs up to that.
+const uint64_t kOwnPairs = (uint64_t)4 << 20;
 
-extern "C" int sj_join_lsh(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p,
-                           const void *Q, uint32_t n_q, uint32_t d, double thr, uint32_t L,
-                           uint32_t k, const int8_t *A, const int32_t *B, int32_t w,
-                           uint32_t *pairs, uint64_t cap, uint64_t *n_out, uint64_t *n_cand)
+int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, const void *Q,
+             uint32_t n_q, uint32_t d, double thr, uint32_t L, uint32_t k, const int8_t *A,
+             const int32_t *B, int32_t w, uint32_t *pairs, uint64_t cap, const Sized *sized,
+             uint64_t *n_out, uint64_t *n_cand)
 {
     g_err.clear();
     if (!c)
@@ -145,6 +148,8 @@ extern "C" int sj_join_lsh(sj_ctx *c, int metric, int dtype, const void *P, uint
     const size_t off_aw = take(a_bytes);
     // keys on the matrix cores where they apply
     const bool fast = sjl::keys_fast_applies(dtype, (uint32_t)krow, L, k, w);
+    const uint64_t own = sized ? std::min((uint64_t)n_p * n_q, kOwnPairs) : 0;
+    const size_t off_own = take((size_t)own * 8);
     const size_t off_ws = fast ? take(sjl::keys_fast_bytes((uint32_t)n_max, L, k, (uint32_t)krow)) : 0;
     if ((st = grow_scratch(c, need)) != SJ_OK)
         return st;
@@ -262,8 +267,8 @@ extern "C" int sj_join_lsh(sj_ctx *c, int metric, int dtype, const void *P, uint
     }
     g.norm_p = scr + off_np;
     g.norm_q = scr + off_nq;
-    g.pairs = pairs;
-    g.cap = cap;
+    g.pairs = sized ? (uint32_t *)(scr + off_own) : pairs;
+    g.cap = sized ? own : cap;
     g.counter = c->d_small;
     SJ_HIP(sjl::launch_join(dtype, metric, g, c->num_cus, s));
     SJ_HIP(hipEventRecord(c->ev[3], s));
@@ -271,6 +276,30 @@ extern "C" int sj_join_lsh(sj_ctx *c, int metric, int dtype, const void *P, uint
     SJ_HIP(hipStreamSynchronize(s));
     c->counter_clear = true;
     const uint64_t total = c->h_small[0];
+    if (sized && total > 0) {
+        uint32_t *out = (uint32_t *)sized->alloc(sized->user, total);
+        if (!out)
+            return fail(SJ_E_NOMEM, "no room for %llu pairs", (unsigned long long)total);
+        if (total > (uint64_t)SIZE_MAX / 8)
+            return fail(SJ_E_INVAL, "too many pairs");
+        if ((st = check_device_ptr(c, out, (size_t)total * 8, "pairs")) != SJ_OK)
+            return st;
+        if ((uintptr_t)out % 8 != 0)
+            return fail(SJ_E_INVAL, "pairs must be 8-byte aligned");
+        if (total <= own) {
+            SJ_HIP(hipMemcpyAsync(out, g.pairs, (size_t)total * 8, hipMemcpyDeviceToDevice, s));
+        } else {
+            // more than the scratch holds: the bucket join once more
+            g.pairs = out;
+            g.cap = total;
+            c->counter_clear = false;
+            SJ_HIP(sjl::launch_join(dtype, metric, g, c->num_cus, s));
+            SJ_HIP(sjk::launch_publish(c->d_small, c->h_small, s));
+        }
+        SJ_HIP(hipStreamSynchronize(s));
+        c->counter_clear = true;
+        cap = total;
+    }
     c->stats.total = total;
     c->stats.ms_norms = elapsed_ms(c->ev[0], c->ev[1]);
     c->stats.ms_scan = elapsed_ms(c->ev[1], c->ev[2]);
@@ -285,6 +314,31 @@ extern "C" int sj_join_lsh(sj_ctx *c, int metric, int dtype, const void *P, uint
         return fail(SJ_E_OVERFLOW, "%llu matches exceed the capacity of %llu pairs",
                     (unsigned long long)total, (unsigned long long)cap);
     return SJ_OK;
+}
+
+}  // namespace
+
+extern "C" int sj_join_lsh(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p,
+                           const void *Q, uint32_t n_q, uint32_t d, double thr, uint32_t L,
+                           uint32_t k, const int8_t *A, const int32_t *B, int32_t w,
+                           uint32_t *pairs, uint64_t cap, uint64_t *n_out, uint64_t *n_cand)
+{
+    return lsh_join(c, metric, dtype, P, n_p, Q, n_q, d, thr, L, k, A, B, w, pairs, cap, nullptr,
+                    n_out, n_cand);
+}
+
+extern "C" int sji_lsh_sized(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p,
+                             const void *Q, uint32_t n_q, uint32_t d, double thr, uint32_t L,
+                             uint32_t k, const int8_t *A, const int32_t *B, int32_t w,
+                             sj_alloc_fn alloc, void *user, uint64_t *n_out, uint64_t *n_cand)
+{
+    if (!alloc) {
+        g_err.clear();
+        return fail(SJ_E_INVAL, "no allocation function");
+    }
+    const Sized sized{alloc, user};
+    return lsh_join(c, metric, dtype, P, n_p, Q, n_q, d, thr, L, k, A, B, w, nullptr, 0, &sized,
+                    n_out, n_cand);
 }
 
 // The grouping of the LSH-bucketed join's tables on its own (Section 4: the

@@ -174,3 +174,41 @@ def test_unknown_metric_is_rejected(env):
     A = torch.zeros((2, 16), dtype=torch.int8, device="cuda")
     with pytest.raises(ValueError, match="metric"):
         sj.join_lsh(P, P, 0.0, "L2", L=1, k=2, A=A, ctx=ctx)
+
+
+def test_outputs_sized_by_the_library(env, monkeypatch):
+    """Calls without a capacity allocate their output half-way: no pairs, an
+    LSH output past the 4 Mi pairs its scratch holds (the bucket join then runs
+    twice), an allocation that fails (its exception arrives, the next call
+    works), and the same arrays as count-then-emit into a buffer."""
+    sj, ctx, torch = env
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    P = torch.randint(-3, 4, (2100, 33), generator=g, dtype=torch.int8, device="cuda")
+    Q = torch.randint(-3, 4, (2110, 33), generator=g, dtype=torch.int8, device="cuda")
+    say("sized: none, some, all")
+    assert sj.join_ip(P, Q, 1e6).shape == (0, 2)
+    for thr in (60.0, -1e6):
+        a = sj.join_ip(P, Q, thr)
+        out = torch.empty((2100 * 2110, 2), dtype=torch.int32, device="cuda")
+        assert torch.equal(a, sj.join_ip(P, Q, thr, out=out, two_pass=True)) and len(a) > 0
+    A = torch.zeros((0, 33), dtype=torch.int8, device="cuda")
+    say("sized: LSH")
+    a, cand = sj.join_lsh(P, Q, -1e6, "ip", L=1, k=0, A=A)
+    assert a.shape == (2100 * 2110, 2) and cand == 2100 * 2110
+    key = torch.sort(a.view(torch.int64).view(-1))[0]
+    assert torch.equal(key, torch.sort(out.view(torch.int64).view(-1))[0])
+    a, _ = sj.join_lsh(P, Q, 1e6, "ip", L=1, k=0, A=A)
+    assert a.shape == (0, 2)
+    empty = torch.empty
+
+    def no_room(*args, **kw):
+        raise torch.cuda.OutOfMemoryError("no room")
+    say("sized: allocation fails")
+    monkeypatch.setattr(torch, "empty", no_room)
+    for call in (lambda: sj.join_ip(P, Q, 60.0), lambda: sj.join_lsh(P, Q, 60.0, "ip", L=1, k=0, A=A)):
+        with pytest.raises(torch.cuda.OutOfMemoryError):
+            call()
+    monkeypatch.setattr(torch, "empty", empty)
+    assert torch.equal(sj.join_ip(P, Q, 60.0), sj.join_ip(P, Q, 60.0))
+    assert sj.count(P, Q, -1e6) == 2100 * 2110
