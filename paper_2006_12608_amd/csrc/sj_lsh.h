@@ -55,7 +55,7 @@ hipError_t sort_tables(const uint64_t *keys, uint64_t *sorted, uint32_t *perm, u
                        uint32_t L, uint32_t bits, void *temp, hipStream_t s);
 
 // Tile edge of the bucket join (rows of P and of Q per workgroup tile).
-constexpr uint32_t TILE = 128;
+constexpr uint32_t TILE = 256;
 
 // The buckets P and Q share, as records in key order within each table,
 // tables in order: record r is table t[r] and pq[r] = {p0, np, q0, nq}: P's
@@ -66,9 +66,11 @@ struct Records {
     uint4 *pq;
 };
 
-// Per row a 16-byte fingerprint of its keys in the first min(L, 16) tables
-// (byte t: 8 bits of a multiplicative hash of keys[t n + row]), for the
-// bucket join's first-table rule.
+// Per row a fingerprint of its keys in the first min(L, 64) tables, in
+// fp_chunks(L) chunks of 16 bytes (byte t: 8 bits of a multiplicative hash of
+// keys[t n + row]), for the bucket join's first-table rule.
+constexpr uint32_t FP_MAX = 64;
+constexpr uint32_t fp_chunks(uint32_t L) { return ((L < FP_MAX ? L : FP_MAX) + 15) / 16; }
 hipError_t launch_fingerprints(const uint64_t *keys, uint32_t n, uint32_t L, uint4 *fp,
                                hipStream_t s);
 
@@ -92,47 +94,40 @@ hipError_t launch_bucket_write(uint32_t n_p, uint32_t L, const uint32_t *flag,
                                hipStream_t s);
 
 // Tiles.  The records are cut into chunks of PACK_CHUNK; within a chunk,
-// consecutive records that each fit one tile (np, nq <= TILE) are packed
-// greedily into groups of at most TILE P rows and TILE Q rows, one tile per
-// group, and every other record is tiled alone by ceil(np / TILE) x
-// ceil(nq / TILE) tiles.  A descriptor is (first record, number of records:
-// 0 for a record tiled alone, with the record's table and rows copied into
-// it, else the group's size) and its first tile.
+// consecutive records of one table that each fit one tile (np, nq <= TILE) are
+// packed greedily into groups of at most TILE P rows and TILE Q rows, one tile
+// per group, and every other record is tiled alone by ceil(np / TILE) x
+// ceil(nq / TILE) tiles.  A descriptor is pq = {p0, np, q0, nq} and info =
+// {table, packed, first tile (64 bits)}: P's rows of the tiles are the entries
+// [t n_p + p0, + np) of the sorted permutation, or, for a group, of list_p, where
+// the group's rows (a subset of the sorted positions from its first record's
+// on) are written one after the other with their record's place in the group
+// in tag_p; Q's alike.
 // count pass (write = false): per chunk the number of descriptors and of
 // tiles (chunk_desc, chunk_tiles; *overflow set when a chunk's tiles do not
 // fit 32 bits); write pass: the descriptors at desc_off[chunk] with tiles
-// numbered from tile_off[chunk].
-constexpr uint32_t PACK_CHUNK = 256;
+// numbered from tile_off[chunk], and the lists.
+constexpr uint32_t PACK_CHUNK = 128;
 struct Descs {
-    uint4 *head;                  // {first record, count, table (count 0), 0}
-    uint4 *pq;                    // count 0: the record's {p0, np, q0, nq}
-    unsigned long long *tile;     // first tile
+    uint4 *pq, *info;
+};
+struct Lists {
+    uint32_t n_p, n_q;
+    const uint32_t *perm_p, *perm_q;      // L x n sorted position -> row
+    uint32_t *list_p, *list_q;            // L x n
+    uint8_t *tag_p, *tag_q;               // L x n
 };
 hipError_t launch_pack(const Records &rec, uint32_t n_rec, bool write, uint32_t *chunk_desc,
                        uint32_t *chunk_tiles, const unsigned long long *desc_off,
-                       const unsigned long long *tile_off, const Descs &desc,
+                       const unsigned long long *tile_off, const Descs &desc, const Lists &ls,
                        unsigned long long *overflow, hipStream_t s);
-
-// Row records (rows of rb <= REC_ROW bytes): per row one 128-byte line
-// holding the row zero-padded to a multiple of 32 bytes (the k-steps' reads),
-// then fingerprint bytes of its keys in the first min(L, F) tables, F = 112 -
-// that length (byte 16 rec_fp_chunk(rb) + t for table t, as in
-// launch_fingerprints; zero past L), and its squared norm (bytes 112..115:
-// int32 for int8 rows, float otherwise; zero for inner products, norm null),
-// so that the bucket join gathers each row with one request.
-constexpr uint32_t REC_ROW = 96, REC_BYTES = 128;
-__host__ __device__ constexpr uint32_t rec_fp_chunk(uint32_t rb) { return (rb + 31) / 32 * 2; }
-hipError_t launch_rowrec(const Rows &r, const void *norm, const uint64_t *keys, uint32_t L,
-                         uint8_t *out, hipStream_t s);
 
 struct JoinArgs {
     Rows P, Q;
-    const uint8_t *rec_p, *rec_q;         // row records, or null (rows, norms, fp)
     uint32_t L;
-    const uint32_t *perm_p, *perm_q;      // L x n sorted-position -> row
+    Lists ls;
     const uint64_t *keys_p, *keys_q;      // L x n row -> key (first-table rule)
     const uint4 *fp_p, *fp_q;             // per row: launch_fingerprints
-    Records rec;
     Descs desc;
     uint32_t n_desc;
     uint64_t n_tiles;

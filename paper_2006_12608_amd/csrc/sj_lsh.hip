@@ -710,70 +710,136 @@ __global__ void __launch_bounds__(256) bucket_write_kernel(uint32_t n_p, uint64_
     rec.pq[r] = make_uint4((uint32_t)(at % n_p), f_np[at], f_q0[at], f_nq[at]);
 }
 
-// One block per chunk of PACK_CHUNK records: the sizes go to LDS and the
-// first thread walks them in order (greedy packing, see sj_lsh.h).
+// One block per chunk of PACK_CHUNK records (see sj_lsh.h).  The sizes of the
+// records that fit a tile are prefix-summed; then the first wave forms the
+// groups, each in one step: lane k tests whether records i .. i + k still fit.
+// In the write pass the block copies the groups' rows to their lists, a thread
+// per row.  (One thread walking the records took 70 us for 660 000 of them.)
 __global__ void __launch_bounds__(256) pack_kernel(Records rec, uint32_t n_rec, int write,
                                                    uint32_t *chunk_desc, uint32_t *chunk_tiles,
                                                    const unsigned long long *desc_off,
                                                    const unsigned long long *tile_off, Descs desc,
-                                                   unsigned long long *overflow)
+                                                   Lists ls, unsigned long long *overflow)
 {
-    static_assert(PACK_CHUNK == 256, "one record per thread");
+    static_assert(PACK_CHUNK <= 256, "one record per thread");
     __shared__ uint4 spq[PACK_CHUNK];
-    __shared__ uint32_t st[PACK_CHUNK];
-    const uint32_t c = blockIdx.x, r0 = c * PACK_CHUNK, tid = threadIdx.x;
+    __shared__ uint32_t st[PACK_CHUNK], sfirst[PACK_CHUNK];
+    __shared__ uint32_t PS[PACK_CHUNK + 1], QS[PACK_CHUNK + 1], sw[8];
+    const uint32_t c = blockIdx.x, r0 = c * PACK_CHUNK, tid = threadIdx.x, lane = tid & 63;
     const uint32_t rn = min((uint32_t)PACK_CHUNK, n_rec - r0);
+    uint4 pq = make_uint4(0, 0, 0, 0);
     if (tid < rn) {
-        spq[tid] = rec.pq[r0 + tid];
+        pq = rec.pq[r0 + tid];
+        spq[tid] = pq;
         st[tid] = rec.t[r0 + tid];
     }
+    const bool big = pq.y > TILE || pq.w > TILE;
+    uint32_t ip = big ? 0u : pq.y, iq = big ? 0u : pq.w;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t up = __shfl_up(ip, o, 64), uq = __shfl_up(iq, o, 64);
+        if ((int)lane >= o) {
+            ip += up;
+            iq += uq;
+        }
+    }
+    if (lane == 63) {
+        sw[tid >> 6] = ip;
+        sw[4 + (tid >> 6)] = iq;
+    }
     __syncthreads();
-    if (tid != 0)
-        return;
-    const uint64_t dbase = write ? desc_off[c] : 0, tbase = write ? tile_off[c] : 0;
-    uint32_t nd = 0;
-    uint64_t nt = 0;
-    uint32_t gs = 0, gp = 0, gq = 0, gc = 0;   // the open group: first, rows, records
-    auto emit = [&](uint32_t first, uint32_t count, uint64_t tiles) {
-        if (write) {
-            desc.head[dbase + nd] = make_uint4(r0 + first, count, count ? 0u : st[first], 0u);
-            if (count == 0)
-                desc.pq[dbase + nd] = spq[first];
-            desc.tile[dbase + nd] = tbase + nt;
-        }
-        ++nd;
-        nt += tiles;
-    };
-    for (uint32_t i = 0; i < rn; ++i) {
-        const uint32_t np = spq[i].y, nq = spq[i].w;
-        if (np > TILE || nq > TILE) {
-            if (gc) {
-                emit(gs, gc, 1);
-                gc = 0;
+    for (uint32_t w = 0; w < tid >> 6; ++w) {
+        ip += sw[w];
+        iq += sw[4 + w];
+    }
+    if (tid < PACK_CHUNK) {   // inclusive sums (a chunk's rows fit 32 bits)
+        PS[tid + 1] = ip;
+        QS[tid + 1] = iq;
+    }
+    if (tid == 0)
+        PS[0] = QS[0] = 0;
+    __syncthreads();
+    if (tid < 64) {
+        const uint64_t dbase = write ? desc_off[c] : 0, tbase = write ? tile_off[c] : 0;
+        uint32_t nd = 0;
+        uint64_t nt = 0;
+        auto emit = [&](uint4 rows, uint32_t table, uint32_t packed, uint64_t tiles) {
+            if (write && lane == 0) {
+                const uint64_t tl = tbase + nt;
+                desc.pq[dbase + nd] = rows;
+                desc.info[dbase + nd] = make_uint4(table, packed, (uint32_t)tl, (uint32_t)(tl >> 32));
             }
-            emit(i, 0, (uint64_t)((np + TILE - 1) / TILE) * ((nq + TILE - 1) / TILE));
-            continue;
+            ++nd;
+            nt += tiles;
+        };
+        for (uint32_t i = 0; i < rn;) {
+            const uint4 ri = spq[i];
+            const uint32_t ti = st[i];
+            if (ri.y > TILE || ri.w > TILE) {
+                emit(ri, ti, 0, (uint64_t)((ri.y + TILE - 1) / TILE) * ((ri.w + TILE - 1) / TILE));
+                if (lane == 0)
+                    sfirst[i] = 0xffffffffu;
+                ++i;
+                continue;
+            }
+            uint32_t e = i;   // the group is [i, e)
+            for (;;) {
+                const uint32_t k = e + lane;
+                bool ok = k < rn;
+                if (ok)
+                    ok = spq[k].y <= TILE && spq[k].w <= TILE && st[k] == ti &&
+                         PS[k + 1] - PS[i] <= TILE && QS[k + 1] - QS[i] <= TILE;
+                const uint64_t m = __ballot(ok);
+                const uint32_t run = m == ~0ull ? 64u : (uint32_t)__builtin_ctzll(~m);
+                if (lane < run)
+                    sfirst[k] = i;
+                e += run;
+                if (run < 64)
+                    break;
+            }
+            if (e == i + 1) {   // alone in its tile: no list
+                if (lane == 0)
+                    sfirst[i] = 0xffffffffu;
+                emit(ri, ti, 0, 1);
+            } else {
+                emit(make_uint4(ri.x, PS[e] - PS[i], ri.z, QS[e] - QS[i]), ti, 1, 1);
+            }
+            i = e;
         }
-        if (gc && (gp + np > TILE || gq + nq > TILE)) {
-            emit(gs, gc, 1);
-            gc = 0;
+        if (!write && lane == 0) {
+            chunk_desc[c] = nd;
+            chunk_tiles[c] = (uint32_t)min(nt, (uint64_t)0xffffffffu);
+            if (nt > 0xffffffffull)
+                atomicMax(overflow, 1ull);
         }
-        if (gc == 0) {
-            gs = i;
-            gp = gq = 0;
-        }
-        gp += np;
-        gq += nq;
-        ++gc;
     }
-    if (gc)
-        emit(gs, gc, 1);
-    if (!write) {
-        chunk_desc[c] = nd;
-        chunk_tiles[c] = (uint32_t)min(nt, (uint64_t)0xffffffffu);
-        if (nt > 0xffffffffull)
-            atomicMax(overflow, 1ull);
-    }
+    if (!write)
+        return;
+    __syncthreads();
+    // the groups' rows: x is the row's place among the chunk's packed rows
+    auto copy = [&](const uint32_t *S, bool q) {
+        const uint32_t total = S[rn];
+        for (uint32_t x = tid; x < total; x += 256) {
+            uint32_t lo = 0, hi = rn;   // the last record with S[lo] <= x
+            while (hi - lo > 1) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (S[mid] <= x)
+                    lo = mid;
+                else
+                    hi = mid;
+            }
+            const uint32_t first = sfirst[lo];
+            if (first == 0xffffffffu)
+                continue;
+            const size_t tb = (size_t)st[lo] * (q ? ls.n_q : ls.n_p);
+            const uint32_t p0 = q ? spq[lo].z : spq[lo].x, d0 = q ? spq[first].z : spq[first].x;
+            const size_t dst = tb + d0 + (x - S[first]);
+            (q ? ls.list_q : ls.list_p)[dst] = (q ? ls.perm_q : ls.perm_p)[tb + p0 + (x - S[lo])];
+            (q ? ls.tag_q : ls.tag_p)[dst] = (uint8_t)(lo - first);
+        }
+    };
+    copy(PS, false);
+    copy(QS, true);
 }
 
 // ------------------------------------------------------------ bucket join
@@ -796,522 +862,485 @@ __device__ __forceinline__ bool matches(typename sjk::Mma<DT>::val_t acc,
     }
 }
 
-// A workgroup of 4 waves takes a contiguous range of the tiles (see the
-// descriptors in sj_lsh.h): a tile of a record tiled alone holds up to TILE
-// of its P rows and TILE of its Q rows; a packed tile holds the P rows and
-// the Q rows of a group of records, each row tagged with its record's place
-// in the group, and only pairs with equal tags (the same bucket) are
-// candidates.  The rows are gathered through the tables' sorted permutations
-// into LDS in chunks of 128 bytes of each row (16-byte chunks, rows padded by
-// one chunk), wave (wr, wc) multiplies its 64 x 64 quarter (2 x 2 blocks of
-// 32 x 32: per k-step two A- and two B-fragments for four MFMAs) over the
-// chunk's k-steps, and the epilogue applies the exact test to the candidates,
-// drops pairs that share a bucket in an earlier table (so every pair is
-// reported once) and appends the rest with one atomic per wave and block.
-// With row records (REC) each row comes with its fingerprint and norm in one
-// 128-byte line: the load of a row's 8 chunks brings all three into LDS.
-template <int DT, int MET, bool REC>
-__global__ void __launch_bounds__(256, 4) join_kernel(JoinArgs g)
+// Whether rows i of P and j of Q agree in a table before t (the first-table
+// rule: such a pair is reported there).  Tables with a fingerprint byte first
+// (equal keys give equal bytes), each equal byte confirmed with the keys; later
+// tables by their keys, 8 per round of independent loads.
+__device__ __forceinline__ bool in_earlier_table(const JoinArgs &g, uint32_t i, uint32_t j,
+                                                 uint32_t t)
+{
+    if (t == 0)
+        return false;
+    const uint32_t fc = fp_chunks(g.L), tf = t < FP_MAX ? t : FP_MAX;
+    for (uint32_t c = 0; 16 * c < tf; ++c) {
+        const uint4 fi = g.fp_p[(size_t)i * fc + c], fj = g.fp_q[(size_t)j * fc + c];
+        const uint32_t xw[4] = {fi.x ^ fj.x, fi.y ^ fj.y, fi.z ^ fj.z, fi.w ^ fj.w};
+        uint32_t eq = 0;   // bit u: byte u (table 16 c + u) equal
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t x = xw[q];
+            const uint32_t y = ~(((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x | 0x7f7f7f7fu);
+            eq |= (((y >> 7) & 1u) | ((y >> 14) & 2u) | ((y >> 21) & 4u) | ((y >> 28) & 8u))
+                  << (4 * q);
+        }
+        const uint32_t rem = tf - 16 * c;
+        eq &= rem >= 16 ? 0xffffu : (1u << rem) - 1u;
+        while (eq) {
+            const uint32_t t2 = 16 * c + __builtin_ctz(eq);
+            eq &= eq - 1;
+            if (g.keys_p[(size_t)t2 * g.P.n + i] == g.keys_q[(size_t)t2 * g.Q.n + j])
+                return true;
+        }
+    }
+    for (uint32_t t2 = FP_MAX; t2 < t; t2 += 8) {
+        bool same = false;
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) {
+            const uint32_t tt = t2 + u < t ? t2 + u : t - 1;
+            same |= g.keys_p[(size_t)tt * g.P.n + i] == g.keys_q[(size_t)tt * g.Q.n + j];
+        }
+        if (same)
+            return true;
+    }
+    return false;
+}
+
+// The bucket join.  A persistent workgroup of 8 waves takes a contiguous range
+// of the tiles (TILE x TILE results at most; descriptors in sj_lsh.h) and walks
+// it as one stream of stages, a stage being 128 bytes of each row of a tile.
+// Bound by the gathers: every stage needs loads that depend on loads (the
+// descriptor, the rows' indices, the rows), so they run ahead by whole stages
+// and a stage waits for all of its loads once, at its end:
+//   rows of the next stage (the tile's next 128 bytes, or the next tile's first)
+//   straight into the other LDS buffer; with a tile's first stage the row
+//   indices (and tags) of the tile after the next; with its last stage the
+//   next tile's norms; descriptors one ahead, through the scalar path.
+// Rows of 128-byte stages are 8 chunks of 16 bytes, chunk c of row r at position
+// c ^ (r / 2 % 8) of the row: 16 consecutive rows' reads of one chunk hit all
+// banks.  Wave (wr, wc) of 4 x 2 multiplies rows 64 wr .. by columns 128 wc ..
+// (2 x 4 blocks of 32 x 32).  Tiles of 256 x 256 instead of 128 x 128 read a
+// bucket's rows once or twice instead of two or three times.  Measured against
+// 128 x 128 tiles with four workgroups per CU that each ran the chain of loads
+// tile by tile: 262144 x 256 fp16, 16 tables x 10 signs 2150 -> 1765 us (5.4
+// TB/s of gathers); 1048576 x 64 int8, 16 tables x 6 values 4160 -> 2890 us, and
+// the 300 us for copying rows, norms and fingerprints into records are gone.
+// Matches go to an LDS list (JCAP pairs with their table); the first-table rule,
+// a chain of loads per match, then runs for the list at once, a thread per
+// match, and reserves output slots per wave.  A block of results whose matches
+// do not fit the list's end is resolved by its wave.
+// FAR: operands of 4 GiB or more, rows through registers (64-bit addresses).
+constexpr int JT = 512;            // threads
+constexpr uint32_t JCAP = 1024;    // list entries: a whole 32 x 32 block fits an empty list
+
+template <int DT, int MET, bool FAR>
+__global__ void __launch_bounds__(JT) join_kernel(JoinArgs g)
 {
     typedef sjk::Mma<DT> M;
     typedef typename M::acc_t acc_t;
     typedef typename M::val_t V;
-    constexpr int CS = 9;            // LDS positions per tile row: 8 chunks + 1 pad
-    constexpr int LPT = TILE / 32;   // rows each thread loads per operand and chunk
-    __shared__ i32x4 sA[TILE * CS], sB[TILE * CS];
-    __shared__ uint32_t sIP[TILE], sIQ[TILE];
-    __shared__ V sNP[TILE], sNQ[TILE];
-    __shared__ uint8_t sGP[TILE], sGQ[TILE];                 // row's record in the group
-    __shared__ uint32_t sRT[TILE];                           // group record's table
-    // With row records each wave stages up to OUTW of its pairs here and
-    // reserves their slots with one atomic per flush (the records leave room
-    // in LDS); otherwise it reserves once per tile with matches.
-    constexpr uint32_t OUTW = REC ? 64 : 1;
-    __shared__ uint64_t sOut[4][OUTW];
-    // used only while a packed tile's row indices are gathered, before the
-    // rows themselves go to sA: the group's row prefix sums and its records'
-    // first positions
-    uint2 *const sR0 = (uint2 *)sA;
-    uint32_t *const sPS = (uint32_t *)(sR0 + TILE), *const sQS = sPS + (TILE + 1);
-    static_assert(2 * TILE + 2 * (TILE + 1) <= TILE * CS * 4, "group tables fit sA");
+    constexpr bool L2N = MET == MET_L2;
+    constexpr int SA = 2, SB = 4;
+    constexpr int ROWS = 2 * TILE;              // P rows, then Q rows
+    constexpr int NLD = ROWS * 8 / JT;          // 16-byte loads per thread and stage
+    __shared__ __attribute__((aligned(16))) uint8_t s_r0[ROWS * 128], s_r1[ROWS * 128];
+    __shared__ uint32_t s_idx[3][ROWS];         // row indices of tiles k % 3
+    __shared__ uint8_t s_tag[3][ROWS];          // packed tiles: the rows' records
+    __shared__ V s_norm[2][L2N ? ROWS : 1];     // norms of tiles k % 2
+    __shared__ uint2 s_pair[JCAP];
+    __shared__ uint8_t s_pt[JCAP];
+    __shared__ uint32_t s_cnt, s_lim;           // list entries reserved; first that did not fit
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave >> 1, wc = wave & 1, half = lane >> 5, c32 = lane & 31;
+    const int wv = __builtin_amdgcn_readfirstlane(wave);
+    const int wr = wv >> 1, wc = wv & 1, half = lane >> 5, c32 = lane & 31;
     const uint32_t rb = g.P.row_bytes;   // == g.Q.row_bytes
-    const uint32_t lc = tid & 7, lr = tid >> 3;   // load chunk; rows lr + 32 e
-    // tables with a fingerprint byte: a record's chunks fc0 .. 6 hold 16 each
-    // (fc0: past the k-steps' 32-byte reads of the row); otherwise the first 16
-    const uint32_t fc0 = rec_fp_chunk(rb);
-    const uint32_t FT = REC ? 16 * (7 - fc0) : 16u;
-
-    // a contiguous range of tiles per workgroup: one search for the
-    // descriptor of its first tile, then a walk
-    const uint64_t per = (g.n_tiles + gridDim.x - 1) / gridDim.x;
-    const uint64_t T0 = (uint64_t)blockIdx.x * per;
-    const uint64_t T1 = min(T0 + per, g.n_tiles);
+    const uint32_t n_st = (rb + 127) / 128;
+    const uint64_t T0 = (uint64_t)blockIdx.x * g.n_tiles / gridDim.x;
+    const uint64_t T1 = (uint64_t)(blockIdx.x + 1) * g.n_tiles / gridDim.x;
     if (T0 >= T1)
-        return;   // the whole workgroup: no barrier is skipped by part of it
+        return;   // the whole workgroup
+
+    // ---- the tiles in order (all uniform)
+    // what stays with a tile, in one register: its rows of P and Q (9 bits
+    // each), its table, whether it is packed
+    struct Tile {
+        uint32_t w;
+        __device__ __forceinline__ uint32_t np() const { return w & 511u; }
+        __device__ __forceinline__ uint32_t nq() const { return (w >> 9) & 511u; }
+        __device__ __forceinline__ uint32_t t() const { return (w >> 18) & 255u; }
+        __device__ __forceinline__ bool packed() const { return (w >> 26) != 0; }
+    };
+    static_assert(TILE < 512, "9 bits");
     uint32_t dsc = 0;
     {
         uint32_t hi = g.n_desc;
         while (hi - dsc > 1) {
             const uint32_t mid = (dsc + hi) >> 1;
-            if (g.desc.tile[mid] <= T0)
+            const uint4 f = g.desc.info[mid];
+            if ((((uint64_t)f.w << 32) | f.z) <= T0)
                 dsc = mid;
             else
                 hi = mid;
         }
     }
-    uint64_t local = T0 - g.desc.tile[dsc];
-    uint32_t staged = 0;   // wave-uniform: pairs in sOut[wave]
-    // one reservation for the wave's staged pairs, then each lane writes a
-    // share of them
-    auto flush = [&]() {
-        unsigned long long base = 0;
-        if (lane == 0)
-            base = atomicAdd(g.counter, (unsigned long long)staged);
-        base = sjk::first_lane_u64(base);
-        for (uint32_t l = lane; l < staged; l += 64)
-            if (base + l < g.cap)
-                ((sjk::global_pair *)g.pairs)[base + l] = sOut[wave][l];
-        staged = 0;
-    };
-    for (uint64_t T = T0; T < T1; ++T) {
-        const uint4 hd = g.desc.head[dsc];
-        const uint32_t first = hd.x, ngrp = hd.y;
-        uint32_t rows_p, rows_q;
-        __syncthreads();   // the previous tile's reads of the LDS tables are done
-        if (ngrp == 0) {
-            // a record tiled alone: sub-tile (tp, tq) of its ntp x ntq tiles
-            const uint32_t t = hd.z;
-            const uint4 rq = g.desc.pq[dsc];
-            const uint32_t np = rq.y, nq = rq.w;
-            const uint32_t ntq = (nq + TILE - 1) / TILE, ntp = (np + TILE - 1) / TILE;
-            const uint32_t tp = (uint32_t)(local / ntq), tq = (uint32_t)(local % ntq);
-            rows_p = min(np - tp * TILE, TILE);
-            rows_q = min(nq - tq * TILE, TILE);
-            if (++local == (uint64_t)ntp * ntq) {
-                local = 0;
+    uint4 dpq = g.desc.pq[dsc], npq = g.desc.pq[min(dsc + 1, g.n_desc - 1)];
+    uint2 dinf, ninf = *(const uint2 *)&g.desc.info[min(dsc + 1, g.n_desc - 1)];   // table, packed
+    uint32_t tp, tq;
+    {
+        const uint4 f = g.desc.info[dsc];
+        dinf = make_uint2(f.x, f.y);
+        const uint32_t ntq = (dpq.w + TILE - 1) / TILE;
+        const uint64_t local = T0 - (((uint64_t)f.w << 32) | f.z);
+        tp = (uint32_t)(local / ntq);
+        tq = (uint32_t)(local % ntq);
+    }
+    // thread tid < TILE: P row tid of a tile, else Q row tid - TILE
+    const bool is_q = tid >= (int)TILE;
+    const uint32_t li = tid & (TILE - 1);
+    // the next tile: this thread's row of it is loaded (0xffffffff: none)
+    auto take = [&](uint32_t &idx, uint32_t &tag) -> Tile {
+        const uint32_t np = min(dpq.y - tp * TILE, TILE), nq = min(dpq.w - tq * TILE, TILE);
+        const uint32_t t = dinf.x;
+        const bool packed = dinf.y != 0;
+        const size_t at = is_q ? (size_t)t * g.Q.n + dpq.z + tq * TILE + li
+                               : (size_t)t * g.P.n + dpq.x + tp * TILE + li;
+        idx = 0xffffffffu;
+        tag = 0;
+        if (li < (is_q ? nq : np)) {
+            const uint32_t *src = packed ? (is_q ? g.ls.list_q : g.ls.list_p)
+                                         : (is_q ? g.ls.perm_q : g.ls.perm_p);
+            idx = src[at];
+            if (packed)
+                tag = (is_q ? g.ls.tag_q : g.ls.tag_p)[at];
+        }
+        if (++tq * TILE >= dpq.w) {
+            tq = 0;
+            if (++tp * TILE >= dpq.y) {
+                tp = 0;
                 ++dsc;
-            }
-            if (tid < (int)TILE) {
-                const bool okp = (uint32_t)tid < rows_p;
-                sIP[tid] = okp ? g.perm_p[(size_t)t * g.P.n + rq.x + tp * TILE + tid] : 0u;
-                const bool okq = (uint32_t)tid < rows_q;
-                sIQ[tid] = okq ? g.perm_q[(size_t)t * g.Q.n + rq.z + tq * TILE + tid] : 0u;
-                sGP[tid] = 0;
-                sGQ[tid] = 0;
-                if (tid == 0)
-                    sRT[0] = t;
-            }
-        } else {
-            // a packed group of ngrp records, one tile: the records' row
-            // counts, prefix-summed by the first two waves (ngrp <= TILE)
-            ++dsc;
-            local = 0;
-            uint32_t np = 0, nq = 0;
-            if (tid < (int)ngrp) {
-                const uint4 rq = g.rec.pq[first + tid];
-                np = rq.y;
-                nq = rq.w;
-                sRT[tid] = g.rec.t[first + tid];
-                sR0[tid] = make_uint2(rq.x, rq.z);
-            }
-            uint32_t ip = np, iq = nq;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t up = __shfl_up(ip, o, 64), uq = __shfl_up(iq, o, 64);
-                if (lane >= o) {
-                    ip += up;
-                    iq += uq;
-                }
-            }
-            if (tid == 63) {
-                sPS[TILE] = ip;   // first wave's totals, for the second wave
-                sQS[TILE] = iq;
-            }
-            __syncthreads();
-            if (tid >= 64 && tid < (int)TILE) {
-                ip += sPS[TILE];
-                iq += sQS[TILE];
-            }
-            __syncthreads();
-            if (tid < (int)TILE) {
-                sPS[tid + 1] = ip;   // inclusive sums: row prefix of record tid + 1
-                sQS[tid + 1] = iq;
-            }
-            if (tid == 0)
-                sPS[0] = sQS[0] = 0;
-            __syncthreads();
-            rows_p = sPS[ngrp];
-            rows_q = sQS[ngrp];
-            if (tid < (int)TILE) {
-                // this thread's P row and Q row: the record holding it (the last
-                // prefix at or below it), then its sorted position
-                uint32_t gi = 0, gj = 0, lo, hi;
-                if ((uint32_t)tid < rows_p) {
-                    lo = 0, hi = ngrp;
-                    while (hi - lo > 1) {
-                        const uint32_t mid = (lo + hi) >> 1;
-                        if (sPS[mid] <= (uint32_t)tid)
-                            lo = mid;
-                        else
-                            hi = mid;
-                    }
-                    gi = lo;
-                    sIP[tid] = g.perm_p[(size_t)sRT[gi] * g.P.n + sR0[gi].x + (tid - sPS[gi])];
-                } else {
-                    sIP[tid] = 0u;
-                }
-                if ((uint32_t)tid < rows_q) {
-                    lo = 0, hi = ngrp;
-                    while (hi - lo > 1) {
-                        const uint32_t mid = (lo + hi) >> 1;
-                        if (sQS[mid] <= (uint32_t)tid)
-                            lo = mid;
-                        else
-                            hi = mid;
-                    }
-                    gj = lo;
-                    sIQ[tid] = g.perm_q[(size_t)sRT[gj] * g.Q.n + sR0[gj].y + (tid - sQS[gj])];
-                } else {
-                    sIQ[tid] = 0u;
-                }
-                sGP[tid] = (uint8_t)gi;
-                sGQ[tid] = (uint8_t)gj;
+                dpq = npq;
+                dinf = ninf;
+                const uint32_t nx = min(dsc + 1, g.n_desc - 1);
+                npq = g.desc.pq[nx];
+                const uint2 f = *(const uint2 *)&g.desc.info[nx];
+                ninf = f;
             }
         }
-        __syncthreads();
-        if constexpr (MET == MET_L2 && !REC) {
-            if (tid < (int)TILE) {
-                sNP[tid] = (uint32_t)tid < rows_p ? ((const V *)g.norm_p)[sIP[tid]] : V(0);
-                sNQ[tid] = (uint32_t)tid < rows_q ? ((const V *)g.norm_q)[sIQ[tid]] : V(0);
-            }
-            __syncthreads();
+        return Tile{np | (nq << 9) | (t << 18) | (packed ? 1u << 26 : 0u)};
+    };
+    auto norm_load = [&](uint32_t idx) -> V {
+        V v = V(0);
+        if constexpr (L2N) {
+            if (idx != 0xffffffffu)
+                v = ((const V *)(is_q ? g.norm_q : g.norm_p))[idx];
         }
-        const bool packed = ngrp != 0;
-
-        acc_t acc[2][2];
+        return v;
+    };
+    // One stage of a tile's rows into `dst`: wave instruction k fills rows
+    // 8 k .. 8 k + 7; lane l its row l / 8 and position l % 8.  Rows past the
+    // tile's and chunks past a row read zeros (an offset past the buffer).
+    static_assert(JT / 64 * 8 * (NLD / 2) == (int)TILE, "a thread's first half of loads is P's");
+    const uint32_t bytes_p = FAR ? 0u : g.P.n * rb, bytes_q = FAR ? 0u : g.Q.n * rb;
+    auto rows_issue = [&](const uint32_t *idx, uint32_t st, uint8_t *dst) {
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-                acc[a][b] = acc_t{};
-        // rows are addressed through the tile's indices in LDS at every load
-        // (no per-thread row pointers: fewer registers, four waves per SIMD)
-        for (uint32_t kc = 0; kc < rb; kc += 128) {
-            if constexpr (REC) {
-                // whole records straight into LDS (one pass: rows of at most
-                // REC_ROW bytes).  A wave's load fills 64 consecutive 16-byte
-                // positions; position p holds chunk p % CS of the record of
-                // tile row p / CS (the pad position reloads chunk 0).  Rows
-                // past the tile's (index 0) load row 0: their results are
-                // never read.
-                constexpr int NLD = TILE * CS / 64;
-#pragma unroll
-                for (int k = 0; k < (NLD + 3) / 4; ++k) {
-                    const int kk = 4 * k + wave;
-                    if (kk < NLD) {
-                        const uint32_t pos = 64 * kk + lane, row = pos / CS, ch = pos % CS;
-                        const uint32_t cb = 16 * (ch == CS - 1 ? 0 : ch);
-                        sjk::buffer_load_lds16(g.rec_p, g.P.n * REC_BYTES, sIP[row] * REC_BYTES + cb,
-                                               (uint8_t *)sA + 1024 * kk);
-                        sjk::buffer_load_lds16(g.rec_q, g.Q.n * REC_BYTES, sIQ[row] * REC_BYTES + cb,
-                                               (uint8_t *)sB + 1024 * kk);
-                    }
-                }
-                __builtin_amdgcn_s_waitcnt(0);   // this wave's loads landed
-                __syncthreads();
+        for (int i = 0; i < NLD; ++i) {
+            const int k = wv + (JT / 64) * i;
+            const uint32_t row = 8 * k + (lane >> 3);
+            const uint32_t c = 128 * st + 16 * ((lane & 7) ^ ((row >> 1) & 7));
+            const uint32_t r = idx[row];
+            const bool in = r != 0xffffffffu && c < rb;
+            const bool q = i >= NLD / 2;         // 8 k >= TILE
+            if constexpr (FAR) {
+                i32x4 v = {0, 0, 0, 0};
+                if (in)
+                    v = *(const i32x4 *)((q ? g.Q.X : g.P.X) + (size_t)r * rb + c);
+                *(i32x4 *)(dst + 1024 * k + 16 * lane) = v;
             } else {
-                const uint32_t off = kc + 16 * lc;
-                const i32x4 z = {0, 0, 0, 0};
-                const bool in = off < rb;
-                i32x4 la[LPT], lb[LPT];
-#pragma unroll
-                for (int e = 0; e < LPT; ++e) {
-                    const uint32_t rr = lr + 32 * e;
-                    la[e] = rr < rows_p && in
-                                ? *(const i32x4 *)(g.P.X + (size_t)sIP[rr] * rb + off) : z;
-                    lb[e] = rr < rows_q && in
-                                ? *(const i32x4 *)(g.Q.X + (size_t)sIQ[rr] * rb + off) : z;
-                }
-                if (kc)
-                    __syncthreads();   // the previous chunk's fragments are read
-#pragma unroll
-                for (int e = 0; e < LPT; ++e) {
-                    sA[(lr + 32 * e) * CS + lc] = la[e];
-                    sB[(lr + 32 * e) * CS + lc] = lb[e];
-                }
-                __syncthreads();
+                sjk::buffer_load_lds16(q ? g.Q.X : g.P.X, q ? bytes_q : bytes_p,
+                                       in ? r * rb + c : q ? bytes_q : bytes_p, dst + 1024 * k);
             }
-            const uint32_t nks = min(4u, (rb - kc + 31) / 32);
-#pragma unroll
-            for (uint32_t ks = 0; ks < 4; ++ks)
-                if (ks < nks) {
-                    i32x4 fa[2], fb[2];
-#pragma unroll
-                    for (int a = 0; a < 2; ++a) {
-                        fa[a] = sA[(wr * 64 + 32 * a + c32) * CS + 2 * ks + half];
-                        fb[a] = sB[(wc * 64 + 32 * a + c32) * CS + 2 * ks + half];
-                    }
-#pragma unroll
-                    for (int a = 0; a < 2; ++a)
-#pragma unroll
-                        for (int b = 0; b < 2; ++b)
-                            acc[a][b] = M::mma(fa[a], fb[b], acc[a][b]);
-                }
         }
+    };
 
-        // epilogue.  Result register r of block (a, b) of this lane is (row
-        // wr*64 + 32a + 8(r/4) + 4 half + r%4, column wc*64 + 32b + c32).
-        // First the exact test of every result (in a packed tile also the
-        // bucket tags of its matches); then, only in a wave with a match, the
-        // first-table rule from the rows' key fingerprints, which the wave
-        // stages in the operand LDS the MFMAs no longer read.
-        // A record's norm is the first word of its chunk 7, its fingerprints
-        // chunks fc0..6 (the MFMAs read only the row's chunks).
-        auto norm_p = [&](uint32_t il) {
-            if constexpr (REC)
-                return *(const V *)&sA[il * CS + 7];
-            else
-                return sNP[il];
-        };
-        auto norm_q = [&](uint32_t jl) {
-            if constexpr (REC)
-                return *(const V *)&sB[jl * CS + 7];
-            else
-                return sNQ[jl];
-        };
-        uint32_t mk[2][2];
-        bool any = false;
+    // ---- list of matches
+    auto resolve_list = [&]() {
+        // every wave calls it, after a barrier; another barrier follows
+        const uint32_t n = min(min(s_cnt, s_lim), JCAP);
+        for (uint32_t b = 0; b < n; b += JT) {
+            const uint32_t e = b + tid;
+            bool keep = e < n;
+            uint2 pr = make_uint2(0, 0);
+            if (keep) {
+                pr = s_pair[e];
+                keep = !in_earlier_table(g, pr.x, pr.y, s_pt[e]);
+            }
+            const uint64_t bits = __ballot(keep);
+            unsigned long long base = 0;
+            if (bits != 0 && lane == 0)
+                base = atomicAdd(g.counter, (unsigned long long)__popcll(bits));
+            const uint64_t slot = sjk::first_lane_u64(base) + sjk::lanes_below(bits);
+            if (keep && slot < g.cap)
+                ((sjk::global_pair *)g.pairs)[slot] = sjk::pack_pair(pr.x, pr.y);
+        }
+    };
+    // matches m (bit r: register r of a block) of this lane's column jl, rows il0 + ..
+    auto push = [&](uint32_t m, uint32_t il0, uint32_t jl, uint32_t t, const uint32_t *idx) {
+        auto row_of = [&](int r) { return idx[il0 + 8 * (r >> 2) + (r & 3)]; };
+        auto totals = [&](uint32_t mm, uint32_t &tot, uint32_t &pre) {
+            const uint32_t cnt = (uint32_t)__builtin_popcount(mm);
+            tot = pre = 0;
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const uint32_t jl = wc * 64 + 32 * b + c32;
-            const bool jok = jl < rows_q;
-            const V ny = MET == MET_L2 ? norm_q(jl) : V(0);
+            for (int b = 0; b < 5; ++b) {
+                const uint64_t bits = __ballot((cnt >> b) & 1);
+                tot += (uint32_t)__popcll(bits) << b;
+                pre += sjk::lanes_below(bits) << b;
+            }
+        };
+        uint32_t tot, pre;
+        totals(m, tot, pre);
+        if (tot == 0)
+            return;
+        const uint32_t j = idx[TILE + jl];
+        uint32_t base = 0;
+        if (lane == 0)
+            base = atomicAdd(&s_cnt, tot);
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (base + tot <= JCAP) {
+            uint32_t at = base + pre;
+            while (m) {
+                const int r = __builtin_ctz(m);
+                m &= m - 1;
+                s_pair[at] = make_uint2(row_of(r), j);
+                s_pt[at++] = (uint8_t)t;
+            }
+            return;
+        }
+        // no room: this and every later reservation of the tile (entries from
+        // the first refused one on are not read)
+        if (lane == 0)
+            atomicMin(&s_lim, base);
+        uint32_t keep = 0;
+        while (m) {
+            const int r = __builtin_ctz(m);
+            m &= m - 1;
+            if (!in_earlier_table(g, row_of(r), j, t))
+                keep |= 1u << r;
+        }
+        totals(keep, tot, pre);
+        if (tot == 0)
+            return;
+        unsigned long long b = 0;
+        if (lane == 0)
+            b = atomicAdd(g.counter, (unsigned long long)tot);
+        uint64_t slot = sjk::first_lane_u64(b) + pre;
+        while (keep) {
+            const int r = __builtin_ctz(keep);
+            keep &= keep - 1;
+            if (slot < g.cap)
+                ((sjk::global_pair *)g.pairs)[slot] = sjk::pack_pair(row_of(r), j);
+            ++slot;
+        }
+    };
+
+    acc_t acc[SA][SB];
+    auto epilogue = [&](const Tile &x, const uint32_t *idx, const uint8_t *tag, const V *nm) {
+        const uint32_t i0 = 64 * wr + 4 * half;
+        uint32_t w[SB] = {};   // match bits: row block a of column block b at 16 a
 #pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                const uint32_t ib = wr * 64 + 32 * a + 4 * half;
+        for (int a = 0; a < SA; ++a) {
+            if (64 * wr + 32 * a >= (int)x.np())
+                continue;   // uniform
+            const uint32_t il0 = i0 + 32 * a;
+            V nx[L2N ? 16 : 1];
+            V nmin = V(0);
+            if constexpr (L2N) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    nx[r] = nm[il0 + 8 * (r >> 2) + (r & 3)];
+                    nmin = r == 0 ? nx[0] : sjk::vmin(nmin, nx[r]);
+                }
+            }
+#pragma unroll
+            for (int b = 0; b < SB; ++b) {
+                if (128 * wc + 32 * b >= (int)x.nq())
+                    continue;   // uniform
+                const uint32_t jl = 128 * wc + 32 * b + c32;
+                const V ny = L2N ? nm[TILE + jl] : V(0);
+                // a necessary condition from the block's largest product (rows
+                // and columns past the tile's have norm 0 and products 0 and
+                // are excluded below)
+                V mx = acc[a][b][0];
+#pragma unroll
+                for (int r = 1; r < 16; ++r)
+                    mx = sjk::vmax(mx, acc[a][b][r]);
+                if (__ballot(matches<DT, MET>(mx, nmin, ny, g)) == 0)
+                    continue;
                 uint32_t m = 0;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const uint32_t il = ib + 8 * (r >> 2) + (r & 3);
-                    const V nx = MET == MET_L2 ? norm_p(il) : V(0);
-                    const bool ok = jok && il < rows_p && matches<DT, MET>(acc[a][b][r], nx, ny, g);
+                    const uint32_t il = il0 + 8 * (r >> 2) + (r & 3);
+                    const bool ok = il < x.np() && matches<DT, MET>(acc[a][b][r], L2N ? nx[L2N ? r : 0] : V(0), ny, g);
                     m |= ok ? (1u << r) : 0u;
                 }
-                mk[a][b] = m;
-                any |= m != 0;
+                w[b] |= (jl < x.nq() ? m : 0u) << (16 * a);
             }
         }
-        if constexpr (!REC)
-            __syncthreads();   // every wave's MFMAs are done with sA and sB
-        if (__ballot(any) == 0)
-            continue;
-        uint4 *const wf = (uint4 *)sA + wave * 128;   // fingerprints: 64 P rows, 64 Q rows
-        if (!REC && g.L > 1) {
-            const uint32_t pr = wr * 64 + lane, qr = wc * 64 + lane;
-            const uint4 z4 = make_uint4(0u, 0u, 0u, 0u);
-            wf[lane] = pr < rows_p ? g.fp_p[sIP[pr]] : z4;
-            wf[64 + lane] = qr < rows_q ? g.fp_q[sIQ[qr]] : z4;
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        }
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const uint32_t jl = wc * 64 + 32 * b + c32;
-            const uint32_t j = sIQ[jl];
-            const uint32_t gq = sGQ[jl];
-            const uint32_t t = sRT[gq];   // the pair's table (its bucket's)
-#pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                const uint32_t ib = wr * 64 + 32 * a + 4 * half;
-                uint32_t m = mk[a][b];
-                if (__ballot(m != 0) == 0)
-                    continue;
-                if (packed) {
-                    // candidates of a packed tile: rows of the same bucket
-                    uint32_t mm = m;
-                    while (mm) {
-                        const int r = __builtin_ctz(mm);
-                        mm &= mm - 1;
-                        if (sGP[ib + 8 * (r >> 2) + (r & 3)] != gq)
-                            m &= ~(1u << r);
-                    }
-                }
-                if (t > 0 && m != 0) {
-                    // the first-table rule: drop the pair when its keys agree
-                    // in an earlier table.  Tables below FT by fingerprint (a
-                    // byte per table; equal keys give equal bytes), each equal
-                    // byte confirmed with the keys; later tables by their
-                    // keys, 8 tables per round of independent loads.
-                    const uint32_t tf = t < FT ? t : FT;
-                    uint32_t mm = m;
-                    while (mm) {
-                        const int r = __builtin_ctz(mm);
-                        mm &= mm - 1;
-                        const uint32_t il = ib + 8 * (r >> 2) + (r & 3);
-                        const uint32_t i = sIP[il];
-                        bool same = false;
-                        for (uint32_t c = 0; 16 * c < tf && !same; ++c) {
-                            const uint4 fi = REC ? ((const uint4 *)sA)[il * CS + fc0 + c]
-                                                 : wf[il - wr * 64];
-                            const uint4 fj = REC ? ((const uint4 *)sB)[jl * CS + fc0 + c]
-                                                 : wf[64 + (jl - wc * 64)];
-                            const uint32_t xw[4] = {fi.x ^ fj.x, fi.y ^ fj.y, fi.z ^ fj.z,
-                                                    fi.w ^ fj.w};
-                            uint32_t eq = 0;   // bit u: byte u (table 16 c + u) equal
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) {
-                                const uint32_t x = xw[q];
-                                const uint32_t y =
-                                    ~(((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x | 0x7f7f7f7fu);
-                                eq |= (((y >> 7) & 1u) | ((y >> 14) & 2u) | ((y >> 21) & 4u) |
-                                       ((y >> 28) & 8u)) << (4 * q);
-                            }
-                            const uint32_t rem = tf - 16 * c;
-                            eq &= rem >= 16 ? 0xffffu : (1u << rem) - 1u;
-                            while (eq && !same) {
-                                const uint32_t t2 = 16 * c + __builtin_ctz(eq);
-                                eq &= eq - 1;
-                                same = g.keys_p[(size_t)t2 * g.P.n + i] ==
-                                       g.keys_q[(size_t)t2 * g.Q.n + j];
-                            }
-                        }
-                        for (uint32_t t2 = FT; t2 < t && !same; t2 += 8) {
-#pragma unroll
-                            for (uint32_t u = 0; u < 8; ++u) {
-                                const uint32_t tt = t2 + u < t ? t2 + u : t - 1;
-                                same |= g.keys_p[(size_t)tt * g.P.n + i] ==
-                                        g.keys_q[(size_t)tt * g.Q.n + j];
-                            }
-                        }
-                        if (same)
-                            m &= ~(1u << r);
-                    }
-                }
-                mk[a][b] = m;
-            }
-        }
-        // one slot reservation for the wave's matches of the whole tile: the
-        // lanes' counts (at most 64) give the wave's total and each lane's
-        // prefix through seven ballots, and each lane writes its pairs in
-        // (block, register) order
-        const uint32_t cnt = (uint32_t)(__builtin_popcount(mk[0][0]) + __builtin_popcount(mk[1][0]) +
-                                        __builtin_popcount(mk[0][1]) + __builtin_popcount(mk[1][1]));
-        uint32_t tot = 0, pre = 0;
-#pragma unroll
-        for (int bit = 0; bit < 7; ++bit) {
-            const uint64_t bits = __ballot((cnt >> bit) & 1);
-            tot += (uint32_t)__popcll(bits) << bit;
-            pre += sjk::lanes_below(bits) << bit;
-        }
-        if (tot == 0)
-            continue;
-        if constexpr (REC) {
-            if (staged + tot > OUTW) {
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                flush();
-            }
-            if (tot <= OUTW) {
-                // stage: each lane's pairs at its prefix, in (block, register) order
-                uint32_t at = staged + pre;
-#pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    const uint32_t j = sIQ[wc * 64 + 32 * b + c32];
-#pragma unroll
-                    for (int a = 0; a < 2; ++a) {
-                        const uint32_t ib = wr * 64 + 32 * a + 4 * half;
-                        uint32_t m = mk[a][b];
-                        while (m) {
-                            const int r = __builtin_ctz(m);
-                            m &= m - 1;
-                            sOut[wave][at++] = sjk::pack_pair(sIP[ib + 8 * (r >> 2) + (r & 3)], j);
-                        }
-                    }
-                }
-                staged += tot;
+        static_assert(SB == 4 && SA == 2, "one word per column block");
+        if (__ballot((w[0] | w[1] | w[2] | w[3]) != 0) == 0)
+            return;
+#pragma nounroll
+        for (int s = 0; s < SA * SB; ++s) {
+            const int b = s >> 1, a = s & 1;
+            const uint32_t wb = b == 0 ? w[0] : b == 1 ? w[1] : b == 2 ? w[2] : w[3];
+            uint32_t m = (wb >> (16 * a)) & 0xffffu;
+            if (__ballot(m != 0) == 0)
                 continue;
-            }
-        }
-        unsigned long long base = 0;
-        if (lane == 0)
-            base = atomicAdd(g.counter, (unsigned long long)tot);
-        uint64_t pos = sjk::first_lane_u64(base) + pre;
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const uint32_t j = sIQ[wc * 64 + 32 * b + c32];
-#pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                const uint32_t ib = wr * 64 + 32 * a + 4 * half;
-                uint32_t m = mk[a][b];
-                while (m) {
-                    const int r = __builtin_ctz(m);
-                    m &= m - 1;
-                    if (pos < g.cap) {
-                        const uint32_t i = sIP[ib + 8 * (r >> 2) + (r & 3)];
-                        ((sjk::global_pair *)g.pairs)[pos] = sjk::pack_pair(i, j);
-                    }
-                    ++pos;
+            const uint32_t il0 = i0 + 32 * a, jl = 128 * wc + 32 * b + c32;
+            if (x.packed()) {
+                // rows of the same bucket only
+                const uint32_t tj = tag[TILE + jl];
+                uint32_t mm = m;
+                while (mm) {
+                    const int r = __builtin_ctz(mm);
+                    mm &= mm - 1;
+                    if (tag[il0 + 8 * (r >> 2) + (r & 3)] != tj)
+                        m &= ~(1u << r);
                 }
             }
+            push(m, il0, jl, x.t(), idx);
         }
+    };
+
+    // ---- prologue: indices of the first two tiles, the first tile's norms and
+    // first stage
+    uint64_t left = T1 - T0;   // tiles from the current one on
+    uint32_t idx0, tag0;
+    Tile cur = take(idx0, tag0);
+    s_idx[0][tid] = idx0;
+    s_tag[0][tid] = (uint8_t)tag0;
+    if constexpr (L2N)
+        s_norm[0][tid] = norm_load(idx0);
+    Tile nxt = cur;
+    if (left > 1) {
+        nxt = take(idx0, tag0);
+        s_idx[1][tid] = idx0;
+        s_tag[1][tid] = (uint8_t)tag0;
     }
-    if constexpr (REC) {
-        if (staged) {
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            flush();
+    Tile pend = nxt;   // the one after the next
+    if (tid == 0) {
+        s_cnt = 0;
+        s_lim = 0xffffffffu;
+    }
+    __syncthreads();
+    rows_issue(s_idx[0], 0, s_r0);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+
+    uint32_t k3 = 0, par = 0, st = 0;   // current tile mod 3 and mod 2, its stage
+    auto stage = [&](const uint8_t *buf, uint8_t *oth) __attribute__((always_inline)) -> bool {
+        const uint32_t n3 = k3 == 2 ? 0 : k3 + 1, f3 = n3 == 2 ? 0 : n3 + 1;
+        const bool first = st == 0, last = st + 1 == n_st;
+        // loads ahead
+        uint32_t idx = 0xffffffffu, tag = 0;
+        V nrm = V(0);
+        if (first && left > 2)
+            pend = take(idx, tag);
+        if (last && left > 1) {
+            if constexpr (L2N)
+                nrm = norm_load(s_idx[n3][tid]);
+            rows_issue(s_idx[n3], 0, oth);
+        } else if (!last) {
+            rows_issue(s_idx[k3], st + 1, oth);
         }
+        // products
+        if (64 * wr < (int)cur.np() && 128 * wc < (int)cur.nq()) {   // uniform
+            if (first) {
+#pragma unroll
+                for (int a = 0; a < SA; ++a)
+#pragma unroll
+                    for (int b = 0; b < SB; ++b)
+                        acc[a][b] = acc_t{};
+            }
+            const uint32_t nks = min(4u, (rb - 128 * st + 31) / 32);
+            const uint32_t sw = (c32 >> 1) & 7;   // (row / 2) % 8 of every row this lane reads
+            const uint8_t *pa = buf + (64 * wr + c32) * 128;
+            const uint8_t *pb = buf + (TILE + 128 * wc + c32) * 128;
+#pragma unroll
+            for (uint32_t ks = 0; ks < 4; ++ks)
+                if (ks < nks) {
+                    const uint32_t o = 16 * ((2 * ks + half) ^ sw);
+                    i32x4 fa[SA], fb[SB];
+#pragma unroll
+                    for (int a = 0; a < SA; ++a)
+                        fa[a] = *(const i32x4 *)(pa + 32 * 128 * a + o);
+#pragma unroll
+                    for (int b = 0; b < SB; ++b)
+                        fb[b] = *(const i32x4 *)(pb + 32 * 128 * b + o);
+#pragma unroll
+                    for (int a = 0; a < SA; ++a)
+#pragma unroll
+                        for (int b = 0; b < SB; ++b)
+                            acc[a][b] = M::mma(fa[a], fb[b], acc[a][b]);
+                }
+            if (last)
+                epilogue(cur, s_idx[k3], s_tag[k3], s_norm[par]);
+        }
+        __builtin_amdgcn_s_waitcnt(0);   // this stage's loads landed
+        if (first && left > 2) {
+            s_idx[f3][tid] = idx;
+            s_tag[f3][tid] = (uint8_t)tag;
+        }
+        if constexpr (L2N) {
+            if (last && left > 1)
+                s_norm[par ^ 1][tid] = nrm;
+        }
+        __syncthreads();
+        if (last) {
+            const uint32_t n_list = s_cnt;
+            __syncthreads();   // every wave has read it before the next tile's pushes
+            if (n_list >= JCAP / 2 || left == 1) {   // uniform
+                resolve_list();
+                __syncthreads();
+                if (tid == 0) {
+                    s_cnt = 0;
+                    s_lim = 0xffffffffu;
+                }
+                __syncthreads();
+            }
+            if (--left == 0)
+                return false;
+            cur = nxt;
+            nxt = pend;
+            k3 = n3;
+            par ^= 1;
+            st = 0;
+        } else {
+            ++st;
+        }
+        return true;
+    };
+    for (;;) {
+        if (!stage(s_r0, s_r1) || !stage(s_r1, s_r0))
+            break;
     }
 }
 
-// Fingerprints of the keys of the first min(L, 16) tables: byte t of fp[row]
-// is the top byte of keys[t n + row] times an odd constant, so rows with equal
-// keys in table t have equal bytes t (and rows with different keys rarely do).
+// Fingerprints (sj_lsh.h), a thread per row and 16 tables: byte t is the top
+// byte of keys[t n + row] times an odd constant, so rows with equal keys in
+// table t have equal bytes t (and rows with different keys rarely do).
 __global__ void __launch_bounds__(256) fingerprint_kernel(const uint64_t *keys, uint32_t n,
-                                                          uint32_t L, uint4 *fp)
+                                                          uint32_t L, uint32_t fc, uint4 *fp)
 {
-    const uint32_t row = blockIdx.x * 256 + threadIdx.x;
+    const uint32_t row = blockIdx.x * 256 + threadIdx.x, c = blockIdx.y;
     if (row >= n)
         return;
     uint32_t w[4] = {0u, 0u, 0u, 0u};
-    const uint32_t tl = L < 16 ? L : 16;
+    const uint32_t t0 = 16 * c, tl = min(L - t0, 16u);
     for (uint32_t t = 0; t < tl; ++t) {
-        const uint32_t byte = (uint32_t)((keys[(size_t)t * n + row] * 0x9E3779B97F4A7C15ull) >> 56);
+        const uint32_t byte =
+            (uint32_t)((keys[(size_t)(t0 + t) * n + row] * 0x9E3779B97F4A7C15ull) >> 56);
         w[t >> 2] |= byte << (8 * (t & 3));
     }
-    fp[row] = make_uint4(w[0], w[1], w[2], w[3]);
-}
-
-// Row records (sj_lsh.h): thread per row (the lanes' key loads are
-// coalesced over consecutive rows).  Chunk c in fc0 .. 6 holds the
-// fingerprint bytes of tables 16 (c - fc0) .. + 15 (byte u: the top byte of
-// the table's key times an odd constant), chunk 7 the norm.
-__global__ void __launch_bounds__(256) rowrec_kernel(Rows r, const uint32_t *norm,
-                                                     const uint64_t *keys, uint32_t L, i32x4 *out)
-{
-    const uint32_t row = blockIdx.x * 256 + threadIdx.x;
-    if (row >= r.n)
-        return;
-    const uint32_t fc0 = rec_fp_chunk(r.row_bytes);
-    i32x4 *o = out + (size_t)row * (REC_BYTES / 16);
-    for (uint32_t c = 0; c < REC_BYTES / 16; ++c) {
-        i32x4 v = {0, 0, 0, 0};
-        if (16 * c < r.row_bytes) {
-            v = *(const i32x4 *)(r.X + (size_t)row * r.row_bytes + 16 * c);
-        } else if (c >= fc0 && c < 7) {
-            const uint32_t t0 = 16 * (c - fc0);
-            uint32_t w[4] = {0u, 0u, 0u, 0u};
-            for (uint32_t u = 0; u < 16 && t0 + u < L; ++u) {
-                const uint32_t byte =
-                    (uint32_t)((keys[(size_t)(t0 + u) * r.n + row] * 0x9E3779B97F4A7C15ull) >> 56);
-                w[u >> 2] |= byte << (8 * (u & 3));
-            }
-            v = i32x4{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-        } else if (c == 7 && norm) {
-            v[0] = (int)norm[row];
-        }
-        o[c] = v;
-    }
+    fp[(size_t)row * fc + c] = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
 template <int DT>
@@ -1333,12 +1362,14 @@ hipError_t launch_keys_t(const Rows &r, uint32_t d, uint32_t L, uint32_t k, cons
 template <int DT, int MET>
 hipError_t launch_join_t(const JoinArgs &g, int num_cus, hipStream_t s)
 {
-    const uint64_t want = (uint64_t)num_cus * 8;
-    const uint32_t grid = (uint32_t)(g.n_tiles < want ? g.n_tiles : want);
-    if (g.rec_p)
-        hipLaunchKernelGGL((join_kernel<DT, MET, true>), dim3(grid), dim3(256), 0, s, g);
+    // one workgroup per CU (their LDS fills it)
+    const uint32_t grid = (uint32_t)(g.n_tiles < (uint64_t)num_cus ? g.n_tiles : num_cus);
+    // the row gathers' 32-bit offsets reach 4 GiB
+    const uint64_t far = (uint64_t)max(g.P.n, g.Q.n) * g.P.row_bytes;
+    if (far < 0xffffffffull)
+        hipLaunchKernelGGL((join_kernel<DT, MET, false>), dim3(grid), dim3(JT), 0, s, g);
     else
-        hipLaunchKernelGGL((join_kernel<DT, MET, false>), dim3(grid), dim3(256), 0, s, g);
+        hipLaunchKernelGGL((join_kernel<DT, MET, true>), dim3(grid), dim3(JT), 0, s, g);
     return hipGetLastError();
 }
 
@@ -1485,19 +1516,9 @@ hipError_t launch_fingerprints(const uint64_t *keys, uint32_t n, uint32_t L, uin
 {
     if (n == 0)
         return hipSuccess;
-    hipLaunchKernelGGL(fingerprint_kernel, dim3((n + 255) / 256), dim3(256), 0, s, keys, n, L, fp);
-    return hipGetLastError();
-}
-
-hipError_t launch_rowrec(const Rows &r, const void *norm, const uint64_t *keys, uint32_t L,
-                         uint8_t *out, hipStream_t s)
-{
-    if (r.n == 0)
-        return hipSuccess;
-    if (r.row_bytes > REC_ROW)
-        return hipErrorInvalidValue;
-    hipLaunchKernelGGL(rowrec_kernel, dim3((r.n + 255) / 256), dim3(256), 0, s, r,
-                       (const uint32_t *)norm, keys, L, (i32x4 *)out);
+    const uint32_t fc = fp_chunks(L);
+    hipLaunchKernelGGL(fingerprint_kernel, dim3((n + 255) / 256, fc), dim3(256), 0, s, keys, n, L,
+                       fc, fp);
     return hipGetLastError();
 }
 
@@ -1543,14 +1564,14 @@ hipError_t launch_bucket_write(uint32_t n_p, uint32_t L, const uint32_t *flag,
 
 hipError_t launch_pack(const Records &rec, uint32_t n_rec, bool write, uint32_t *chunk_desc,
                        uint32_t *chunk_tiles, const unsigned long long *desc_off,
-                       const unsigned long long *tile_off, const Descs &desc,
+                       const unsigned long long *tile_off, const Descs &desc, const Lists &ls,
                        unsigned long long *overflow, hipStream_t s)
 {
     if (n_rec == 0)
         return hipSuccess;
     hipLaunchKernelGGL(pack_kernel, dim3((n_rec + PACK_CHUNK - 1) / PACK_CHUNK), dim3(256), 0, s,
                        rec, n_rec, write ? 1 : 0, chunk_desc, chunk_tiles, desc_off, tile_off,
-                       desc, overflow);
+                       desc, ls, overflow);
     return hipGetLastError();
 }
 

@@ -98,10 +98,10 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
     const size_t a_bytes = sjl::widened_bytes(dtype, L, k, d);
 
     // scratch: [rows P][rows Q][norms P][norms Q][keys P][keys Q][sorted P]
-    //          [sorted Q][perm P][perm Q][fingerprints P, Q][row records P, Q]
-    //          [bucket marks, sizes and numbers]
+    //          [sorted Q][perm P][perm Q][fingerprints P, Q][packed tiles' rows
+    //          and tags P, Q][bucket marks, sizes and numbers]
     //          [records][chunk counts and offsets][descriptors][scan partials]
-    //          [counters][sort temp][widened projections]
+    //          [counters][sort temp][widened projections][own output]
     size_t need = 0;
     auto take = [&](size_t bytes) {
         const size_t at = need;
@@ -118,14 +118,14 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
     const size_t off_sq = self ? off_sp : take((size_t)L * n_q * 8);
     const size_t off_pp = take((size_t)L * n_p * 4);
     const size_t off_pq = self ? off_pp : take((size_t)L * n_q * 4);
-    // short rows travel to the bucket join as records with their norm and
-    // fingerprints (one cache line per row); longer ones with 16 fingerprint
-    // bytes per row in an array of their own
-    const bool use_rec = krow <= sjl::REC_ROW && n_max * sjl::REC_BYTES <= 0xffffffffull;
-    const size_t off_fpp = use_rec ? 0 : take((size_t)n_p * 16);
-    const size_t off_fpq = use_rec || self ? off_fpp : take((size_t)n_q * 16);
-    const size_t off_recp = use_rec ? take((size_t)n_p * sjl::REC_BYTES) : 0;
-    const size_t off_recq = use_rec && !self ? take((size_t)n_q * sjl::REC_BYTES) : off_recp;
+    const uint32_t fc = sjl::fp_chunks(L);
+    const size_t off_fpp = L > 1 ? take((size_t)n_p * 16 * fc) : 0;
+    const size_t off_fpq = L > 1 && !self ? take((size_t)n_q * 16 * fc) : off_fpp;
+    // the rows of packed tiles (a self-join's buckets are the same on both sides)
+    const size_t off_lp = take(pos_p * 4);
+    const size_t off_lq = self ? off_lp : take((size_t)L * n_q * 4);
+    const size_t off_tp = take(pos_p);
+    const size_t off_tq = self ? off_tp : take((size_t)L * n_q);
     const size_t off_flag = take(pos_p * 4);
     const size_t off_fnp = take(pos_p * 4);
     const size_t off_fq0 = take(pos_p * 4);
@@ -137,9 +137,8 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
     const size_t off_ctile = take(chunk_cap * 4);
     const size_t off_doff = take(chunk_cap * 8);
     const size_t off_toff = take(chunk_cap * 8);
-    const size_t off_dhead = take(bp_cap * 16);
+    const size_t off_dinfo = take(bp_cap * 16);
     const size_t off_dpq = take(bp_cap * 16);
-    const size_t off_dtile = take(bp_cap * 8);
     const size_t off_part = take(sjk::scan_partials_size(pos_p > chunk_cap ? pos_p : chunk_cap) * 8);
     // counters: [0] pair evaluations, [1] records, [2] descriptors, [3] [4]
     // the hash's fix queues, [5] tiles, [6] tile overflow, [7] bucket rows
@@ -183,12 +182,7 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
             SJ_HIP(sjl::launch_keys(dtype, rq, d, L, k, scr + off_aw, B, w, keys_q, s));
     }
     uint4 *fp_p = (uint4 *)(scr + off_fpp), *fp_q = (uint4 *)(scr + off_fpq);
-    if (use_rec) {
-        SJ_HIP(sjl::launch_rowrec(rp, l2 ? scr + off_np : nullptr, keys_p, L, scr + off_recp, s));
-        if (!self)
-            SJ_HIP(sjl::launch_rowrec(rq, l2 ? scr + off_nq : nullptr, keys_q, L,
-                                      scr + off_recq, s));
-    } else if (L > 1) {
+    if (L > 1) {
         SJ_HIP(sjl::launch_fingerprints(keys_p, n_p, L, fp_p, s));
         if (!self)
             SJ_HIP(sjl::launch_fingerprints(keys_q, n_q, L, fp_q, s));
@@ -216,19 +210,21 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
     SJ_HIP(hipStreamSynchronize(s));
     const uint64_t n_rec = c->h_small[0];
     const uint64_t n_chunk = (n_rec + sjl::PACK_CHUNK - 1) / sjl::PACK_CHUNK;
-    const sjl::Descs desc{(uint4 *)(scr + off_dhead), (uint4 *)(scr + off_dpq),
-                          (unsigned long long *)(scr + off_dtile)};
+    const sjl::Descs desc{(uint4 *)(scr + off_dpq), (uint4 *)(scr + off_dinfo)};
+    const sjl::Lists lists{n_p, n_q, perm_p, perm_q,
+                           (uint32_t *)(scr + off_lp), (uint32_t *)(scr + off_lq),
+                           scr + off_tp, scr + off_tq};
     uint32_t *cdesc = (uint32_t *)(scr + off_cdesc), *ctile = (uint32_t *)(scr + off_ctile);
     unsigned long long *doff = (unsigned long long *)(scr + off_doff);
     unsigned long long *toff = (unsigned long long *)(scr + off_toff);
     SJ_HIP(sjl::launch_pack(rec, (uint32_t)n_rec, false, cdesc, ctile, nullptr, nullptr, desc,
-                            cnt + 6, s));
+                            lists, cnt + 6, s));
     if (n_chunk) {
         SJ_HIP(sjk::launch_scan(cdesc, n_chunk, doff, part, cnt + 2, s));
         SJ_HIP(sjk::launch_scan(ctile, n_chunk, toff, part, cnt + 5, s));
     }
-    SJ_HIP(sjl::launch_pack(rec, (uint32_t)n_rec, true, cdesc, ctile, doff, toff, desc, cnt + 6,
-                            s));
+    SJ_HIP(sjl::launch_pack(rec, (uint32_t)n_rec, true, cdesc, ctile, doff, toff, desc, lists,
+                            cnt + 6, s));
     SJ_HIP(hipEventRecord(c->ev[2], s));
     unsigned long long hc[8];
     SJ_HIP(hipMemcpyAsync(hc, cnt, sizeof hc, hipMemcpyDeviceToHost, s));
@@ -241,15 +237,11 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
     g.P = rp;
     g.Q = rq;
     g.L = L;
-    g.perm_p = perm_p;
-    g.perm_q = perm_q;
+    g.ls = lists;
     g.keys_p = keys_p;
     g.keys_q = keys_q;
-    g.fp_p = use_rec ? nullptr : fp_p;
-    g.fp_q = use_rec ? nullptr : fp_q;
-    g.rec_p = use_rec ? scr + off_recp : nullptr;
-    g.rec_q = use_rec ? scr + off_recq : nullptr;
-    g.rec = rec;
+    g.fp_p = fp_p;
+    g.fp_q = fp_q;
     g.desc = desc;
     g.n_desc = (uint32_t)hc[2];
     g.n_tiles = n_tiles;

@@ -208,6 +208,60 @@ def test_lsh_many_tables_first_table_rule(d, L, thr):
     assert len(g) == len(ref) > 0
 
 
+@pytest.mark.parametrize("metric,every", [("ip", False), ("l2", False), ("ip", True)])
+@pytest.mark.parametrize("dtype,d", [("i8", 16), ("i8", 64), ("f16", 72), ("bf16", 300)])
+def test_lsh_bucket_sizes_around_the_tile(dtype, d, metric, every):
+    """Buckets of chosen sizes around the bucket join's tile edge (256 rows),
+    next to small ones that are packed into one tile: the table's three
+    functions are the signs of three coordinates.  Two tables (the second with
+    the functions reversed: the same buckets), so every match of the second is
+    dropped by the first-table rule; all-matching thresholds overflow the
+    workgroup's list of matches.  Integer inputs: the oracle's set."""
+    rng = np.random.default_rng(9100 + d)
+
+    def rows(sizes):
+        v = rng.integers(-4, 5, size=(sum(sizes), d))
+        b = np.repeat(np.arange(8), sizes)
+        for u in range(3):
+            v[:, u] = np.where((b >> u) & 1, 4, -4)
+        return v[rng.permutation(len(v))]
+    P, Q = rows([256, 257, 1, 255, 3, 128, 128, 600]), rows([256, 1, 300, 255, 7, 128, 129, 513])
+    # a few per cent of a bucket's pairs
+    thr = -1e6 if every else 48 + 10 * d ** 0.5 if metric == "ip" else 13.33 * (d - 3) - 28 * d ** 0.5
+    w = workloads.gen.Workload("bucket sizes", metric, dtype, workloads.encode(P, dtype),
+                               workloads.encode(Q, dtype), thr, np.zeros((0, 2), np.int64))
+    A = np.zeros((6, d), np.int8)
+    for u in range(3):
+        A[u, u] = A[3 + u, 2 - u] = 1
+    h = workloads.LshParams(2, 3, A, np.zeros(6, np.int32), 0)
+    g, ref, *_ = run_lsh(w, h)
+    assert len(ref) > 0
+    if every:
+        assert len(ref) == 256 * 256 + 257 + 300 + 255 * 255 + 21 + 128 * 128 + 128 * 129 + 600 * 513
+
+
+def test_lsh_operand_past_4_gib():
+    """Rows past 4 GiB (66000 x 32768 fp16): the bucket join's gathers use
+    64-bit addresses.  One bucket (k = 0): the all-pairs join's pairs."""
+    import torch
+    import paper_2006_12608_amd as sj
+    n, d = 66000, 32768
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    P = torch.empty((n, d), dtype=torch.float16, device="cuda")
+    for a in range(0, n, 6000):
+        P[a:a + 6000] = torch.randint(-1, 2, (min(6000, n - a), d), generator=g, device="cuda",
+                                      dtype=torch.int8)
+    Q = P[torch.randint(0, n, (70,), generator=g, device="cuda")].contiguous()
+    Q[0] = P[n - 1]
+    say("lsh past 4 GiB")
+    A = torch.zeros((0, d), dtype=torch.int8, device="cuda")
+    got, cand = sj.join_lsh(P, Q, 500.0, "ip", L=1, k=0, A=A)
+    want = sj.join_ip(P, Q, 500.0)
+    assert cand == n * 70 and len(want) >= 70
+    assert np.array_equal(sorted_pairs(got), sorted_pairs(want))
+
+
 def test_lsh_overflow_and_errors():
     import torch
     import paper_2006_12608_amd as sj
