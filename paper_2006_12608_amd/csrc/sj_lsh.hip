@@ -291,181 +291,243 @@ __global__ void pad_b_kernel(const int8_t *A, int8_t *Ab, uint32_t d, uint32_t r
     }
 }
 
-// Upper bounds of Euclidean norms: rows of A (int8, d entries) or of X
-// (stored rows); the double sum is rounded up by a relative 2^-20.
-__global__ void anorm_kernel(const int8_t *A, uint32_t d, uint32_t n_fn, float *out)
+// Upper bounds of the projection rows' Euclidean norms, a wave per row: the
+// double sum rounded up by a relative 2^-20.
+__global__ void __launch_bounds__(64) anorm_kernel(const int8_t *A, uint32_t d, float *out)
 {
-    const uint32_t f = blockIdx.x * 256 + threadIdx.x;
-    if (f < n_fn) {
-        double s = 0.0;
-        for (uint32_t m = 0; m < d; ++m)
-            s += (double)A[(uint64_t)f * d + m] * A[(uint64_t)f * d + m];
-        out[f] = (float)(sqrt(s) * (1.0 + 0x1p-20));
-    }
-}
-
-template <int DT>
-__global__ void xnorm_kernel(Rows r, uint32_t d, float *out)
-{
-    const uint32_t row = blockIdx.x * 256 + threadIdx.x;
-    if (row < r.n) {
-        const uint8_t *x = r.X + (size_t)row * r.row_bytes;
-        double s = 0.0;
-        for (uint32_t c = 0; c < padded_d<DT>(d) / Chunk<DT>::E; ++c) {
-            const i32x4 v = *(const i32x4 *)(x + 16 * c);
+    const uint32_t f = blockIdx.x;
+    double s = 0.0;
+    for (uint32_t m = threadIdx.x; m < d; m += 64)
+        s += (double)A[(uint64_t)f * d + m] * A[(uint64_t)f * d + m];
 #pragma unroll
-            for (int e = 0; e < Chunk<DT>::E; ++e) {
-                const double xe = (double)Chunk<DT>::at(v, e);
-                s += xe * xe;
-            }
-        }
-        out[row] = (float)(sqrt(s) * (1.0 + 0x1p-20));
-    }
+    for (int o = 32; o > 0; o >>= 1)
+        s += __shfl_xor(s, o, 64);
+    if (threadIdx.x == 0)
+        out[f] = (float)(sqrt(s) * (1.0 + 0x1p-20));
 }
 
-// A wave takes 32 rows (A-fragments of KS k-steps in registers) and sweeps the
-// L k functions in MFMA blocks of 32; each lane folds its function's value
-// into the (row, table) key in LDS (64-bit atomic OR), and marks uncertain
-// ones; then the wave writes the keys and queues each (row, table) with its
-// mask of uncertain functions (one queue atomic per wave).
-template <int DT, int KS>
+// floor(n / w) mod 2^32 for integers |n| < 2^53, 0 < w < 2^31, given inv = 1 / w:
+// the quotient from the reciprocal is within one of the floor, which the
+// remainder (exact) settles.
+__device__ __forceinline__ uint32_t floor_div_low(double n, double w, double inv)
+{
+    double t = __builtin_floor(n * inv);
+    const double r = __builtin_fma(-t, w, n);
+    t += r < 0.0 ? -1.0 : r >= w ? 1.0 : 0.0;
+    return (uint32_t)__builtin_fma(-__builtin_floor(t * 0x1p-32), 0x1p32, t);
+}
+
+// Functions come in MFMA blocks of at most 32: whole tables (32 / k of them) or,
+// for k > 32, one half of a table (its first 32 functions, then the rest).  A
+// workgroup of 4 waves stages each block's projection rows in LDS (the next
+// block's while the current one is multiplied); each wave holds 32 rows as
+// A-fragments of KS k-steps in registers.  In a result register the lanes of a
+// half hold one row's 32 functions, so a sign ballot is that row's bits of the
+// block, and a row's keys are bit ranges of one word; quantised values pass
+// through LDS to be put together.  Uncertain decisions are ballots too: each
+// (row, table) with some goes to the wave's list and from there to the queue,
+// one reservation per 64.  262144 x 256 fp16, 160 signs: 121 us (196 us with
+// 64-bit LDS atomics per decision, every wave reading all projection rows
+// itself, and 53 us for the row norms in a kernel of their own); 1048576 x 64
+// int8, 96 quantised values: 98 us (179 us with a double division per value).
+template <int DT, int KS, bool QUANT>
 __global__ void __launch_bounds__(256) keys_mfma_kernel(
-    Rows r, uint32_t L, uint32_t k, const uint8_t *Ah, const float *anorm, const float *xnorm,
-    const int32_t *B, int32_t w, float gam, uint64_t *keys, uint4 *fix,
-    unsigned long long *nfix)
+    Rows r, uint32_t L, uint32_t k, const uint8_t *Ah, const float *anorm, const int32_t *B,
+    int32_t w, float gam, uint64_t *keys, uint4 *fix, unsigned long long *nfix)
 {
     typedef sjk::Mma<DT> M;
     typedef typename M::acc_t acc_t;
-    __shared__ unsigned long long skey[4][32 * 64];
-    __shared__ unsigned long long sunc[4][32][HF_MAX / 64];   // uncertain (row, function)
+    constexpr int CPR = 2 * KS;                       // chunks per staged row
+    constexpr int SWS = KS == 2 ? 2 : KS == 4 ? 1 : 0;   // chunk c of row i at c ^ (i >> SWS) % 16:
+    constexpr int SWM = CPR < 16 ? CPR - 1 : 15;         // 16 rows' reads of a chunk hit all banks
+    constexpr bool EXACT = DT == DT_I8;               // sums exact: nothing uncertain
+    __shared__ __attribute__((aligned(16))) uint8_t s_b0[32 * CPR * 16], s_b1[32 * CPR * 16];
+    __shared__ uint32_t s_val[QUANT ? 4 : 1][QUANT ? 32 : 1][33];
+    __shared__ uint4 s_fix[EXACT ? 1 : 4][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wv = __builtin_amdgcn_readfirstlane(wave);
     const int h = lane >> 5, c32 = lane & 31;
-    const uint32_t row0 = (blockIdx.x * 4 + wave) * 32;
-    const uint32_t nf = L * k;
-    const uint32_t beta = 64 / k;
-    const uint64_t low = beta >= 64 ? ~0ull : (1ull << beta) - 1;
-    unsigned long long *kk = skey[wave];
-    for (uint32_t i = lane; i < 32 * L; i += 64)
-        kk[i] = 0ull;
-    for (uint32_t i = lane; i < 32 * (HF_MAX / 64); i += 64)
-        sunc[wave][i / (HF_MAX / 64)][i % (HF_MAX / 64)] = 0ull;
+    const uint32_t row0 = (blockIdx.x * 4 + wv) * 32, row = row0 + c32;
+    const uint32_t nf = L * k, beta = 64 / k;
+    const uint32_t low = beta >= 32 ? 0xffffffffu : (1u << beta) - 1u;
+    const uint32_t tpb = k <= 32 ? 32 / k : 1;        // tables per block
+    const uint32_t n_blk = k <= 32 ? (L + tpb - 1) / tpb : 2 * L;
+    auto first_fn = [&](uint32_t b) { return k <= 32 ? b * tpb * k : (b >> 1) * k + 32 * (b & 1); };
+    auto n_fn = [&](uint32_t b) {
+        return k <= 32 ? min(tpb * k, nf - b * tpb * k) : b & 1 ? k - 32 : 32u;
+    };
+
     i32x4 af[KS];
-    const uint32_t arow = row0 + c32;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
         const uint32_t off = 32 * ks + 16 * h;
-        af[ks] = arow < r.n && off < r.row_bytes
-                     ? *(const i32x4 *)(r.X + (size_t)arow * r.row_bytes + off)
+        af[ks] = row < r.n && off < r.row_bytes
+                     ? *(const i32x4 *)(r.X + (size_t)row * r.row_bytes + off)
                      : i32x4{0, 0, 0, 0};
     }
-    float xn[16] = {};
-    if constexpr (DT != DT_I8) {
+    // upper bounds of the rows' norms (as anorm_kernel's): this lane's half of
+    // row c32, then both halves, then the rows of its result registers
+    float xn[EXACT ? 1 : 16];
+    if constexpr (!EXACT) {
+        double s = 0.0;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const uint32_t R = row0 + 8 * (q >> 2) + 4 * h + (q & 3);
-            xn[q] = R < r.n ? xnorm[R] : 0.0f;
-        }
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int e = 0; e < Chunk<DT>::E; ++e) {
+                const double x = Chunk<DT>::at(af[ks], e);
+                s += x * x;
+            }
+        s += __shfl_xor(s, 32, 64);
+        const float nx = (float)(sqrt(s) * (1.0 + 0x1p-20));
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+            xn[q] = __shfl(nx, 8 * (q >> 2) + 4 * h + (q & 3), 64);
     }
-    __builtin_amdgcn_wave_barrier();
-    for (uint32_t f0 = 0; f0 < nf; f0 += 32) {
-        const uint32_t f = f0 + c32;
+    auto stage = [&](uint32_t b, uint8_t *dst) {
+        const uint32_t f0 = first_fn(b), n = n_fn(b), bytes = nf * r.row_bytes;
+#pragma unroll
+        for (int i = 0; i < (KS + 3) / 4; ++i) {
+            const int kk = 4 * i + wv;
+            if (kk < KS) {
+                const uint32_t p = 64 * kk + lane, fr = p / CPR, pos = p % CPR;
+                const uint32_t off = 16 * (pos ^ ((fr >> SWS) & SWM));
+                const bool in = fr < n && off < r.row_bytes;
+                sjk::buffer_load_lds16(Ah, bytes, in ? (f0 + fr) * r.row_bytes + off : bytes,
+                                       dst + 1024 * kk);
+            }
+        }
+    };
+    uint32_t n_list = 0;   // wave-uniform: entries of s_fix[wave]
+    auto flush = [&]() {
+        unsigned long long base = 0;
+        if (lane == 0)
+            base = atomicAdd(nfix, (unsigned long long)n_list);
+        base = sjk::first_lane_u64(base);
+        if ((uint32_t)lane < n_list)
+            fix[base + lane] = s_fix[EXACT ? 0 : wave][lane];
+        n_list = 0;
+    };
+    auto queue = [&](bool some, uint32_t t, uint64_t m) {
+        const uint64_t bits = __ballot(some);
+        const uint32_t n = (uint32_t)__popcll(bits);
+        if (n == 0)
+            return;
+        if (n_list + n > 64) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            flush();
+        }
+        if (some)
+            s_fix[EXACT ? 0 : wave][n_list + sjk::lanes_below(bits)] =
+                make_uint4(row, t, (uint32_t)m, (uint32_t)(m >> 32));
+        n_list += n;
+    };
+
+    uint64_t key0 = 0, unc0 = 0;   // k > 32: the table's first half
+    auto block = [&](uint32_t b, const uint8_t *cur, uint8_t *nxt) __attribute__((always_inline)) {
+        if (b + 1 < n_blk)
+            stage(b + 1, nxt);
         acc_t acc = acc_t{};
+        const uint32_t sw = (c32 >> SWS) & SWM;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            const uint32_t off = 32 * ks + 16 * h;
-            const i32x4 b = f < nf && off < r.row_bytes
-                                ? *(const i32x4 *)(Ah + (size_t)f * r.row_bytes + off)
-                                : i32x4{0, 0, 0, 0};
-            acc = M::mma(af[ks], b, acc);
+            const i32x4 fb = *(const i32x4 *)(cur + c32 * CPR * 16 + 16 * ((2 * ks + h) ^ sw));
+            acc = M::mma(af[ks], fb, acc);
         }
-        if (f >= nf)
-            continue;
-        const uint32_t t = f / k, u = f - t * k;
-        const float na = DT == DT_I8 ? 0.0f : anorm[f];
-        const double bf = w > 0 ? (double)B[f] : 0.0;
+        const uint32_t f0 = first_fn(b), n = n_fn(b), f = f0 + c32;
+        const bool fok = (uint32_t)c32 < n;
+        const float na = EXACT || !fok ? 0.0f : anorm[f];
+        const double bf = QUANT && fok ? (double)B[f] : 0.0;
+        const double wd = (double)w, inv = 1.0 / wd;
+        uint32_t word = 0, unc = 0;   // row c32's sign bits / uncertain functions
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
-            const int Rl = 8 * (q >> 2) + 4 * h + (q & 3);
-            uint64_t contrib;
-            bool sure;
-            if constexpr (DT == DT_I8) {
-                // int8 products summed exactly in int32: every decision is the
-                // exact one (and the double evaluation's, which is exact too)
-                const int32_t z = acc[q];
-                sure = true;
-                if (w == 0)
-                    contrib = (uint64_t)(z >= 0) << u;
+            const int ra = 8 * (q >> 2) + (q & 3);   // the lower half's row; ra + 4 the upper's
+            bool sure = true;
+            uint32_t v = 0;
+            bool pos = false;
+            if constexpr (EXACT) {
+                if constexpr (QUANT)
+                    v = floor_div_low((double)acc[q] + bf, wd, inv) & low;
                 else
-                    contrib = ((uint64_t)(int64_t)floor(((double)z + bf) / (double)w) & low)
-                              << (beta * u);
+                    pos = acc[q] >= 0;
             } else {
-                const float z = acc[q];
-                const float e = gam * na * xn[q];
-                if (w == 0) {
-                    sure = __builtin_fabsf(z) > e;
-                    contrib = (uint64_t)(z >= 0.0f) << u;
-                } else {
-                    const double lo = floor(((double)z - (double)e + bf) / (double)w);
-                    const double hi = floor(((double)z + (double)e + bf) / (double)w);
+                const float z = acc[q], e = gam * na * xn[q];
+                if constexpr (QUANT) {
+                    const double lo = floor(((double)z - (double)e + bf) / wd);
+                    const double hi = floor(((double)z + (double)e + bf) / wd);
                     sure = lo == hi;
-                    contrib = ((uint64_t)(int64_t)lo & low) << (beta * u);
+                    v = sure ? (uint32_t)((uint64_t)(int64_t)lo) & low : 0u;
+                } else {
+                    sure = __builtin_fabsf(z) > e;
+                    pos = z >= 0.0f && sure;
+                }
+                const uint64_t nb = __ballot(fok && !sure);
+                if (nb != 0) {   // uniform, rare
+                    unc = c32 == ra ? (uint32_t)nb : unc;
+                    unc = c32 == ra + 4 ? (uint32_t)(nb >> 32) : unc;
                 }
             }
-            if (sure)
-                atomicOr(&kk[Rl * L + t], (unsigned long long)contrib);
-            else
-                atomicOr(&sunc[wave][Rl][f >> 6], 1ull << (f & 63));
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    // the uncertain functions of (row Rl, table t): bits t k .. t k + k - 1 of
-    // the row's function mask
-    auto umask = [&](uint32_t Rl, uint32_t t) -> uint64_t {
-        const uint32_t b0 = t * k;
-        const unsigned long long *m = sunc[wave][Rl];
-        uint64_t v = m[b0 >> 6] >> (b0 & 63);
-        if ((b0 & 63) != 0 && (b0 >> 6) + 1 < HF_MAX / 64)
-            v |= m[(b0 >> 6) + 1] << (64 - (b0 & 63));
-        return k >= 64 ? v : v & ((1ull << k) - 1);
-    };
-    // keys (certain bits), then the queue entries of the wave with one atomic
-    uint32_t total = 0;
-    for (uint32_t i0 = 0; i0 < 32 * L; i0 += 64) {
-        const uint32_t i = i0 + lane;
-        bool q = false;
-        if (i < 32 * L) {
-            const uint32_t Rl = i / L, t = i - Rl * L;
-            const uint32_t R = row0 + Rl;
-            if (R < r.n) {
-                keys[(size_t)t * r.n + R] = kk[i];
-                q = umask(Rl, t) != 0;
+            if constexpr (QUANT) {
+                s_val[wave][ra + 4 * h][c32] = v;
+            } else {
+                const uint64_t bits = __ballot(pos);
+                word = c32 == ra ? (uint32_t)bits : word;
+                word = c32 == ra + 4 ? (uint32_t)(bits >> 32) : word;
             }
         }
-        total += (uint32_t)__popcll(__ballot(q));
-    }
-    if (total == 0)
-        return;
-    unsigned long long base = 0;
-    if (lane == 0)
-        base = atomicAdd(nfix, (unsigned long long)total);
-    base = sjk::first_lane_u64(base);
-    for (uint32_t i0 = 0; i0 < 32 * L; i0 += 64) {
-        const uint32_t i = i0 + lane;
-        uint64_t m = 0;
-        uint32_t Rl = 0, t = 0;
-        if (i < 32 * L) {
-            Rl = i / L;
-            t = i - Rl * L;
-            if (row0 + Rl < r.n)
-                m = umask(Rl, t);
+        if constexpr (QUANT) {
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
-        const uint64_t bits = __ballot(m != 0);
-        if (m != 0)
-            fix[base + sjk::lanes_below(bits)] =
-                make_uint4(row0 + Rl, t, (uint32_t)m, (uint32_t)(m >> 32));
-        base += (uint32_t)__popcll(bits);
+        // the block's tables: lanes of half h take tables h, h + 2, ...
+        const uint32_t kb = k <= 32 ? k : n;             // functions per table here
+        const uint32_t t0 = k <= 32 ? b * tpb : b >> 1, nt = k <= 32 ? n / k : 1;
+        for (uint32_t tl2 = 0; tl2 < nt; tl2 += 2) {
+            const uint32_t tl = tl2 + h;
+            const bool on = tl < nt && row < r.n;
+            const uint32_t sh = on ? tl * kb : 0u, mask = kb >= 32 ? 0xffffffffu : (1u << kb) - 1u;
+            uint64_t key = 0, um = (unc >> sh) & mask;
+            if constexpr (QUANT) {
+                if (on)
+                    for (uint32_t u = 0; u < kb; ++u)
+                        key |= (uint64_t)s_val[wave][c32][sh + u]
+                               << (beta * (u + (k > 32 ? 32 * (b & 1) : 0)));
+            } else {
+                key = (word >> sh) & mask;
+                if (k > 32)
+                    key <<= 32 * (b & 1);
+            }
+            if (k > 32) {
+                um <<= 32 * (b & 1);
+                if (!(b & 1)) {   // the first half: kept for the second
+                    key0 = key;
+                    unc0 = um;
+                    continue;
+                }
+                key |= key0;
+                um |= unc0;
+            }
+            if (on)
+                keys[(size_t)(t0 + tl) * r.n + row] = key;
+            if constexpr (!EXACT)
+                queue(on && um != 0, t0 + tl, um);
+        }
+        __builtin_amdgcn_s_waitcnt(0);   // the next block's rows landed
+        __syncthreads();
+    };
+    stage(0, s_b0);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    for (uint32_t b = 0; b < n_blk; b += 2) {
+        block(b, s_b0, s_b1);
+        if (b + 1 < n_blk)
+            block(b + 1, s_b1, s_b0);
+    }
+    if constexpr (!EXACT) {
+        if (n_list) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            flush();
+        }
     }
 }
 
@@ -1415,18 +1477,22 @@ bool keys_fast_applies(int dtype, uint32_t row_bytes, uint32_t L, uint32_t k, in
 
 size_t keys_fast_bytes(uint32_t n_max, uint32_t L, uint32_t k, uint32_t row_bytes)
 {
-    // fp16 / bf16 projection rows, their norms, row norms, the fix queue
-    return (size_t)L * k * row_bytes + 256 + (size_t)L * k * 4 + 256 + (size_t)n_max * 4 + 256 +
-           (size_t)L * n_max * 16;
+    // fp16 / bf16 projection rows, their norms, the fix queue
+    return (size_t)L * k * row_bytes + 256 + (size_t)L * k * 4 + 256 + (size_t)L * n_max * 16;
 }
 
 template <int DT, int KS>
 static void launch_mfma_t(const Rows &r, uint32_t L, uint32_t k, const uint8_t *Ah,
-                          const float *an, const float *xn, const int32_t *B, int32_t w, float gam, uint64_t *keys, uint4 *fix,
-                          unsigned long long *nfix, hipStream_t s)
+                          const float *an, const int32_t *B, int32_t w, float gam, uint64_t *keys,
+                          uint4 *fix, unsigned long long *nfix, hipStream_t s)
 {
-    hipLaunchKernelGGL((keys_mfma_kernel<DT, KS>), dim3((r.n + 127) / 128), dim3(256), 0, s, r,
-                       L, k, Ah, an, xn, B, w, gam, keys, fix, nfix);
+    const dim3 grid((r.n + 127) / 128);
+    if (w > 0)
+        hipLaunchKernelGGL((keys_mfma_kernel<DT, KS, true>), grid, dim3(256), 0, s, r, L, k, Ah,
+                           an, B, w, gam, keys, fix, nfix);
+    else
+        hipLaunchKernelGGL((keys_mfma_kernel<DT, KS, false>), grid, dim3(256), 0, s, r, L, k, Ah,
+                           an, B, w, gam, keys, fix, nfix);
 }
 
 template <int DT>
@@ -1437,8 +1503,7 @@ static hipError_t keys_fast_t(const Rows &r, uint32_t d, uint32_t L, uint32_t k,
     const uint32_t nf = L * k;
     uint8_t *Ah = ws;
     float *an = (float *)(ws + (((size_t)nf * r.row_bytes + 255) & ~(size_t)255));
-    float *xn = (float *)((uint8_t *)an + (((size_t)nf * 4 + 255) & ~(size_t)255));
-    uint4 *fix = (uint4 *)((uint8_t *)xn + (((size_t)r.n * 4 + 255) & ~(size_t)255));
+    uint4 *fix = (uint4 *)((uint8_t *)an + (((size_t)nf * 4 + 255) & ~(size_t)255));
     if constexpr (DT == DT_I8) {
         // the projection rows as int8 operand rows; sums exact: no norms, no queue
         if (widen) {
@@ -1452,10 +1517,8 @@ static hipError_t keys_fast_t(const Rows &r, uint32_t d, uint32_t L, uint32_t k,
             const uint64_t n_out = (uint64_t)nf * rl;
             hipLaunchKernelGGL(widen_h_kernel<DT>, dim3((unsigned)((n_out + 255) / 256)),
                                dim3(256), 0, s, A, (uint16_t *)Ah, d, rl, n_out);
-            hipLaunchKernelGGL(anorm_kernel, dim3((nf + 255) / 256), dim3(256), 0, s, A, d, nf,
-                               an);
+            hipLaunchKernelGGL(anorm_kernel, dim3(nf), dim3(64), 0, s, A, d, an);
         }
-        hipLaunchKernelGGL(xnorm_kernel<DT>, dim3((r.n + 255) / 256), dim3(256), 0, s, r, d, xn);
     }
     // twice the fp32 and double summation bounds for d terms
     const double dd = d ? (double)d : 1.0;
@@ -1464,13 +1527,13 @@ static hipError_t keys_fast_t(const Rows &r, uint32_t d, uint32_t L, uint32_t k,
     const float gam = (float)(2.0 * (g24 + g53) * (1.0 + 0x1p-10));
     const uint32_t ks = (r.row_bytes + 31) / 32;
     if (ks <= 2)
-        launch_mfma_t<DT, 2>(r, L, k, Ah, an, xn, B, w, gam, keys, fix, nfix, s);
+        launch_mfma_t<DT, 2>(r, L, k, Ah, an, B, w, gam, keys, fix, nfix, s);
     else if (ks <= 4)
-        launch_mfma_t<DT, 4>(r, L, k, Ah, an, xn, B, w, gam, keys, fix, nfix, s);
+        launch_mfma_t<DT, 4>(r, L, k, Ah, an, B, w, gam, keys, fix, nfix, s);
     else if (ks <= 8)
-        launch_mfma_t<DT, 8>(r, L, k, Ah, an, xn, B, w, gam, keys, fix, nfix, s);
+        launch_mfma_t<DT, 8>(r, L, k, Ah, an, B, w, gam, keys, fix, nfix, s);
     else
-        launch_mfma_t<DT, 16>(r, L, k, Ah, an, xn, B, w, gam, keys, fix, nfix, s);
+        launch_mfma_t<DT, 16>(r, L, k, Ah, an, B, w, gam, keys, fix, nfix, s);
     if constexpr (DT != DT_I8)
         hipLaunchKernelGGL(fix_kernel<DT>, dim3(512), dim3(256), 0, s, r, d, k,
                            (const typename Chunk<DT>::a_t *)Aw, B, w, fix,
