@@ -878,26 +878,64 @@ __global__ void __launch_bounds__(256) pack_kernel(Records rec, uint32_t n_rec, 
     if (!write)
         return;
     __syncthreads();
-    // the groups' rows: x is the row's place among the chunk's packed rows
+    // the groups' rows alone, prefix-summed again (a chunk of large buckets has
+    // few); then x is a row's place among them
+    const bool mine = tid < rn && sfirst[tid] != 0xffffffffu;
+    ip = mine ? pq.y : 0u;
+    iq = mine ? pq.w : 0u;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t up = __shfl_up(ip, o, 64), uq = __shfl_up(iq, o, 64);
+        if ((int)lane >= o) {
+            ip += up;
+            iq += uq;
+        }
+    }
+    if (lane == 63) {
+        sw[tid >> 6] = ip;
+        sw[4 + (tid >> 6)] = iq;
+    }
+    __syncthreads();
+    for (uint32_t w = 0; w < tid >> 6; ++w) {
+        ip += sw[w];
+        iq += sw[4 + w];
+    }
+    if (tid < PACK_CHUNK) {
+        PS[tid + 1] = ip;
+        QS[tid + 1] = iq;
+    }
+    __syncthreads();
     auto copy = [&](const uint32_t *S, bool q) {
         const uint32_t total = S[rn];
-        for (uint32_t x = tid; x < total; x += 256) {
-            uint32_t lo = 0, hi = rn;   // the last record with S[lo] <= x
-            while (hi - lo > 1) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (S[mid] <= x)
-                    lo = mid;
-                else
-                    hi = mid;
+        constexpr int U = 4;   // rows per thread and round: their loads overlap
+        for (uint32_t x0 = tid; x0 < total; x0 += 256 * U) {
+            uint32_t row[U];
+            size_t dst[U];
+            uint8_t tag[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t x = min(x0 + 256 * u, total - 1);
+                uint32_t lo = 0, hi = rn;   // the last record with S[lo] <= x
+                while (hi - lo > 1) {
+                    const uint32_t mid = (lo + hi) >> 1;
+                    if (S[mid] <= x)
+                        lo = mid;
+                    else
+                        hi = mid;
+                }
+                const uint32_t first = sfirst[lo];
+                const size_t tb = (size_t)st[lo] * (q ? ls.n_q : ls.n_p);
+                const uint32_t p0 = q ? spq[lo].z : spq[lo].x, d0 = q ? spq[first].z : spq[first].x;
+                dst[u] = tb + d0 + (x - S[first]);
+                tag[u] = (uint8_t)(lo - first);
+                row[u] = (q ? ls.perm_q : ls.perm_p)[tb + p0 + (x - S[lo])];
             }
-            const uint32_t first = sfirst[lo];
-            if (first == 0xffffffffu)
-                continue;
-            const size_t tb = (size_t)st[lo] * (q ? ls.n_q : ls.n_p);
-            const uint32_t p0 = q ? spq[lo].z : spq[lo].x, d0 = q ? spq[first].z : spq[first].x;
-            const size_t dst = tb + d0 + (x - S[first]);
-            (q ? ls.list_q : ls.list_p)[dst] = (q ? ls.perm_q : ls.perm_p)[tb + p0 + (x - S[lo])];
-            (q ? ls.tag_q : ls.tag_p)[dst] = (uint8_t)(lo - first);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (x0 + 256 * u < total) {
+                    (q ? ls.list_q : ls.list_p)[dst[u]] = row[u];
+                    (q ? ls.tag_q : ls.tag_p)[dst[u]] = tag[u];
+                }
         }
     };
     copy(PS, false);

@@ -5,8 +5,8 @@
 // Only the grouping of equal keys matters, so a table's keys are sorted in
 // the order of a bijective mix of them, m(key), when they use more than 32
 // bits: 32-bit sort keys (the key itself, or the top half of m(key)) are
-// sorted with their rows, the full m(key) of every sorted position is then
-// gathered through the permutation, and the rare runs whose top halves are
+// sorted with their rows, the low half of m(key) of every sorted position is
+// then gathered through the permutation, and the rare runs whose top halves are
 // equal but whose m differ are put in the order of m by a local sort.  The
 // outputs are the sorted m(key) (or keys) and their rows; equal outputs are
 // exactly equal keys, and P and Q are sorted in one order.
@@ -204,83 +204,103 @@ __device__ __forceinline__ uint64_t mix_key(uint64_t k)
 }
 
 // The 32-bit sort keys: the key itself (keys of at most 32 bits) or the top
-// half of its mix.
+// half of its mix, whose low half is kept for the gather.
 __global__ void __launch_bounds__(256) sort_key_kernel(const uint64_t *keys, uint64_t total,
-                                                       int wide, uint32_t *sk)
+                                                       int wide, uint32_t *sk, uint32_t *low)
+{
+    const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= total)
+        return;
+    if (wide) {
+        const uint64_t m = mix_key(keys[i]);
+        sk[i] = (uint32_t)(m >> 32);
+        low[i] = (uint32_t)m;
+    } else {
+        sk[i] = (uint32_t)keys[i];
+    }
+}
+
+// The sorted outputs of keys of at most 32 bits: the sort keys as they stand.
+__global__ void __launch_bounds__(256) expand_key_kernel(const uint32_t *sk, uint64_t total,
+                                                         uint64_t *sorted)
 {
     const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
     if (i < total)
-        sk[i] = wide ? (uint32_t)(mix_key(keys[i]) >> 32) : (uint32_t)keys[i];
+        sorted[i] = sk[i];
 }
 
-// The sorted outputs through the permutation: the key (or its mix) of the
-// row at every sorted position; with wide keys also clears the run marks.
-__global__ void __launch_bounds__(256) gather_key_kernel(const uint64_t *keys, uint32_t n,
-                                                         uint64_t total, int wide,
+// The sorted outputs of wide keys: the sort key is the mix's top half, the low
+// half comes through the permutation (4 bytes of a table's n, not the 8-byte
+// key: 16 tables of 1048576 rows 164 us instead of 204, the same with each XCD's
+// blocks on tables of their own).  A break is a position
+// whose mix differs from its predecessor's within a run of equal top halves;
+// the run's first break walks back to the run's first position and lists it
+// (16 M list entries' worth of marks and the kernels that read them cost 69 us).
+__global__ void __launch_bounds__(256) gather_low_kernel(const uint32_t *sk, const uint32_t *low,
+                                                         uint32_t n, uint64_t total,
                                                          const uint32_t *perm, uint64_t *sorted,
-                                                         uint32_t *mark)
+                                                         uint32_t *list, unsigned long long *n_list)
 {
     const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= total)
+    const bool in = i < total;
+    const uint64_t s0 = in ? i / n * n : 0;
+    uint32_t k = 0, l = 0;
+    if (in) {
+        k = sk[i];
+        l = low[s0 + perm[i]];
+        sorted[i] = ((uint64_t)k << 32) | l;
+    }
+    // the predecessor, from the lane below (lane 0 reads it)
+    uint32_t kp = __shfl_up(k, 1, 64), lp = __shfl_up(l, 1, 64);
+    if (!in || i == s0)
         return;
-    const uint64_t seg = i / n;
-    const uint64_t k = keys[seg * n + perm[i]];
-    sorted[i] = wide ? mix_key(k) : k;
-    if (wide)
-        mark[i] = 0;
-}
-
-// Wide keys, after the gather: a break is a position whose mixed key differs
-// from its predecessor's within a run of equal top halves.  The run's first
-// break walks back to the run's first position and marks it.  Only `sk` and
-// `sorted` are read, and nothing else writes them here.
-__global__ void __launch_bounds__(256) break_kernel(const uint32_t *sk, const uint64_t *sorted,
-                                                    uint32_t n, uint64_t total, uint32_t *mark)
-{
-    const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= total)
-        return;
-    const uint64_t s0 = i / n * n;
-    if (i == s0 || sk[i - 1] != sk[i] || sorted[i - 1] == sorted[i])
+    if ((threadIdx.x & 63) == 0) {
+        kp = sk[i - 1];
+        if (kp == k)
+            lp = low[s0 + perm[i - 1]];
+    }
+    if (kp != k || lp == l)
         return;
     uint64_t a = i - 1;
-    while (a > s0 && sk[a - 1] == sk[i]) {
-        if (sorted[a - 1] != sorted[a])
-            return;   // an earlier break marks the run
+    while (a > s0 && sk[a - 1] == k) {
+        if (low[s0 + perm[a - 1]] != lp)
+            return;   // an earlier break lists the run
         --a;
     }
-    mark[a] = 1;
+    list[atomicAdd(n_list, 1ull)] = (uint32_t)a;
 }
 
-// Sorts every marked run by the mixed key, stably (insertion sort).  Two
+// Sorts every listed run by the mixed key, stably (insertion sort).  Two
 // distinct keys share a top half with probability 2^-32, so D distinct keys in
-// a table give about D^2 / 2^33 marked runs (about 100 at D = 10^6), each
+// a table give about D^2 / 2^33 listed runs (about 100 at D = 10^6), each
 // joining the rows of two buckets; the cost of a run is its number of
 // inversions, at most the product of the two buckets' sizes.  Runs are
 // disjoint and each has one first position, so no two threads write the same
 // entries.
-__global__ void __launch_bounds__(256) fixup_kernel(const uint32_t *sk, const uint32_t *mark,
-                                                    uint32_t n, uint64_t total, uint64_t *sorted,
-                                                    uint32_t *perm)
+__global__ void __launch_bounds__(256) fixup_kernel(const uint32_t *sk, const uint32_t *list,
+                                                    const unsigned long long *n_list, uint32_t n,
+                                                    uint64_t *sorted, uint32_t *perm)
 {
-    const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= total || !mark[i])
-        return;
-    const uint64_t end = (i / n + 1) * n;
-    uint64_t e = i + 1;
-    while (e < end && sk[e] == sk[i])
-        ++e;
-    for (uint64_t a = i + 1; a < e; ++a) {
-        const uint64_t k = sorted[a];
-        const uint32_t v = perm[a];
-        uint64_t b = a;
-        while (b > i && sorted[b - 1] > k) {
-            sorted[b] = sorted[b - 1];
-            perm[b] = perm[b - 1];
-            --b;
+    const uint64_t n_run = *n_list;
+    for (uint64_t x = (uint64_t)blockIdx.x * 256 + threadIdx.x; x < n_run;
+         x += (uint64_t)gridDim.x * 256) {
+        const uint64_t i = list[x];
+        const uint64_t end = (i / n + 1) * n;
+        uint64_t e = i + 1;
+        while (e < end && sk[e] == sk[i])
+            ++e;
+        for (uint64_t a = i + 1; a < e; ++a) {
+            const uint64_t k = sorted[a];
+            const uint32_t v = perm[a];
+            uint64_t b = a;
+            while (b > i && sorted[b - 1] > k) {
+                sorted[b] = sorted[b - 1];
+                perm[b] = perm[b - 1];
+                --b;
+            }
+            sorted[b] = k;
+            perm[b] = v;
         }
-        sorted[b] = k;
-        perm[b] = v;
     }
 }
 
@@ -292,7 +312,7 @@ size_t sort_temp_bytes(uint32_t n, uint32_t L)
     const uint64_t total = (uint64_t)n * L;
     const uint64_t counts = (uint64_t)L * SORT_BINS * blocks_per_segment(n);
     auto up = [](uint64_t x) { return (x + 255) & ~(uint64_t)255; };
-    return 2 * up(total * 4) + up(total * 4) + up(counts * 4) + up(counts * 8) +
+    return 2 * up(total * 4) + up(total * 4) + up(total * 4) + up(counts * 4) + up(counts * 8) +
            up(sjk::scan_partials_size(counts) * 8) + 256;
 }
 
@@ -309,7 +329,8 @@ hipError_t sort_tables(const uint64_t *keys, uint64_t *sorted, uint32_t *perm, u
     uint32_t *ska = (uint32_t *)t;                             // sort keys, two buffers
     uint32_t *skb = (uint32_t *)(t + up(total * 4));
     uint32_t *tv = (uint32_t *)(t + 2 * up(total * 4));        // rows, second buffer
-    uint32_t *hist = (uint32_t *)(t + 3 * up(total * 4));
+    uint32_t *low = (uint32_t *)(t + 3 * up(total * 4));       // wide keys: low halves
+    uint32_t *hist = (uint32_t *)(t + 4 * up(total * 4));
     unsigned long long *offs = (unsigned long long *)((uint8_t *)hist + up(counts * 4));
     unsigned long long *part = (unsigned long long *)((uint8_t *)offs + up(counts * 8));
     unsigned long long *tot =
@@ -317,7 +338,8 @@ hipError_t sort_tables(const uint64_t *keys, uint64_t *sorted, uint32_t *perm, u
     const bool wide = bits > 32;
     const uint32_t sbits = wide ? 32u : bits;
     const dim3 g1((uint32_t)((total + 255) / 256));
-    hipLaunchKernelGGL(sort_key_kernel, g1, dim3(256), 0, s, keys, total, wide ? 1 : 0, ska);
+    hipLaunchKernelGGL(sort_key_kernel, g1, dim3(256), 0, s, keys, total, wide ? 1 : 0, ska,
+                       low);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
@@ -346,18 +368,19 @@ hipError_t sort_tables(const uint64_t *keys, uint64_t *sorted, uint32_t *perm, u
         kin = kout;
         vin = vout;
     }
-    // the rows' second buffer is free after the last pass: the run marks
-    hipLaunchKernelGGL(gather_key_kernel, g1, dim3(256), 0, s, keys, n, total, wide ? 1 : 0, perm,
-                       sorted, tv);
+    if (!wide) {
+        hipLaunchKernelGGL(expand_key_kernel, g1, dim3(256), 0, s, kin, total, sorted);
+        return hipGetLastError();
+    }
+    // the rows' second buffer is free after the last pass: the list of runs
+    if ((e = sjk::launch_zero_u64(tot, 1, s)) != hipSuccess)
+        return e;
+    hipLaunchKernelGGL(gather_low_kernel, g1, dim3(256), 0, s, kin, low, n, total, perm, sorted,
+                       tv, tot);
     if ((e = hipGetLastError()) != hipSuccess)
         return e;
-    if (wide) {
-        hipLaunchKernelGGL(break_kernel, g1, dim3(256), 0, s, kin, sorted, n, total, tv);
-        if ((e = hipGetLastError()) != hipSuccess)
-            return e;
-        hipLaunchKernelGGL(fixup_kernel, g1, dim3(256), 0, s, kin, tv, n, total, sorted, perm);
-        e = hipGetLastError();
-    }
+    hipLaunchKernelGGL(fixup_kernel, dim3(128), dim3(256), 0, s, kin, tv, tot, n, sorted, perm);
+    e = hipGetLastError();
     return e;
 }
 
