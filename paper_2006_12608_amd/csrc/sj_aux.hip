@@ -107,6 +107,7 @@ bool plan_join(int dtype, int metric, uint32_t n_p, uint32_t n_q, uint32_t row_b
     plan->qsplit = 1;
     plan->block = kStNW * 64;
     plan->grid = (uint32_t)grid;
+    plan->cus = (uint32_t)num_cus;
     plan->n_blocks = n_pt * n_qt * kStNW;
     plan->wg_blocks32 = 0;
     return true;

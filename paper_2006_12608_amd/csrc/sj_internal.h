@@ -90,7 +90,8 @@ struct JoinArgs {
 struct Plan {
     int family;
     int variant;                 // index into the family's instantiation table
-    uint32_t grid, block;
+    uint32_t grid, block;        // FAM_STREAMED: tile numbers (a workgroup takes several)
+    uint32_t cus;                // FAM_STREAMED: workgroups at most
     uint32_t qsplit;
     bool small;                  // FAM_RESIDENT: the small geometry (sj_join_kernels.h)
     uint64_t n_blocks;           // number of output blocks (entries of block_counts)

@@ -949,32 +949,42 @@ __global__ void __launch_bounds__(NW * 64) join_resident(JoinArgs g)
 // Family 2: both operands streamed through LDS in chunks of KC bytes of d
 // (for rows too long to keep in registers).
 //
-// A workgroup of 8 waves (two per SIMD) computes a 256 x 256 output tile; wave
-// (wr, wc), wr < 4, wc < 2, owns rows [64 wr, +64) (two A-blocks) and columns
-// [128 wc, +128) (four B-blocks), so a k-step reads 2 A- and 4 B-fragments
-// from LDS for 8 MFMAs.  P and Q chunks are double-buffered in LDS (one
-// workgroup per CU).  Tiles are visited in groups of 8 P tiles x 8 Q tiles so
-// that concurrently running workgroups share their operand rows in L2.
+// A persistent workgroup of 8 waves (two per SIMD, one workgroup per CU) walks
+// 256 x 256 output tiles as one stream of chunks; wave (wr, wc), wr < 4, wc < 2,
+// owns rows [64 wr, +64) (two A-blocks) and columns [128 wc, +128) (four
+// B-blocks), so a k-step reads 2 A- and 4 B-fragments from LDS for 8 MFMAs.  P
+// and Q chunks are double-buffered in LDS; the first chunk of the next tile
+// loads during the last one of the current tile.  (One workgroup per tile left
+// the first chunk's latency exposed and its padded rows wrote an eighth more to
+// LDS: the count of 30011 x 20021 rows of 608 bytes 437 -> 383 us, 32768 x 32768
+// of 2048 bytes 1790 -> 1720 us.  The
+// epilogue between the next loads and its own tile's successor's products would
+// hide it too, but then the results spill: 4 x slower.)
+// Rows are unpadded, chunk c of row r at position c ^ (r / 2 % 8): 16 consecutive
+// rows' reads of one chunk hit all banks.  The LDS is the tightest resource: 48
+// of 64 cycles per k-step and wave pair for the fragment reads, 16 for the
+// chunks' writes.  Tiles are visited in groups of 8 P tiles x 8 Q tiles so that
+// concurrently running workgroups share their operand rows in L2.
 // Output block = one wave's 64 x 128 region; index = tile * 8 + wave.
 constexpr int ST_KC = 128;   // K chunk bytes (tile geometry in sj_internal.h)
 
 template <int DT, int MET, int MODE>
-__global__ void __launch_bounds__(ST_NW * 64) join_streamed(JoinArgs g)
+__global__ void __launch_bounds__(ST_NW * 64) join_streamed(JoinArgs g, uint32_t n_idx)
 {
     typedef Mma<DT> M;
     typedef typename M::acc_t acc_t;
     typedef typename M::val_t V;
     constexpr int CPR = ST_KC / 16;                   // 8 chunks per row per K chunk
-    constexpr int LS = (CPR + 1) * 16;                // padded row stride
+    constexpr int LS = CPR * 16;                      // row stride
     constexpr int ROWS = ST_BM + ST_BN;               // P rows, then Q rows
-    constexpr int NPOS = ROWS * (CPR + 1);            // LDS positions per stage
     constexpr int NT = ST_NW * 64;                    // threads
-    constexpr int NLD = NPOS / NT;                    // direct loads per thread
-    constexpr int P_LOADS = ST_BM * (CPR + 1) / 64;   // wave loads below this fill P rows
+    constexpr int NLD = ROWS * CPR / NT;              // direct loads per thread
     constexpr int KSC = ST_KC / 32;                   // k-steps per chunk
     constexpr int SA = ST_SA, SB = ST_SB;             // A- and B-blocks per wave
     constexpr bool NEED_NORMS = (MET == MET_L2);
-    static_assert(NPOS % NT == 0 && (ST_BM * (CPR + 1)) % 64 == 0, "load layout");
+    // the epilogue stages pairs in the operand buffers
+    constexpr bool STAGED = MODE != MODE_MASK && !counting_mode<MODE>();
+    static_assert(ROWS * CPR % NT == 0 && ST_BM * CPR / 64 == ST_NW * NLD / 2, "load layout");
 
     // two stages as distinct arrays (see join_resident)
     __shared__ __attribute__((aligned(16))) uint8_t s_op0[ROWS * LS];
@@ -983,92 +993,194 @@ __global__ void __launch_bounds__(ST_NW * 64) join_streamed(JoinArgs g)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int half = lane >> 5, c32 = lane & 31;
-    const int wr = wave >> 1, wc = wave & 1;
-
-    // tile order: groups of 8 x 8 tiles, row-major inside a group
-    const uint32_t n_pt = (g.n_p + ST_BM - 1) / ST_BM, n_qt = (g.n_q + ST_BN - 1) / ST_BN;
-    const uint32_t tile = blockIdx.x;
-    constexpr uint32_t G = 8;
-    const uint32_t groups_q = (n_qt + G - 1) / G;
-    const uint32_t grp = tile / (G * G), in = tile % (G * G);
-    const uint32_t gp = grp / groups_q, gq = grp % groups_q;
-    const uint32_t hp = min(G, n_pt - gp * G), hq = min(G, n_qt - gq * G);
-    // groups at the ragged edges are smaller; their tiles are numbered densely
-    if (in >= hp * hq)
-        return;
-    const uint32_t pt = gp * G + in / hq, qt = gq * G + in % hq;
-    // self-join triangle: a tile wholly below the diagonal holds no pair i <= j
-    if (MODE == MODE_TRI && pt > qt)
-        return;
-    const uint32_t p0 = pt * ST_BM, q0 = qt * ST_BN;
+    const int wv = __builtin_amdgcn_readfirstlane(wave);
+    const int wr = wv >> 1, wc = wv & 1;
     const uint32_t n_chunks = (g.row_bytes + ST_KC - 1) / ST_KC;
 
+    // tile order: groups of 8 x 8 tiles, row-major inside a group; workgroup b
+    // takes the tiles numbered b, b + gridDim.x, ...
+    const uint32_t n_pt = (g.n_p + ST_BM - 1) / ST_BM, n_qt = (g.n_q + ST_BN - 1) / ST_BN;
+    constexpr uint32_t G = 8;
+    const uint32_t groups_q = (n_qt + G - 1) / G;
+    struct Tile {
+        uint32_t pt, qt;
+    };
+    uint32_t idx = blockIdx.x;
+    // the next tile at or after idx, stepping by the grid; false past the last
+    auto next_tile = [&](Tile &x) -> bool {
+        for (; idx < n_idx; idx += gridDim.x) {
+            const uint32_t grp = idx / (G * G), in = idx % (G * G);
+            const uint32_t gp = grp / groups_q, gq = grp % groups_q;
+            const uint32_t hp = min(G, n_pt - gp * G), hq = min(G, n_qt - gq * G);
+            // groups at the ragged edges are smaller; their tiles are numbered densely
+            if (in >= hp * hq)
+                continue;
+            x.pt = gp * G + in / hq;
+            x.qt = gq * G + in % hq;
+            // self-join triangle: a tile wholly below the diagonal holds no pair i <= j
+            if (MODE == MODE_TRI && x.pt > x.qt)
+                continue;
+            idx += gridDim.x;   // (n_idx < 2^31: no wrap)
+            return true;
+        }
+        return false;
+    };
+
     // Direct loads: wave instruction k = wave + ST_NW i fills LDS positions
-    // [64 k, 64 k + 64); position p holds chunk p % (CPR + 1) (the pad position
-    // repeats chunk 0) of tile row p / (CPR + 1).  Per-lane offsets within the
-    // P or Q descriptor (rows past n_p / n_q read zeros), plus the chunk's byte
-    // offset kc * KC.
-    const uint32_t bytes_p = min(g.n_p - p0, (uint32_t)ST_BM) * g.row_bytes;
-    const uint32_t bytes_q = min(g.n_q - q0, (uint32_t)ST_BN) * g.row_bytes;
-    const uint8_t *base_p = g.P + (size_t)p0 * g.row_bytes;
-    const uint8_t *base_q = g.Q + (size_t)q0 * g.row_bytes;
-    const int wv = __builtin_amdgcn_readfirstlane(wave);
+    // [64 k, 64 k + 64), i.e. rows 8 k .. 8 k + 7; lane l row l / 8, position l %
+    // 8, chunk (l % 8) ^ (row / 2 % 8).  Per-lane offsets within the P or Q
+    // descriptor (rows past n_p / n_q read zeros), plus the chunk's byte offset.
     uint32_t voff[NLD], vcol[NLD];
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
-        const int pos = 64 * (wv + ST_NW * i) + lane;
-        const int r = pos / (CPR + 1), cp = pos % (CPR + 1);
-        vcol[i] = 16 * (cp == CPR ? 0 : cp);
-        voff[i] = (uint32_t)(r < ST_BM ? r : r - ST_BM) * g.row_bytes + vcol[i];
+        const uint32_t r = 8 * (wv + ST_NW * i) + (lane >> 3);
+        vcol[i] = 16 * ((lane & 7) ^ ((r >> 1) & 7));
+        voff[i] = (i < NLD / 2 ? r : r - ST_BM) * g.row_bytes + vcol[i];
     }
-    auto stage_issue = [&](uint32_t kc, uint8_t *dst) {
+    auto stage_issue = [&](const Tile &x, uint32_t kc, uint8_t *dst) {
+        const uint32_t p0 = x.pt * ST_BM, q0 = x.qt * ST_BN;
+        const uint32_t bytes_p = min(g.n_p - p0, (uint32_t)ST_BM) * g.row_bytes;
+        const uint32_t bytes_q = min(g.n_q - q0, (uint32_t)ST_BN) * g.row_bytes;
+        const uint8_t *base_p = g.P + (size_t)p0 * g.row_bytes;
+        const uint8_t *base_q = g.Q + (size_t)q0 * g.row_bytes;
         const uint32_t kb = kc * ST_KC;
         if (kb + ST_KC <= g.row_bytes) {                 // uniform
 #pragma unroll
             for (int i = 0; i < NLD; ++i) {
-                const int k = wv + ST_NW * i;
-                const bool is_p = k < P_LOADS;
+                const bool is_p = i < NLD / 2;
                 buffer_load_lds16(is_p ? base_p : base_q, is_p ? bytes_p : bytes_q, voff[i],
-                                  dst + 1024 * k, kb);
+                                  dst + 1024 * (wv + ST_NW * i), kb);
             }
         } else {
             // the last chunk of a row that is not a multiple of KC: columns
             // past the row read zeros (offset at the descriptor's end)
 #pragma unroll
             for (int i = 0; i < NLD; ++i) {
-                const int k = wv + ST_NW * i;
-                const bool is_p = k < P_LOADS;
+                const bool is_p = i < NLD / 2;
                 const uint32_t nbytes = is_p ? bytes_p : bytes_q;
                 const uint32_t vo = kb + vcol[i] >= g.row_bytes ? nbytes : voff[i] + kb;
-                buffer_load_lds16(is_p ? base_p : base_q, nbytes, vo, dst + 1024 * k);
+                buffer_load_lds16(is_p ? base_p : base_q, nbytes, vo,
+                                  dst + 1024 * (wv + ST_NW * i));
             }
         }
     };
 
     acc_t acc[SA][SB];
+    auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int a = 0; a < SA; ++a)
+        for (int a = 0; a < SA; ++a)
 #pragma unroll
-        for (int s = 0; s < SB; ++s)
-            acc[a][s] = acc_t{};
+            for (int s = 0; s < SB; ++s)
+                acc[a][s] = acc_t{};
+    };
 
-    // One K chunk: KSC k-steps, each reading SA A- and SB B-fragments (a ring
-    // of LOOK + 1 steps, LOOK steps ahead) and issuing SA * SB MFMAs.
-    constexpr int LOOK = 2, RING = LOOK + 1;
-    auto chunk = [&](uint32_t kc, const uint8_t *cur, uint8_t *nxt)
-                     __attribute__((always_inline)) {
-        if (kc + 1 < n_chunks)
-            stage_issue(kc + 1, nxt);
-        const uint8_t *pa = cur + (32 * SA * wr + c32) * LS + 16 * half;
-        const uint8_t *pb = cur + (ST_BM + 32 * SB * wc + c32) * LS + 16 * half;
-        i32x4 ring[RING][SA + SB];
-        auto fetch = [&](i32x4(&f)[SA + SB], int ks) __attribute__((always_inline)) {
+    // A tile's results (in acc): counted, kept as match bits, or staged in
+    // `stage_mem` (this wave's share) and written.
+    auto epilogue = [&](const Tile &x, uint8_t *stage_mem) __attribute__((always_inline)) {
+        const uint32_t p0 = x.pt * ST_BM, q0 = x.qt * ST_BN;
+        const uint32_t prow0 = p0 + 32 * SA * wr;
+        const uint32_t ibase = prow0 + 4 * half;
+        V nmin = big_val<V>();
+        const V *nrows = nullptr;
+        if constexpr (NEED_NORMS) {
+            nmin = stage_row_norms<DT, SA>(prow0, lane, s_np[wave], g);
+            nrows = &s_np[wave][4 * half];
+        }
+        const V nb = bound_base<DT, MET>(nmin, g);
+        constexpr uint32_t STAGE_BYTES = ROWS * LS / ST_NW;
+        static_assert(STAGE_BYTES / 8 >= 1024, "a whole 32x32 block must fit the staging buffer");
+        WaveOut wo{(lds_pair *)stage_mem, STAGE_BYTES / 8, 0u, 0ull};
+        const uint64_t blk = ((uint64_t)x.pt * n_qt + x.qt) * ST_NW + wv;
+        uint64_t blk_run = 0;
+        if constexpr (MODE == MODE_MASK) {
+            // Every block is tested exactly and its match bits are kept for the
+            // emit pass (one 16-byte store per lane); the output block's count is
+            // the wave's sum of the lanes' popcounts (at most 16 SA SB < 2^8).
+            typedef __attribute__((address_space(1))) i32x4 global_i32x4;
+            uint32_t mw[SA * SB / 2] = {};
+            uint32_t lane_cnt = 0;
+#pragma unroll
+            for (int b = 0; b < SB; ++b) {
+                const uint32_t j = q0 + 32 * SB * wc + 32 * b + c32;
+                V ny = V(0);
+                if constexpr (NEED_NORMS)
+                    ny = j < g.n_q ? ((const V *)g.norm_q)[j] : big_val<V>();
+#pragma unroll
+                for (int a = 0; a < SA; ++a) {
+                    const uint32_t m =
+                        block_mask<DT, MET>(acc[a][b], ibase + 32 * a, j, ny, nrows + 32 * a, g);
+                    const int sb = b * SA + a;
+                    mw[sb / 2] |= m << (16 * (sb % 2));
+                    lane_cnt += (uint32_t)__builtin_popcount(m);
+                }
+            }
+            static_assert(SA * SB == 8 && 16 * SA * SB < 256, "mask record and count bits");
+            *((global_i32x4 *)g.masks + (blk * 64 + lane)) =
+                i32x4{(int)mw[0], (int)mw[1], (int)mw[2], (int)mw[3]};
+            uint32_t tot = 0;
+#pragma unroll
+            for (int bit = 0; bit < 8; ++bit)
+                tot += (uint32_t)__popcll(__ballot((lane_cnt >> bit) & 1)) << bit;
+            if (lane == 0)
+                g.block_counts[blk] = tot;
+            return;
+        }
+        if constexpr (MODE == MODE_EMIT)
+            wo.dst = g.block_offsets[blk];
+#pragma unroll
+        for (int b = 0; b < SB; ++b) {
+            const uint32_t j = q0 + 32 * SB * wc + 32 * b + c32;
+            V ny = V(0);
+            if constexpr (NEED_NORMS)
+                ny = j < g.n_q ? ((const V *)g.norm_q)[j] : big_val<V>();
+            acc_t blk_acc[SA];
 #pragma unroll
             for (int a = 0; a < SA; ++a)
-                f[a] = *(const i32x4 *)(pa + 32 * a * LS + 32 * ks);
+                blk_acc[a] = acc[a][b];
+            V mb[SA];
+            fold_max_blk<0, 16 * SA, SA>(blk_acc, mb);
+            const bool may = lane_bound<DT, MET>(max_of<SA>(mb), nb, ny, g);
+            if (__ballot(may) != 0)
+                exact_blocks<DT, MET, MODE, SA>(blk_acc, mb, ibase, j, lane, nb, ny, nrows, g,
+                                                blk_run, wo);
+        }
+        if constexpr (STAGED)
+            flush_wave_out<MODE>(wo, lane, g);
+        if constexpr (MODE == MODE_COUNT) {
+            if (lane == 0)
+                g.block_counts[blk] = (uint32_t)blk_run;
+        }
+    };
+
+    Tile cur{0, 0}, nxt{0, 0};
+    if (!next_tile(cur))
+        return;   // the whole workgroup
+    bool more = next_tile(nxt);
+    uint32_t kc = 0;
+
+    // One K chunk: the next chunk's loads, then KSC k-steps, each reading SA A- and
+    // SB B-fragments (a ring of LOOK + 1 steps, LOOK steps ahead) and issuing SA *
+    // SB MFMAs.
+    constexpr int LOOK = 2, RING = LOOK + 1;
+    const uint32_t sw = (c32 >> 1) & 7;   // row / 2 % 8 of the rows this lane reads
+    auto chunk = [&](const uint8_t *buf, uint8_t *oth) __attribute__((always_inline)) {
+        if (kc + 1 < n_chunks)
+            stage_issue(cur, kc + 1, oth);
+        else if (more)
+            stage_issue(nxt, 0, oth);
+        if (kc == 0)
+            clear();
+        const uint8_t *pa = buf + (32 * SA * wr + c32) * LS;
+        const uint8_t *pb = buf + (ST_BM + 32 * SB * wc + c32) * LS;
+        i32x4 ring[RING][SA + SB];
+        auto fetch = [&](i32x4(&f)[SA + SB], int ks) __attribute__((always_inline)) {
+            const uint32_t o = 16 * ((2 * ks + half) ^ sw);
+#pragma unroll
+            for (int a = 0; a < SA; ++a)
+                f[a] = *(const i32x4 *)(pa + 32 * a * LS + o);
 #pragma unroll
             for (int b = 0; b < SB; ++b)
-                f[SA + b] = *(const i32x4 *)(pb + 32 * b * LS + 32 * ks);
+                f[SA + b] = *(const i32x4 *)(pb + 32 * b * LS + o);
         };
         static_for<0, LOOK>([&](auto Q) __attribute__((always_inline)) {
             fetch(ring[decltype(Q)::value], decltype(Q)::value);
@@ -1085,96 +1197,34 @@ __global__ void __launch_bounds__(ST_NW * 64) join_streamed(JoinArgs g)
                     acc[a][b] = M::mma(f[a], f[SA + b], acc[a][b]);
             __builtin_amdgcn_sched_barrier(0);
         });
-        __builtin_amdgcn_s_waitcnt(0);   // this wave's loads of chunk kc + 1 landed
+        __builtin_amdgcn_s_waitcnt(0);   // this wave's loads of the next chunk landed
         __syncthreads();
     };
-
-    stage_issue(0, s_op0);
+    // After a chunk: the next one of the tile, or the next tile; false at the end.
+    auto advance = [&](uint8_t *buf) __attribute__((always_inline)) -> bool {
+        if (++kc < n_chunks)
+            return true;
+        kc = 0;
+        // (the buffer just read is free until the next chunk's loads)
+        epilogue(cur, buf + wv * (ROWS * LS / ST_NW));
+        if constexpr (STAGED)
+            __syncthreads();
+        if (!more)
+            return false;
+        cur = nxt;
+        more = next_tile(nxt);
+        return true;
+    };
+    stage_issue(cur, 0, s_op0);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    for (uint32_t kc = 0; kc < n_chunks; kc += 2) {
-        chunk(kc, s_op0, s_op1);
-        if (kc + 1 < n_chunks)
-            chunk(kc + 1, s_op1, s_op0);
-    }
-
-    const uint32_t prow0 = p0 + 32 * SA * wr;
-    const uint32_t ibase = prow0 + 4 * half;
-    V nmin = big_val<V>();
-    const V *nrows = nullptr;
-    if constexpr (NEED_NORMS) {
-        nmin = stage_row_norms<DT, SA>(prow0, lane, s_np[wave], g);
-        nrows = &s_np[wave][4 * half];
-    }
-    const V nb = bound_base<DT, MET>(nmin, g);
-    // After the last chunk's barrier the operand stages are free: each wave
-    // stages its matches in an eighth of them (2304 pairs), for the single
-    // pass and the emit pass alike.
-    constexpr uint32_t STAGE_BYTES = 2 * ROWS * LS / ST_NW;
-    static_assert(STAGE_BYTES / 8 >= 1024, "a whole 32x32 block must fit the staging buffer");
-    uint8_t *stage_mem = (wave < ST_NW / 2 ? s_op0 : s_op1) + (wave % (ST_NW / 2)) * STAGE_BYTES;
-    WaveOut wo{(lds_pair *)stage_mem, STAGE_BYTES / 8, 0u, 0ull};
-    const uint64_t blk = (uint64_t)(pt * n_qt + qt) * ST_NW + wave;
-    uint64_t blk_run = 0;
-    if constexpr (MODE == MODE_MASK) {
-        // Every block is tested exactly and its match bits are kept for the
-        // emit pass (one 16-byte store per lane); the output block's count is
-        // the wave's sum of the lanes' popcounts (at most 16 SA SB < 2^8).
-        typedef __attribute__((address_space(1))) i32x4 global_i32x4;
-        uint32_t mw[SA * SB / 2] = {};
-        uint32_t lane_cnt = 0;
-#pragma unroll
-        for (int b = 0; b < SB; ++b) {
-            const uint32_t j = q0 + 32 * SB * wc + 32 * b + c32;
-            V ny = V(0);
-            if constexpr (NEED_NORMS)
-                ny = j < g.n_q ? ((const V *)g.norm_q)[j] : big_val<V>();
-#pragma unroll
-            for (int a = 0; a < SA; ++a) {
-                const uint32_t m =
-                    block_mask<DT, MET>(acc[a][b], ibase + 32 * a, j, ny, nrows + 32 * a, g);
-                const int sb = b * SA + a;
-                mw[sb / 2] |= m << (16 * (sb % 2));
-                lane_cnt += (uint32_t)__builtin_popcount(m);
-            }
-        }
-        static_assert(SA * SB == 8 && 16 * SA * SB < 256, "mask record and count bits");
-        *((global_i32x4 *)g.masks + (blk * 64 + lane)) =
-            i32x4{(int)mw[0], (int)mw[1], (int)mw[2], (int)mw[3]};
-        uint32_t tot = 0;
-#pragma unroll
-        for (int bit = 0; bit < 8; ++bit)
-            tot += (uint32_t)__popcll(__ballot((lane_cnt >> bit) & 1)) << bit;
-        if (lane == 0)
-            g.block_counts[blk] = tot;
-        return;
-    }
-    if constexpr (MODE == MODE_EMIT)
-        wo.dst = g.block_offsets[blk];
-#pragma unroll
-    for (int b = 0; b < SB; ++b) {
-        const uint32_t j = q0 + 32 * SB * wc + 32 * b + c32;
-        V ny = V(0);
-        if constexpr (NEED_NORMS)
-            ny = j < g.n_q ? ((const V *)g.norm_q)[j] : big_val<V>();
-        acc_t blk_acc[SA];
-#pragma unroll
-        for (int a = 0; a < SA; ++a)
-            blk_acc[a] = acc[a][b];
-        V mb[SA];
-        fold_max_blk<0, 16 * SA, SA>(blk_acc, mb);
-        const bool may = lane_bound<DT, MET>(max_of<SA>(mb), nb, ny, g);
-        if (__ballot(may) != 0)
-            exact_blocks<DT, MET, MODE, SA>(blk_acc, mb, ibase, j, lane, nb, ny, nrows, g,
-                                            blk_run, wo);
-    }
-    if constexpr (single_mode<MODE>())
-        flush_workgroup_out<ST_NW>(wo, wave, lane, g);
-    if constexpr (MODE == MODE_EMIT)
-        flush_wave_out<MODE>(wo, lane, g);
-    if constexpr (MODE == MODE_COUNT) {
-        if (lane == 0)
-            g.block_counts[blk] = (uint32_t)blk_run;
+    for (;;) {
+        chunk(s_op0, s_op1);
+        if (!advance(s_op0))
+            break;
+        chunk(s_op1, s_op0);
+        if (!advance(s_op1))
+            break;
     }
 }
 
@@ -1288,8 +1338,9 @@ hipError_t launch_mode(const Plan &p, const JoinArgs &g, hipStream_t st)
 {
     if (p.family == FAM_STREAMED) {
         if constexpr (MODE != MODE_RECORD) {
-            hipLaunchKernelGGL((join_streamed<DT, MET, MODE>), dim3(p.grid), dim3(ST_NW * 64), 0,
-                               st, g);
+            hipLaunchKernelGGL((join_streamed<DT, MET, MODE>),
+                               dim3(p.grid < p.cus ? p.grid : p.cus), dim3(ST_NW * 64), 0, st, g,
+                               p.grid);
             return hipGetLastError();
         }
     } else if constexpr (MODE != MODE_MASK) {
