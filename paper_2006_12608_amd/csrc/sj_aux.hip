@@ -14,7 +14,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // ------------------------------------------------------------------ planning
 // Resident-P limits: 32-byte k-steps of the largest variant (16 for 2-byte
 // elements, 8 for int8, i.e. d <= 256 either way; 16 for 4-bit ones, d <= 1024); workgroup of 8 waves over
-// 32 * WMB rows each (WMB = 4 for int8 rows of at most 64 bytes, else 2); Q
+// 32 * WMB rows each (WMB = 4 for int8 rows of at most 64 bytes and 4-bit rows
+// of at most 128, else 2); Q
 // tiles of 256 rows for rows of at most 64 bytes, 128 up to 256 bytes and 64
 // for the longest rows.  Must agree with sj_join_kernels.h.
 static const int kResKS16[4] = {2, 4, 8, 16};
@@ -49,7 +50,7 @@ bool plan_join(int dtype, int metric, uint32_t n_p, uint32_t n_q, uint32_t row_b
     plan->small = false;
     if (variant >= 0) {
         const int ks = tab[variant];
-        const uint32_t wmb = (dtype == DT_I8 && ks <= 2) ? 4 : 2;
+        const uint32_t wmb = (dtype == DT_I8 && ks <= 2) || (dtype == DT_FP4 && ks <= 4) ? 4 : 2;
         uint32_t nw = kResNW, bm = nw * 32 * wmb;
         uint64_t bn = res_bn(ks);
         uint64_t n_pb = (n_p + (uint64_t)bm - 1) / bm;

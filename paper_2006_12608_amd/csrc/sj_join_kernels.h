@@ -68,7 +68,7 @@ struct Mma<DT_I8> {
 // 4-bit floats (E2M1), 32 per lane and operand: one 32x32x64 MFMA per k-step,
 // unscaled (both block scales 2^0), sums in fp32 (exact for the +-1 rows of
 // the Hamming front end: |sum| <= 16384).  Twice the multiply-adds of the int8
-// MFMA in the same 32 cycles: 65536 x 65536 codes of 256 bits take 0.41 ms a
+// MFMA in the same 32 cycles: 65536 x 65536 codes of 256 bits take 0.40 ms a
 // call, where int8 rows of (x, 1 - x) took 2.08 ms.
 template <>
 struct Mma<DT_FP4> {
@@ -1255,12 +1255,14 @@ struct ResidentCfg<DT_I8> {
 constexpr int RES_NW = 8;
 // 32-row A-blocks per wave: two, which with the two accumulator sets of the
 // sub-tile pipeline keeps every variant within 256 VGPRs; four for int8 rows
-// of at most 64 bytes, whose A-fragments are small (each B-fragment read from
-// LDS then feeds four MFMAs, and a workgroup covers 512 rows of P).
+// of at most 64 bytes and 4-bit rows of at most 128, whose A-fragments are small
+// (each B-fragment read from LDS then feeds four MFMAs, and a workgroup covers
+// 1024 rows of P; 65536 x 65536 codes of 256 bits: a call 427 us with two, 412
+// with four).
 template <int DT, int KS>
 constexpr int res_wmb()
 {
-    return DT == DT_I8 && KS <= 2 ? 4 : 2;
+    return (DT == DT_I8 && KS <= 2) || (DT == DT_FP4 && KS <= 4) ? 4 : 2;
 }
 // Q tile rows: 256 for rows of at most 64 bytes (a short tile would spend a
 // large share of its time in the barrier and the next tile's loads), else 128
