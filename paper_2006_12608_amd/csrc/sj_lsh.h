@@ -74,22 +74,20 @@ constexpr uint32_t fp_chunks(uint32_t L) { return ((L < FP_MAX ? L : FP_MAX) + 1
 hipError_t launch_fingerprints(const uint64_t *keys, uint32_t n, uint32_t L, uint4 *fp,
                                hipStream_t s);
 
-// Marks, for every table t and sorted position p of P that starts a bucket
-// whose key Q also has, flag[t n_p + p] = 1 (else 0) with the bucket's sizes
-// and Q's first position in f_np / f_q0 / f_nq at that index; writes the
-// bucket pairs' pair evaluations (sum of np nq) to n_cand[0] and their rows
-// (sum of np + nq) to n_cand[7].  ws: bucket_find_ws_bytes(n_p, L) bytes.
+// The records, in blocks of 256 sorted positions of P (find_blocks(n_p) per
+// table, tables in order): n_rec[block] records at tmp[256 block ..]; writes the
+// bucket pairs' pair evaluations (sum of np nq) to n_cand[0] and their rows (sum
+// of np + nq) to n_cand[7].  ws: bucket_find_ws_bytes(n_p, L) bytes.
+inline uint32_t find_blocks(uint32_t n_p) { return (uint32_t)(((uint64_t)n_p + 255) / 256); }
 inline size_t bucket_find_ws_bytes(uint32_t n_p, uint32_t L)
 {
-    return (size_t)((n_p + 255) / 256) * L * 24;
+    return (size_t)find_blocks(n_p) * L * 24;
 }
 hipError_t launch_bucket_find(const uint64_t *sorted_p, uint32_t n_p, const uint64_t *sorted_q,
-                              uint32_t n_q, uint32_t L, void *ws, uint32_t *flag, uint32_t *f_np,
-                              uint32_t *f_q0, uint32_t *f_nq, unsigned long long *n_cand,
-                              hipStream_t s);
-// Writes the marked positions as records (rec_off: exclusive scan of flag).
-hipError_t launch_bucket_write(uint32_t n_p, uint32_t L, const uint32_t *flag,
-                               const uint32_t *f_np, const uint32_t *f_q0, const uint32_t *f_nq,
+                              uint32_t n_q, uint32_t L, void *ws, uint4 *tmp, uint32_t *n_rec,
+                              unsigned long long *n_cand, hipStream_t s);
+// Writes them one after the other (rec_off: exclusive scan of n_rec).
+hipError_t launch_bucket_write(uint32_t n_p, uint32_t L, const uint4 *tmp, const uint32_t *n_rec,
                                const unsigned long long *rec_off, const Records &rec,
                                hipStream_t s);
 

@@ -637,73 +637,95 @@ __global__ void __launch_bounds__(256) qrange_kernel(const uint64_t *sorted_p, u
 // One thread per (sorted position of P, table): a position that starts a P
 // bucket looks its key up in Q's sorted keys within the block's range
 // (qrange_kernel), staged in LDS when it holds at most QCAP keys, and, when Q
-// has the key, marks the position with the bucket's sizes.
+// has the key, is a record.  A bucket ends at the block's next start (a bit
+// mask of the starts), only the block's last one is followed in memory.  The
+// block's records are written one after the other at tmp[256 block] with their
+// number in n_rec, so that the scan and the copy that follow work on blocks and
+// records instead of positions.  16 tables of 1048576 positions: 233 us (291
+// with a search for every end and three words written per position), the scan
+// and the copy that follow 30 us (190).
 constexpr uint32_t QCAP = 2048;
 
 __global__ void __launch_bounds__(256) bucket_find_kernel(const uint64_t *sorted_p, uint32_t n_p,
                                                           const uint64_t *sorted_q, uint32_t n_q,
-                                                          const uint2 *qr, uint32_t *flag,
-                                                          uint32_t *f_np, uint32_t *f_q0,
-                                                          uint32_t *f_nq, ulonglong2 *part)
+                                                          const uint2 *qr, uint4 *tmp,
+                                                          uint32_t *n_rec, ulonglong2 *part)
 {
     __shared__ uint64_t s_q[QCAP];
     __shared__ unsigned long long s_cand[4], s_rows[4];
-    const uint32_t t = blockIdx.y, tid = threadIdx.x;
+    __shared__ uint64_t s_start[4];
+    __shared__ uint32_t s_n[4];
+    const uint32_t t = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t pf = blockIdx.x * 256, p = pf + tid;
+    const size_t blk = (size_t)t * gridDim.x + blockIdx.x;
     const uint64_t *sp = sorted_p + (size_t)t * n_p;
     const uint64_t *sq = sorted_q + (size_t)t * n_q;
-    const uint2 range = qr[(size_t)t * gridDim.x + blockIdx.x];
-    const uint32_t qa = range.x, qb = range.y;
-    const bool staged = qb - qa <= QCAP;   // uniform
-    if (staged) {
-        for (uint32_t i = tid; i < qb - qa; i += 256)
+    const uint2 range = qr[blk];
+    const uint32_t qa = range.x, qb = range.y, qn = qb - qa;
+    const bool staged = qn <= QCAP;   // uniform
+    const uint64_t key = p < n_p ? sp[p] : 0;
+    const bool start = p < n_p && (p == 0 || sp[p - 1] != key);
+    const uint64_t starts = __ballot(start);
+    if (lane == 0)
+        s_start[wave] = starts;
+    if (staged)
+        for (uint32_t i = tid; i < qn; i += 256)
             s_q[i] = sq[qa + i];
-        __syncthreads();
-    }
+    __syncthreads();
     uint64_t cand = 0, rows = 0;
-    if (p < n_p) {
-        const size_t at = (size_t)t * n_p + p;
-        uint32_t fl = 0;
-        const uint64_t key = sp[p];
-        if (p == 0 || sp[p - 1] != key) {
-            uint32_t q0, qe;
-            if (staged) {
-                // first position with key >= key, then first with key > key
-                uint32_t lo = 0, hi = qb - qa;
-                while (lo < hi) {
-                    const uint32_t mid = lo + (hi - lo) / 2;
-                    if (s_q[mid] < key)
-                        lo = mid + 1;
-                    else
-                        hi = mid;
-                }
-                uint32_t e = lo;
-                hi = qb - qa;
-                while (e < hi) {
-                    const uint32_t mid = e + (hi - e) / 2;
-                    if (s_q[mid] <= key)
-                        e = mid + 1;
-                    else
-                        hi = mid;
-                }
-                q0 = qa + lo;
-                qe = qa + e;
-            } else {
-                q0 = lower_bound(sq, qa, qb, key);
-                qe = upper_bound(sq, q0, qb, key);
+    uint4 rec = make_uint4(0, 0, 0, 0);
+    bool found = false;
+    if (start) {
+        uint32_t q0, qe;
+        if (staged) {
+            // first position with key >= key, then doubling steps to the end of
+            // its run
+            uint32_t lo = 0, hi = qn;
+            while (lo < hi) {
+                const uint32_t mid = lo + (hi - lo) / 2;
+                if (s_q[mid] < key)
+                    lo = mid + 1;
+                else
+                    hi = mid;
             }
-            if (q0 < qe) {
-                const uint32_t np = run_end(sp, p + 1, n_p, key) - p;
-                fl = 1;
-                f_np[at] = np;
-                f_q0[at] = q0;
-                f_nq[at] = qe - q0;
-                cand = (uint64_t)np * (qe - q0);
-                rows = (uint64_t)np + (qe - q0);
+            uint32_t e = lo, step = 1;
+            while (e + step <= qn && s_q[e + step - 1] == key) {
+                e += step;
+                step *= 2;
             }
+            hi = min(e + step, qn);
+            while (e < hi) {
+                const uint32_t mid = e + (hi - e) / 2;
+                if (s_q[mid] == key)
+                    e = mid + 1;
+                else
+                    hi = mid;
+            }
+            q0 = qa + lo;
+            qe = qa + e;
+        } else {
+            q0 = lower_bound(sq, qa, qb, key);
+            qe = upper_bound(sq, q0, qb, key);
         }
-        flag[at] = fl;
+        found = q0 < qe;
+        if (found) {
+            uint32_t np = 0;
+            uint64_t m = lane < 63 ? s_start[wave] >> (lane + 1) << (lane + 1) : 0;
+            uint32_t w = wave;
+            while (m == 0 && ++w < 4)
+                m = s_start[w];
+            if (m != 0)
+                np = 64 * w + (uint32_t)__builtin_ctzll(m) - tid;
+            else   // the block's last bucket: up to the block's end and beyond
+                np = run_end(sp, min(pf + 256, n_p), n_p, key) - p;
+            rec = make_uint4(p, np, q0, qe - q0);
+            cand = (uint64_t)np * (qe - q0);
+            rows = (uint64_t)np + (qe - q0);
+        }
     }
+    const uint64_t bits = __ballot(found);
+    if (lane == 0)
+        s_n[wave] = (uint32_t)__popcll(bits);
     // the block's pair evaluations and rows, summed by sum_parts_kernel (one
     // counter updated by every block serialises the blocks on its address)
 #pragma unroll
@@ -711,15 +733,22 @@ __global__ void __launch_bounds__(256) bucket_find_kernel(const uint64_t *sorted
         cand += __shfl_xor(cand, o, 64);
         rows += __shfl_xor(rows, o, 64);
     }
-    if ((tid & 63) == 0) {
-        s_cand[tid >> 6] = cand;
-        s_rows[tid >> 6] = rows;
+    if (lane == 0) {
+        s_cand[wave] = cand;
+        s_rows[wave] = rows;
     }
     __syncthreads();
-    if (tid == 0)
-        part[(size_t)t * gridDim.x + blockIdx.x] =
-            make_ulonglong2(s_cand[0] + s_cand[1] + s_cand[2] + s_cand[3],
-                            s_rows[0] + s_rows[1] + s_rows[2] + s_rows[3]);
+    if (found) {
+        uint32_t at = sjk::lanes_below(bits);
+        for (uint32_t w = 0; w < wave; ++w)
+            at += s_n[w];
+        tmp[blk * 256 + at] = rec;
+    }
+    if (tid == 0) {
+        n_rec[blk] = s_n[0] + s_n[1] + s_n[2] + s_n[3];
+        part[blk] = make_ulonglong2(s_cand[0] + s_cand[1] + s_cand[2] + s_cand[3],
+                                    s_rows[0] + s_rows[1] + s_rows[2] + s_rows[3]);
+    }
 }
 
 // One block of 1024 threads: out[0] = sum of the parts' pair evaluations,
@@ -756,20 +785,22 @@ __global__ void __launch_bounds__(1024) sum_parts_kernel(const ulonglong2 *part,
     }
 }
 
-__global__ void __launch_bounds__(256) bucket_write_kernel(uint32_t n_p, uint64_t total,
-                                                           const uint32_t *flag,
-                                                           const uint32_t *f_np,
-                                                           const uint32_t *f_q0,
-                                                           const uint32_t *f_nq,
+// The blocks' records (bucket_find_kernel) one after the other; a wave per
+// block, rec_off the scan of n_rec, nb blocks per table.
+__global__ void __launch_bounds__(256) bucket_write_kernel(uint32_t nb, uint64_t n_blk,
+                                                           const uint4 *tmp, const uint32_t *n_rec,
                                                            const unsigned long long *rec_off,
                                                            Records rec)
 {
-    const uint64_t at = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (at >= total || !flag[at])
+    const uint64_t blk = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (blk >= n_blk)
         return;
-    const uint64_t r = rec_off[at];
-    rec.t[r] = (uint32_t)(at / n_p);
-    rec.pq[r] = make_uint4((uint32_t)(at % n_p), f_np[at], f_q0[at], f_nq[at]);
+    const uint32_t n = n_rec[blk], t = (uint32_t)(blk / nb);
+    const unsigned long long off = rec_off[blk];
+    for (uint32_t i = threadIdx.x & 63; i < n; i += 64) {
+        rec.t[off + i] = t;
+        rec.pq[off + i] = tmp[blk * 256 + i];
+    }
 }
 
 // One block per chunk of PACK_CHUNK records (see sj_lsh.h).  The sizes of the
@@ -1624,13 +1655,12 @@ hipError_t launch_fingerprints(const uint64_t *keys, uint32_t n, uint32_t L, uin
 }
 
 hipError_t launch_bucket_find(const uint64_t *sorted_p, uint32_t n_p, const uint64_t *sorted_q,
-                              uint32_t n_q, uint32_t L, void *ws, uint32_t *flag, uint32_t *f_np,
-                              uint32_t *f_q0, uint32_t *f_nq, unsigned long long *n_cand,
-                              hipStream_t s)
+                              uint32_t n_q, uint32_t L, void *ws, uint4 *tmp, uint32_t *n_rec,
+                              unsigned long long *n_cand, hipStream_t s)
 {
     if (n_p == 0 || n_q == 0 || L == 0)
         return hipSuccess;
-    const uint32_t nb = (n_p + 255) / 256;
+    const uint32_t nb = find_blocks(n_p);
     const uint64_t nr = (uint64_t)nb * L;
     // workspace: the block sums, then the block ranges of Q
     ulonglong2 *part = (ulonglong2 *)ws;
@@ -1641,7 +1671,7 @@ hipError_t launch_bucket_find(const uint64_t *sorted_p, uint32_t n_p, const uint
     if (e != hipSuccess)
         return e;
     hipLaunchKernelGGL(bucket_find_kernel, dim3(nb, L), dim3(256), 0, s, sorted_p, n_p, sorted_q,
-                       n_q, (const uint2 *)qr, flag, f_np, f_q0, f_nq, part);
+                       n_q, (const uint2 *)qr, tmp, n_rec, part);
     e = hipGetLastError();
     if (e != hipSuccess)
         return e;
@@ -1650,16 +1680,16 @@ hipError_t launch_bucket_find(const uint64_t *sorted_p, uint32_t n_p, const uint
     return hipGetLastError();
 }
 
-hipError_t launch_bucket_write(uint32_t n_p, uint32_t L, const uint32_t *flag,
-                               const uint32_t *f_np, const uint32_t *f_q0, const uint32_t *f_nq,
+hipError_t launch_bucket_write(uint32_t n_p, uint32_t L, const uint4 *tmp, const uint32_t *n_rec,
                                const unsigned long long *rec_off, const Records &rec,
                                hipStream_t s)
 {
-    const uint64_t total = (uint64_t)n_p * L;
-    if (total == 0)
+    const uint32_t nb = find_blocks(n_p);
+    const uint64_t n_blk = (uint64_t)nb * L;
+    if (n_blk == 0)
         return hipSuccess;
-    hipLaunchKernelGGL(bucket_write_kernel, dim3((uint32_t)((total + 255) / 256)), dim3(256), 0,
-                       s, n_p, total, flag, f_np, f_q0, f_nq, rec_off, rec);
+    hipLaunchKernelGGL(bucket_write_kernel, dim3((uint32_t)((n_blk + 3) / 4)), dim3(256), 0, s, nb,
+                       n_blk, tmp, n_rec, rec_off, rec);
     return hipGetLastError();
 }
 

@@ -99,7 +99,7 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
 
     // scratch: [rows P][rows Q][norms P][norms Q][keys P][keys Q][sorted P]
     //          [sorted Q][perm P][perm Q][fingerprints P, Q][packed tiles' rows
-    //          and tags P, Q][bucket marks, sizes and numbers]
+    //          and tags P, Q][buckets found, their numbers and offsets]
     //          [records][chunk counts and offsets][descriptors][scan partials]
     //          [counters][sort temp][widened projections][own output]
     size_t need = 0;
@@ -126,11 +126,10 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
     const size_t off_lq = self ? off_lp : take((size_t)L * n_q * 4);
     const size_t off_tp = take(pos_p);
     const size_t off_tq = self ? off_tp : take((size_t)L * n_q);
-    const size_t off_flag = take(pos_p * 4);
-    const size_t off_fnp = take(pos_p * 4);
-    const size_t off_fq0 = take(pos_p * 4);
-    const size_t off_fnq = take(pos_p * 4);
-    const size_t off_roff = take(pos_p * 8);
+    const uint64_t n_find = (uint64_t)sjl::find_blocks(n_p) * L;
+    const size_t off_tmp = take((size_t)n_find * 256 * 16);
+    const size_t off_nrec = take((size_t)n_find * 4);
+    const size_t off_roff = take((size_t)n_find * 8);
     const size_t off_rect = take(bp_cap * 4);
     const size_t off_recpq = take(bp_cap * 16);
     const size_t off_cdesc = take(chunk_cap * 4);
@@ -139,7 +138,7 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
     const size_t off_toff = take(chunk_cap * 8);
     const size_t off_dinfo = take(bp_cap * 16);
     const size_t off_dpq = take(bp_cap * 16);
-    const size_t off_part = take(sjk::scan_partials_size(pos_p > chunk_cap ? pos_p : chunk_cap) * 8);
+    const size_t off_part = take(sjk::scan_partials_size(n_find > chunk_cap ? n_find : chunk_cap) * 8);
     // counters: [0] pair evaluations, [1] records, [2] descriptors, [3] [4]
     // the hash's fix queues, [5] tiles, [6] tile overflow, [7] bucket rows
     const size_t off_cnt = take(8 * 8);
@@ -194,18 +193,16 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
     if (!self)
         SJ_HIP(sjl::sort_tables(keys_q, sorted_q, perm_q, n_q, L, bits, scr + off_temp, s));
     // the buckets P and Q share, as records in key order, then their tiles
-    uint32_t *flag = (uint32_t *)(scr + off_flag);
+    uint4 *found = (uint4 *)(scr + off_tmp);
+    uint32_t *n_found = (uint32_t *)(scr + off_nrec);
     // (its per-block sums in the sorts' workspace, free by now)
-    SJ_HIP(sjl::launch_bucket_find(sorted_p, n_p, sorted_q, n_q, L, scr + off_temp, flag,
-                                   (uint32_t *)(scr + off_fnp), (uint32_t *)(scr + off_fq0),
-                                   (uint32_t *)(scr + off_fnq), cnt, s));
+    SJ_HIP(sjl::launch_bucket_find(sorted_p, n_p, sorted_q, n_q, L, scr + off_temp, found, n_found,
+                                   cnt, s));
     unsigned long long *part = (unsigned long long *)(scr + off_part);
-    SJ_HIP(sjk::launch_scan(flag, pos_p, (unsigned long long *)(scr + off_roff), part, cnt + 1, s));
+    unsigned long long *rec_off = (unsigned long long *)(scr + off_roff);
+    SJ_HIP(sjk::launch_scan(n_found, n_find, rec_off, part, cnt + 1, s));
     const sjl::Records rec{(uint32_t *)(scr + off_rect), (uint4 *)(scr + off_recpq)};
-    SJ_HIP(sjl::launch_bucket_write(n_p, L, flag, (const uint32_t *)(scr + off_fnp),
-                                    (const uint32_t *)(scr + off_fq0),
-                                    (const uint32_t *)(scr + off_fnq),
-                                    (const unsigned long long *)(scr + off_roff), rec, s));
+    SJ_HIP(sjl::launch_bucket_write(n_p, L, found, n_found, rec_off, rec, s));
     SJ_HIP(hipMemcpyAsync(c->h_small, cnt + 1, 8, hipMemcpyDeviceToHost, s));
     SJ_HIP(hipStreamSynchronize(s));
     const uint64_t n_rec = c->h_small[0];
