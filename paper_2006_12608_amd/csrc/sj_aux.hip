@@ -155,14 +155,14 @@ template <int DT, int TEAM, bool COPY, bool NORM>
 __global__ void __launch_bounds__(256) prep_rows(PrepArgs a)
 {
     const uint64_t gt = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    const uint64_t r = gt / TEAM;
+    const uint64_t n = (uint64_t)a.n_p + a.n_q, step = (uint64_t)gridDim.x * (256 / TEAM);
     const uint32_t sub = (uint32_t)(gt % TEAM);
-    const bool is_q = r >= a.n_p;
-    const uint64_t row = is_q ? r - a.n_p : r;
-    const bool in = row < (is_q ? a.n_q : a.n_p);
     typedef typename std::conditional<DT == DT_I8, int, float>::type V;
-    V acc = V(0);
-    if (in) {
+    // (a team's lanes leave together)
+    for (uint64_t r = gt / TEAM; r < n; r += step) {
+        const bool is_q = r >= a.n_p;
+        const uint64_t row = is_q ? r - a.n_p : r;
+        V acc = V(0);
         const uint8_t *p = (is_q ? a.Q : a.P) + (size_t)row * a.src_bytes;
         uint8_t *o = COPY ? (is_q ? a.copy_q : a.copy_p) + (size_t)row * a.row_bytes : nullptr;
         for (uint32_t off = 16 * sub; off < a.row_bytes; off += 16 * TEAM) {
@@ -207,21 +207,23 @@ __global__ void __launch_bounds__(256) prep_rows(PrepArgs a)
                 }
             }
         }
-    }
-    if constexpr (NORM) {
+        if constexpr (NORM) {
 #pragma unroll
-        for (int m = TEAM / 2; m > 0; m >>= 1)
-            acc += __shfl_xor(acc, m, TEAM);
-        if (in && sub == 0)
-            ((V *)(is_q ? a.norm_q : a.norm_p))[row] = acc;
+            for (int m = TEAM / 2; m > 0; m >>= 1)
+                acc += __shfl_xor(acc, m, TEAM);
+            if (sub == 0)
+                ((V *)(is_q ? a.norm_q : a.norm_p))[row] = acc;
+        }
     }
 }
 
 template <int DT, int TEAM>
 static hipError_t prep_team(const PrepArgs &a, hipStream_t st)
 {
+    // a launch holds fewer than 2^32 threads: past 2^20 workgroups they take
+    // several rows each
     const uint64_t blocks = (((uint64_t)a.n_p + a.n_q) * TEAM + 255) / 256;
-    const dim3 grid((uint32_t)blocks);
+    const dim3 grid((uint32_t)(blocks < (1u << 20) ? blocks : 1u << 20));
     if (a.copy_p && a.norm_p)
         hipLaunchKernelGGL((prep_rows<DT, TEAM, true, true>), grid, dim3(256), 0, st, a);
     else if (a.copy_p)

@@ -203,17 +203,29 @@ __global__ void __launch_bounds__(256) normalize_rows(const uint8_t *X, uint32_t
     }
 }
 
+static const uint64_t kRowsPerLaunch = 1ull << 29;
+
 template <int DT>
 static hipError_t normalize_dt(const uint8_t *X, uint32_t n, uint32_t d, uint16_t *Y,
                                hipStream_t st)
 {
-    const dim3 grid((uint32_t)(((uint64_t)n + 63) / 64));
     // whole 16-byte chunks, both sides aligned
-    if (d % FrontChunk<DT>::E == 0 && (((uintptr_t)X | (uintptr_t)Y) & 15) == 0)
-        hipLaunchKernelGGL((normalize_rows<DT, true>), grid, dim3(256), 0, st, X, n, d, Y);
-    else
-        hipLaunchKernelGGL((normalize_rows<DT, false>), grid, dim3(256), 0, st, X, n, d, Y);
-    return hipGetLastError();
+    const bool vec = d % FrontChunk<DT>::E == 0 && (((uintptr_t)X | (uintptr_t)Y) & 15) == 0;
+    // (a launch holds fewer than 2^32 threads; 2^29 rows are a multiple of 16 bytes)
+    for (uint64_t r = 0; r < n; r += kRowsPerLaunch) {
+        const uint32_t m = (uint32_t)(n - r < kRowsPerLaunch ? n - r : kRowsPerLaunch);
+        const dim3 grid((m + 63) / 64);
+        const uint8_t *x = X + (size_t)r * d * (DT == DT_I8 ? 1 : 2);
+        uint16_t *y = Y + (size_t)r * d;
+        if (vec)
+            hipLaunchKernelGGL((normalize_rows<DT, true>), grid, dim3(256), 0, st, x, m, d, y);
+        else
+            hipLaunchKernelGGL((normalize_rows<DT, false>), grid, dim3(256), 0, st, x, m, d, y);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_normalize(int dtype, const void *X, uint32_t n, uint32_t d, void *Y,
@@ -246,29 +258,29 @@ __global__ void __launch_bounds__(256) unpack_hamming(const uint8_t *bits, uint3
                                                       uint32_t out_bytes, uint32_t team_lg,
                                                       uint8_t *out)
 {
-    const uint32_t row = blockIdx.x * (256u >> team_lg) + (threadIdx.x >> team_lg);
-    if (row >= n)
-        return;
-    const uint32_t in_stride = (d + 7) / 8, team = 1u << team_lg;
-    const uint8_t *rb = bits + (size_t)row * in_stride;
-    uint8_t *o = out + (size_t)row * out_bytes;
-    for (uint32_t c = threadIdx.x & (team - 1); c < out_bytes / 16; c += team) {
-        u32x4 v;
-#pragma unroll
-        for (uint32_t w = 0; w < 4; ++w) {
-            const uint32_t byte = 4 * c + w;
-            // bit k of the byte to bit 4 k, then to the nibble's sign
-            uint32_t x = byte < in_stride ? rb[byte] : 0u;
-            x = (x | (x << 12)) & 0x000f000fu;
-            x = (x | (x << 6)) & 0x03030303u;
-            x = (x | (x << 3)) & 0x11111111u;
-            const uint32_t m0 = 8 * byte;   // the word's first coordinate
-            const uint32_t valid = m0 + 8 <= d ? 0xffffffffu
-                                   : m0 >= d   ? 0u
-                                               : (1u << (4 * (d - m0))) - 1u;
-            v[w] = (0x22222222u | (x << 3)) & valid;
+    const uint32_t in_stride = (d + 7) / 8, team = 1u << team_lg, rows = 256u >> team_lg;
+    for (uint64_t row = (uint64_t)blockIdx.x * rows + (threadIdx.x >> team_lg); row < n;
+         row += (uint64_t)gridDim.x * rows) {
+        const uint8_t *rb = bits + (size_t)row * in_stride;
+        uint8_t *o = out + (size_t)row * out_bytes;
+        for (uint32_t c = threadIdx.x & (team - 1); c < out_bytes / 16; c += team) {
+            u32x4 v;
+    #pragma unroll
+            for (uint32_t w = 0; w < 4; ++w) {
+                const uint32_t byte = 4 * c + w;
+                // bit k of the byte to bit 4 k, then to the nibble's sign
+                uint32_t x = byte < in_stride ? rb[byte] : 0u;
+                x = (x | (x << 12)) & 0x000f000fu;
+                x = (x | (x << 6)) & 0x03030303u;
+                x = (x | (x << 3)) & 0x11111111u;
+                const uint32_t m0 = 8 * byte;   // the word's first coordinate
+                const uint32_t valid = m0 + 8 <= d ? 0xffffffffu
+                                       : m0 >= d   ? 0u
+                                                   : (1u << (4 * (d - m0))) - 1u;
+                v[w] = (0x22222222u | (x << 3)) & valid;
+            }
+            *(u32x4 *)(o + 16 * c) = v;
         }
-        *(u32x4 *)(o + 16 * c) = v;
     }
 }
 
@@ -281,8 +293,11 @@ hipError_t launch_unpack_hamming(const uint8_t *bits, uint32_t n, uint32_t d, ui
     while (team_lg < 8 && (16u << team_lg) < out_bytes)
         ++team_lg;
     const uint64_t rows = 256u >> team_lg;
-    hipLaunchKernelGGL(unpack_hamming, dim3((uint32_t)((n + rows - 1) / rows)), dim3(256), 0,
-                       stream, bits, n, d, out_bytes, team_lg, out);
+    // (a launch holds fewer than 2^32 threads)
+    const uint64_t blocks = (n + rows - 1) / rows;
+    const dim3 grid((uint32_t)(blocks < (1u << 20) ? blocks : 1u << 20));
+    hipLaunchKernelGGL(unpack_hamming, grid, dim3(256), 0, stream, bits, n, d, out_bytes, team_lg,
+                       out);
     return hipGetLastError();
 }
 

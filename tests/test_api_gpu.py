@@ -212,3 +212,42 @@ def test_outputs_sized_by_the_library(env, monkeypatch):
     monkeypatch.setattr(torch, "empty", empty)
     assert torch.equal(sj.join_ip(P, Q, 60.0), sj.join_ip(P, Q, 60.0))
     assert sj.count(P, Q, -1e6) == 2100 * 2110
+
+
+def test_more_rows_than_a_launch_has_threads(env):
+    """Row counts whose lanes pass the 2^32 threads one launch holds: rows
+    normalised by four lanes each, unaligned rows repacked by 32, codes unpacked
+    by 256.  The first, middle and last rows carry what is found."""
+    sj, _, torch = env
+    n = (1 << 30) + 70
+    say("rows past a launch: normalize", n)
+    X = torch.empty((n, 1), dtype=torch.int8, device="cuda").random_(-1, 2)
+    Y = torch.empty((n, 1), dtype=torch.float16, device="cuda")
+    ctx = sj.sj_create(0)
+    try:
+        assert sj.sj_normalize(ctx, sj.SJ_I8, X.data_ptr(), n, 1, Y.data_ptr()) == sj.SJ_OK
+        assert torch.equal(Y, X.to(torch.float16))
+        del X, Y
+        n = (1 << 27) + 5
+        say("rows past a launch: repack", n)
+        P = torch.zeros((n, 129), dtype=torch.int8, device="cuda")
+        Q = torch.ones((2, 129), dtype=torch.int8, device="cuda")
+        at = [0, n // 2, n - 1]
+        P[at] = 1
+        want = [[i, j] for i in at for j in (0, 1)]
+        for join, thr in ((sj.join_ip, 129.0), (sj.join_l2, 0.0)):
+            got = join(P, Q, thr, cap=64, ctx=ctx)
+            assert sorted(got.cpu().tolist()) == want
+        del P
+        n, d = (1 << 24) + 3, 8192
+        say("rows past a launch: unpack", n)
+        P = torch.zeros((n, d // 8), dtype=torch.uint8, device="cuda")
+        Q = torch.full((1, d // 8), 0xff, dtype=torch.uint8, device="cuda")
+        at = [0, n // 2, n - 1]
+        P[at] = 0xff
+        got = sj.join_hamming(P, Q, d, 0.0, cap=64, ctx=ctx)
+        assert sorted(got[:, 0].cpu().tolist()) == at
+        del P
+    finally:
+        sj.sj_destroy(ctx)
+        torch.cuda.empty_cache()
