@@ -263,10 +263,12 @@ int run(sj_ctx *c, const Request &rq, uint64_t *n_out, const Fixed *fx = nullptr
     const bool self = rq.P == rq.Q && rq.n_p == rq.n_q;
     const bool blocks = rq.two_pass || rq.count_only;
     const bool tri = self && !blocks;
+    // (the fixed scratch holds what it held with ordinary output blocks)
+    const bool small_ok = !tri && !(fx && blocks);
     sjk::Plan plan;
     if (!sjk::plan_join(rq.dtype, rq.metric, rq.n_p, rq.n_q,
-                        (uint32_t)(row_bytes == 0 ? 16 : (row_bytes + 15) & ~(size_t)15), tri,
-                        c->num_cus, &plan))
+                        (uint32_t)(row_bytes == 0 ? 16 : (row_bytes + 15) & ~(size_t)15),
+                        small_ok, c->num_cus, &plan))
         return fail(SJ_E_UNSUPPORTED, "shape %u x %u x %u is too large for one launch", rq.n_p,
                     rq.n_q, rq.d);
     // The kernels read rows as 16-byte chunks: inputs whose rows are not

@@ -36,8 +36,8 @@ static int resident_occupancy(int dtype, int metric, int variant)
     }
 }
 
-bool plan_join(int dtype, int metric, uint32_t n_p, uint32_t n_q, uint32_t row_bytes, bool tri,
-               int num_cus, Plan *plan)
+bool plan_join(int dtype, int metric, uint32_t n_p, uint32_t n_q, uint32_t row_bytes,
+               bool small_ok, int num_cus, Plan *plan)
 {
     const uint32_t ks_needed = row_bytes == 0 ? 1u : (row_bytes + 31) / 32;
     const int *tab = dtype == DT_I8 ? kResKS8 : kResKS16;
@@ -60,7 +60,7 @@ bool plan_join(int dtype, int metric, uint32_t n_p, uint32_t n_q, uint32_t row_b
         // 128 x 64 take 6.4).  Above that its tiles, which hold a quarter of
         // the rows per element of Q staged, lose (20000 x 300 x 256 fp16, 200
         // ordinary tiles: 8 us more).
-        if (!tri && n_pb * n_qt <= (uint64_t)num_cus / 2) {
+        if (small_ok && n_pb * n_qt <= (uint64_t)num_cus / 2) {
             plan->small = true;
             nw = kSmallNW;
             bm = nw * 32 * wmb;

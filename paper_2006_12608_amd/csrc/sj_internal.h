@@ -99,9 +99,11 @@ struct Plan {
 };
 
 // Chooses the kernel for (dtype, metric, shape) on a GPU with `num_cus` CUs
-// (tri: for MODE_TRI).  Returns false when the shape is unsupported.
-bool plan_join(int dtype, int metric, uint32_t n_p, uint32_t n_q, uint32_t row_bytes, bool tri,
-               int num_cus, Plan *plan);
+// (small_ok: the small geometry may be taken; MODE_TRI has none, and its
+// smaller output blocks need a little more room in count-then-emit's arrays).
+// Returns false when the shape is unsupported.
+bool plan_join(int dtype, int metric, uint32_t n_p, uint32_t n_q, uint32_t row_bytes,
+               bool small_ok, int num_cus, Plan *plan);
 
 hipError_t launch_join(const Plan &plan, int dtype, int metric, int mode, const JoinArgs &args,
                        hipStream_t stream);

@@ -111,3 +111,19 @@ def test_noalloc_rejects_what_does_not_fit(env):
                                0.0, out.data_ptr(), 16, sj.SJ_FLAG_TWO_PASS)
     assert st == sj.SJ_OK
     assert sj.sj_join_noalloc(None, 0, 1, None, 0, None, 0, 0, 0.0, None, 0)[0] == sj.SJ_E_INVAL
+
+
+def test_noalloc_two_pass_up_to_the_limit(env):
+    """A count-then-emit call whose repacked rows and block arrays fill the fixed
+    region up to its last 8 KiB: few enough tiles for the small geometry, whose
+    larger block arrays would not fit, so the ordinary one runs there."""
+    sj, ctx, torch = env
+    say("noalloc at the limit")
+    n_p, n_q, d = 65362, 100, 250
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4)
+    P = torch.randint(-3, 4, (n_p, d), generator=g, dtype=torch.int8, device="cuda")
+    Q = torch.randint(-3, 4, (n_q, d), generator=g, dtype=torch.int8, device="cuda")
+    a, b = _both(sj, ctx, torch, "ip", "i8", P, n_p, Q, n_q, d, 200.0,
+                 sj.SJ_FLAG_TWO_PASS | sj.SJ_FLAG_RECOMPUTE)
+    assert a.shape[0] > 0 and torch.equal(a, b)
