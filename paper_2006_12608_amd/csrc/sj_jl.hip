@@ -6,9 +6,10 @@
 // read as n r_i rows of c_i entries, is multiplied by A_i^T as one dense
 // product, and the result (n r_i rows of k_i entries) read back as n rows of
 // r_i k_i entries is the next level's input -- no data moves between levels.
-// Each level is one fp32 product Y = X A_i^T on the matrix cores
-// (v_mfma_f32_32x32x2_f32) with its operands staged through LDS; the first
-// level decodes fp16 / bf16 / int8 rows exactly to fp32.
+// Each level is an fp32 product Y = X A_i^T on the matrix cores
+// (v_mfma_f32_32x32x2_f32); the first level decodes fp16 / bf16 / int8 rows
+// exactly to fp32.  Chains of two or three levels whose factors fit LDS run in
+// one kernel (jl_chain); others one kernel per level (jl_level).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -252,6 +253,309 @@ hipError_t launch_level(int src, const void *X, uint64_t rows, uint32_t K, const
     case DT_I8: return launch_level_t<DT_I8>(X, rows, K, A, N, Y, s);
     }
     return hipErrorInvalidValue;
+}
+
+// ------------------------------------------------- all levels in one kernel
+//
+// A wave takes 32 of the batch's rows through every level, the intermediate
+// values in its registers.  Each product is taken transposed, D = A_i X^T: lane
+// l of the result holds features 8 (r / 4) + 4 (l / 32) + r % 4 (register r) of
+// row l % 32, and as the other operand of the next level's product register r of
+// the two halves is one step's pair of features of that row, so a result is the
+// next level's operand as it stands when the next factor's columns are taken in
+// that order.  The order of a sum is free, so LDS holds every factor as the lanes
+// read it: four consecutive columns of a row (float4) per half and four steps,
+// at [(4 steps) * 2 + half][row].  The levels are walked depth first (a level-1
+// product row is added to its level-2 row as soon as it is complete, and so on),
+// which keeps B1 + B2 + B3 blocks of 32 x 32 per wave whatever r_1 is.
+// Bound by the fp32 matrix cores: 262144 x 256 fp16 to 32 (zeta = 2) are 10.7
+// GFLOP, 68 us at their peak; HBM moves X and Y only (168 MB, 21 us at 8 TB/s)
+// where a kernel per level moves every level's values out and in (705 MB): that
+// call 180 -> 111 us (162 -> 91 us of it on the GPU), 32768 rows of 1024 to 16
+// (zeta = 4) 51 -> 34 us.
+struct ChainArgs {
+    const uint8_t *X;
+    const float *A;
+    float *Y;
+    uint32_t n, row_bytes;
+    uint32_t k1, c1, k2, c2, k3, c3;   // level sizes (k3 = c3 = 0: two levels)
+    uint32_t z1, z2;                   // level-1 rows per level-2 row, level-2 rows per level-3 row
+};
+
+typedef int jl_i32x4 __attribute__((ext_vector_type(4)));
+typedef float jl_f32x4 __attribute__((ext_vector_type(4)));
+
+// Element e of a 16-byte chunk.
+template <int SRC>
+__device__ __forceinline__ float chunk_at(const jl_i32x4 &v, int e)
+{
+    if constexpr (SRC == DT_I8)
+        return (float)(int8_t)((uint32_t)v[e >> 2] >> (8 * (e & 3)));
+    else
+        return dec1<SRC>(((uint32_t)v[e >> 1] >> (16 * (e & 1))) & 0xffffu);
+}
+
+// A factor (N x K, N padded with zero rows to 32 B) as the lanes read it; col(kq, h):
+// the first of the four columns of steps 4 kq .. 4 kq + 3 in half h.
+template <int B, typename F>
+__device__ __forceinline__ void stage_factor(jl_f32x4 *dst, const float *A, uint32_t N, uint32_t K,
+                                             F col)
+{
+    for (uint32_t i = threadIdx.x; i < K / 4 * 32 * B; i += blockDim.x) {
+        const uint32_t o = i % (32 * B), hq = i / (32 * B);
+        jl_f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (o < N)
+            __builtin_memcpy(&v, A + (size_t)o * K + col(hq >> 1, hq & 1), 16);
+        dst[i] = v;
+    }
+}
+
+// acc += A_{i+1}[:, one level-i row's features] * those features (k of them in x,
+// first float4 step kq0); w: the factor at this lane's half and row.
+template <int BI, int BO>
+__device__ __forceinline__ void chain_step(const f32x16 (&x)[BI], uint32_t k, uint32_t kq0,
+                                           const jl_f32x4 *w, f32x16 (&acc)[BO])
+{
+#pragma unroll
+    for (int ib = 0; ib < BI; ++ib)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (32u * ib + 8u * q < k) {   // uniform
+                const jl_f32x4 *wq = w + (size_t)(kq0 + 4 * ib + q) * 64 * BO;
+                jl_f32x4 f[BO];
+#pragma unroll
+                for (int b = 0; b < BO; ++b)
+                    f[b] = wq[32 * b];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int b = 0; b < BO; ++b)
+                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(f[b][e], x[ib][4 * q + e],
+                                                                      acc[b], 0, 0, 0);
+            }
+}
+
+constexpr int CHAIN_T = 512;   // threads
+
+// B1, B2, B3: 32-feature blocks of the levels (B3 = 0: two levels); SC: 32-byte
+// pieces of a row loaded at once (a whole number of times in a level-1 row);
+// CAP: float4 of factors LDS holds (two workgroups per CU up to 80 KB).
+template <int SRC, int B1, int B2, int B3, int SC, int CAP>
+__global__ void __launch_bounds__(CHAIN_T, CAP <= 5120 ? 4 : 2) jl_chain(ChainArgs g)
+{
+    constexpr int E = SRC == DT_I8 ? 16 : 8;   // elements per 16-byte chunk
+    constexpr int BL = B3 ? B3 : B2;
+    __shared__ jl_f32x4 s_w[CAP];
+    const int lane = threadIdx.x & 63, h = lane >> 5, c32 = lane & 31;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    jl_f32x4 *w1 = s_w, *w2 = w1 + g.c1 * 8 * B1, *w3 = w2 + g.c2 * 8 * B2;
+    // level 1: half h holds chunk h of each 32-byte piece of a row
+    stage_factor<B1>(w1, g.A, g.k1, g.c1, [](uint32_t kq, uint32_t hh) {
+        return kq / (E / 4) * 2 * E + hh * E + kq % (E / 4) * 4;
+    });
+    auto packed = [](uint32_t kq, uint32_t hh) { return 8 * kq + 4 * hh; };
+    const float *A2 = g.A + (size_t)g.k1 * g.c1;
+    stage_factor<B2>(w2, A2, g.k2, g.c2, packed);
+    if constexpr (B3 != 0)
+        stage_factor<B3>(w3, A2 + (size_t)g.k2 * g.c2, g.k3, g.c3, packed);
+    __syncthreads();
+    w1 += 32 * B1 * h + c32;
+    w2 += 32 * B2 * h + c32;
+    w3 += 32 * B3 * h + c32;
+
+    // blocks of 32 rows, dealt over the workgroups first
+    const uint32_t n_blk = (uint32_t)(((uint64_t)g.n + 31) / 32), step = gridDim.x * (CHAIN_T / 64);
+    const uint32_t spc = g.c1 * (SRC == DT_I8 ? 1 : 2) / (32 * SC);   // loads per level-1 row
+    auto row_at = [&](uint64_t blk) {   // rows past the batch read its last one
+        const uint64_t r = 32 * blk + c32;
+        return g.X + (size_t)(r < g.n ? r : g.n - 1) * g.row_bytes + 16 * h;
+    };
+    uint32_t blk = wave * gridDim.x + blockIdx.x;
+    if (blk >= n_blk)
+        return;
+    jl_i32x4 xv[SC];
+    const uint8_t *at = row_at(blk);
+#pragma unroll
+    for (int c = 0; c < SC; ++c)
+        xv[c] = *(const jl_i32x4 *)(at + 32 * c);
+    for (;;) {
+        const uint8_t *end = at + g.row_bytes, *after = row_at((uint64_t)blk + step);
+        f32x16 last[BL];
+#pragma unroll
+        for (int b = 0; b < BL; ++b)
+            last[b] = f32x16{};
+        for (uint32_t j2 = 0; j2 < g.z2; ++j2) {
+            f32x16 acc2[B2];
+#pragma unroll
+            for (int b = 0; b < B2; ++b)
+                acc2[b] = f32x16{};
+            for (uint32_t j1 = 0; j1 < g.z1; ++j1) {
+                f32x16 acc1[B1];
+#pragma unroll
+                for (int b = 0; b < B1; ++b)
+                    acc1[b] = f32x16{};
+                for (uint32_t s = 0; s < spc; ++s) {
+                    // the row's next piece, or the next row's first
+                    at += 32 * SC;
+                    if (at == end)
+                        at = after;
+                    jl_i32x4 xn[SC];
+#pragma unroll
+                    for (int c = 0; c < SC; ++c)
+                        xn[c] = *(const jl_i32x4 *)(at + 32 * c);
+                    const jl_f32x4 *ws = w1 + (size_t)s * (SC * (E / 4)) * 64 * B1;
+#pragma unroll
+                    for (int c = 0; c < SC; ++c)
+#pragma unroll
+                        for (int q = 0; q < E / 4; ++q) {
+                            jl_f32x4 f[B1];
+#pragma unroll
+                            for (int b = 0; b < B1; ++b)
+                                f[b] = ws[(c * (E / 4) + q) * 64 * B1 + 32 * b];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const float x = chunk_at<SRC>(xv[c], 4 * q + e);
+#pragma unroll
+                                for (int b = 0; b < B1; ++b)
+                                    acc1[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                                        f[b][e], x, acc1[b], 0, 0, 0);
+                            }
+                        }
+#pragma unroll
+                    for (int c = 0; c < SC; ++c)
+                        xv[c] = xn[c];
+                }
+                if constexpr (B3 != 0)
+                    chain_step<B1, B2>(acc1, g.k1, j1 * (g.k1 / 8), w2, acc2);
+                else
+                    chain_step<B1, B2>(acc1, g.k1, j1 * (g.k1 / 8), w2, last);
+            }
+            if constexpr (B3 != 0)
+                chain_step<B2, B3>(acc2, g.k2, j2 * (g.k2 / 8), w3, last);
+        }
+        const uint64_t row = 32 * (uint64_t)blk + c32;
+        if (row < g.n) {
+            const uint32_t kl = B3 ? g.k3 : g.k2;
+            float *y = g.Y + row * kl + 4 * h;
+#pragma unroll
+            for (int b = 0; b < BL; ++b)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (32u * b + 8u * q < kl)
+                        *(jl_f32x4 *)(y + 32 * b + 8 * q) =
+                            jl_f32x4{last[b][4 * q], last[b][4 * q + 1], last[b][4 * q + 2],
+                                     last[b][4 * q + 3]};
+        }
+        if (n_blk - blk <= step)
+            break;
+        blk += step;
+    }
+}
+
+template <int SRC, int B1, int B2, int B3, int CAP>
+hipError_t launch_chain_b(const ChainArgs &g, int num_cus, hipStream_t s)
+{
+    // one workgroup per CU while it has a wave for every block (its waves spread
+    // over the SIMDs: 32768 x 256 fp16 28 us with two, 19 with one), else as many as
+    // LDS holds
+    const uint64_t n_blk = ((uint64_t)g.n + 31) / 32;
+    const uint64_t wgs = (uint64_t)num_cus *
+                         (CAP <= 5120 && n_blk > (uint64_t)num_cus * (CHAIN_T / 64) ? 2 : 1);
+    const dim3 grid((uint32_t)(n_blk < wgs ? n_blk : wgs));
+    const uint32_t piece = g.c1 * (SRC == DT_I8 ? 1 : 2);
+    if (piece % 128 == 0)
+        hipLaunchKernelGGL((jl_chain<SRC, B1, B2, B3, 4, CAP>), grid, dim3(CHAIN_T), 0, s, g);
+    else if (piece % 64 == 0)
+        hipLaunchKernelGGL((jl_chain<SRC, B1, B2, B3, 2, CAP>), grid, dim3(CHAIN_T), 0, s, g);
+    else
+        hipLaunchKernelGGL((jl_chain<SRC, B1, B2, B3, 1, CAP>), grid, dim3(CHAIN_T), 0, s, g);
+    return hipGetLastError();
+}
+
+// The variants: blocks of each level, float4 of LDS (launch_chain_t).
+static const uint32_t kChainB[5][4] = {{1, 1, 0, 5120}, {1, 1, 1, 5120}, {1, 2, 1, 5120},
+                                       {2, 2, 0, 10240}, {2, 4, 2, 10240}};
+
+// The variant whose blocks cover the levels' sizes: its number, or -1.
+static int chain_variant(const ChainArgs &g)
+{
+    for (int v = 0; v < 5; ++v) {
+        const uint32_t b1 = kChainB[v][0], b2 = kChainB[v][1], b3 = kChainB[v][2];
+        if ((b3 != 0) == (g.k3 != 0) && g.k1 <= 32 * b1 && g.k2 <= 32 * b2 && g.k3 <= 32 * b3)
+            return (uint64_t)g.c1 * 8 * b1 + (uint64_t)g.c2 * 8 * b2 + (uint64_t)g.c3 * 8 * b3 <=
+                           kChainB[v][3]
+                       ? v
+                       : -1;
+    }
+    return -1;
+}
+
+template <int SRC>
+hipError_t launch_chain_t(int v, const ChainArgs &g, int num_cus, hipStream_t s)
+{
+    switch (v) {
+    case 0: return launch_chain_b<SRC, 1, 1, 0, 5120>(g, num_cus, s);
+    case 1: return launch_chain_b<SRC, 1, 1, 1, 5120>(g, num_cus, s);
+    case 2: return launch_chain_b<SRC, 1, 2, 1, 5120>(g, num_cus, s);
+    case 3: return launch_chain_b<SRC, 2, 2, 0, 10240>(g, num_cus, s);
+    default: return launch_chain_b<SRC, 2, 4, 2, 10240>(g, num_cus, s);
+    }
+}
+
+// Whether jl_chain takes the transform: two or three levels, the last of one row;
+// sizes k_i in whole quads of both halves (multiples of 8), level-1 rows of whole
+// 32-byte pieces, rows and results 16-byte aligned, factors that fit LDS, and
+// enough rows: one wave works through 32 rows alone, so few rows leave matrix
+// cores idle where a kernel per level spreads their level-1 rows.  Measured (256
+// CUs, us, this against a kernel per level): 320 MFMAs per 32 rows, 512 to 32
+// (zeta = 4): 8192 rows 17.7 / 15.6, 12288 rows 18.1 / 19.0, 262144 rows 97 / 159;
+// 1280, 1024 to 64 (zeta = 4): 16384 rows 55 / 47, 24576 rows 56 / 57, 262144 rows
+// 341 / 456; 1664, 2048 to 32 (zeta = 4): 16384 rows 70 / 60, 24576 rows 72 / 78,
+// 262144 rows 447 / 700.
+static bool chain_args(int src, const void *X, uint32_t n, uint32_t d, uint32_t levels,
+                       const uint32_t *shape, const float *A, float *Y, int num_cus, ChainArgs *g)
+{
+    if (levels < 2 || levels > 3)
+        return false;
+    const uint32_t *l1 = shape, *l2 = shape + 3, *l3 = shape + 6;
+    const uint32_t *last = levels == 3 ? l3 : l2;
+    const uint64_t es = src == DT_I8 ? 1 : 2;
+    if (last[2] != 1 || (l1[0] | l2[0] | last[0]) % 8 != 0 || l1[1] * es % 32 != 0 ||
+        l1[2] % l2[2] != 0 || (((uintptr_t)X | (uintptr_t)Y) & 15) != 0)
+        return false;
+    *g = ChainArgs{(const uint8_t *)X, A, Y, n, (uint32_t)(d * es), l1[0], l1[1], l2[0], l2[1],
+                   levels == 3 ? l3[0] : 0, levels == 3 ? l3[1] : 0, l1[2] / l2[2], l2[2]};
+    // MFMAs per 32 rows
+    const int v = d * es < ((uint64_t)1 << 32) ? chain_variant(*g) : -1;
+    if (v < 0)
+        return false;
+    const uint64_t steps = (uint64_t)l1[2] * kChainB[v][0] * l1[1] / 2 +
+                           (uint64_t)l2[2] * kChainB[v][1] * l2[1] / 2 +
+                           (uint64_t)kChainB[v][2] * g->c3 / 2;
+    return (uint64_t)n >= (steps <= 400 ? 48ull : 96ull) * (uint64_t)num_cus;
+}
+
+bool chain_applies(int src, const void *X, uint32_t n, uint32_t d, uint32_t levels,
+                   const uint32_t *shape, const float *A, float *Y, int num_cus)
+{
+    ChainArgs g;
+    return chain_args(src, X, n, d, levels, shape, A, Y, num_cus, &g);
+}
+
+// The whole transform, where chain_applies.
+hipError_t launch_chain(int src, const void *X, uint32_t n, uint32_t d, uint32_t levels,
+                        const uint32_t *shape, const float *A, float *Y, int num_cus,
+                        hipStream_t s)
+{
+    ChainArgs g;
+    if (!chain_args(src, X, n, d, levels, shape, A, Y, num_cus, &g))
+        return hipErrorInvalidValue;
+    const int v = chain_variant(g);
+    switch (src) {
+    case DT_F16: return launch_chain_t<DT_F16>(v, g, num_cus, s);
+    case DT_BF16: return launch_chain_t<DT_BF16>(v, g, num_cus, s);
+    default: return launch_chain_t<DT_I8>(v, g, num_cus, s);
+    }
 }
 
 }  // namespace sjj

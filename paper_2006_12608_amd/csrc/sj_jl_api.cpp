@@ -1,7 +1,7 @@
 // sj_jl_api.cpp -- host side of the TCU Johnson-Lindenstrauss transform
 // (sj_jl; contract in include/sj.h): size-chain checks, scratch for the
-// intermediate levels, one matrix-core product per level on the context's
-// stream (kernels in sj_jl.hip).
+// intermediate levels, and the transform on the context's stream: one kernel for
+// all levels where it applies (no scratch), else one per level (sj_jl.hip).
 #include <hip/hip_runtime.h>
 
 #include "sj.h"
@@ -12,6 +12,11 @@ using namespace sjh;
 namespace sjj {
 hipError_t launch_level(int src, const void *X, uint64_t rows, uint32_t K, const float *A,
                         uint32_t N, float *Y, hipStream_t s);
+bool chain_applies(int src, const void *X, uint32_t n, uint32_t d, uint32_t levels,
+                   const uint32_t *shape, const float *A, float *Y, int num_cus);
+hipError_t launch_chain(int src, const void *X, uint32_t n, uint32_t d, uint32_t levels,
+                        const uint32_t *shape, const float *A, float *Y, int num_cus,
+                        hipStream_t s);
 }
 
 extern "C" int sj_jl(sj_ctx *c, int dtype, const void *X, uint32_t n, uint32_t d,
@@ -55,23 +60,28 @@ extern "C" int sj_jl(sj_ctx *c, int dtype, const void *X, uint32_t n, uint32_t d
     c->stats = sj_stats{};
     if (n == 0)
         return SJ_OK;
-    const size_t half = align_up((size_t)tmp * 4);
-    if ((st = grow_scratch(c, 2 * half + 256)) != SJ_OK)
-        return st;
-    float *buf[2] = {(float *)c->scratch, (float *)((uint8_t *)c->scratch + half)};
-    hipStream_t s = c->stream;
     SJ_HIP(hipSetDevice(c->device));
+    hipStream_t s = c->stream;
+    const bool chain = sjj::chain_applies(dtype, X, n, d, levels, shape, A, Y, c->num_cus);
+    const size_t half = align_up((size_t)tmp * 4);
+    if (!chain && (st = grow_scratch(c, 2 * half + 256)) != SJ_OK)
+        return st;
     SJ_HIP(hipEventRecord(c->ev[0], s));
-    const void *in = X;
-    int src = dtype;
-    const float *a = A;
-    for (uint32_t i = 0; i < levels; ++i) {
-        const uint32_t k = shape[3 * i], cc = shape[3 * i + 1], r = shape[3 * i + 2];
-        float *out = i + 1 == levels ? Y : buf[i & 1];
-        SJ_HIP(sjj::launch_level(src, in, (uint64_t)n * r, cc, a, k, out, s));
-        in = out;
-        src = 0;
-        a += (size_t)k * cc;
+    if (chain) {
+        SJ_HIP(sjj::launch_chain(dtype, X, n, d, levels, shape, A, Y, c->num_cus, s));
+    } else {
+        float *buf[2] = {(float *)c->scratch, (float *)((uint8_t *)c->scratch + half)};
+        const void *in = X;
+        int src = dtype;
+        const float *a = A;
+        for (uint32_t i = 0; i < levels; ++i) {
+            const uint32_t k = shape[3 * i], cc = shape[3 * i + 1], r = shape[3 * i + 2];
+            float *out = i + 1 == levels ? Y : buf[i & 1];
+            SJ_HIP(sjj::launch_level(src, in, (uint64_t)n * r, cc, a, k, out, s));
+            in = out;
+            src = 0;
+            a += (size_t)k * cc;
+        }
     }
     SJ_HIP(hipEventRecord(c->ev[1], s));
     SJ_HIP(hipStreamSynchronize(s));

@@ -89,6 +89,55 @@ def test_jl_parity_real_factors(dtype, n, d, k, zeta):
     assert np.all(err <= bound), (err / np.maximum(bound, 1e-300)).max()
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "i8"])
+@pytest.mark.parametrize("d,k,zeta", [(256, 32, 2), (128, 32, 2), (128, 16, 2), (1024, 16, 4),
+                                      (64, 8, 2), (192, 24, 2), (512, 64, 2), (256, 64, 2),
+                                      (1024, 64, 4), (2048, 32, 4), (4096, 64, 4)])
+def test_jl_all_levels_in_one_kernel(dtype, d, k, zeta):
+    """Row counts around the least the one-kernel transform takes (48 or 96 per
+    CU), one and several blocks of 32 rows per wave, a ragged last block; every
+    variant by levels and size, sizes that fill no whole 32 features, and a chain
+    whose factors do not fit; rows that are not 16-byte aligned take the kernels
+    per level.  Each against the oracle, within the bound of the arithmetic."""
+    import torch
+    import paper_2006_12608_amd as sj
+    rng = np.random.default_rng(d + k)
+    shapes = chain(d, k, zeta)
+    As = [(rng.standard_normal((kk, c)) / np.sqrt(kk)).astype(np.float32).astype(np.float64)
+          for (kk, c, r) in shapes]
+    Ad = [torch.from_numpy(A.astype(np.float32)).cuda() for A in As]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    n_most = 140001 if d <= 256 else 98 * cus
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + k)
+    if dtype == "i8":
+        X = torch.randint(-20, 21, (n_most, d), generator=g, device="cuda", dtype=torch.int8)
+    else:
+        X = torch.randn((n_most, d), generator=g, device="cuda").to(
+            torch.float16 if dtype == "f16" else torch.bfloat16)
+    buf = torch.empty(n_most * d + 1, dtype=X.dtype, device="cuda")
+    odd = buf[1:].view(n_most, d)
+    odd.copy_(X)
+
+    def check(rows, name):
+        n = rows.shape[0]
+        say("jl one kernel", dtype, d, k, zeta, n, name)
+        Y = sj.jl_transform(rows, shapes, Ad)
+        at = torch.from_numpy(np.unique(np.concatenate(
+            [np.arange(70), n - 1 - np.arange(200), rng.integers(0, n, 400)]))).cuda()
+        x = rows[at].double().cpu().numpy()
+        bound = 2 * sum(gamma(c) for (_, c, _) in shapes) * jl.abs_bound(x, shapes, As)
+        err = np.abs(Y[at].double().cpu().numpy() - jl.transform(x, shapes, As))
+        assert np.all(err <= bound), (err / np.maximum(bound, 1e-300)).max()
+        return Y.double()
+    whole, levels = check(X, "aligned"), check(odd, "unaligned")
+    # every row: both sum the same products in fp32
+    assert (whole - levels).norm() <= 2e-6 * whole.norm()
+    for per_cu in (48, 96):
+        for n in (per_cu * cus - 1, per_cu * cus, per_cu * cus + 1):
+            check(X[:n], "least rows")
+
+
 @pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
 def test_jl_exact_on_integers(dtype):
     """Integer factors and inputs: every partial sum is an integer below 2^24,
