@@ -14,15 +14,21 @@
 // The 32-bit sort is a stable least-significant-digit radix sort over 8-bit
 // digits, run on all L tables at once: each table is a segment of n entries,
 // each segment is cut into blocks of SORT_TILE entries, and every pass is
-//   sort_hist:    per (segment, digit, block) counts of the pass's digit;
-//   exclusive scan of the counts laid out [segment][digit][block] (segment s
-//                 then starts at s n, since every segment holds n entries):
-//                 each (segment, digit, block)'s first output position;
+//   sort_hist:    per (segment, block, digit) counts of the pass's digit;
+//   sort_columns: per (segment, digit) the running sums of the counts over the
+//                 blocks, in their place, and the total;
 //   sort_scatter: each block ranks its entries stably by digit (wave ballots
 //                 find the lanes that share a digit; a per-wave running count
 //                 per digit continues the rank across the wave's rounds), puts
 //                 them in digit order in LDS and writes each digit's run to its
-//                 position, so a block's stores are contiguous runs.
+//                 position (s n, since every segment holds n entries, + the
+//                 segment's smaller digits + the digit's earlier blocks), so a
+//                 block's stores are contiguous runs.
+// A block's counts lie together: laid out [segment][digit][block] for one scan
+// over all of them, every count was a store and a load of 4 and 8 bytes in a line
+// of its own (16 tables of 1048576 entries: counts 44 -> 36 us, sums 30 -> 7 us a
+// pass; the LSH call on 1048576 x 64 int8 5719 -> 5527 us, 262144 x 256 fp16 2633 ->
+// 2568 us).
 // Bound by HBM: each pass reads the sort keys twice and the rows once and
 // writes both (20 bytes per entry).
 #include "sj_internal.h"
@@ -65,7 +71,46 @@ __global__ void __launch_bounds__(SORT_T) sort_hist(const uint32_t *keys, uint32
 #pragma unroll
     for (int w = 0; w < SORT_T / 64; ++w)
         c += cnt[w][tid];
-    hist[((uint64_t)seg * SORT_BINS + tid) * bps + blk] = c;
+    hist[(uint64_t)b * SORT_BINS + tid] = c;
+}
+
+// The counts of COL_D digits of one segment: their exclusive sums over the
+// segment's blocks, in place, and the digits' totals.  COL_C threads share a digit,
+// a run of blocks each (loaded twice; the second time from cache).
+constexpr int COL_D = 8, COL_C = 128;
+constexpr uint32_t kColSegs = 1u << 20;   // segments of one launch
+
+__global__ void __launch_bounds__(COL_D * COL_C) sort_columns(uint32_t *hist, uint32_t bps,
+                                                              uint32_t *total)
+{
+    __shared__ uint32_t s_sum[COL_C][COL_D];
+    const uint32_t d = threadIdx.x % COL_D, c = threadIdx.x / COL_D, seg = blockIdx.x;
+    const uint32_t dg = blockIdx.y * COL_D + d;
+    const uint32_t per = (bps + COL_C - 1) / COL_C;
+    const uint32_t b0 = min(c * per, bps), b1 = min(b0 + per, bps);
+    uint32_t *h = hist + (uint64_t)seg * bps * SORT_BINS + dg;
+    uint32_t sum = 0;
+#pragma unroll 8
+    for (uint32_t b = b0; b < b1; ++b)
+        sum += h[(uint64_t)b * SORT_BINS];
+    s_sum[c][d] = sum;
+    __syncthreads();
+    // inclusive sums over the digit's threads, by doubling steps
+    for (uint32_t o = 1; o < COL_C; o <<= 1) {
+        const uint32_t up = c >= o ? s_sum[c - o][d] : 0u;
+        __syncthreads();
+        s_sum[c][d] += up;
+        __syncthreads();
+    }
+    uint32_t run = s_sum[c][d] - sum;
+    if (c == COL_C - 1)
+        total[seg * SORT_BINS + dg] = s_sum[c][d];
+#pragma unroll 8
+    for (uint32_t b = b0; b < b1; ++b) {
+        const uint32_t v = h[(uint64_t)b * SORT_BINS];
+        h[(uint64_t)b * SORT_BINS] = run;
+        run += v;
+    }
 }
 
 __device__ __forceinline__ uint32_t lanes_below_mask(uint64_t m)
@@ -103,15 +148,15 @@ __device__ __forceinline__ uint32_t block_excl_prefix(uint32_t v, uint32_t *s_w)
 __global__ void __launch_bounds__(SORT_T) sort_scatter(const uint32_t *kin, const uint32_t *vin,
                                                        uint32_t *kout, uint32_t *vout, uint32_t n,
                                                        uint32_t bps, uint32_t shift,
-                                                       uint32_t nbits,
-                                                       const unsigned long long *offs)
+                                                       uint32_t nbits, const uint32_t *offs,
+                                                       const uint32_t *total)
 {
     __shared__ uint32_t s_k[SORT_TILE];
     __shared__ uint32_t s_v[SORT_TILE];
     __shared__ uint32_t s_run[SORT_T / 64][SORT_BINS];
     __shared__ uint32_t s_start[SORT_BINS];
     __shared__ unsigned long long s_off[SORT_BINS];
-    __shared__ uint32_t s_w[SORT_T / 64];
+    __shared__ uint32_t s_w[2][SORT_T / 64];
     const uint32_t b = blockIdx.x, seg = b / bps, blk = b - seg * bps;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t mask = (1u << nbits) - 1u;
@@ -163,8 +208,9 @@ __global__ void __launch_bounds__(SORT_T) sort_scatter(const uint32_t *kin, cons
             s_run[w][tid] = run;
             run += c;
         }
-        s_start[tid] = block_excl_prefix(run, s_w);
-        s_off[tid] = offs[((uint64_t)seg * SORT_BINS + tid) * bps + blk];
+        s_start[tid] = block_excl_prefix(run, s_w[0]);
+        s_off[tid] = (uint64_t)seg * n + block_excl_prefix(total[seg * SORT_BINS + tid], s_w[1]) +
+                     offs[(uint64_t)b * SORT_BINS + tid];
     }
     __syncthreads();
 #pragma unroll
@@ -312,8 +358,7 @@ size_t sort_temp_bytes(uint32_t n, uint32_t L)
     const uint64_t total = (uint64_t)n * L;
     const uint64_t counts = (uint64_t)L * SORT_BINS * blocks_per_segment(n);
     auto up = [](uint64_t x) { return (x + 255) & ~(uint64_t)255; };
-    return 2 * up(total * 4) + up(total * 4) + up(total * 4) + up(counts * 4) + up(counts * 8) +
-           up(sjk::scan_partials_size(counts) * 8) + 256;
+    return 4 * up(total * 4) + up(counts * 4) + up((uint64_t)L * SORT_BINS * 4) + 256;
 }
 
 hipError_t sort_tables(const uint64_t *keys, uint64_t *sorted, uint32_t *perm, uint32_t n,
@@ -331,10 +376,9 @@ hipError_t sort_tables(const uint64_t *keys, uint64_t *sorted, uint32_t *perm, u
     uint32_t *tv = (uint32_t *)(t + 2 * up(total * 4));        // rows, second buffer
     uint32_t *low = (uint32_t *)(t + 3 * up(total * 4));       // wide keys: low halves
     uint32_t *hist = (uint32_t *)(t + 4 * up(total * 4));
-    unsigned long long *offs = (unsigned long long *)((uint8_t *)hist + up(counts * 4));
-    unsigned long long *part = (unsigned long long *)((uint8_t *)offs + up(counts * 8));
+    uint32_t *total_d = (uint32_t *)((uint8_t *)hist + up(counts * 4));
     unsigned long long *tot =
-        (unsigned long long *)((uint8_t *)part + up(sjk::scan_partials_size(counts) * 8));
+        (unsigned long long *)((uint8_t *)total_d + up((uint64_t)L * SORT_BINS * 4));
     const bool wide = bits > 32;
     const uint32_t sbits = wide ? 32u : bits;
     const dim3 g1((uint32_t)((total + 255) / 256));
@@ -359,10 +403,17 @@ hipError_t sort_tables(const uint64_t *keys, uint64_t *sorted, uint32_t *perm, u
                            (1u << nbits) - 1u, hist);
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
-        if ((e = sjk::launch_scan(hist, counts, offs, part, tot, s)) != hipSuccess)
-            return e;
+        for (uint32_t l = 0; l < L; l += kColSegs) {   // (fewer than 2^32 threads a launch)
+            hipLaunchKernelGGL(sort_columns, dim3(min(L - l, kColSegs), SORT_BINS / COL_D),
+                               dim3(COL_D * COL_C), 0, s, hist + (uint64_t)l * bps * SORT_BINS,
+                               bps, total_d + (uint64_t)l * SORT_BINS);
+            if ((e = hipGetLastError()) != hipSuccess)
+                return e;
+            if (L - l <= kColSegs)
+                break;
+        }
         hipLaunchKernelGGL(sort_scatter, dim3(grid), dim3(SORT_T), 0, s, kin, vin, kout, vout, n,
-                           bps, shift, nbits, offs);
+                           bps, shift, nbits, hist, total_d);
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
         kin = kout;

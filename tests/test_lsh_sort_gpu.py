@@ -111,6 +111,19 @@ def test_sort_groups_rows(n, L, bits):
         same_relative_order(group_order(keys[0], perm[0]), group_order(k2, perm2[0]))
 
 
+@pytest.mark.parametrize("n,L,bits", [
+    (128 * 2048, 2, 20), (128 * 2048 + 1, 1, 32), (300 * 2048 - 5, 3, 9), (3, (1 << 20) + 3, 12),
+])
+def test_sort_block_counts(n, L, bits):
+    """Tables of about 128 and 300 blocks of 2048 (128 threads share a digit's
+    blocks), and more tables than one launch of the counts' sums takes: the
+    stable sort's rows."""
+    say("lsh_sort blocks", n, L, bits)
+    rng = np.random.default_rng(n + bits)
+    keys = rng.integers(0, 1 << bits, size=(L, n), dtype=np.uint64)
+    assert np.array_equal(gpu_sort(keys, bits), np.argsort(keys, axis=1, kind="stable"))
+
+
 def colliding_keys(rng, count: int) -> np.ndarray:
     """`count` distinct 64-bit keys whose mixes share their top 32 bits."""
     inv = pow(MIX_C, -1, 1 << 64)
