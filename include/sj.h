@@ -297,8 +297,8 @@ int sj_lsh_plan(double p1, double p2, uint64_t n, uint32_t tile, double recall, 
  * r_i k_i = r_{i+1} c_{i+1}; the output dimension is r_l k_l.  A (device,
  * fp32) holds A_1, ..., A_l one after the other, each row-major.  Y (device,
  * fp32) receives n x (r_l k_l) values.  Each level is one fp32 product on the
- * matrix cores (inputs decoded exactly to fp32; intermediate levels in fp32
- * device scratch of at most 2 n max_i(r_i k_i) floats).  The JL guarantee
+ * matrix cores (inputs decoded exactly to fp32; intermediate levels in fp32, in
+ * registers or in device scratch of at most 2 n max_i(r_i k_i) floats).  The JL guarantee
  * (norms kept within 1 +- eps with probability 1 - delta) is a property of
  * the caller's A_i (e.g. i.i.d. N(0, 1/k_i) entries), not of this call.
  * Errors as sj_join_ip (SJ_E_INVAL for a broken size chain, SJ_E_UNSUPPORTED

@@ -7,7 +7,7 @@
 // The bucket join is the brute-force join of Section 4 restricted to a pair of
 // buckets: Theorem 3's cost is the sum over tables and shared buckets of
 // |P bucket| x |Q bucket| inner products, each bucket pair handled as a
-// blocked product on 128 x 128 workgroup tiles (32 x 32 MFMA blocks), with the
+// blocked product on 256 x 256 workgroup tiles (32 x 32 MFMA blocks), with the
 // same fused threshold test and wave-ballot compaction as the all-pairs join.
 #include "sj_lsh.h"
 
