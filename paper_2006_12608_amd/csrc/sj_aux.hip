@@ -100,14 +100,13 @@ bool plan_join(int dtype, int metric, uint32_t n_p, uint32_t n_q, uint32_t row_b
     const uint64_t n_pt = (n_p + (uint64_t)kStBM - 1) / kStBM;
     const uint64_t n_qt = (n_q + (uint64_t)kStBN - 1) / kStBN;
     const uint64_t groups = ((n_pt + kStG - 1) / kStG) * ((n_qt + kStG - 1) / kStG);
-    const uint64_t grid = groups * kStG * kStG;
-    if (grid > 0x7fffffffull)
+    if (groups * kStG * kStG > 0x7fffffffull)
         return false;
     plan->family = FAM_STREAMED;
     plan->variant = 0;
     plan->qsplit = 1;
     plan->block = kStNW * 64;
-    plan->grid = (uint32_t)grid;
+    plan->grid = (uint32_t)(n_pt * n_qt);
     plan->cus = (uint32_t)num_cus;
     plan->n_blocks = n_pt * n_qt * kStNW;
     plan->wg_blocks32 = 0;

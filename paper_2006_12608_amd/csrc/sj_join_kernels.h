@@ -997,11 +997,12 @@ __global__ void __launch_bounds__(ST_NW * 64) join_streamed(JoinArgs g, uint32_t
     const int wr = wv >> 1, wc = wv & 1;
     const uint32_t n_chunks = (g.row_bytes + ST_KC - 1) / ST_KC;
 
-    // tile order: groups of 8 x 8 tiles, row-major inside a group; workgroup b
-    // takes the tiles numbered b, b + gridDim.x, ...
+    // tile order: groups of 8 x 8 tiles, row-major inside a group, numbered without
+    // gaps where groups at the edges are smaller; workgroup b takes the tiles
+    // numbered b, b + gridDim.x, ...  (Numbers left out of small groups would fall
+    // to the same workgroups in every group: few rows of P would occupy few CUs.)
     const uint32_t n_pt = (g.n_p + ST_BM - 1) / ST_BM, n_qt = (g.n_q + ST_BN - 1) / ST_BN;
     constexpr uint32_t G = 8;
-    const uint32_t groups_q = (n_qt + G - 1) / G;
     struct Tile {
         uint32_t pt, qt;
     };
@@ -1009,12 +1010,10 @@ __global__ void __launch_bounds__(ST_NW * 64) join_streamed(JoinArgs g, uint32_t
     // the next tile at or after idx, stepping by the grid; false past the last
     auto next_tile = [&](Tile &x) -> bool {
         for (; idx < n_idx; idx += gridDim.x) {
-            const uint32_t grp = idx / (G * G), in = idx % (G * G);
-            const uint32_t gp = grp / groups_q, gq = grp % groups_q;
-            const uint32_t hp = min(G, n_pt - gp * G), hq = min(G, n_qt - gq * G);
-            // groups at the ragged edges are smaller; their tiles are numbered densely
-            if (in >= hp * hq)
-                continue;
+            const uint32_t gp = idx / (G * n_qt), rem = idx - gp * (G * n_qt);
+            const uint32_t hp = min(G, n_pt - gp * G);
+            const uint32_t gq = rem / (hp * G), in = rem - gq * (hp * G);
+            const uint32_t hq = min(G, n_qt - gq * G);
             x.pt = gp * G + in / hq;
             x.qt = gq * G + in % hq;
             // self-join triangle: a tile wholly below the diagonal holds no pair i <= j
