@@ -2,6 +2,7 @@
 // exclusive scan of the count-then-emit protocol and its emit pass from match
 // bits (gfx950).
 #include "sj_internal.h"
+#include "sj_tiles.h"
 
 #include <type_traits>
 
@@ -22,7 +23,7 @@ static const int kResKS16[4] = {2, 4, 8, 16};
 static const int kResKS8[4] = {1, 2, 4, 8};
 static const uint32_t kResNW = 8, kSmallNW = 2, kSmallBN = 64;
 static uint32_t res_bn(int ks) { return ks <= 2 ? 256 : ks <= 8 ? 128 : 64; }
-static const uint32_t kStBM = ST_BM, kStBN = ST_BN, kStG = 8, kStNW = ST_NW;
+static const uint32_t kStBM = ST_BM, kStBN = ST_BN, kStG = ST_G, kStNW = ST_NW;
 
 static int resident_occupancy(int dtype, int metric, int variant)
 {

@@ -18,6 +18,7 @@
 #pragma once
 
 #include "sj_internal.h"
+#include "sj_tiles.h"
 
 #include <type_traits>
 
@@ -969,7 +970,7 @@ __global__ void __launch_bounds__(NW * 64) join_resident(JoinArgs g)
 constexpr int ST_KC = 128;   // K chunk bytes (tile geometry in sj_internal.h)
 
 template <int DT, int MET, int MODE>
-__global__ void __launch_bounds__(ST_NW * 64) join_streamed(JoinArgs g, uint32_t n_idx)
+__global__ void __launch_bounds__(ST_NW * 64) join_streamed(JoinArgs g)
 {
     typedef Mma<DT> M;
     typedef typename M::acc_t acc_t;
@@ -997,33 +998,10 @@ __global__ void __launch_bounds__(ST_NW * 64) join_streamed(JoinArgs g, uint32_t
     const int wr = wv >> 1, wc = wv & 1;
     const uint32_t n_chunks = (g.row_bytes + ST_KC - 1) / ST_KC;
 
-    // tile order: groups of 8 x 8 tiles, row-major inside a group, numbered without
-    // gaps where groups at the edges are smaller; workgroup b takes the tiles
-    // numbered b, b + gridDim.x, ...  (Numbers left out of small groups would fall
-    // to the same workgroups in every group: few rows of P would occupy few CUs.)
+    // the tiles this workgroup takes, in order (sj_tiles.h)
     const uint32_t n_pt = (g.n_p + ST_BM - 1) / ST_BM, n_qt = (g.n_q + ST_BN - 1) / ST_BN;
-    constexpr uint32_t G = 8;
-    struct Tile {
-        uint32_t pt, qt;
-    };
-    uint32_t idx = blockIdx.x;
-    // the next tile at or after idx, stepping by the grid; false past the last
-    auto next_tile = [&](Tile &x) -> bool {
-        for (; idx < n_idx; idx += gridDim.x) {
-            const uint32_t gp = idx / (G * n_qt), rem = idx - gp * (G * n_qt);
-            const uint32_t hp = min(G, n_pt - gp * G);
-            const uint32_t gq = rem / (hp * G), in = rem - gq * (hp * G);
-            const uint32_t hq = min(G, n_qt - gq * G);
-            x.pt = gp * G + in / hq;
-            x.qt = gq * G + in % hq;
-            // self-join triangle: a tile wholly below the diagonal holds no pair i <= j
-            if (MODE == MODE_TRI && x.pt > x.qt)
-                continue;
-            idx += gridDim.x;   // (n_idx < 2^31: no wrap)
-            return true;
-        }
-        return false;
-    };
+    typedef TileAt Tile;
+    TileWalk<MODE == MODE_TRI> walk(n_pt, n_qt, blockIdx.x, gridDim.x);
 
     // Direct loads: wave instruction k = wave + ST_NW i fills LDS positions
     // [64 k, 64 k + 64), i.e. rows 8 k .. 8 k + 7; lane l row l / 8, position l %
@@ -1152,9 +1130,9 @@ __global__ void __launch_bounds__(ST_NW * 64) join_streamed(JoinArgs g, uint32_t
     };
 
     Tile cur{0, 0}, nxt{0, 0};
-    if (!next_tile(cur))
+    if (!walk.next(cur))
         return;   // the whole workgroup
-    bool more = next_tile(nxt);
+    bool more = walk.next(nxt);
     uint32_t kc = 0;
 
     // One K chunk: the next chunk's loads, then KSC k-steps, each reading SA A- and
@@ -1211,7 +1189,7 @@ __global__ void __launch_bounds__(ST_NW * 64) join_streamed(JoinArgs g, uint32_t
         if (!more)
             return false;
         cur = nxt;
-        more = next_tile(nxt);
+        more = walk.next(nxt);
         return true;
     };
     stage_issue(cur, 0, s_op0);
@@ -1339,9 +1317,11 @@ hipError_t launch_mode(const Plan &p, const JoinArgs &g, hipStream_t st)
 {
     if (p.family == FAM_STREAMED) {
         if constexpr (MODE != MODE_RECORD) {
+            // the self-join triangle takes the tiles on and above the diagonal
+            const uint32_t n_pt = (g.n_p + ST_BM - 1) / ST_BM;
+            const uint32_t tiles = MODE == MODE_TRI ? TileWalk<true>::count(n_pt, n_pt) : p.grid;
             hipLaunchKernelGGL((join_streamed<DT, MET, MODE>),
-                               dim3(p.grid < p.cus ? p.grid : p.cus), dim3(ST_NW * 64), 0, st, g,
-                               p.grid);
+                               dim3(tiles < p.cus ? tiles : p.cus), dim3(ST_NW * 64), 0, st, g);
             return hipGetLastError();
         }
     } else if constexpr (MODE != MODE_MASK) {
