@@ -15,8 +15,9 @@
 // digits, run on all L tables at once: each table is a segment of n entries,
 // each segment is cut into blocks of SORT_TILE entries, and every pass is
 //   sort_hist:    per (segment, block, digit) counts of the pass's digit;
-//   sort_columns: per (segment, digit) the running sums of the counts over the
-//                 blocks, in their place, and the total;
+//   column_sums:  per (segment, digit) the running sums of the counts over the
+//                 blocks, in their place, and the total (sort_columns or
+//                 sort_runs, by the number of blocks);
 //   sort_scatter: each block ranks its entries stably by digit (wave ballots
 //                 find the lanes that share a digit; a per-wave running count
 //                 per digit continues the rank across the wave's rounds), puts
@@ -72,6 +73,34 @@ __global__ void __launch_bounds__(SORT_T) sort_hist(const uint32_t *keys, uint32
     for (int w = 0; w < SORT_T / 64; ++w)
         c += cnt[w][tid];
     hist[(uint64_t)b * SORT_BINS + tid] = c;
+}
+
+// Runs of at most RUN_B blocks of a segment, a workgroup each, a thread per digit
+// (every block's counts are one coalesced load).  SUMS: the run's sums to part[run].
+// Otherwise the counts become their exclusive sums in place, from part[run] on
+// (part null: the segment is one run, whose totals are written).
+constexpr uint32_t RUN_B = 64;
+
+template <bool SUMS>
+__global__ void __launch_bounds__(SORT_BINS) sort_runs(uint32_t *hist, uint32_t bps, uint32_t runs,
+                                                       uint32_t *part, uint32_t *total)
+{
+    const uint32_t b = blockIdx.x, seg = b / runs, dg = threadIdx.x;
+    const uint32_t b0 = (b - seg * runs) * RUN_B, b1 = min(b0 + RUN_B, bps);
+    uint32_t *h = hist + (uint64_t)seg * bps * SORT_BINS + dg;
+    const uint64_t at = (uint64_t)b * SORT_BINS + dg;
+    uint32_t run = SUMS || !part ? 0u : part[at];
+#pragma unroll 16
+    for (uint32_t k = b0; k < b1; ++k) {
+        const uint32_t v = h[(uint64_t)k * SORT_BINS];
+        if constexpr (!SUMS)
+            h[(uint64_t)k * SORT_BINS] = run;
+        run += v;
+    }
+    if constexpr (SUMS)
+        part[at] = run;
+    else if (!part)
+        total[at] = run;
 }
 
 // The counts of COL_D digits of one segment: their exclusive sums over the
@@ -210,7 +239,7 @@ __global__ void __launch_bounds__(SORT_T) sort_scatter(const uint32_t *kin, cons
         }
         s_start[tid] = block_excl_prefix(run, s_w[0]);
         s_off[tid] = (uint64_t)seg * n + block_excl_prefix(total[seg * SORT_BINS + tid], s_w[1]) +
-                     offs[(uint64_t)b * SORT_BINS + tid];
+                     (offs ? offs[(uint64_t)b * SORT_BINS + tid] : 0u);
     }
     __syncthreads();
 #pragma unroll
@@ -350,15 +379,65 @@ __global__ void __launch_bounds__(256) fixup_kernel(const uint32_t *sk, const ui
     }
 }
 
-// Blocks per segment, and the counts' length (segments x digits x blocks).
-static uint32_t blocks_per_segment(uint32_t n) { return (n + SORT_TILE - 1) / SORT_TILE; }
+// Blocks per segment, and their runs of RUN_B.
+static uint32_t blocks_per_segment(uint32_t n)
+{
+    return (uint32_t)(((uint64_t)n + SORT_TILE - 1) / SORT_TILE);
+}
+static uint32_t runs_per_segment(uint32_t bps) { return (bps + RUN_B - 1) / RUN_B; }
 
 size_t sort_temp_bytes(uint32_t n, uint32_t L)
 {
     const uint64_t total = (uint64_t)n * L;
     const uint64_t counts = (uint64_t)L * SORT_BINS * blocks_per_segment(n);
     auto up = [](uint64_t x) { return (x + 255) & ~(uint64_t)255; };
-    return 4 * up(total * 4) + up(counts * 4) + up((uint64_t)L * SORT_BINS * 4) + 256;
+    const uint64_t parts = (uint64_t)L * SORT_BINS * runs_per_segment(blocks_per_segment(n));
+    return 4 * up(total * 4) + up(counts * 4) + up(parts * 4) + up((uint64_t)L * SORT_BINS * 4) + 256;
+}
+
+// sort_columns over the counts (or the runs' sums) of L segments.
+static hipError_t launch_columns(uint32_t *hist, uint32_t bps, uint32_t L, uint32_t *total,
+                                 hipStream_t s)
+{
+    for (uint64_t l = 0; l < L; l += kColSegs) {   // (fewer than 2^32 threads a launch)
+        hipLaunchKernelGGL(sort_columns, dim3((uint32_t)min((uint64_t)L - l, (uint64_t)kColSegs),
+                                              SORT_BINS / COL_D),
+                           dim3(COL_D * COL_C), 0, s, hist + l * bps * SORT_BINS, bps,
+                           total + l * SORT_BINS);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
+}
+
+// The counts' exclusive sums over each segment's blocks, in place, and the totals.
+// sort_columns has 32 workgroups of 1024 threads per segment: too many for segments
+// of a few blocks (1000 tables of 1000 entries, 24 bits: a call 384 us, 71 with
+// none; 100000 of 50: 34 ms and 1.5 ms), too few for one segment of many (67108864
+// entries: 2764 us, 2292 by runs; with 48 bits 8.6 ms).  A single run's chain of
+// loads takes about as long as sort_columns at 16 blocks and a few segments or 64
+// blocks and some 50 (16 tables of 64 blocks: 119 us against 110).  By runs and their
+// sums, three launches, from 4096 blocks on (1 and 4 tables of 4096 blocks: 313 and
+// 1128 us by columns, 288 and 1092 by runs; of 512 blocks 97 and 167 against 113 and
+// 179).
+static hipError_t column_sums(uint32_t *hist, uint32_t bps, uint32_t runs, uint32_t L,
+                              uint32_t *part, uint32_t *total, hipStream_t s)
+{
+    if (bps <= 1)
+        return hipSuccess;   // a block's counts are its segment's totals
+    if (runs > 1 ? bps < 4096 : bps > (uint64_t)L + 16)
+        return launch_columns(hist, bps, L, total, s);
+    if (runs > 1) {
+        hipLaunchKernelGGL(sort_runs<true>, dim3(L * runs), dim3(SORT_BINS), 0, s, hist, bps, runs,
+                           part, nullptr);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess || (e = launch_columns(part, runs, L, total, s)) != hipSuccess)
+            return e;
+    }
+    hipLaunchKernelGGL(sort_runs<false>, dim3(L * runs), dim3(SORT_BINS), 0, s, hist, bps, runs,
+                       runs > 1 ? part : nullptr, total);
+    return hipGetLastError();
 }
 
 hipError_t sort_tables(const uint64_t *keys, uint64_t *sorted, uint32_t *perm, uint32_t n,
@@ -376,7 +455,10 @@ hipError_t sort_tables(const uint64_t *keys, uint64_t *sorted, uint32_t *perm, u
     uint32_t *tv = (uint32_t *)(t + 2 * up(total * 4));        // rows, second buffer
     uint32_t *low = (uint32_t *)(t + 3 * up(total * 4));       // wide keys: low halves
     uint32_t *hist = (uint32_t *)(t + 4 * up(total * 4));
-    uint32_t *total_d = (uint32_t *)((uint8_t *)hist + up(counts * 4));
+    const uint32_t runs = runs_per_segment(bps);
+    const uint64_t parts = (uint64_t)L * SORT_BINS * runs;
+    uint32_t *part = (uint32_t *)((uint8_t *)hist + up(counts * 4));
+    uint32_t *total_d = (uint32_t *)((uint8_t *)part + up(parts * 4));
     unsigned long long *tot =
         (unsigned long long *)((uint8_t *)total_d + up((uint64_t)L * SORT_BINS * 4));
     const bool wide = bits > 32;
@@ -403,17 +485,10 @@ hipError_t sort_tables(const uint64_t *keys, uint64_t *sorted, uint32_t *perm, u
                            (1u << nbits) - 1u, hist);
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
-        for (uint32_t l = 0; l < L; l += kColSegs) {   // (fewer than 2^32 threads a launch)
-            hipLaunchKernelGGL(sort_columns, dim3(min(L - l, kColSegs), SORT_BINS / COL_D),
-                               dim3(COL_D * COL_C), 0, s, hist + (uint64_t)l * bps * SORT_BINS,
-                               bps, total_d + (uint64_t)l * SORT_BINS);
-            if ((e = hipGetLastError()) != hipSuccess)
-                return e;
-            if (L - l <= kColSegs)
-                break;
-        }
+        if ((e = column_sums(hist, bps, runs, L, part, total_d, s)) != hipSuccess)
+            return e;
         hipLaunchKernelGGL(sort_scatter, dim3(grid), dim3(SORT_T), 0, s, kin, vin, kout, vout, n,
-                           bps, shift, nbits, hist, total_d);
+                           bps, shift, nbits, bps > 1 ? hist : nullptr, bps > 1 ? total_d : hist);
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
         kin = kout;

@@ -179,3 +179,27 @@ def test_sort_empty_and_errors():
     assert e.value.status == sj.SJ_E_INVAL
     with pytest.raises(ValueError):
         sj.lsh_sort(torch.zeros((1, 16), dtype=torch.int32, device="cuda"), 8)
+
+
+@pytest.mark.parametrize("L,n", [
+    (5, 2048), (5, 2049),                        # one block per table, two
+    (1, 17 * 2048), (1, 17 * 2048 + 1),          # 17 and 18 blocks: one run, columns
+    (60, 64 * 2048), (60, 64 * 2048 + 1),        # 64 and 65 blocks
+    (1, 4095 * 2048), (2, 4095 * 2048 + 1),      # 4095 and 4096 blocks: columns, runs
+    (70000, 33), (3000, 2100)])
+def test_sort_tables_of_any_number_of_blocks(L, n):
+    """The sums over a table's blocks take another kernel for one block, a run of
+    at most 64, many blocks and very many; each must give the stable order."""
+    import torch
+    import paper_2006_12608_amd as sj
+    say("sort", L, n)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7000 + n)
+    for bits in (9, 20):
+        k = torch.randint(0, 1 << bits, (L, n), generator=g, device="cuda", dtype=torch.int64)
+        perm = sj.lsh_sort(k, bits).long()
+        s = k.gather(1, perm)
+        up = s[:, 1:] > s[:, :-1]
+        assert bool((up | ((s[:, 1:] == s[:, :-1]) & (perm[:, 1:] > perm[:, :-1]))).all())
+        assert bool((torch.zeros_like(k).scatter_(1, perm, 1) == 1).all())
+        del k, perm, s, up
