@@ -309,13 +309,19 @@ __global__ void __launch_bounds__(256) expand_key_kernel(const uint32_t *sk, uin
 // key: 16 tables of 1048576 rows 164 us instead of 204, the same with each XCD's
 // blocks on tables of their own).  A break is a position
 // whose mix differs from its predecessor's within a run of equal top halves;
-// the run's first break walks back to the run's first position and lists it
-// (16 M list entries' worth of marks and the kernels that read them cost 69 us).
+// the run's first break walks back to the run's first position and lists it, in
+// its block's 256 entries of the list (the block's number in n_list; one counter
+// for all blocks serialised them: 524000 runs among 67108864 keys, 8.0 ms a call,
+// 4.2 by blocks).
 __global__ void __launch_bounds__(256) gather_low_kernel(const uint32_t *sk, const uint32_t *low,
                                                          uint32_t n, uint64_t total,
                                                          const uint32_t *perm, uint64_t *sorted,
-                                                         uint32_t *list, unsigned long long *n_list)
+                                                         uint32_t *list, uint32_t *n_list)
 {
+    __shared__ uint32_t s_n;
+    if (threadIdx.x == 0)
+        s_n = 0;
+    __syncthreads();
     const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
     const bool in = i < total;
     const uint64_t s0 = in ? i / n * n : 0;
@@ -327,22 +333,26 @@ __global__ void __launch_bounds__(256) gather_low_kernel(const uint32_t *sk, con
     }
     // the predecessor, from the lane below (lane 0 reads it)
     uint32_t kp = __shfl_up(k, 1, 64), lp = __shfl_up(l, 1, 64);
-    if (!in || i == s0)
-        return;
-    if ((threadIdx.x & 63) == 0) {
-        kp = sk[i - 1];
-        if (kp == k)
-            lp = low[s0 + perm[i - 1]];
+    if (in && i != s0) {
+        if ((threadIdx.x & 63) == 0) {
+            kp = sk[i - 1];
+            if (kp == k)
+                lp = low[s0 + perm[i - 1]];
+        }
+        if (kp == k && lp != l) {
+            uint64_t a = i - 1;
+            bool first = true;   // else an earlier break lists the run
+            while (first && a > s0 && sk[a - 1] == k) {
+                first = low[s0 + perm[a - 1]] == lp;
+                --a;
+            }
+            if (first)
+                list[(uint64_t)blockIdx.x * 256 + atomicAdd(&s_n, 1u)] = (uint32_t)a;
+        }
     }
-    if (kp != k || lp == l)
-        return;
-    uint64_t a = i - 1;
-    while (a > s0 && sk[a - 1] == k) {
-        if (low[s0 + perm[a - 1]] != lp)
-            return;   // an earlier break lists the run
-        --a;
-    }
-    list[atomicAdd(n_list, 1ull)] = (uint32_t)a;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        n_list[blockIdx.x] = s_n;
 }
 
 // Sorts every listed run by the mixed key, stably (insertion sort).  Two
@@ -351,15 +361,15 @@ __global__ void __launch_bounds__(256) gather_low_kernel(const uint32_t *sk, con
 // joining the rows of two buckets; the cost of a run is its number of
 // inversions, at most the product of the two buckets' sizes.  Runs are
 // disjoint and each has one first position, so no two threads write the same
-// entries.
+// entries.  A thread per block of the list (gather_low_kernel).
 __global__ void __launch_bounds__(256) fixup_kernel(const uint32_t *sk, const uint32_t *list,
-                                                    const unsigned long long *n_list, uint32_t n,
-                                                    uint64_t *sorted, uint32_t *perm)
+                                                    const uint32_t *n_list, uint32_t blocks,
+                                                    uint32_t n, uint64_t *sorted, uint32_t *perm)
 {
-    const uint64_t n_run = *n_list;
-    for (uint64_t x = (uint64_t)blockIdx.x * 256 + threadIdx.x; x < n_run;
-         x += (uint64_t)gridDim.x * 256) {
-        const uint64_t i = list[x];
+    const uint64_t blk = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    const uint32_t n_run = blk < blocks ? n_list[blk] : 0u;
+    for (uint32_t x = 0; x < n_run; ++x) {
+        const uint64_t i = list[256 * blk + x];
         const uint64_t end = (i / n + 1) * n;
         uint64_t e = i + 1;
         while (e < end && sk[e] == sk[i])
@@ -392,7 +402,7 @@ size_t sort_temp_bytes(uint32_t n, uint32_t L)
     const uint64_t counts = (uint64_t)L * SORT_BINS * blocks_per_segment(n);
     auto up = [](uint64_t x) { return (x + 255) & ~(uint64_t)255; };
     const uint64_t parts = (uint64_t)L * SORT_BINS * runs_per_segment(blocks_per_segment(n));
-    return 4 * up(total * 4) + up(counts * 4) + up(parts * 4) + up((uint64_t)L * SORT_BINS * 4) + 256;
+    return 4 * up(total * 4) + up(counts * 4) + up(parts * 4) + up((uint64_t)L * SORT_BINS * 4);
 }
 
 // sort_columns over the counts (or the runs' sums) of L segments.
@@ -459,8 +469,6 @@ hipError_t sort_tables(const uint64_t *keys, uint64_t *sorted, uint32_t *perm, u
     const uint64_t parts = (uint64_t)L * SORT_BINS * runs;
     uint32_t *part = (uint32_t *)((uint8_t *)hist + up(counts * 4));
     uint32_t *total_d = (uint32_t *)((uint8_t *)part + up(parts * 4));
-    unsigned long long *tot =
-        (unsigned long long *)((uint8_t *)total_d + up((uint64_t)L * SORT_BINS * 4));
     const bool wide = bits > 32;
     const uint32_t sbits = wide ? 32u : bits;
     const dim3 g1((uint32_t)((total + 255) / 256));
@@ -498,16 +506,15 @@ hipError_t sort_tables(const uint64_t *keys, uint64_t *sorted, uint32_t *perm, u
         hipLaunchKernelGGL(expand_key_kernel, g1, dim3(256), 0, s, kin, total, sorted);
         return hipGetLastError();
     }
-    // the rows' second buffer is free after the last pass: the list of runs
-    if ((e = sjk::launch_zero_u64(tot, 1, s)) != hipSuccess)
-        return e;
+    // the rows' second buffer is free after the last pass, and so are the counts:
+    // the list of runs, and each block's number of them
     hipLaunchKernelGGL(gather_low_kernel, g1, dim3(256), 0, s, kin, low, n, total, perm, sorted,
-                       tv, tot);
+                       tv, hist);
     if ((e = hipGetLastError()) != hipSuccess)
         return e;
-    hipLaunchKernelGGL(fixup_kernel, dim3(128), dim3(256), 0, s, kin, tv, tot, n, sorted, perm);
-    e = hipGetLastError();
-    return e;
+    hipLaunchKernelGGL(fixup_kernel, dim3((g1.x + 255) / 256), dim3(256), 0, s, kin, tv, hist,
+                       g1.x, n, sorted, perm);
+    return hipGetLastError();
 }
 
 }  // namespace sjl

@@ -203,3 +203,21 @@ def test_sort_tables_of_any_number_of_blocks(L, n):
         assert bool((up | ((s[:, 1:] == s[:, :-1]) & (perm[:, 1:] > perm[:, :-1]))).all())
         assert bool((torch.zeros_like(k).scatter_(1, perm, 1) == 1).all())
         del k, perm, s, up
+
+
+def test_many_colliding_runs():
+    """Hundreds of runs of colliding top halves, of two to five keys each, several
+    in one 256-position block and across blocks and tables."""
+    say("lsh_sort many colliding runs")
+    rng = np.random.default_rng(78)
+    coll = np.concatenate([colliding_keys(rng, int(rng.integers(2, 6))) for _ in range(400)])
+    L, n = 3, 7001
+    keys = coll[rng.integers(0, coll.size, size=(L, n))]
+    keys[:, ::7] = rng.integers(0, 1 << 62, size=keys[:, ::7].shape).astype(np.uint64)
+    perm = gpu_sort(keys, 64)
+    orders = [group_order(keys[t], perm[t]) for t in range(L)]
+    for o in orders:
+        mixed = [mix(int(k)) for k in o]
+        assert mixed == sorted(mixed)
+    same_relative_order(orders[0], orders[1])
+    same_relative_order(orders[1], orders[2])
