@@ -12,6 +12,7 @@
 #include "sj_host.h"
 #include "sj_internal.h"
 #include "sj_lsh.h"
+#include "sj_lsh_layout.h"
 #include "sj_sized.h"
 
 using namespace sjh;
@@ -87,77 +88,51 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
     const bool self = P == Q && n_p == n_q;
     const bool l2 = metric == SJ_L2;
     const uint32_t bits = sjl::key_bits(k, w);
+    // keys on the matrix cores where they apply
+    const bool fast = sjl::keys_fast_applies(dtype, (uint32_t)krow, L, k, w);
     // records: at most min(n_p, n_q) per table (a table has at most that
     // many keys shared by P and Q); packing chunks of them
     const uint64_t bp_cap = (uint64_t)L * (n_p < n_q ? n_p : n_q);
     const uint64_t chunk_cap = (bp_cap + sjl::PACK_CHUNK - 1) / sjl::PACK_CHUNK;
-    const uint64_t pos_p = (uint64_t)L * n_p;   // sorted positions of P, all tables
-    // one sort workspace, used by P and then by Q
-    const size_t temp_bytes = std::max(sjl::sort_temp_bytes(n_max, L),
-                                       sjl::bucket_find_ws_bytes(n_p, L));
-    const size_t a_bytes = sjl::widened_bytes(dtype, L, k, d);
-
-    // scratch: [rows P][rows Q][norms P][norms Q][keys P][keys Q][sorted P]
-    //          [sorted Q][perm P][perm Q][fingerprints P, Q][packed tiles' rows
-    //          and tags P, Q][buckets found, their numbers and offsets]
-    //          [records][chunk counts and offsets][descriptors][scan partials]
-    //          [counters][sort temp][widened projections][own output]
-    size_t need = 0;
-    auto take = [&](size_t bytes) {
-        const size_t at = need;
-        need = align_up(need + bytes);
-        return at;
-    };
-    const size_t off_rp = aligned ? 0 : take((size_t)n_p * krow);
-    const size_t off_rq = aligned || self ? off_rp : take((size_t)n_q * krow);
-    const size_t off_np = l2 ? take((size_t)n_p * 4) : 0;
-    const size_t off_nq = l2 && !self ? take((size_t)n_q * 4) : off_np;
-    const size_t off_kp = take((size_t)L * n_p * 8);
-    const size_t off_kq = self ? off_kp : take((size_t)L * n_q * 8);
-    const size_t off_sp = take((size_t)L * n_p * 8);
-    const size_t off_sq = self ? off_sp : take((size_t)L * n_q * 8);
-    const size_t off_pp = take((size_t)L * n_p * 4);
-    const size_t off_pq = self ? off_pp : take((size_t)L * n_q * 4);
-    const uint32_t fc = sjl::fp_chunks(L);
-    const size_t off_fpp = L > 1 ? take((size_t)n_p * 16 * fc) : 0;
-    const size_t off_fpq = L > 1 && !self ? take((size_t)n_q * 16 * fc) : off_fpp;
-    // the rows of packed tiles (a self-join's buckets are the same on both sides)
-    const size_t off_lp = take(pos_p * 4);
-    const size_t off_lq = self ? off_lp : take((size_t)L * n_q * 4);
-    const size_t off_tp = take(pos_p);
-    const size_t off_tq = self ? off_tp : take((size_t)L * n_q);
     const uint64_t n_find = (uint64_t)sjl::find_blocks(n_p) * L;
-    const size_t off_tmp = take((size_t)n_find * 256 * 16);
-    const size_t off_nrec = take((size_t)n_find * 4);
-    const size_t off_roff = take((size_t)n_find * 8);
-    const size_t off_rect = take(bp_cap * 4);
-    const size_t off_recpq = take(bp_cap * 16);
-    const size_t off_cdesc = take(chunk_cap * 4);
-    const size_t off_ctile = take(chunk_cap * 4);
-    const size_t off_doff = take(chunk_cap * 8);
-    const size_t off_toff = take(chunk_cap * 8);
-    const size_t off_dinfo = take(bp_cap * 16);
-    const size_t off_dpq = take(bp_cap * 16);
-    const size_t off_part = take(sjk::scan_partials_size(n_find > chunk_cap ? n_find : chunk_cap) * 8);
-    // counters: [0] pair evaluations, [1] records, [2] descriptors, [3] [4]
-    // the hash's fix queues, [5] tiles, [6] tile overflow, [7] bucket rows
-    const size_t off_cnt = take(8 * 8);
-    const size_t off_temp = take(temp_bytes);
-    const size_t off_aw = take(a_bytes);
-    // keys on the matrix cores where they apply
-    const bool fast = sjl::keys_fast_applies(dtype, (uint32_t)krow, L, k, w);
-    const uint64_t own = sized ? std::min((uint64_t)n_p * n_q, kOwnPairs) : 0;
-    const size_t off_own = take((size_t)own * 8);
-    const size_t off_ws = fast ? take(sjl::keys_fast_bytes((uint32_t)n_max, L, k, (uint32_t)krow)) : 0;
-    if ((st = grow_scratch(c, need)) != SJ_OK)
-        return st;
+    sjl::ScratchNeeds needs = {};
+    needs.n_p = n_p;
+    needs.n_q = n_q;
+    needs.L = L;
+    needs.self = self;
+    needs.copy_row = aligned ? 0 : krow;
+    needs.norm = l2 ? 4 : 0;
+    needs.fingerprint = L > 1 ? 16 * sjl::fp_chunks(L) : 0;
+    needs.hash_ws = fast ? sjl::keys_fast_bytes((uint32_t)n_max, L, k, (uint32_t)krow) : 0;
+    needs.widened = sjl::widened_bytes(dtype, L, k, d);
+    // used by P's sort, then by Q's, then by the bucket search
+    needs.sort_ws = std::max(sjl::sort_temp_bytes(n_max, L), sjl::bucket_find_ws_bytes(n_p, L));
+    needs.find_blocks = n_find;
+    needs.records = bp_cap;
+    needs.chunks = chunk_cap;
+    needs.scan_partials = sjk::scan_partials_size(n_find > chunk_cap ? n_find : chunk_cap) * 8;
+    needs.own_pairs = sized ? std::min((uint64_t)n_p * n_q, kOwnPairs) : 0;
+    sjl::ScratchLayout lay = sjl::scratch_layout(needs);
+    if ((st = grow_scratch(c, lay.total)) != SJ_OK) {
+        if (needs.own_pairs == 0)
+            return st;
+        // without room of its own for the output the bucket join runs twice
+        needs.own_pairs = 0;
+        lay = sjl::scratch_layout(needs);
+        g_err.clear();
+        if ((st = grow_scratch(c, lay.total)) != SJ_OK)
+            return st;
+    }
+    const uint64_t own = needs.own_pairs;
     uint8_t *scr = (uint8_t *)c->scratch;
     hipStream_t s = c->stream;
     SJ_HIP(hipSetDevice(c->device));
 
-    sjl::Rows rp{aligned ? (const uint8_t *)P : scr + off_rp, n_p, (uint32_t)krow};
-    sjl::Rows rq{aligned ? (const uint8_t *)Q : scr + off_rq, n_q, (uint32_t)krow};
-    unsigned long long *cnt = (unsigned long long *)(scr + off_cnt);
+    sjl::Rows rp{aligned ? (const uint8_t *)P : scr + lay.row_p, n_p, (uint32_t)krow};
+    sjl::Rows rq{aligned ? (const uint8_t *)Q : scr + lay.row_q, n_q, (uint32_t)krow};
+    // counters: [0] pair evaluations, [1] records, [2] descriptors, [3] [4]
+    // the hash's fix queues, [5] tiles, [6] tile overflow, [7] bucket rows
+    unsigned long long *cnt = (unsigned long long *)(scr + lay.counters);
     SJ_HIP(hipMemsetAsync(cnt, 0, 8 * 8, s));
     if (!c->counter_clear)
         SJ_HIP(sjk::launch_zero_u64(c->d_small, 1, s));
@@ -165,55 +140,49 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
     SJ_HIP(hipEventRecord(c->ev[0], s));
     SJ_HIP(sjk::launch_prep(dtype, P, n_p, Q, self ? 0u : n_q,
                             aligned ? (uint32_t)krow : (uint32_t)row_bytes, (uint32_t)krow,
-                            aligned ? nullptr : scr + off_rp, aligned ? nullptr : scr + off_rq,
-                            l2 ? scr + off_np : nullptr, l2 ? scr + off_nq : nullptr, s));
-    uint64_t *keys_p = (uint64_t *)(scr + off_kp), *keys_q = (uint64_t *)(scr + off_kq);
-    SJ_HIP(sjl::launch_widen(dtype, A, L * k, d, scr + off_aw, s));
+                            aligned ? nullptr : scr + lay.row_p, aligned ? nullptr : scr + lay.row_q,
+                            l2 ? scr + lay.norm_p : nullptr, l2 ? scr + lay.norm_q : nullptr, s));
+    uint64_t *keys_p = (uint64_t *)(scr + lay.key_p), *keys_q = (uint64_t *)(scr + lay.key_q);
+    SJ_HIP(sjl::launch_widen(dtype, A, L * k, d, scr + lay.widened, s));
     if (fast) {
-        SJ_HIP(sjl::launch_keys_fast(dtype, rp, d, L, k, A, scr + off_aw, B, w, keys_p,
-                                     scr + off_ws, true, cnt + 3, s));
+        SJ_HIP(sjl::launch_keys_fast(dtype, rp, d, L, k, A, scr + lay.widened, B, w, keys_p,
+                                     scr + lay.hash_ws, true, cnt + 3, s));
         if (!self)
-            SJ_HIP(sjl::launch_keys_fast(dtype, rq, d, L, k, A, scr + off_aw, B, w,
-                                         keys_q, scr + off_ws, false, cnt + 4, s));
+            SJ_HIP(sjl::launch_keys_fast(dtype, rq, d, L, k, A, scr + lay.widened, B, w,
+                                         keys_q, scr + lay.hash_ws, false, cnt + 4, s));
     } else {
-        SJ_HIP(sjl::launch_keys(dtype, rp, d, L, k, scr + off_aw, B, w, keys_p, s));
+        SJ_HIP(sjl::launch_keys(dtype, rp, d, L, k, scr + lay.widened, B, w, keys_p, s));
         if (!self)
-            SJ_HIP(sjl::launch_keys(dtype, rq, d, L, k, scr + off_aw, B, w, keys_q, s));
-    }
-    uint4 *fp_p = (uint4 *)(scr + off_fpp), *fp_q = (uint4 *)(scr + off_fpq);
-    if (L > 1) {
-        SJ_HIP(sjl::launch_fingerprints(keys_p, n_p, L, fp_p, s));
-        if (!self)
-            SJ_HIP(sjl::launch_fingerprints(keys_q, n_q, L, fp_q, s));
+            SJ_HIP(sjl::launch_keys(dtype, rq, d, L, k, scr + lay.widened, B, w, keys_q, s));
     }
     SJ_HIP(hipEventRecord(c->ev[1], s));
-    uint64_t *sorted_p = (uint64_t *)(scr + off_sp), *sorted_q = (uint64_t *)(scr + off_sq);
-    uint32_t *perm_p = (uint32_t *)(scr + off_pp), *perm_q = (uint32_t *)(scr + off_pq);
-    SJ_HIP(sjl::sort_tables(keys_p, sorted_p, perm_p, n_p, L, bits, scr + off_temp, s));
+    uint64_t *sorted_p = (uint64_t *)(scr + lay.sorted_p), *sorted_q = (uint64_t *)(scr + lay.sorted_q);
+    uint32_t *perm_p = (uint32_t *)(scr + lay.perm_p), *perm_q = (uint32_t *)(scr + lay.perm_q);
+    SJ_HIP(sjl::sort_tables(keys_p, sorted_p, perm_p, n_p, L, bits, scr + lay.sort_ws, s));
     if (!self)
-        SJ_HIP(sjl::sort_tables(keys_q, sorted_q, perm_q, n_q, L, bits, scr + off_temp, s));
+        SJ_HIP(sjl::sort_tables(keys_q, sorted_q, perm_q, n_q, L, bits, scr + lay.sort_ws, s));
     // the buckets P and Q share, as records in key order, then their tiles
-    uint4 *found = (uint4 *)(scr + off_tmp);
-    uint32_t *n_found = (uint32_t *)(scr + off_nrec);
+    uint4 *found = (uint4 *)(scr + lay.found);
+    uint32_t *n_found = (uint32_t *)(scr + lay.n_found);
     // (its per-block sums in the sorts' workspace, free by now)
-    SJ_HIP(sjl::launch_bucket_find(sorted_p, n_p, sorted_q, n_q, L, scr + off_temp, found, n_found,
+    SJ_HIP(sjl::launch_bucket_find(sorted_p, n_p, sorted_q, n_q, L, scr + lay.sort_ws, found, n_found,
                                    cnt, s));
-    unsigned long long *part = (unsigned long long *)(scr + off_part);
-    unsigned long long *rec_off = (unsigned long long *)(scr + off_roff);
+    unsigned long long *part = (unsigned long long *)(scr + lay.partials);
+    unsigned long long *rec_off = (unsigned long long *)(scr + lay.found_off);
     SJ_HIP(sjk::launch_scan(n_found, n_find, rec_off, part, cnt + 1, s));
-    const sjl::Records rec{(uint32_t *)(scr + off_rect), (uint4 *)(scr + off_recpq)};
+    const sjl::Records rec{(uint32_t *)(scr + lay.rec_t), (uint4 *)(scr + lay.rec_pq)};
     SJ_HIP(sjl::launch_bucket_write(n_p, L, found, n_found, rec_off, rec, s));
     SJ_HIP(hipMemcpyAsync(c->h_small, cnt + 1, 8, hipMemcpyDeviceToHost, s));
     SJ_HIP(hipStreamSynchronize(s));
     const uint64_t n_rec = c->h_small[0];
     const uint64_t n_chunk = (n_rec + sjl::PACK_CHUNK - 1) / sjl::PACK_CHUNK;
-    const sjl::Descs desc{(uint4 *)(scr + off_dpq), (uint4 *)(scr + off_dinfo)};
+    const sjl::Descs desc{(uint4 *)(scr + lay.desc_pq), (uint4 *)(scr + lay.desc_info)};
     const sjl::Lists lists{n_p, n_q, perm_p, perm_q,
-                           (uint32_t *)(scr + off_lp), (uint32_t *)(scr + off_lq),
-                           scr + off_tp, scr + off_tq};
-    uint32_t *cdesc = (uint32_t *)(scr + off_cdesc), *ctile = (uint32_t *)(scr + off_ctile);
-    unsigned long long *doff = (unsigned long long *)(scr + off_doff);
-    unsigned long long *toff = (unsigned long long *)(scr + off_toff);
+                           (uint32_t *)(scr + lay.list_p), (uint32_t *)(scr + lay.list_q),
+                           scr + lay.tag_p, scr + lay.tag_q};
+    uint32_t *cdesc = (uint32_t *)(scr + lay.n_desc), *ctile = (uint32_t *)(scr + lay.n_tile);
+    unsigned long long *doff = (unsigned long long *)(scr + lay.desc_off);
+    unsigned long long *toff = (unsigned long long *)(scr + lay.tile_off);
     SJ_HIP(sjl::launch_pack(rec, (uint32_t)n_rec, false, cdesc, ctile, nullptr, nullptr, desc,
                             lists, cnt + 6, s));
     if (n_chunk) {
@@ -222,6 +191,12 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
     }
     SJ_HIP(sjl::launch_pack(rec, (uint32_t)n_rec, true, cdesc, ctile, doff, toff, desc, lists,
                             cnt + 6, s));
+    uint4 *fp_p = (uint4 *)(scr + lay.fp_p), *fp_q = (uint4 *)(scr + lay.fp_q);
+    if (L > 1) {
+        SJ_HIP(sjl::launch_fingerprints(keys_p, n_p, L, fp_p, s));
+        if (!self)
+            SJ_HIP(sjl::launch_fingerprints(keys_q, n_q, L, fp_q, s));
+    }
     SJ_HIP(hipEventRecord(c->ev[2], s));
     unsigned long long hc[8];
     SJ_HIP(hipMemcpyAsync(hc, cnt, sizeof hc, hipMemcpyDeviceToHost, s));
@@ -254,9 +229,9 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
     } else {
         g.thr_f = l2 ? float_at_or_below(thr) : float_at_or_above(thr);
     }
-    g.norm_p = scr + off_np;
-    g.norm_q = scr + off_nq;
-    g.pairs = sized ? (uint32_t *)(scr + off_own) : pairs;
+    g.norm_p = scr + lay.norm_p;
+    g.norm_q = scr + lay.norm_q;
+    g.pairs = sized ? (uint32_t *)(scr + lay.own) : pairs;
     g.cap = sized ? own : cap;
     g.counter = c->d_small;
     SJ_HIP(sjl::launch_join(dtype, metric, g, c->num_cus, s));

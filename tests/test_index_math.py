@@ -10,6 +10,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 SOURCE = r"""
+#include "sj_lsh_layout.h"
 #include "sj_tiles.h"
 // Tiles of workgroup b of `grid`, as pt << 32 | qt; returns their number.
 template <bool TRI>
@@ -26,6 +27,22 @@ extern "C" uint32_t tiles(int tri, uint32_t n_pt, uint32_t n_qt, uint32_t b, uin
                           uint64_t *out)
 {
     return tri ? walk<true>(n_pt, n_qt, b, grid, out) : walk<false>(n_pt, n_qt, b, grid, out);
+}
+extern "C" void layout(const uint64_t *n, uint64_t *out)
+{
+    sjl::ScratchNeeds c = {};
+    c.n_p = n[0], c.n_q = n[1], c.L = n[2], c.self = n[3], c.copy_row = n[4], c.norm = n[5];
+    c.fingerprint = n[6], c.hash_ws = n[7], c.widened = n[8], c.sort_ws = n[9];
+    c.find_blocks = n[10], c.records = n[11], c.chunks = n[12], c.scan_partials = n[13];
+    c.own_pairs = n[14];
+    const sjl::ScratchLayout y = sjl::scratch_layout(c);
+    const size_t v[] = {y.row_p, y.row_q, y.norm_p, y.norm_q, y.key_p, y.key_q, y.perm_p, y.perm_q,
+                        y.counters, y.partials, y.hash_ws, y.widened, y.sorted_p, y.sorted_q,
+                        y.sort_ws, y.found, y.n_found, y.found_off, y.rec_t, y.rec_pq, y.n_desc,
+                        y.n_tile, y.desc_off, y.tile_off, y.list_p, y.list_q, y.tag_p, y.tag_q,
+                        y.desc_info, y.desc_pq, y.fp_p, y.fp_q, y.own, y.total};
+    for (unsigned i = 0; i < sizeof v / sizeof *v; ++i)
+        out[i] = v[i];
 }
 """
 
@@ -75,3 +92,76 @@ def test_streamed_triangle_tiles(lib, n):
     want = {(p, q) for p in range(n) for q in range(p, n)}
     for grid in (1, min(256, len(want)), min(304, len(want))):
         check(workgroup_tiles(lib, True, n, n, grid), want)
+
+
+NAMES = ("row_p row_q norm_p norm_q key_p key_q perm_p perm_q counters partials hash_ws widened "
+         "sorted_p sorted_q sort_ws found n_found found_off rec_t rec_pq n_desc n_tile desc_off "
+         "tile_off list_p list_q tag_p tag_q desc_info desc_pq fp_p fp_q own total").split()
+# the steps of a call (0 hash, 1 sorts, 2 bucket search, 3 records, 4 packing, 5
+# fingerprints, 6 join) from an array's first write to its last read
+LIVE = {"hash_ws": (0, 0), "widened": (0, 0), "perm_p": (1, 6), "perm_q": (1, 6),
+        "sorted_p": (1, 2), "sorted_q": (1, 2), "sort_ws": (1, 2), "found": (2, 3),
+        "n_found": (2, 3), "found_off": (2, 3), "rec_t": (3, 4), "rec_pq": (3, 4), "n_desc": (4, 4),
+        "n_tile": (4, 4), "desc_off": (4, 4), "tile_off": (4, 4), "list_p": (4, 6),
+        "list_q": (4, 6), "tag_p": (4, 6), "tag_q": (4, 6), "desc_info": (4, 6), "desc_pq": (4, 6),
+        "fp_p": (5, 6), "fp_q": (5, 6), "own": (6, 6)}
+
+
+@pytest.mark.parametrize("n_p,n_q", [(1, 1), (700, 300), (50000, 50000), (1 << 20, 1 << 20),
+                                     (1000, 1 << 24), (1 << 24, 1000), (3 << 20, 5 << 20)])
+@pytest.mark.parametrize("L", [1, 2, 16, 64, 200])
+@pytest.mark.parametrize("self_join", [False, True])
+@pytest.mark.parametrize("long_rows", [False, True])
+def test_lsh_scratch_layout(lib, n_p, n_q, L, self_join, long_rows):
+    """Arrays that are needed at the same time never overlap, and without the room for
+    its own output a call needs no more than the arrays one after the other took when
+    none shared its place (so no call that fitted the card stops fitting)."""
+    if self_join:
+        n_q = n_p
+    if L * max(n_p, n_q) >= 1 << 32:
+        pytest.skip("refused")
+    n_max, fast = max(n_p, n_q), L <= 64
+    pos_p, pos_q, rec = L * n_p, L * n_q, L * min(n_p, n_q)
+    find, chunks = L * ((n_p + 255) // 256), (rec + 127) // 128
+    bps, krow, k = (n_max + 2047) // 2048, 512 if long_rows else 64, 8
+    counts = L * 256 * bps
+    hash_ws = L * k * (krow + 4) + 512 + L * n_max * 16 if fast else 0
+    widened = L * k * (krow // 2) * 8
+    sort_ws = max(4 * (4 * L * n_max + 256) + 4 * counts + 4 * L * 256 * ((bps + 63) // 64)
+                  + L * 1024 + 1024, find * 24)
+    fp = 16 * ((min(L, 64) + 15) // 16) if L > 1 else 0
+    partials = 8 * (max(find, chunks) // 4096 + 2)
+    for own in (0, min(n_p * n_q, 4 << 20)):
+        vals = [n_p, n_q, L, int(self_join), krow, 4, fp, hash_ws, widened, sort_ws, find, rec,
+                chunks, partials, own]
+        out = (ctypes.c_uint64 * len(NAMES))()
+        lib.layout((ctypes.c_uint64 * len(vals))(*vals), out)
+        at = dict(zip(NAMES, out))
+        size = dict(row_p=n_p * krow, norm_p=4 * n_p, key_p=8 * pos_p, perm_p=4 * pos_p,
+                    sorted_p=8 * pos_p, list_p=4 * pos_p, tag_p=pos_p, fp_p=fp * n_p,
+                    counters=64, partials=partials, hash_ws=hash_ws, widened=widened,
+                    sort_ws=sort_ws, found=4096 * find, n_found=4 * find, found_off=8 * find,
+                    rec_t=4 * rec, rec_pq=16 * rec, n_desc=4 * chunks, n_tile=4 * chunks,
+                    desc_off=8 * chunks, tile_off=8 * chunks, desc_info=16 * rec,
+                    desc_pq=16 * rec, own=8 * own)
+        for q in ("row", "norm", "key", "perm", "sorted", "list", "tag", "fp"):
+            if self_join:
+                assert at[q + "_q"] == at[q + "_p"]
+            else:
+                size[q + "_q"] = size[q + "_p"] // n_p * n_q
+        for a in size:
+            assert at[a] % 256 == 0 and at[a] + size[a] <= at["total"], a
+            for b in size:
+                (a0, a1), (b0, b1) = LIVE.get(a, (0, 6)), LIVE.get(b, (0, 6))
+                if a < b and a0 <= b1 and b0 <= a1:
+                    assert at[a] + size[a] <= at[b] or at[b] + size[b] <= at[a], (a, b)
+        if own == 0:
+            per_pos = pos_p if self_join else pos_p + pos_q
+            rows = n_p if self_join else n_p + n_q
+            before = (rows * (krow + 4) + 20 * per_pos      # copies, norms; keys, sorted, perm
+                      + rows * (16 if long_rows else 128)   # fingerprints or row records
+                      + 24 * pos_p + 60 * rec + 24 * chunks # marks, sizes; records, tiles
+                      + 16 * L * n_max + 12 * counts        # sort
+                      + hash_ws + widened + 8 * pos_p // 4096)
+            # apart from rounding: to 256 bytes, and found buckets to whole blocks of 256
+            assert at["total"] <= before + 256 * len(NAMES) + 4096 * 2 * L * (n_max < 4096)
