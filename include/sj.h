@@ -235,7 +235,8 @@ int sj_join_noalloc(sj_ctx *ctx, int metric, int dtype, const void *P, uint32_t 
  * sj_join_ip.  *n_cand (host, may be NULL) receives the number of pair
  * evaluations made (the sum over tables and shared buckets of |P bucket| x
  * |Q bucket|).  Device scratch grows to about L * (n_p + n_q) * 48 bytes (half of
- * it for a self-join) plus 16 to 64 bytes per row of P and of Q. */
+ * it for a self-join) plus 16 to 64 bytes per row of P and of Q, at least 15 MiB
+ * (less where the device has no room for it). */
 int sj_join_lsh(sj_ctx *ctx, int metric, int dtype, const void *P, uint32_t n_p, const void *Q,
                 uint32_t n_q, uint32_t d, double thr, uint32_t L, uint32_t k, const int8_t *A,
                 const int32_t *B, int32_t w, uint32_t *pairs, uint64_t cap, uint64_t *n_out,

@@ -120,6 +120,15 @@ hipError_t launch_pack(const Records &rec, uint32_t n_rec, bool write, uint32_t 
                        const unsigned long long *tile_off, const Descs &desc, const Lists &ls,
                        unsigned long long *overflow, hipStream_t s);
 
+// A wave's matches of one tile that found no room in the join's list: match bits of
+// its 64 x 128 results (four column blocks of 32; lane l's word b: bit x is row 32 (x /
+// 16) + 8 (x % 16 / 4) + 4 (l / 32) + x % 4, column 32 b + l % 32), the rows they
+// stand for (0xffffffff: none) and the tile's table.
+struct Held {
+    uint32_t w[4][64], p[64], q[128], t, pad[3];
+};
+constexpr uint32_t HELD_MIN = 8;   // records a tile may need
+
 struct JoinArgs {
     Rows P, Q;
     uint32_t L;
@@ -135,8 +144,23 @@ struct JoinArgs {
     uint32_t *pairs;
     uint64_t cap;
     unsigned long long *counter;
+    Held *held;                           // held_cap records per workgroup (at least HELD_MIN)
+    uint32_t held_cap;
+    uint32_t *n_held;                     // per workgroup: records held
+    uint64_t *next;                       // per workgroup: the tile it goes on with
+    bool resume;
 };
 
-hipError_t launch_join(int dtype, int metric, const JoinArgs &g, int num_cus, hipStream_t s);
+// The join takes launches of join_grid(..) workgroups (`held`: records in all): a
+// workgroup stops when its records may not hold another tile's.  launch_join_state
+// tells (host: pinned memory, read after synchronising) the pairs so far, the records
+// held and the workgroups with tiles left, and clears the pair counter when both are
+// 0; launch_held resolves the records; then, with tiles left, launch_join again with
+// `resume`.
+uint32_t join_grid(uint64_t n_tiles, uint64_t held, int num_cus);
+hipError_t launch_join(int dtype, int metric, const JoinArgs &g, uint32_t grid, hipStream_t s);
+hipError_t launch_join_state(const JoinArgs &g, uint32_t grid, unsigned long long *host,
+                             hipStream_t s);
+hipError_t launch_held(const JoinArgs &g, uint32_t grid, uint64_t records, hipStream_t s);
 
 }  // namespace sjl

@@ -993,36 +993,41 @@ __device__ __forceinline__ bool matches(typename sjk::Mma<DT>::val_t acc,
     }
 }
 
-// Whether rows i of P and j of Q agree in a table before t (the first-table
-// rule: such a pair is reported there).  Tables with a fingerprint byte first
-// (equal keys give equal bytes), each equal byte confirmed with the keys; later
-// tables by their keys, 8 per round of independent loads.
-__device__ __forceinline__ bool in_earlier_table(const JoinArgs &g, uint32_t i, uint32_t j,
-                                                 uint32_t t)
+// Bit u: byte u of two rows' 16 fingerprint bytes is equal, of the first `tables`
+// bytes (equal keys give equal bytes).
+__device__ __forceinline__ uint32_t equal_bytes(const uint4 &fi, const uint4 &fj, uint32_t tables)
 {
-    if (t == 0)
-        return false;
-    const uint32_t fc = fp_chunks(g.L), tf = t < FP_MAX ? t : FP_MAX;
-    for (uint32_t c = 0; 16 * c < tf; ++c) {
-        const uint4 fi = g.fp_p[(size_t)i * fc + c], fj = g.fp_q[(size_t)j * fc + c];
-        const uint32_t xw[4] = {fi.x ^ fj.x, fi.y ^ fj.y, fi.z ^ fj.z, fi.w ^ fj.w};
-        uint32_t eq = 0;   // bit u: byte u (table 16 c + u) equal
+    const uint32_t xw[4] = {fi.x ^ fj.x, fi.y ^ fj.y, fi.z ^ fj.z, fi.w ^ fj.w};
+    uint32_t eq = 0;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint32_t x = xw[q];
-            const uint32_t y = ~(((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x | 0x7f7f7f7fu);
-            eq |= (((y >> 7) & 1u) | ((y >> 14) & 2u) | ((y >> 21) & 4u) | ((y >> 28) & 8u))
-                  << (4 * q);
-        }
-        const uint32_t rem = tf - 16 * c;
-        eq &= rem >= 16 ? 0xffffu : (1u << rem) - 1u;
-        while (eq) {
-            const uint32_t t2 = 16 * c + __builtin_ctz(eq);
-            eq &= eq - 1;
-            if (g.keys_p[(size_t)t2 * g.P.n + i] == g.keys_q[(size_t)t2 * g.Q.n + j])
-                return true;
-        }
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t x = xw[q];
+        const uint32_t y = ~(((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x | 0x7f7f7f7fu);
+        eq |= (((y >> 7) & 1u) | ((y >> 14) & 2u) | ((y >> 21) & 4u) | ((y >> 28) & 8u))
+              << (4 * q);
     }
+    return eq & (tables >= 16 ? 0xffffu : (1u << tables) - 1u);
+}
+
+// Whether the keys of rows i of P and j of Q are equal in one of the tables t0 + u,
+// bit u of eq.
+__device__ __forceinline__ bool equal_key(const JoinArgs &g, uint32_t i, uint32_t j, uint32_t t0,
+                                          uint32_t eq)
+{
+    while (eq) {
+        const uint32_t t2 = t0 + __builtin_ctz(eq);
+        eq &= eq - 1;
+        if (g.keys_p[(size_t)t2 * g.P.n + i] == g.keys_q[(size_t)t2 * g.Q.n + j])
+            return true;
+    }
+    return false;
+}
+
+// The same for the tables without a fingerprint byte before t, 8 per round of
+// independent loads.
+__device__ __forceinline__ bool equal_later_key(const JoinArgs &g, uint32_t i, uint32_t j,
+                                                uint32_t t)
+{
     for (uint32_t t2 = FP_MAX; t2 < t; t2 += 8) {
         bool same = false;
 #pragma unroll
@@ -1034,6 +1039,37 @@ __device__ __forceinline__ bool in_earlier_table(const JoinArgs &g, uint32_t i, 
             return true;
     }
     return false;
+}
+
+// Whether rows i of P and j of Q agree in a table before t (the first-table
+// rule: such a pair is reported there).
+__device__ __forceinline__ bool in_earlier_table(const JoinArgs &g, uint32_t i, uint32_t j,
+                                                 uint32_t t)
+{
+    if (t == 0)
+        return false;
+    const uint32_t fc = fp_chunks(g.L), tf = t < FP_MAX ? t : FP_MAX;
+    for (uint32_t c = 0; 16 * c < tf; ++c) {
+        const uint32_t eq = equal_bytes(g.fp_p[(size_t)i * fc + c], g.fp_q[(size_t)j * fc + c],
+                                        tf - 16 * c);
+        if (equal_key(g, i, j, 16 * c, eq))
+            return true;
+    }
+    return equal_later_key(g, i, j, t);
+}
+
+// The bits set in a wave's w[4] and this lane's exclusive prefix of them.
+__device__ __forceinline__ void wave_totals(const uint32_t (&w)[4], uint32_t &tot, uint32_t &pre)
+{
+    const uint32_t cnt = (uint32_t)(__builtin_popcount(w[0]) + __builtin_popcount(w[1]) +
+                                    __builtin_popcount(w[2]) + __builtin_popcount(w[3]));
+    tot = pre = 0;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {   // at most 128 a lane
+        const uint64_t bits = __ballot((cnt >> b) & 1);
+        tot += (uint32_t)__popcll(bits) << b;
+        pre += sjk::lanes_below(bits) << b;
+    }
 }
 
 // The bucket join.  A persistent workgroup of 8 waves takes a contiguous range
@@ -1057,8 +1093,11 @@ __device__ __forceinline__ bool in_earlier_table(const JoinArgs &g, uint32_t i, 
 // the 300 us for copying rows, norms and fingerprints into records are gone.
 // Matches go to an LDS list (JCAP pairs with their table); the first-table rule,
 // a chain of loads per match, then runs for the list at once, a thread per
-// match, and reserves output slots per wave.  A block of results whose matches
-// do not fit the list's end is resolved by its wave.
+// match, and reserves output slots once.  A wave whose matches of a tile do not
+// fit the list's end holds them: their bits and the rows' indices go to its
+// workgroup's held records (resolved by held_kernel, which has the waves to hide
+// the rule's chains of loads), and a workgroup whose records may not hold another
+// tile's stops and is launched again after they are resolved.
 // FAR: operands of 4 GiB or more, rows through registers (64-bit addresses).
 constexpr int JT = 512;            // threads
 constexpr uint32_t JCAP = 1024;    // list entries: a whole 32 x 32 block fits an empty list
@@ -1080,15 +1119,23 @@ __global__ void __launch_bounds__(JT) join_kernel(JoinArgs g)
     __shared__ uint2 s_pair[JCAP];
     __shared__ uint8_t s_pt[JCAP];
     __shared__ uint32_t s_cnt, s_lim;           // list entries reserved; first that did not fit
+    __shared__ uint32_t s_held;                 // held records
+    __shared__ uint32_t s_sum[JT / 64];         // list: pairs of each wave
+    __shared__ unsigned long long s_base;       // list: their first output slot
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wv = __builtin_amdgcn_readfirstlane(wave);
     const int wr = wv >> 1, wc = wv & 1, half = lane >> 5, c32 = lane & 31;
     const uint32_t rb = g.P.row_bytes;   // == g.Q.row_bytes
     const uint32_t n_st = (rb + 127) / 128;
-    const uint64_t T0 = (uint64_t)blockIdx.x * g.n_tiles / gridDim.x;
+    const uint64_t T0 = g.resume ? g.next[blockIdx.x] : (uint64_t)blockIdx.x * g.n_tiles / gridDim.x;
     const uint64_t T1 = (uint64_t)(blockIdx.x + 1) * g.n_tiles / gridDim.x;
-    if (T0 >= T1)
-        return;   // the whole workgroup
+    if (T0 >= T1) {   // the whole workgroup
+        if (tid == 0) {
+            g.n_held[blockIdx.x] = 0;
+            g.next[blockIdx.x] = T1;
+        }
+        return;
+    }
 
     // ---- the tiles in order (all uniform)
     // what stays with a tile, in one register: its rows of P and Q (9 bits
@@ -1125,8 +1172,12 @@ __global__ void __launch_bounds__(JT) join_kernel(JoinArgs g)
         tq = (uint32_t)(local % ntq);
     }
     // thread tid < TILE: P row tid of a tile, else Q row tid - TILE
-    const bool is_q = tid >= (int)TILE;
+    const bool is_q = wv >= (int)TILE / 64;   // uniform
     const uint32_t li = tid & (TILE - 1);
+    // (this wave's norms: read from the arguments once, not at every tile before the
+    // load that waits for it)
+    const V *norms = (const V *)(is_q ? g.norm_q : g.norm_p);
+    asm volatile("" : "+s"(norms));
     // the next tile: this thread's row of it is loaded (0xffffffff: none)
     auto take = [&](uint32_t &idx, uint32_t &tag) -> Tile {
         const uint32_t np = min(dpq.y - tp * TILE, TILE), nq = min(dpq.w - tq * TILE, TILE);
@@ -1162,7 +1213,7 @@ __global__ void __launch_bounds__(JT) join_kernel(JoinArgs g)
         V v = V(0);
         if constexpr (L2N) {
             if (idx != 0xffffffffu)
-                v = ((const V *)(is_q ? g.norm_q : g.norm_p))[idx];
+                v = norms[idx];
         }
         return v;
     };
@@ -1192,89 +1243,71 @@ __global__ void __launch_bounds__(JT) join_kernel(JoinArgs g)
         }
     };
 
-    // ---- list of matches
-    auto resolve_list = [&]() {
-        // every wave calls it, after a barrier; another barrier follows
-        const uint32_t n = min(min(s_cnt, s_lim), JCAP);
-        for (uint32_t b = 0; b < n; b += JT) {
-            const uint32_t e = b + tid;
-            bool keep = e < n;
-            uint2 pr = make_uint2(0, 0);
-            if (keep) {
-                pr = s_pair[e];
-                keep = !in_earlier_table(g, pr.x, pr.y, s_pt[e]);
-            }
-            const uint64_t bits = __ballot(keep);
-            unsigned long long base = 0;
-            if (bits != 0 && lane == 0)
-                base = atomicAdd(g.counter, (unsigned long long)__popcll(bits));
-            const uint64_t slot = sjk::first_lane_u64(base) + sjk::lanes_below(bits);
-            if (keep && slot < g.cap)
-                ((sjk::global_pair *)g.pairs)[slot] = sjk::pack_pair(pr.x, pr.y);
-        }
+    // ---- matches
+    // block s of a wave's results: row block a = s % SA, column block b = s / SA; its
+    // match bits (bit r: register r) are w[b] >> 16 a.  Places come from the lane
+    // given: one that the compiler does not know as such, so that it computes them
+    // where they are needed and keeps no register for them.
+    auto bits_of = [](const uint32_t (&w)[SB], int s) {
+        const int b = s >> 1;
+        const uint32_t wb = b == 0 ? w[0] : b == 1 ? w[1] : b == 2 ? w[2] : w[3];
+        return (wb >> (16 * (s & 1))) & 0xffffu;
     };
-    // matches m (bit r: register r of a block) of this lane's column jl, rows il0 + ..
-    auto push = [&](uint32_t m, uint32_t il0, uint32_t jl, uint32_t t, const uint32_t *idx) {
-        auto row_of = [&](int r) { return idx[il0 + 8 * (r >> 2) + (r & 3)]; };
-        auto totals = [&](uint32_t mm, uint32_t &tot, uint32_t &pre) {
-            const uint32_t cnt = (uint32_t)__builtin_popcount(mm);
-            tot = pre = 0;
+    auto row_of = [&](int s, int l, int r) {
+        return 64 * wr + 32 * (s & 1) + 4 * (l >> 5) + 8 * (r >> 2) + (r & 3);
+    };
+    auto col_of = [&](int s, int l) { return 128 * wc + 32 * (s >> 1) + (l & 31); };
+    // The list's pairs to the output, and the list empty.  Every wave calls it after a
+    // barrier (and passes two more in it).
+    auto resolve_list = [&]() __attribute__((always_inline)) {
+        constexpr int U = JCAP / JT;
+        const uint32_t n = min(min(s_cnt, s_lim), JCAP);
+        uint2 pr[U];
+        uint64_t kept[U];
+        uint32_t tot = 0;
 #pragma unroll
-            for (int b = 0; b < 5; ++b) {
-                const uint64_t bits = __ballot((cnt >> b) & 1);
-                tot += (uint32_t)__popcll(bits) << b;
-                pre += sjk::lanes_below(bits) << b;
+        for (int u = 0; u < U; ++u) {
+            const uint32_t e = u * JT + tid;
+            bool keep = e < n;
+            pr[u] = make_uint2(0, 0);
+            if (keep) {
+                pr[u] = s_pair[e];
+                keep = !in_earlier_table(g, pr[u].x, pr[u].y, s_pt[e]);
             }
-        };
-        uint32_t tot, pre;
-        totals(m, tot, pre);
-        if (tot == 0)
-            return;
-        const uint32_t j = idx[TILE + jl];
-        uint32_t base = 0;
-        if (lane == 0)
-            base = atomicAdd(&s_cnt, tot);
-        base = __builtin_amdgcn_readfirstlane(base);
-        if (base + tot <= JCAP) {
-            uint32_t at = base + pre;
-            while (m) {
-                const int r = __builtin_ctz(m);
-                m &= m - 1;
-                s_pair[at] = make_uint2(row_of(r), j);
-                s_pt[at++] = (uint8_t)t;
-            }
-            return;
+            kept[u] = __ballot(keep);
+            tot += (uint32_t)__popcll(kept[u]);
         }
-        // no room: this and every later reservation of the tile (entries from
-        // the first refused one on are not read)
         if (lane == 0)
-            atomicMin(&s_lim, base);
-        uint32_t keep = 0;
-        while (m) {
-            const int r = __builtin_ctz(m);
-            m &= m - 1;
-            if (!in_earlier_table(g, row_of(r), j, t))
-                keep |= 1u << r;
+            s_sum[wv] = tot;
+        __syncthreads();   // (every wave has read the list)
+        if (tid == 0) {
+            uint32_t sum = 0;
+            for (int k = 0; k < JT / 64; ++k)
+                sum += s_sum[k];
+            s_base = sum ? atomicAdd(g.counter, (unsigned long long)sum) : 0ull;
+            s_cnt = 0;
+            s_lim = 0xffffffffu;
         }
-        totals(keep, tot, pre);
-        if (tot == 0)
-            return;
-        unsigned long long b = 0;
-        if (lane == 0)
-            b = atomicAdd(g.counter, (unsigned long long)tot);
-        uint64_t slot = sjk::first_lane_u64(b) + pre;
-        while (keep) {
-            const int r = __builtin_ctz(keep);
-            keep &= keep - 1;
-            if (slot < g.cap)
-                ((sjk::global_pair *)g.pairs)[slot] = sjk::pack_pair(row_of(r), j);
-            ++slot;
+        __syncthreads();
+        uint64_t slot = s_base;
+        for (int k = 0; k < wv; ++k)
+            slot += s_sum[k];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint64_t at = slot + sjk::lanes_below(kept[u]);
+            if (((kept[u] >> lane) & 1) && at < g.cap)
+                ((sjk::global_pair *)g.pairs)[at] = sjk::pack_pair(pr[u].x, pr[u].y);
+            slot += (uint64_t)__popcll(kept[u]);
         }
     };
 
     acc_t acc[SA][SB];
+    // Tile x's matches to the list, or the wave's to a held record.
     auto epilogue = [&](const Tile &x, const uint32_t *idx, const uint8_t *tag, const V *nm) {
-        const uint32_t i0 = 64 * wr + 4 * half;
+        int l = tid;
+        asm volatile("" : "+v"(l));
+        l &= 63;
+        const uint32_t i0 = 64 * wr + 4 * (l >> 5);
         uint32_t w[SB] = {};   // match bits: row block a of column block b at 16 a
 #pragma unroll
         for (int a = 0; a < SA; ++a) {
@@ -1294,7 +1327,7 @@ __global__ void __launch_bounds__(JT) join_kernel(JoinArgs g)
             for (int b = 0; b < SB; ++b) {
                 if (128 * wc + 32 * b >= (int)x.nq())
                     continue;   // uniform
-                const uint32_t jl = 128 * wc + 32 * b + c32;
+                const uint32_t jl = 128 * wc + 32 * b + (l & 31);
                 const V ny = L2N ? nm[TILE + jl] : V(0);
                 // a necessary condition from the block's largest product (rows
                 // and columns past the tile's have norm 0 and products 0 and
@@ -1318,26 +1351,64 @@ __global__ void __launch_bounds__(JT) join_kernel(JoinArgs g)
         static_assert(SB == 4 && SA == 2, "one word per column block");
         if (__ballot((w[0] | w[1] | w[2] | w[3]) != 0) == 0)
             return;
+        if (x.packed()) {
+            // rows of the same bucket only
+#pragma nounroll
+            for (int s = 0; s < SA * SB; ++s) {
+                uint32_t m = bits_of(w, s), drop = 0;
+                const uint32_t tj = tag[TILE + col_of(s, l)];
+                while (m) {
+                    const int r = __builtin_ctz(m);
+                    m &= m - 1;
+                    if (tag[row_of(s, l, r)] != tj)
+                        drop |= 1u << r;
+                }
+                drop <<= 16 * (s & 1);
+#pragma unroll
+                for (int b = 0; b < SB; ++b)
+                    w[b] &= b == s >> 1 ? ~drop : ~0u;
+            }
+        }
+        uint32_t tot, pre, base = 0;
+        wave_totals(w, tot, pre);
+        if (tot == 0)
+            return;
+        if (l == 0)
+            base = atomicAdd(&s_cnt, tot);
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (base + tot > JCAP) {
+            // no room: nor for any later reservation of the tile (entries from the
+            // first refused one on are not read)
+            uint32_t k = 0;
+            if (l == 0) {
+                atomicMin(&s_lim, base);
+                k = atomicAdd(&s_held, 1u);
+            }
+            k = __builtin_amdgcn_readfirstlane(k);
+            if (k < g.held_cap) {   // always: a workgroup stops before its records are full
+                Held *hd = g.held + (uint64_t)blockIdx.x * g.held_cap + k;
+#pragma unroll
+                for (int b = 0; b < SB; ++b)
+                    hd->w[b][l] = w[b];
+                hd->p[l] = idx[64 * wr + l];
+                hd->q[l] = idx[TILE + 128 * wc + l];
+                hd->q[64 + l] = idx[TILE + 128 * wc + 64 + l];
+                if (l == 0)
+                    hd->t = x.t();
+            }
+            return;
+        }
+        uint32_t at = base + pre;
 #pragma nounroll
         for (int s = 0; s < SA * SB; ++s) {
-            const int b = s >> 1, a = s & 1;
-            const uint32_t wb = b == 0 ? w[0] : b == 1 ? w[1] : b == 2 ? w[2] : w[3];
-            uint32_t m = (wb >> (16 * a)) & 0xffffu;
-            if (__ballot(m != 0) == 0)
-                continue;
-            const uint32_t il0 = i0 + 32 * a, jl = 128 * wc + 32 * b + c32;
-            if (x.packed()) {
-                // rows of the same bucket only
-                const uint32_t tj = tag[TILE + jl];
-                uint32_t mm = m;
-                while (mm) {
-                    const int r = __builtin_ctz(mm);
-                    mm &= mm - 1;
-                    if (tag[il0 + 8 * (r >> 2) + (r & 3)] != tj)
-                        m &= ~(1u << r);
-                }
+            uint32_t m = bits_of(w, s);
+            const uint32_t j = idx[TILE + col_of(s, l)];
+            while (m) {
+                const int r = __builtin_ctz(m);
+                m &= m - 1;
+                s_pair[at] = make_uint2(idx[row_of(s, l, r)], j);
+                s_pt[at++] = (uint8_t)x.t();
             }
-            push(m, il0, jl, x.t(), idx);
         }
     };
 
@@ -1358,7 +1429,7 @@ __global__ void __launch_bounds__(JT) join_kernel(JoinArgs g)
     }
     Tile pend = nxt;   // the one after the next
     if (tid == 0) {
-        s_cnt = 0;
+        s_cnt = s_held = 0;
         s_lim = 0xffffffffu;
     }
     __syncthreads();
@@ -1426,19 +1497,22 @@ __global__ void __launch_bounds__(JT) join_kernel(JoinArgs g)
         }
         __syncthreads();
         if (last) {
-            const uint32_t n_list = s_cnt;
-            __syncthreads();   // every wave has read it before the next tile's pushes
-            if (n_list >= JCAP / 2 || left == 1) {   // uniform
+            // (both read by every wave before the next tile's matches change them)
+            const uint32_t n_list = s_cnt, n_held = s_held;
+            // a tile's waves may hold one record each
+            const bool stop = left == 1 || n_held + JT / 64 > g.held_cap;   // uniform
+            if (n_list >= JCAP / 2 || stop)
                 resolve_list();
+            else
                 __syncthreads();
+            --left;
+            if (stop) {
                 if (tid == 0) {
-                    s_cnt = 0;
-                    s_lim = 0xffffffffu;
+                    g.n_held[blockIdx.x] = n_held;
+                    g.next[blockIdx.x] = T1 - left;
                 }
-                __syncthreads();
-            }
-            if (--left == 0)
                 return false;
+            }
             cur = nxt;
             nxt = pend;
             k3 = n3;
@@ -1452,6 +1526,156 @@ __global__ void __launch_bounds__(JT) join_kernel(JoinArgs g)
     for (;;) {
         if (!stage(s_r0, s_r1) || !stage(s_r1, s_r0))
             break;
+    }
+}
+
+// The held records of every workgroup of join_kernel: the first-table rule on their
+// bits, then the pairs.  Four waves per record, one for each column block; workgroups
+// (b, *) take b's records, two at a time.  The rows' fingerprints wait in LDS; a lane
+// tests its bits there (its column's bytes against its rows') and looks keys up only
+// for the ones with an equal byte, four pairs' first at once.  The pairs are written
+// by ballots, contiguous over the lanes, with one reservation for the two records.
+// Where join_kernel's waves resolved such matches one after the other from
+// memory, with a reservation per 32 x 32 block: 50000 x 100 int8, 16 tables x 10 signs, 14.7 M
+// pairs, a call 1983 us, now 851; 262144 x 64 int8, one table of 10, 23.9 M pairs 1759
+// and 688.
+constexpr int HT = 512, HR = HT / 256;   // threads, records
+
+__global__ void __launch_bounds__(HT) held_kernel(JoinArgs g)
+{
+    constexpr int RN = 192;           // rows of a record: 64 of P, 128 of Q
+    extern __shared__ uint4 s_fp[];   // [record][chunk][row]
+    __shared__ uint32_t s_row[HR][RN];
+    __shared__ uint32_t s_sum[HT / 64];
+    __shared__ unsigned long long s_base;
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, c32 = lane & 31;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = wv >> 2, b = wv & 3;
+    const uint32_t n = g.n_held[blockIdx.x], fc = fp_chunks(g.L);
+    uint4 *fp = s_fp + (size_t)h * fc * RN;
+    const uint32_t *rows = s_row[h];
+    const int jl = 64 + 32 * b + c32;   // this lane's column
+    // bit x of a word: row block x / 16, register x % 16
+    auto row_of = [&](int x) { return 2 * (x & 28) + 4 * half + (x & 3); };
+    for (uint32_t k0 = HR * blockIdx.y; k0 < n; k0 += HR * gridDim.y) {   // uniform
+        const bool on = k0 + h < n;   // uniform for a record's waves
+        const Held *hd = g.held + ((uint64_t)blockIdx.x * g.held_cap + k0 + h);
+        uint32_t w = 0, t = 0, tf = 0;
+        if (on) {
+            w = hd->w[b][lane];
+            t = __builtin_amdgcn_readfirstlane(hd->t);
+            tf = min(t, FP_MAX);
+            const int r = tid & 255;
+            if (r < RN) {
+                const uint32_t i = r < 64 ? hd->p[r] : hd->q[r - 64];
+                s_row[h][r] = i;
+                if (i != 0xffffffffu)
+                    for (uint32_t c = 0; 16 * c < tf; ++c)
+                        fp[c * RN + r] = (r < 64 ? g.fp_p : g.fp_q)[(size_t)i * fc + c];
+            }
+        }
+        __syncthreads();
+        if (t != 0) {
+            uint32_t maybe = t > FP_MAX ? w : 0u;
+            for (uint32_t c = 0; 16 * c < tf; ++c) {
+                const uint4 fj = fp[c * RN + jl];
+                uint32_t mm = w & ~maybe;
+                while (mm) {
+                    const int x = __builtin_ctz(mm);
+                    mm &= mm - 1;
+                    if (equal_bytes(fp[c * RN + row_of(x)], fj, tf - 16 * c))
+                        maybe |= 1u << x;
+                }
+            }
+            const uint32_t j = rows[jl];
+            while (maybe) {
+                constexpr int K = 4;
+                uint32_t bit[K];
+                uint64_t kp[K], kq[K];
+#pragma unroll
+                for (int u = 0; u < K; ++u) {
+                    bit[u] = maybe & (0u - maybe);
+                    maybe &= maybe - 1u;
+                    const int il = bit[u] ? row_of(__builtin_ctz(bit[u])) : 0;
+                    uint32_t eq = 0, c = 0;
+                    if (bit[u])
+                        for (; 16 * c < tf; ++c)
+                            if ((eq = equal_bytes(fp[c * RN + il], fp[c * RN + jl], tf - 16 * c)))
+                                break;
+                    kp[u] = 0;
+                    kq[u] = 1;
+                    if (eq) {   // (none: the pair goes through the other tables)
+                        const size_t t2 = 16 * c + __builtin_ctz(eq);
+                        kp[u] = g.keys_p[t2 * g.P.n + rows[il]];
+                        kq[u] = g.keys_q[t2 * g.Q.n + j];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < K; ++u)
+                    if (kp[u] == kq[u] ||
+                        (bit[u] && in_earlier_table(g, rows[row_of(__builtin_ctz(bit[u]))], j, t)))
+                        w &= ~bit[u];
+            }
+        }
+        const uint32_t cnt = (uint32_t)__builtin_popcount(w);
+        uint32_t tot = 0;
+#pragma unroll
+        for (int u = 0; u < 6; ++u)
+            tot += (uint32_t)__popcll(__ballot((cnt >> u) & 1)) << u;
+        if (lane == 0)
+            s_sum[wv] = tot;
+        __syncthreads();
+        if (tid == 0) {
+            uint32_t sum = 0;
+            for (int u = 0; u < HT / 64; ++u)
+                sum += s_sum[u];
+            s_base = sum ? atomicAdd(g.counter, (unsigned long long)sum) : 0ull;
+        }
+        __syncthreads();
+        if (tot) {
+            uint64_t slot = s_base;
+            for (int u = 0; u < wv; ++u)
+                slot += s_sum[u];
+            const uint32_t j = rows[jl];
+#pragma nounroll
+            for (int x = 0; x < 32; ++x) {
+                const bool set = (w >> x) & 1u;
+                const uint64_t bits = __ballot(set);
+                if (bits == 0)
+                    continue;
+                const uint64_t at = slot + sjk::lanes_below(bits);
+                if (set && at < g.cap)
+                    ((sjk::global_pair *)g.pairs)[at] = sjk::pack_pair(rows[row_of(x)], j);
+                slot += (uint64_t)__popcll(bits);
+            }
+        }
+        __syncthreads();   // the rows and sums are read
+    }
+}
+
+// After join_kernel: host[0] = pairs so far, host[1] = held records, host[2] =
+// workgroups with tiles left; the counter is cleared when that is all.
+__global__ void __launch_bounds__(256) join_state_kernel(unsigned long long *counter,
+                                                         const uint32_t *n_held,
+                                                         const uint64_t *next, uint64_t n_tiles,
+                                                         uint32_t grid, unsigned long long *host)
+{
+    __shared__ uint32_t s_h, s_l;
+    if (threadIdx.x == 0)
+        s_h = s_l = 0;
+    __syncthreads();
+    for (uint32_t b = threadIdx.x; b < grid; b += 256) {
+        if (n_held[b])
+            atomicAdd(&s_h, n_held[b]);
+        if (next[b] < (uint64_t)(b + 1) * n_tiles / grid)
+            atomicAdd(&s_l, 1u);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        host[0] = *counter;
+        host[1] = s_h;
+        host[2] = s_l;
+        if (s_h == 0 && s_l == 0)
+            *counter = 0ull;
     }
 }
 
@@ -1491,10 +1715,8 @@ hipError_t launch_keys_t(const Rows &r, uint32_t d, uint32_t L, uint32_t k, cons
 }
 
 template <int DT, int MET>
-hipError_t launch_join_t(const JoinArgs &g, int num_cus, hipStream_t s)
+hipError_t launch_join_t(const JoinArgs &g, uint32_t grid, hipStream_t s)
 {
-    // one workgroup per CU (their LDS fills it)
-    const uint32_t grid = (uint32_t)(g.n_tiles < (uint64_t)num_cus ? g.n_tiles : num_cus);
     // the row gathers' 32-bit offsets reach 4 GiB
     const uint64_t far = (uint64_t)max(g.P.n, g.Q.n) * g.P.row_bytes;
     if (far < 0xffffffffull)
@@ -1706,22 +1928,51 @@ hipError_t launch_pack(const Records &rec, uint32_t n_rec, bool write, uint32_t 
     return hipGetLastError();
 }
 
-hipError_t launch_join(int dtype, int metric, const JoinArgs &g, int num_cus, hipStream_t s)
+uint32_t join_grid(uint64_t n_tiles, uint64_t held, int num_cus)
 {
-    if (g.n_tiles == 0)
+    // one workgroup per CU (their LDS fills it), and room for a tile's records each
+    uint64_t n = (uint64_t)num_cus;
+    n = n < n_tiles ? n : n_tiles;
+    n = n < held / HELD_MIN ? n : held / HELD_MIN;
+    return (uint32_t)n;
+}
+
+hipError_t launch_join(int dtype, int metric, const JoinArgs &g, uint32_t grid, hipStream_t s)
+{
+    static_assert(HELD_MIN == JT / 64, "a record per wave");
+    if (grid == 0)
         return hipSuccess;
     const bool l2 = metric == MET_L2;
     switch (dtype) {
     case DT_F16:
-        return l2 ? launch_join_t<DT_F16, MET_L2>(g, num_cus, s)
-                  : launch_join_t<DT_F16, MET_IP>(g, num_cus, s);
+        return l2 ? launch_join_t<DT_F16, MET_L2>(g, grid, s)
+                  : launch_join_t<DT_F16, MET_IP>(g, grid, s);
     case DT_BF16:
-        return l2 ? launch_join_t<DT_BF16, MET_L2>(g, num_cus, s)
-                  : launch_join_t<DT_BF16, MET_IP>(g, num_cus, s);
+        return l2 ? launch_join_t<DT_BF16, MET_L2>(g, grid, s)
+                  : launch_join_t<DT_BF16, MET_IP>(g, grid, s);
     default:
-        return l2 ? launch_join_t<DT_I8, MET_L2>(g, num_cus, s)
-                  : launch_join_t<DT_I8, MET_IP>(g, num_cus, s);
+        return l2 ? launch_join_t<DT_I8, MET_L2>(g, grid, s)
+                  : launch_join_t<DT_I8, MET_IP>(g, grid, s);
     }
+}
+
+hipError_t launch_join_state(const JoinArgs &g, uint32_t grid, unsigned long long *host,
+                             hipStream_t s)
+{
+    hipLaunchKernelGGL(join_state_kernel, dim3(1), dim3(256), 0, s, g.counter, g.n_held, g.next,
+                       g.n_tiles, grid, host);
+    return hipGetLastError();
+}
+
+hipError_t launch_held(const JoinArgs &g, uint32_t grid, uint64_t records, hipStream_t s)
+{
+    if (grid == 0)
+        return hipSuccess;
+    // workgroups enough for every record were they evenly spread, twice over
+    const uint64_t ny = (records + HR * grid - 1) / (HR * (uint64_t)grid) * 2;
+    const uint32_t lds = HR * 192 * 16 * fp_chunks(g.L);
+    hipLaunchKernelGGL(held_kernel, dim3(grid, (uint32_t)(ny < 256 ? ny : 256)), dim3(HT), lds, s, g);
+    return hipGetLastError();
 }
 
 }  // namespace sjl

@@ -112,12 +112,19 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
     needs.chunks = chunk_cap;
     needs.scan_partials = sjk::scan_partials_size(n_find > chunk_cap ? n_find : chunk_cap) * 8;
     needs.own_pairs = sized ? std::min((uint64_t)n_p * n_q, kOwnPairs) : 0;
+    needs.workgroups = (uint64_t)c->num_cus;
+    // room for the records of a few tiles per workgroup (single buckets' tiles bound
+    // the number of tiles of small calls)
+    const uint64_t few = (uint64_t)c->num_cus * 4 * sjl::HELD_MIN;
+    const uint64_t tiles = (uint64_t)L * ((n_p + 2ull * sjl::TILE - 1) / sjl::TILE) *
+                           ((n_q + 2ull * sjl::TILE - 1) / sjl::TILE);
+    needs.held_bytes = std::min(few, sjl::HELD_MIN * tiles) * sizeof(sjl::Held);
     sjl::ScratchLayout lay = sjl::scratch_layout(needs);
     if ((st = grow_scratch(c, lay.total)) != SJ_OK) {
-        if (needs.own_pairs == 0)
-            return st;
-        // without room of its own for the output the bucket join runs twice
+        // without room of its own for the output the bucket join runs twice, with
+        // less for held records in more launches
         needs.own_pairs = 0;
+        needs.held_bytes = sjl::HELD_MIN * sizeof(sjl::Held);
         lay = sjl::scratch_layout(needs);
         g_err.clear();
         if ((st = grow_scratch(c, lay.total)) != SJ_OK)
@@ -172,6 +179,13 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
     SJ_HIP(sjk::launch_scan(n_found, n_find, rec_off, part, cnt + 1, s));
     const sjl::Records rec{(uint32_t *)(scr + lay.rec_t), (uint4 *)(scr + lay.rec_pq)};
     SJ_HIP(sjl::launch_bucket_write(n_p, L, found, n_found, rec_off, rec, s));
+    // (the fingerprints' place is free from here on)
+    uint4 *fp_p = (uint4 *)(scr + lay.fp_p), *fp_q = (uint4 *)(scr + lay.fp_q);
+    if (L > 1) {
+        SJ_HIP(sjl::launch_fingerprints(keys_p, n_p, L, fp_p, s));
+        if (!self)
+            SJ_HIP(sjl::launch_fingerprints(keys_q, n_q, L, fp_q, s));
+    }
     SJ_HIP(hipMemcpyAsync(c->h_small, cnt + 1, 8, hipMemcpyDeviceToHost, s));
     SJ_HIP(hipStreamSynchronize(s));
     const uint64_t n_rec = c->h_small[0];
@@ -191,12 +205,6 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
     }
     SJ_HIP(sjl::launch_pack(rec, (uint32_t)n_rec, true, cdesc, ctile, doff, toff, desc, lists,
                             cnt + 6, s));
-    uint4 *fp_p = (uint4 *)(scr + lay.fp_p), *fp_q = (uint4 *)(scr + lay.fp_q);
-    if (L > 1) {
-        SJ_HIP(sjl::launch_fingerprints(keys_p, n_p, L, fp_p, s));
-        if (!self)
-            SJ_HIP(sjl::launch_fingerprints(keys_q, n_q, L, fp_q, s));
-    }
     SJ_HIP(hipEventRecord(c->ev[2], s));
     unsigned long long hc[8];
     SJ_HIP(hipMemcpyAsync(hc, cnt, sizeof hc, hipMemcpyDeviceToHost, s));
@@ -234,12 +242,40 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
     g.pairs = sized ? (uint32_t *)(scr + lay.own) : pairs;
     g.cap = sized ? own : cap;
     g.counter = c->d_small;
-    SJ_HIP(sjl::launch_join(dtype, metric, g, c->num_cus, s));
+    g.held = (sjl::Held *)(scr + lay.held);
+    g.n_held = (uint32_t *)(scr + lay.n_held);
+    g.next = (uint64_t *)(scr + lay.next);
+    const uint64_t held = lay.held_bytes / sizeof(sjl::Held);
+    const uint32_t grid = sjl::join_grid(n_tiles, held, c->num_cus);
+    g.held_cap = grid ? (uint32_t)std::min(held / grid, (uint64_t)UINT32_MAX) : 0;
+    // the bucket join into g.pairs, in as many launches as its held records take
+    auto bucket_join = [&](uint64_t *found) -> int {
+        *found = 0;
+        g.resume = false;
+        while (grid) {
+            SJ_HIP(sjl::launch_join(dtype, metric, g, grid, s));
+            SJ_HIP(sjl::launch_join_state(g, grid, c->h_small, s));
+            SJ_HIP(hipStreamSynchronize(s));
+            const uint64_t n_held = c->h_small[1], left = c->h_small[2];
+            *found = c->h_small[0];
+            if (n_held == 0 && left == 0)
+                break;
+            SJ_HIP(sjl::launch_held(g, grid, n_held, s));
+            if (left == 0) {
+                SJ_HIP(sjk::launch_publish(c->d_small, c->h_small, s));
+                SJ_HIP(hipStreamSynchronize(s));
+                *found = c->h_small[0];
+                break;
+            }
+            g.resume = true;
+        }
+        c->counter_clear = true;
+        return SJ_OK;
+    };
+    uint64_t total = 0;
+    if ((st = bucket_join(&total)) != SJ_OK)
+        return st;
     SJ_HIP(hipEventRecord(c->ev[3], s));
-    SJ_HIP(sjk::launch_publish(c->d_small, c->h_small, s));
-    SJ_HIP(hipStreamSynchronize(s));
-    c->counter_clear = true;
-    const uint64_t total = c->h_small[0];
     if (sized && total > 0) {
         uint32_t *out = (uint32_t *)sized->alloc(sized->user, total);
         if (!out)
@@ -257,11 +293,11 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
             g.pairs = out;
             g.cap = total;
             c->counter_clear = false;
-            SJ_HIP(sjl::launch_join(dtype, metric, g, c->num_cus, s));
-            SJ_HIP(sjk::launch_publish(c->d_small, c->h_small, s));
+            uint64_t again = 0;
+            if ((st = bucket_join(&again)) != SJ_OK)
+                return st;
         }
         SJ_HIP(hipStreamSynchronize(s));
-        c->counter_clear = true;
         cap = total;
     }
     c->stats.total = total;

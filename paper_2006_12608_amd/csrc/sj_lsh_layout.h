@@ -8,8 +8,10 @@
 //          then the shared buckets as found per block;
 //   mid:   the buckets' records and the packing's counts, from the found ones;
 //   late:  the packed tiles' row lists and the tiles' descriptors, from the records,
-//          then the fingerprints and the output a call that sizes its own keeps.
-// Late starts where early does; mid follows both.
+//          then the fingerprints and the output a call that sizes its own keeps;
+//   last:  the join's held records.
+// Late starts where early does; mid follows both; the held records have all that
+// late leaves.
 #pragma once
 
 #include <stddef.h>
@@ -28,13 +30,16 @@ struct ScratchNeeds {
     uint64_t records, chunks;     // at most
     size_t scan_partials;
     uint64_t own_pairs;           // 8 bytes each
+    uint64_t held_bytes;          // at least, for the join's held records
+    uint64_t workgroups;          // of the join
 };
 
 struct ScratchLayout {
-    size_t row_p, row_q, norm_p, norm_q, key_p, key_q, perm_p, perm_q, counters, partials;
+    size_t row_p, row_q, norm_p, norm_q, key_p, key_q, perm_p, perm_q, counters, n_held, next, partials;
     size_t hash_ws, widened, sorted_p, sorted_q, sort_ws, found, n_found, found_off;   // early
     size_t rec_t, rec_pq, n_desc, n_tile, desc_off, tile_off;                          // mid
     size_t list_p, list_q, tag_p, tag_q, desc_info, desc_pq, fp_p, fp_q, own;          // late
+    size_t held, held_bytes;
     size_t early, early_end, late_end, mid, total;
 };
 
@@ -58,6 +63,8 @@ inline ScratchLayout scratch_layout(const ScratchNeeds &c)
     both(y.key_p, y.key_q, pos_p, pos_q, 8);
     both(y.perm_p, y.perm_q, pos_p, pos_q, 4);
     y.counters = take(8 * 8);
+    y.n_held = take(c.workgroups * 4);
+    y.next = take(c.workgroups * 8);
     y.partials = take(c.scan_partials);
 
     y.early = at;
@@ -88,7 +95,10 @@ inline ScratchLayout scratch_layout(const ScratchNeeds &c)
     y.n_tile = take(c.chunks * 4);
     y.desc_off = take(c.chunks * 8);
     y.tile_off = take(c.chunks * 8);
-    y.total = at;
+    // the held records: all that is left after late, mid's place included
+    y.held = y.late_end;
+    y.total = at > y.held + c.held_bytes ? at : y.held + c.held_bytes;
+    y.held_bytes = y.total - y.held;
     return y;
 }
 

@@ -425,9 +425,8 @@ static hipError_t launch_columns(uint32_t *hist, uint32_t bps, uint32_t L, uint3
 // sort_columns has 32 workgroups of 1024 threads per segment: too many for segments
 // of a few blocks (1000 tables of 1000 entries, 24 bits: a call 384 us, 71 with
 // none; 100000 of 50: 34 ms and 1.5 ms), too few for one segment of many (67108864
-// entries: 2764 us, 2292 by runs; with 48 bits 8.6 ms).  A single run's chain of
-// loads takes about as long as sort_columns at 16 blocks and a few segments or 64
-// blocks and some 50 (16 tables of 64 blocks: 119 us against 110).  By runs and their
+// entries: 2764 us, 2247 by runs).  A single run takes 2.2 us and 0.12 for each
+// block (25 blocks 5.3), sort_columns 3.8 of 16 segments and 104 of 1000.  By runs and their
 // sums, three launches, from 4096 blocks on (1 and 4 tables of 4096 blocks: 313 and
 // 1128 us by columns, 288 and 1092 by runs; of 512 blocks 97 and 167 against 113 and
 // 179).
@@ -436,7 +435,7 @@ static hipError_t column_sums(uint32_t *hist, uint32_t bps, uint32_t runs, uint3
 {
     if (bps <= 1)
         return hipSuccess;   // a block's counts are its segment's totals
-    if (runs > 1 ? bps < 4096 : bps > (uint64_t)L + 16)
+    if (runs > 1 ? bps < 4096 : bps > 4 + L / 2)
         return launch_columns(hist, bps, L, total, s);
     if (runs > 1) {
         hipLaunchKernelGGL(sort_runs<true>, dim3(L * runs), dim3(SORT_BINS), 0, s, hist, bps, runs,

@@ -34,13 +34,14 @@ extern "C" void layout(const uint64_t *n, uint64_t *out)
     c.n_p = n[0], c.n_q = n[1], c.L = n[2], c.self = n[3], c.copy_row = n[4], c.norm = n[5];
     c.fingerprint = n[6], c.hash_ws = n[7], c.widened = n[8], c.sort_ws = n[9];
     c.find_blocks = n[10], c.records = n[11], c.chunks = n[12], c.scan_partials = n[13];
-    c.own_pairs = n[14];
+    c.own_pairs = n[14], c.held_bytes = n[15], c.workgroups = n[16];
     const sjl::ScratchLayout y = sjl::scratch_layout(c);
     const size_t v[] = {y.row_p, y.row_q, y.norm_p, y.norm_q, y.key_p, y.key_q, y.perm_p, y.perm_q,
                         y.counters, y.partials, y.hash_ws, y.widened, y.sorted_p, y.sorted_q,
                         y.sort_ws, y.found, y.n_found, y.found_off, y.rec_t, y.rec_pq, y.n_desc,
                         y.n_tile, y.desc_off, y.tile_off, y.list_p, y.list_q, y.tag_p, y.tag_q,
-                        y.desc_info, y.desc_pq, y.fp_p, y.fp_q, y.own, y.total};
+                        y.desc_info, y.desc_pq, y.fp_p, y.fp_q, y.own, y.n_held, y.next, y.held,
+                        y.held_bytes, y.total};
     for (unsigned i = 0; i < sizeof v / sizeof *v; ++i)
         out[i] = v[i];
 }
@@ -96,15 +97,17 @@ def test_streamed_triangle_tiles(lib, n):
 
 NAMES = ("row_p row_q norm_p norm_q key_p key_q perm_p perm_q counters partials hash_ws widened "
          "sorted_p sorted_q sort_ws found n_found found_off rec_t rec_pq n_desc n_tile desc_off "
-         "tile_off list_p list_q tag_p tag_q desc_info desc_pq fp_p fp_q own total").split()
-# the steps of a call (0 hash, 1 sorts, 2 bucket search, 3 records, 4 packing, 5
-# fingerprints, 6 join) from an array's first write to its last read
-LIVE = {"hash_ws": (0, 0), "widened": (0, 0), "perm_p": (1, 6), "perm_q": (1, 6),
+         "tile_off list_p list_q tag_p tag_q desc_info desc_pq fp_p fp_q own n_held next held held_bytes "
+         "total").split()
+# the steps of a call (0 hash, 1 sorts, 2 bucket search, 3 records, 4 fingerprints
+# and packing, 5 join) from an array's first write to its last read
+LIVE = {"hash_ws": (0, 0), "widened": (0, 0), "perm_p": (1, 5), "perm_q": (1, 5),
         "sorted_p": (1, 2), "sorted_q": (1, 2), "sort_ws": (1, 2), "found": (2, 3),
         "n_found": (2, 3), "found_off": (2, 3), "rec_t": (3, 4), "rec_pq": (3, 4), "n_desc": (4, 4),
-        "n_tile": (4, 4), "desc_off": (4, 4), "tile_off": (4, 4), "list_p": (4, 6),
-        "list_q": (4, 6), "tag_p": (4, 6), "tag_q": (4, 6), "desc_info": (4, 6), "desc_pq": (4, 6),
-        "fp_p": (5, 6), "fp_q": (5, 6), "own": (6, 6)}
+        "n_tile": (4, 4), "desc_off": (4, 4), "tile_off": (4, 4), "list_p": (4, 5),
+        "list_q": (4, 5), "tag_p": (4, 5), "tag_q": (4, 5), "desc_info": (4, 5), "desc_pq": (4, 5),
+        "fp_p": (4, 5), "fp_q": (4, 5), "own": (5, 5), "n_held": (5, 5), "next": (5, 5),
+        "held": (5, 5)}
 
 
 @pytest.mark.parametrize("n_p,n_q", [(1, 1), (700, 300), (50000, 50000), (1 << 20, 1 << 20),
@@ -114,7 +117,7 @@ LIVE = {"hash_ws": (0, 0), "widened": (0, 0), "perm_p": (1, 6), "perm_q": (1, 6)
 @pytest.mark.parametrize("long_rows", [False, True])
 def test_lsh_scratch_layout(lib, n_p, n_q, L, self_join, long_rows):
     """Arrays that are needed at the same time never overlap, and without the room for
-    its own output a call needs no more than the arrays one after the other took when
+    its own output and held records a call needs no more than the arrays one after the other took when
     none shared its place (so no call that fitted the card stops fitting)."""
     if self_join:
         n_q = n_p
@@ -131,9 +134,9 @@ def test_lsh_scratch_layout(lib, n_p, n_q, L, self_join, long_rows):
                   + L * 1024 + 1024, find * 24)
     fp = 16 * ((min(L, 64) + 15) // 16) if L > 1 else 0
     partials = 8 * (max(find, chunks) // 4096 + 2)
-    for own in (0, min(n_p * n_q, 4 << 20)):
+    for own, held in ((0, 8 * 1808), (min(n_p * n_q, 4 << 20), 4096 * 1808)):
         vals = [n_p, n_q, L, int(self_join), krow, 4, fp, hash_ws, widened, sort_ws, find, rec,
-                chunks, partials, own]
+                chunks, partials, own, held, 256]
         out = (ctypes.c_uint64 * len(NAMES))()
         lib.layout((ctypes.c_uint64 * len(vals))(*vals), out)
         at = dict(zip(NAMES, out))
@@ -143,7 +146,9 @@ def test_lsh_scratch_layout(lib, n_p, n_q, L, self_join, long_rows):
                     sort_ws=sort_ws, found=4096 * find, n_found=4 * find, found_off=8 * find,
                     rec_t=4 * rec, rec_pq=16 * rec, n_desc=4 * chunks, n_tile=4 * chunks,
                     desc_off=8 * chunks, tile_off=8 * chunks, desc_info=16 * rec,
-                    desc_pq=16 * rec, own=8 * own)
+                    desc_pq=16 * rec, own=8 * own, n_held=4 * 256, next=8 * 256,
+                    held=at["held_bytes"])
+        assert at["held_bytes"] >= held
         for q in ("row", "norm", "key", "perm", "sorted", "list", "tag", "fp"):
             if self_join:
                 assert at[q + "_q"] == at[q + "_p"]
@@ -152,7 +157,7 @@ def test_lsh_scratch_layout(lib, n_p, n_q, L, self_join, long_rows):
         for a in size:
             assert at[a] % 256 == 0 and at[a] + size[a] <= at["total"], a
             for b in size:
-                (a0, a1), (b0, b1) = LIVE.get(a, (0, 6)), LIVE.get(b, (0, 6))
+                (a0, a1), (b0, b1) = LIVE.get(a, (0, 5)), LIVE.get(b, (0, 5))
                 if a < b and a0 <= b1 and b0 <= a1:
                     assert at[a] + size[a] <= at[b] or at[b] + size[b] <= at[a], (a, b)
         if own == 0:
@@ -162,6 +167,6 @@ def test_lsh_scratch_layout(lib, n_p, n_q, L, self_join, long_rows):
                       + rows * (16 if long_rows else 128)   # fingerprints or row records
                       + 24 * pos_p + 60 * rec + 24 * chunks # marks, sizes; records, tiles
                       + 16 * L * n_max + 12 * counts        # sort
-                      + hash_ws + widened + 8 * pos_p // 4096)
+                      + hash_ws + widened + 8 * pos_p // 4096 + 12 * 256 + held)
             # apart from rounding: to 256 bytes, and found buckets to whole blocks of 256
             assert at["total"] <= before + 256 * len(NAMES) + 4096 * 2 * L * (n_max < 4096)

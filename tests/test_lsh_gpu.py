@@ -463,3 +463,53 @@ def test_lsh_merged_instances_from_the_plan(name, wid, dist_far):
                                                 x.L, x.k, x.A, x.B, x.w).tolist()))
     assert set(map(tuple, np.asarray(ref).tolist())) == union
     say("found", len(union), "of", exact.total)
+
+
+@pytest.mark.parametrize("L,k,quantile", [(1, 2, 0.0), (3, 1, 0.0), (5, 2, 0.6), (20, 3, 0.0), (20, 6, 0.3),
+                                          (70, 2, 0.9), (67, 1, 0.0)])
+@pytest.mark.parametrize("dtype,metric,d", [("i8", "l2", 20), ("f16", "ip", 72), ("bf16", "l2", 64)])
+def test_lsh_many_matches_per_tile(L, k, quantile, dtype, metric, d):
+    """Tiles with more matches than the bucket join's list holds (their bits go to
+    held records, which a kernel of its own resolves, past the 64th table by the
+    keys alone): single and packed tiles, ragged, every pair of a bucket or a share
+    of them matching, duplicate rows (pairs that share many tables)."""
+    rng = np.random.default_rng(1200 + L + k)
+    w = case(1100 + L + d, 700, 601, d, dtype, metric, 0.0)
+    w.Q[:200] = w.P[rng.choice(700, 200)]
+    w.P[600:] = w.P[:100]
+    rows = np.arange(700)
+    ref = oracle.scores(metric, dtype, w.P, w.Q, np.stack([rows, rows % 601], 1))
+    w.threshold = float(np.quantile(ref, quantile if metric == "ip" else 1 - quantile))
+    if quantile == 0.0:
+        w.threshold = -1e6 if metric == "ip" else 1e6
+    h = workloads.lsh_params(1300 + L, L=L, k=k, d=d, w=0)
+    g, ref_pairs, exact, cand, _ = run_lsh(w, h)
+    assert len(ref_pairs) > 20000
+
+
+def test_lsh_held_records_in_several_rounds():
+    """More held records than there is room for: workgroups stop, the records are
+    resolved, and the join goes on where it stopped (k = 0: one bucket of 24 x 24
+    tiles per table, about 3% of the pairs matching), for a given output, one that
+    the library sizes, and one that is too small."""
+    import torch
+    import paper_2006_12608_amd as sj
+    w = case(1400, 6000, 5900, 32, "i8", "ip", 0.0)
+    x, y = w.P.astype(np.int64), w.Q.astype(np.int64)
+    w.threshold = float(np.quantile(x[:300] @ y.T, 0.97, method="nearest"))
+    Pd, Qd = to_device(w.P, "i8"), to_device(w.Q, "i8")
+    A = torch.zeros((0, 32), dtype=torch.int8, device="cuda")
+    exact = sorted_pairs(sj.join_ip(Pd, Qd, w.threshold))
+    say("held records", exact.shape[0])
+    assert exact.shape[0] > 500000
+    for L in (1, 4):
+        got, cand = sj.join_lsh(Pd, Qd, w.threshold, "ip", L=L, k=0, A=A)
+        assert cand == L * 6000 * 5900
+        assert np.array_equal(sorted_pairs(got), exact)
+        out = torch.full((exact.shape[0] + 10, 2), -1, dtype=torch.int32, device="cuda")
+        got, _ = sj.join_lsh(Pd, Qd, w.threshold, "ip", L=L, k=0, A=A, out=out)
+        assert np.array_equal(sorted_pairs(got), exact) and bool((out[exact.shape[0]:] == -1).all())
+        with pytest.raises(sj.SjError) as e:
+            sj.join_lsh(Pd, Qd, w.threshold, "ip", L=L, k=0, A=A, out=out[:1000])
+        assert e.value.status == sj.SJ_E_OVERFLOW and e.value.n_out == exact.shape[0]
+        assert bool((out[exact.shape[0]:] == -1).all())
