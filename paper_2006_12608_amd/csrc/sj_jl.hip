@@ -502,6 +502,13 @@ hipError_t launch_chain_t(int v, const ChainArgs &g, int num_cus, hipStream_t s)
     }
 }
 
+// Whether [a, a + na) and [b, b + nb) have no byte in common.
+static bool apart(const void *a, uint64_t na, const void *b, uint64_t nb)
+{
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+    return x + na <= y || y + nb <= x;
+}
+
 // Whether jl_chain takes the transform: two or three levels, the last of one row;
 // sizes k_i in whole quads of both halves (multiples of 8), level-1 rows of whole
 // 32-byte pieces, rows and results 16-byte aligned, factors that fit LDS, and
@@ -525,13 +532,27 @@ static bool chain_args(int src, const void *X, uint32_t n, uint32_t d, uint32_t 
         return false;
     *g = ChainArgs{(const uint8_t *)X, A, Y, n, (uint32_t)(d * es), l1[0], l1[1], l2[0], l2[1],
                    levels == 3 ? l3[0] : 0, levels == 3 ? l3[1] : 0, l1[2] / l2[2], l2[2]};
-    // MFMAs per 32 rows
     const int v = d * es < ((uint64_t)1 << 32) ? chain_variant(*g) : -1;
     if (v < 0)
         return false;
-    const uint64_t steps = (uint64_t)l1[2] * kChainB[v][0] * l1[1] / 2 +
-                           (uint64_t)l2[2] * kChainB[v][1] * l2[1] / 2 +
-                           (uint64_t)kChainB[v][2] * g->c3 / 2;
+    // a kernel per level reads the rows before the results are written; here they
+    // are written while other rows and the factors are still read
+    const uint64_t kl = last[0], factors = (uint64_t)l1[0] * l1[1] + (uint64_t)l2[0] * l2[1] +
+                                           (uint64_t)g->k3 * g->c3;
+    if (!apart(Y, n * kl * 4, X, n * d * es) || !apart(Y, n * kl * 4, A, factors * 4))
+        return false;
+    // MFMAs per 32 rows here and by levels, and values between the levels of one row
+    const uint32_t kk[3] = {l1[0], l2[0], g->k3}, cc[3] = {l1[1], l2[1], g->c3};
+    const uint32_t rr[3] = {l1[2], l2[2], 1};
+    uint64_t steps = 0, by_levels = 0, between = 0;
+    for (uint32_t i = 0; i < levels; ++i) {
+        const uint64_t per_block = (uint64_t)rr[i] * cc[i] / 2;
+        steps += per_block * kChainB[v][i];
+        by_levels += per_block * ((kk[i] + 31) / 32);
+        between += i + 1 < levels ? (uint64_t)rr[i] * kk[i] : 0;
+    }
+    if ((levels == 2 ? 5 : 4) * (steps - by_levels) > (levels == 2 ? 7 : 3) * between)
+        return false;
     return (uint64_t)n >= (steps <= 400 ? 48ull : 96ull) * (uint64_t)num_cus;
 }
 

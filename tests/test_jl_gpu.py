@@ -246,3 +246,33 @@ def test_jl_edge_shapes(dtype, n, d, shapes):
     X = workloads.encode(rng.integers(-4, 5, size=(n, d)), dtype)
     Y = run(X, dtype, shapes, As)
     assert np.array_equal(Y, jl.transform(values(dtype, X), shapes, As))
+
+
+@pytest.mark.parametrize("over", ["rows", "factors"])
+def test_jl_results_over_inputs(over):
+    """Results written over the rows or the factors: every level reads its input
+    before the last one writes, whichever kernels run (row counts that the
+    one-kernel transform would take)."""
+    import torch
+    import paper_2006_12608_amd as sj
+    shapes = [(32, 64, 8), (32, 256, 1)]
+    n, d, kl = 60001, 512, 32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(60)
+    X = torch.randn((n, d), generator=g, device="cuda").half()
+    A = torch.randn(32 * 64 + 32 * 256, generator=g, device="cuda")
+    ctx = sj.context()
+    say("jl over", over)
+    ref = torch.empty((n, kl), dtype=torch.float32, device="cuda")
+    assert sj.sj_jl(ctx, sj.SJ_F16, X.data_ptr(), n, d, 2, shapes, A.data_ptr(),
+                    ref.data_ptr()) == sj.SJ_OK
+    if over == "rows":   # the results start half-way into the rows
+        buf = X.clone().view(-1).view(torch.float32)
+        x, a, y = buf.data_ptr(), A.data_ptr(), buf[(n // 2) * d // 2:]
+    else:                # the results' last values lie on the first level's factor
+        buf = torch.empty(n * kl + 32 * 256, device="cuda")
+        buf[n * kl - 32 * 64:] = A
+        x, a, y = X.data_ptr(), buf[n * kl - 32 * 64:].data_ptr(), buf
+    assert sj.sj_jl(ctx, sj.SJ_F16, x, n, d, 2, shapes, a, y.data_ptr()) == sj.SJ_OK
+    got = y[:n * kl].view(n, kl)
+    assert (got - ref).norm() <= 2e-6 * ref.norm()
