@@ -519,6 +519,12 @@ static bool apart(const void *a, uint64_t na, const void *b, uint64_t nb)
 // 1280, 1024 to 64 (zeta = 4): 16384 rows 55 / 47, 24576 rows 56 / 57, 262144 rows
 // 341 / 456; 1664, 2048 to 32 (zeta = 4): 16384 rows 70 / 60, 24576 rows 72 / 78,
 // 262144 rows 447 / 700.
+// A variant with more blocks of 32 features than the sizes fill multiplies zeros: it pays
+// while that is less than what the values between the levels cost in memory, about
+// 1.4 MFMAs per 32 rows for each with two levels and 0.75 with three.  200000 fp16 rows, us,
+// MFMAs here / by levels and values between: 1088 / 576, 64: 269 / 189; 640 / 384, 128: 171
+// / 154; 176 / 112, 48: 73 / 81; 832 / 672, 320: 210 / 241; three levels 1152 / 512, 384: 274 /
+// 218; 960 / 544, 320: 235 / 218; 1104 / 808, 336: 261 / 267; 1024 / 1024, 512: 250 / 353.
 static bool chain_args(int src, const void *X, uint32_t n, uint32_t d, uint32_t levels,
                        const uint32_t *shape, const float *A, float *Y, int num_cus, ChainArgs *g)
 {
