@@ -11,9 +11,9 @@
 // same fused threshold test and wave-ballot compaction as the all-pairs join.
 #include "sj_lsh.h"
 
-
 #include "sj_internal.h"
 #include "sj_join_kernels.h"
+#include "sj_search.h"
 
 namespace sjl {
 namespace {
@@ -579,14 +579,7 @@ __global__ void __launch_bounds__(256) fix_kernel(Rows r, uint32_t d, uint32_t k
 __device__ __forceinline__ uint32_t upper_bound(const uint64_t *s, uint32_t lo, uint32_t hi,
                                                 uint64_t key)
 {
-    while (lo < hi) {
-        const uint32_t mid = lo + (hi - lo) / 2;
-        if (s[mid] <= key)
-            lo = mid + 1;
-        else
-            hi = mid;
-    }
-    return lo;
+    return first_above([s](uint32_t i) { return s[i]; }, lo, hi, key);
 }
 
 __device__ __forceinline__ uint32_t lower_bound(const uint64_t *s, uint32_t lo, uint32_t hi,
@@ -600,18 +593,6 @@ __device__ __forceinline__ uint32_t lower_bound(const uint64_t *s, uint32_t lo, 
             hi = mid;
     }
     return lo;
-}
-
-// Position after the run of `key` that starts at p - 1 (keys ascending):
-// doubling steps, then a binary search in the last step.
-__device__ __forceinline__ uint32_t run_end(const uint64_t *s, uint32_t p, uint32_t n, uint64_t key)
-{
-    uint32_t lo = p, step = 1;
-    while (lo + step <= n && s[lo + step - 1] == key) {
-        lo += step;
-        step *= 2;
-    }
-    return upper_bound(s, lo, min(lo + step, n), key);
 }
 
 // Per table and block of 256 sorted positions of P, the range of Q's sorted
@@ -717,7 +698,7 @@ __global__ void __launch_bounds__(256) bucket_find_kernel(const uint64_t *sorted
             if (m != 0)
                 np = 64 * w + (uint32_t)__builtin_ctzll(m) - tid;
             else   // the block's last bucket: up to the block's end and beyond
-                np = run_end(sp, min(pf + 256, n_p), n_p, key) - p;
+                np = run_end([sp](uint32_t i) { return sp[i]; }, min(pf + 256, n_p), n_p, key) - p;
             rec = make_uint4(p, np, q0, qe - q0);
             cand = (uint64_t)np * (qe - q0);
             rows = (uint64_t)np + (qe - q0);

@@ -34,6 +34,7 @@
 // writes both (20 bytes per entry).
 #include "sj_internal.h"
 #include "sj_lsh.h"
+#include "sj_search.h"
 
 namespace sjl {
 
@@ -55,13 +56,13 @@ __global__ void __launch_bounds__(SORT_T) sort_hist(const uint32_t *keys, uint32
         (&cnt[0][0])[i] = 0u;
     __syncthreads();
     const uint64_t base = (uint64_t)seg * n;
-    const uint32_t lo = blk * SORT_TILE, hi = min(lo + (uint32_t)SORT_TILE, n);
+    const uint32_t lo = blk * SORT_TILE, entries = block_entries(blk, SORT_TILE, n);
     // all of this thread's keys are loaded before the first count
     uint32_t dg[SORT_IPT];
 #pragma unroll
     for (int r = 0; r < SORT_IPT; ++r) {
-        const uint32_t i = lo + r * SORT_T + tid;
-        dg[r] = i < hi ? (keys[base + i] >> shift) & mask : 0xffffffffu;
+        const uint32_t i = r * SORT_T + tid;
+        dg[r] = i < entries ? (keys[base + lo + i] >> shift) & mask : 0xffffffffu;
     }
 #pragma unroll
     for (int r = 0; r < SORT_IPT; ++r)
@@ -190,7 +191,7 @@ __global__ void __launch_bounds__(SORT_T) sort_scatter(const uint32_t *kin, cons
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t mask = (1u << nbits) - 1u;
     const uint32_t lo = blk * SORT_TILE;
-    const uint32_t cnt = min((uint32_t)SORT_TILE, n - lo);
+    const uint32_t cnt = block_entries(blk, SORT_TILE, n);
     const uint64_t base = (uint64_t)seg * n + lo;
     for (int i = tid; i < (SORT_T / 64) * SORT_BINS; i += SORT_T)
         (&s_run[0][0])[i] = 0u;

@@ -11,6 +11,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 SOURCE = r"""
 #include "sj_lsh_layout.h"
+#include "sj_search.h"
 #include "sj_tiles.h"
 // Tiles of workgroup b of `grid`, as pt << 32 | qt; returns their number.
 template <bool TRI>
@@ -27,6 +28,15 @@ extern "C" uint32_t tiles(int tri, uint32_t n_pt, uint32_t n_qt, uint32_t b, uin
                           uint64_t *out)
 {
     return tri ? walk<true>(n_pt, n_qt, b, grid, out) : walk<false>(n_pt, n_qt, b, grid, out);
+}
+// Keys: 5 in [first, end), 9 from there on.
+extern "C" uint32_t run_end_of(uint32_t first, uint32_t end, uint32_t p, uint32_t n)
+{
+    return sjl::run_end([=](uint32_t i) { return i < first ? 1ull : i < end ? 5ull : 9ull; }, p, n, 5);
+}
+extern "C" uint32_t entries(uint32_t blk, uint32_t tile, uint32_t n)
+{
+    return sjl::block_entries(blk, tile, n);
 }
 extern "C" void layout(const uint64_t *n, uint64_t *out)
 {
@@ -59,7 +69,9 @@ def lib(tmp_path_factory):
     subprocess.run([cxx, "-std=c++17", "-O1", "-shared", "-fPIC", "-I",
                     os.path.join(ROOT, "paper_2006_12608_amd", "csrc"), str(d / "index_math.cpp"),
                     "-o", so], check=True)
-    return ctypes.CDLL(so)
+    lib = ctypes.CDLL(so)
+    lib.run_end_of.restype = lib.entries.restype = ctypes.c_uint32
+    return lib
 
 
 def workgroup_tiles(lib, tri, n_pt, n_qt, grid):
@@ -170,3 +182,22 @@ def test_lsh_scratch_layout(lib, n_p, n_q, L, self_join, long_rows):
                       + hash_ws + widened + 8 * pos_p // 4096 + 12 * 256 + held)
             # apart from rounding: to 256 bytes, and found buckets to whole blocks of 256
             assert at["total"] <= before + 256 * len(NAMES) + 4096 * 2 * L * (n_max < 4096)
+
+
+@pytest.mark.parametrize("n", [1, 2, 255, 256, 1000, 1 << 31, (1 << 31) + 300, (1 << 32) - 1])
+def test_run_end(lib, n):
+    """Ends of runs of equal keys of every length, up to the longest (all of 2^32 - 1
+    positions) and from starts near the end."""
+    ends = {1, 2, n // 3, n // 2, n - 1, n, min(n, 1 << 31), min(n, (1 << 31) + 256)}
+    for end in (e for e in ends if 0 < e <= n):
+        for first in {0, end // 2, end - 1}:
+            for p in {first + 1, first + (end - first) // 2, end}:
+                if first < p <= end:
+                    assert lib.run_end_of(first, end, p, n) == end, (first, end, p, n)
+
+
+def test_block_entries(lib):
+    for n in (1, 2047, 2048, 2049, (1 << 32) - 2048, (1 << 32) - 1):
+        nb = (n + 2047) // 2048
+        assert lib.entries(nb - 1, 2048, n) == n - 2048 * (nb - 1)
+        assert lib.entries(0, 2048, n) == min(n, 2048)
