@@ -289,6 +289,41 @@ struct WaveOut {
     uint64_t dst;    // emit pass: next global slot of this wave's block
     uint64_t blk;    // MODE_RECORD: output block of the blocks being tested
     __attribute__((address_space(3))) uint32_t *nrec;   // MODE_RECORD: workgroup's record count
+
+    __device__ __forceinline__ void put(uint32_t k, uint32_t i, uint32_t j) const
+    {
+        buf[k] = pack_pair(i, j);
+    }
+    __device__ __forceinline__ void put_mirror(uint32_t k, uint32_t i, uint32_t j) const
+    {
+        buf[k] = pack_pair(j, i);
+    }
+    __device__ __forceinline__ uint64_t get(uint32_t k) const { return buf[k]; }
+};
+
+// The same for the pairs of one 256 x 256 tile at a time (the K-streamed kernel): an
+// entry is the pair's place in the tile, so the buffer holds twice as many.
+struct TileOut {
+    typedef __attribute__((address_space(3))) uint32_t lds_place;
+    lds_place *buf;
+    uint32_t cap, fill;
+    uint64_t dst, blk;
+    __attribute__((address_space(3))) uint32_t *nrec;
+    uint32_t i0, j0;   // the tile's first row and column
+
+    __device__ __forceinline__ void put(uint32_t k, uint32_t i, uint32_t j) const
+    {
+        buf[k] = (i - i0) | (j - j0) << 8;
+    }
+    __device__ __forceinline__ void put_mirror(uint32_t k, uint32_t i, uint32_t j) const
+    {
+        buf[k] = (i - i0) | (j - j0) << 8 | 1u << 16;
+    }
+    __device__ __forceinline__ uint64_t get(uint32_t k) const
+    {
+        const uint32_t v = buf[k], i = i0 + (v & 255u), j = j0 + (v >> 8 & 255u);
+        return v >> 16 ? pack_pair(j, i) : pack_pair(i, j);
+    }
 };
 
 // Modes whose first pass only counts (no pairs written).
@@ -308,8 +343,9 @@ constexpr bool single_mode()
 // MODE_RECORD: append the block's MatchRecord to the workgroup's list (an LDS
 // counter, so no global atomics in the product loop; records past rec_cap are
 // counted, not written, and the host then recomputes instead of reading them).
+template <typename Out>
 __device__ __forceinline__ void append_record(uint32_t m, uint32_t ib, uint32_t j, int lane,
-                                              uint64_t pos, const JoinArgs &g, const WaveOut &wo)
+                                              uint64_t pos, const JoinArgs &g, const Out &wo)
 {
     typedef __attribute__((address_space(1))) uint16_t global_u16;
     typedef __attribute__((address_space(1))) MatchRecord global_rec;
@@ -331,8 +367,8 @@ __device__ __forceinline__ void append_record(uint32_t m, uint32_t ib, uint32_t 
     }
 }
 
-template <int MODE>
-__device__ __forceinline__ void flush_wave_out(WaveOut &wo, int lane, const JoinArgs &g)
+template <int MODE, typename Out>
+__device__ __forceinline__ void flush_wave_out(Out &wo, int lane, const JoinArgs &g)
 {
     if (wo.fill == 0)
         return;
@@ -348,7 +384,7 @@ __device__ __forceinline__ void flush_wave_out(WaveOut &wo, int lane, const Join
     }
     for (uint32_t k = lane; k < wo.fill; k += 64)
         if (base + k < g.cap)
-            *pair_slot(g, base + k) = wo.buf[k];
+            *pair_slot(g, base + k) = wo.get(k);
     wo.fill = 0;
 }
 
@@ -377,8 +413,39 @@ __device__ __forceinline__ void flush_workgroup_out(WaveOut &wo, int wave, int l
         base += s_fill[w];
     for (uint32_t k = lane; k < wo.fill; k += 64)
         if (base + k < g.cap)
-            *pair_slot(g, base + k) = wo.buf[k];
+            *pair_slot(g, base + k) = wo.get(k);
     wo.fill = 0;
+}
+
+// The staged pairs of a tile's waves with one atomicAdd, the buffers free
+// afterwards (all waves must call it; its barriers are one when no wave has pairs).
+// A reservation per wave took 18000 atomics on one address for 12000 x 12000 fp16 rows of
+// 600 bytes with 1% matches: a call 270 us, now 151 (174 with one workgroup per tile).
+template <int NW>
+__device__ __forceinline__ void flush_tile_out(TileOut &wo, int wave, int lane, const JoinArgs &g)
+{
+    __shared__ uint32_t s_fill[NW];
+    __shared__ unsigned long long s_base;
+    if (lane == 0)
+        s_fill[wave] = wo.fill;
+    __syncthreads();
+    uint32_t tot = 0, before = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const uint32_t n = __builtin_amdgcn_readfirstlane(s_fill[w]);
+        before += w < wave ? n : 0u;
+        tot += n;
+    }
+    if (tot == 0)
+        return;
+    if (wave == 0 && lane == 0)
+        s_base = atomicAdd(g.counter, (unsigned long long)tot);
+    __syncthreads();
+    const uint64_t base = s_base + before;
+    for (uint32_t k = lane; k < wo.fill; k += 64)
+        if (base + k < g.cap)
+            *pair_slot(g, base + k) = wo.get(k);
+    __syncthreads();
 }
 
 // Exact test of every result of one 32x32 block (accumulator `acc`, rows
@@ -429,12 +496,12 @@ __device__ __forceinline__ uint32_t block_mask(const typename Mma<DT>::acc_t &ac
 
 // Single-pass staging of the pairs selected by per-lane masks m (bit r:
 // accumulator register r): the wave's total and each lane's prefix come from
-// five ballots over the lanes' counts, and every lane writes pair(r) for its
-// set bits in register order at its prefix in the wave's LDS buffer (flushed
+// five ballots over the lanes' counts, and every lane calls put(place, r)
+// for its set bits r in register order from its prefix in the wave's LDS buffer (flushed
 // first when the block would not fit).
-template <int MODE, typename F>
-__device__ __forceinline__ void stage_pairs(uint32_t m, int lane, const JoinArgs &g, WaveOut &wo,
-                                            F &&pair)
+template <int MODE, typename Out, typename F>
+__device__ __forceinline__ void stage_pairs(uint32_t m, int lane, const JoinArgs &g, Out &wo,
+                                            F &&put)
 {
     const uint32_t cnt = (uint32_t)__builtin_popcount(m);
     uint32_t tot = 0, pre = 0;
@@ -453,7 +520,7 @@ __device__ __forceinline__ void stage_pairs(uint32_t m, int lane, const JoinArgs
     while (m != 0) {
         const int r = __builtin_ctz(m);
         m &= m - 1;
-        wo.buf[pos++] = pair(r);
+        put(pos++, r);
     }
 }
 
@@ -466,11 +533,11 @@ __device__ __forceinline__ void stage_pairs(uint32_t m, int lane, const JoinArgs
 // counts.  The code is kept short on purpose: it is inlined at every sub-tile
 // and runs rarely, and a long exact path costs instruction-cache misses when
 // it does run.
-template <int DT, int MET, int MODE>
+template <int DT, int MET, int MODE, typename Out>
 __device__ __forceinline__ void exact_block(const typename Mma<DT>::acc_t &acc, uint32_t ib,
                                             uint32_t j, int lane, typename Mma<DT>::val_t ny,
                                             const typename Mma<DT>::val_t *nrow,
-                                            const JoinArgs &g, uint64_t &blk_run, WaveOut &wo)
+                                            const JoinArgs &g, uint64_t &blk_run, Out &wo)
 {
     // Opaque to the optimiser: keeps the per-result row indices from being
     // hoisted into (and occupying registers of) the caller's main loop.
@@ -487,8 +554,8 @@ __device__ __forceinline__ void exact_block(const typename Mma<DT>::acc_t &acc, 
             for (int r = 0; r < 16; ++r)
                 off &= ib + 8 * (r >> 2) + (r & 3) == j ? ~(1u << r) : ~0u;
         }
-        stage_pairs<MODE>(off, lane, g, wo, [&](int r) {
-            return pack_pair(j, ib + 8 * (r >> 2) + (r & 3));
+        stage_pairs<MODE>(off, lane, g, wo, [&](uint32_t k, int r) {
+            wo.put_mirror(k, ib + 8 * (r >> 2) + (r & 3), j);
         });
     }
     const uint32_t cnt = (uint32_t)__builtin_popcount(m);
@@ -514,7 +581,7 @@ __device__ __forceinline__ void exact_block(const typename Mma<DT>::acc_t &acc, 
         while (m != 0) {
             const int r = __builtin_ctz(m);
             m &= m - 1;
-            dst(pos++, pack_pair(ib + 8 * (r >> 2) + (r & 3), j));
+            dst(pos++, ib + 8 * (r >> 2) + (r & 3));
         }
     };
     if (single_mode<MODE>() || wo.cap > 1) {
@@ -523,28 +590,28 @@ __device__ __forceinline__ void exact_block(const typename Mma<DT>::acc_t &acc, 
             flush_wave_out<MODE>(wo, lane, g);
         const uint32_t base = wo.fill;
         wo.fill += tot;
-        write_all([&](uint64_t k, uint64_t v) { wo.buf[k] = v; }, base);
+        write_all([&](uint64_t k, uint32_t i) { wo.put((uint32_t)k, i, j); }, base);
     } else {
         const uint64_t base = blk_run;
         blk_run += tot;
         write_all(
-            [&](uint64_t slot, uint64_t v) {
+            [&](uint64_t slot, uint32_t i) {
                 if (slot < g.cap)
-                    *pair_slot(g, slot) = v;
+                    *pair_slot(g, slot) = pack_pair(i, j);
             },
             base);
     }
 }
 
 // All WMB blocks of a wave's sub-tile whose own bound holds for some lane.
-template <int DT, int MET, int MODE, int WMB>
+template <int DT, int MET, int MODE, int WMB, typename Out>
 __device__ __forceinline__ void exact_blocks(const typename Mma<DT>::acc_t (&acc)[WMB],
                                              const typename Mma<DT>::val_t (&mb)[WMB],
                                              uint32_t ibase, uint32_t j, int lane,
                                              typename Mma<DT>::val_t nb,
                                              typename Mma<DT>::val_t ny,
                                              const typename Mma<DT>::val_t *nrows,
-                                             const JoinArgs &g, uint64_t &blk_run, WaveOut &wo)
+                                             const JoinArgs &g, uint64_t &blk_run, Out &wo)
 {
 #pragma unroll
     for (int a = 0; a < WMB; ++a) {
@@ -983,8 +1050,6 @@ __global__ void __launch_bounds__(ST_NW * 64) join_streamed(JoinArgs g)
     constexpr int KSC = ST_KC / 32;                   // k-steps per chunk
     constexpr int SA = ST_SA, SB = ST_SB;             // A- and B-blocks per wave
     constexpr bool NEED_NORMS = (MET == MET_L2);
-    // the epilogue stages pairs in the operand buffers
-    constexpr bool STAGED = MODE != MODE_MASK && !counting_mode<MODE>();
     static_assert(ROWS * CPR % NT == 0 && ST_BM * CPR / 64 == ST_NW * NLD / 2, "load layout");
 
     // two stages as distinct arrays (see join_resident)
@@ -1065,8 +1130,9 @@ __global__ void __launch_bounds__(ST_NW * 64) join_streamed(JoinArgs g)
         }
         const V nb = bound_base<DT, MET>(nmin, g);
         constexpr uint32_t STAGE_BYTES = ROWS * LS / ST_NW;
-        static_assert(STAGE_BYTES / 8 >= 1024, "a whole 32x32 block must fit the staging buffer");
-        WaveOut wo{(lds_pair *)stage_mem, STAGE_BYTES / 8, 0u, 0ull};
+        static_assert(STAGE_BYTES / 4 >= 1024, "a whole 32x32 block must fit the staging buffer");
+        static_assert(ST_BM == 256 && ST_BN == 256, "places of 8 + 8 bits");
+        TileOut wo{(TileOut::lds_place *)stage_mem, STAGE_BYTES / 4, 0u, 0ull, 0ull, nullptr, p0, q0};
         const uint64_t blk = ((uint64_t)x.pt * n_qt + x.qt) * ST_NW + wv;
         uint64_t blk_run = 0;
         if constexpr (MODE == MODE_MASK) {
@@ -1121,8 +1187,12 @@ __global__ void __launch_bounds__(ST_NW * 64) join_streamed(JoinArgs g)
                 exact_blocks<DT, MET, MODE, SA>(blk_acc, mb, ibase, j, lane, nb, ny, nrows, g,
                                                 blk_run, wo);
         }
-        if constexpr (STAGED)
+        if constexpr (MODE == MODE_EMIT) {
             flush_wave_out<MODE>(wo, lane, g);
+            __syncthreads();   // the buffer is free for the next chunk's loads
+        } else if constexpr (single_mode<MODE>()) {
+            flush_tile_out<ST_NW>(wo, wv, lane, g);
+        }
         if constexpr (MODE == MODE_COUNT) {
             if (lane == 0)
                 g.block_counts[blk] = (uint32_t)blk_run;
@@ -1184,8 +1254,6 @@ __global__ void __launch_bounds__(ST_NW * 64) join_streamed(JoinArgs g)
         kc = 0;
         // (the buffer just read is free until the next chunk's loads)
         epilogue(cur, buf + wv * (ROWS * LS / ST_NW));
-        if constexpr (STAGED)
-            __syncthreads();
         if (!more)
             return false;
         cur = nxt;

@@ -107,6 +107,30 @@ def test_self_join_triangle_streamed(dtype, d, metric, n):
     assert np.array_equal(keys(g2), keys(g))
 
 
+@pytest.mark.parametrize("dtype,d,metric,n,quantile", [
+    ("bf16", 300, "ip", 8200, 0.9995), ("f16", 320, "l2", 8192, 0.99), ("i8", 600, "ip", 9001, 0.98),
+    ("i8", 768, "l2", 8449, 0.9999)])
+def test_self_join_triangle_streamed_many_tiles(dtype, d, metric, n, quantile):
+    """Triangles of more tiles than CUs (33 to 36 rows of tiles): workgroups of the
+    K-streamed kernel take several, from whole, partial and diagonal groups; the
+    oracle's set on sampled rows, symmetric, and the two-pass mode's set."""
+    w = workloads.random_case(91 + d, n, n, d, dtype, lo=-3, hi=3, metric=metric)
+    w.P[n // 3: n // 3 + 20] = w.P[:20]
+    rows = np.sort(np.random.default_rng(d).choice(n, 200, replace=False))
+    x, y = values(dtype, w.P[rows]).astype(np.int64), values(dtype, w.P).astype(np.int64)
+    s = x @ y.T
+    if metric == "l2":
+        s = (x * x).sum(1)[:, None] + (y * y).sum(1)[None, :] - 2 * s
+    thr = float(np.quantile(s, quantile if metric == "ip" else 1 - quantile, method="nearest"))
+    P = to_device(w.P, dtype)
+    say("self streamed, many tiles", dtype, d, metric, n, thr)
+    g = sorted_pairs(gpu_join(metric, P, P, thr))
+    compare(g[np.isin(g[:, 0], rows)], oracle.join(metric, dtype, w.P, w.P, thr, rows=rows), False)
+    assert np.array_equal(np.sort(keys(g[:, ::-1].copy())), keys(g))
+    g2 = sorted_pairs(gpu_join(metric, P, P, thr, two_pass=True))
+    assert np.array_equal(keys(g2), keys(g))
+
+
 @pytest.mark.parametrize("dtype,d,n", [("i8", 64, 5000), ("bf16", 128, 4100), ("f16", 40, 2600)])
 def test_self_join_triangle_block_pairing(dtype, d, n):
     """Several blocks of P rows (odd and even counts): the triangle's
