@@ -220,6 +220,38 @@ def test_hamming_code_lengths(d):
     assert np.array_equal(keys(g), keys(oracle.hamming_join(P, P.copy(), d, d / 2)))
 
 
+@pytest.mark.parametrize("d", [120, 256, 500, 1000, 1500])
+def test_hamming_ordinary_tiles_all_modes(d):
+    """Every 4-bit variant at a size that takes the ordinary tiles (smaller joins
+    take the small geometry; 1500 bits the K-streamed kernel), ragged, in every
+    mode: the oracle's set on sampled rows, and the same array from both second
+    passes of count-then-emit."""
+    import torch
+    import paper_2006_12608_amd as sj
+    n_p, n_q = 8209, 9001
+    rng = np.random.default_rng(7400 + d)
+    P, _ = _bits(rng, n_p, d)
+    Q, _ = _bits(rng, n_q, d)
+    Q[7:200] = P[1000:1193]
+    rows = np.sort(np.concatenate([rng.choice(n_p, 250, replace=False), np.arange(1000, 1050)]))
+    rows = np.unique(rows)
+    r = d / 2 - 1.4 * np.sqrt(d)               # about 0.25% of the pairs
+    Pd, Qd = _bits_device(P), _bits_device(Q)
+    say("hamming ordinary tiles", d)
+    want = oracle.hamming_join(P[rows], Q, d, r).astype(np.int64)
+    want = np.stack([rows[want[:, 0]], want[:, 1]], 1)
+    a = sj.join_hamming(Pd, Qd, d, r)
+    total = a.shape[0]
+    out = torch.empty((total, 2), dtype=torch.int32, device="cuda")
+    st, n = sj.sj_join_hamming(sj.context(), Pd.data_ptr(), n_p, Qd.data_ptr(), n_q, d, r,
+                               out.data_ptr(), total, sj.SJ_FLAG_TWO_PASS | sj.SJ_FLAG_RECOMPUTE)
+    assert st == sj.SJ_OK and n == total and torch.equal(a, out)
+    h = sorted_pairs(a)
+    assert np.array_equal(keys(h[np.isin(h[:, 0], rows)]), np.sort(keys(want)))
+    one = sorted_pairs(sj.join_hamming(Pd, Qd, d, r, two_pass=False, cap=total))
+    assert np.array_equal(keys(one), keys(h))
+
+
 def test_hamming_self_join_and_larger():
     """The same pointer (upper triangle, mirrored: symmetric, diagonal
     present) and a 12000-row, 128-bit join with planted near-duplicates."""

@@ -298,6 +298,38 @@ def test_ordinary_tiles_all_modes(dtype, d, metric):
     assert sj.count(Pd, Qd, w.threshold, metric) == h.shape[0]
 
 
+@pytest.mark.parametrize("dtype,d", [("f16", 300), ("bf16", 320), ("f16", 384), ("bf16", 505),
+                                     ("i8", 600), ("i8", 640), ("i8", 769)])
+@pytest.mark.parametrize("metric", ["ip", "l2"])
+@pytest.mark.parametrize("quantile", [0.9995, 0.98, 0.8])
+def test_streamed_tiles_all_modes(dtype, d, metric, quantile):
+    """The K-streamed kernel at 18 x 19 ragged tiles, more than the CUs, so its
+    workgroups go from tile to tile: rows of an odd and an even number of 128-byte
+    chunks with and without a partial last one, few and many matches (staged pairs
+    that overflow a wave's buffer), in every mode: the oracle's set, and the same
+    array from both second passes of count-then-emit."""
+    import paper_2006_12608_amd as sj
+    n_p, n_q = 4400, 4700
+    w = workloads.random_case(81 + d, n_p, n_q, d, dtype, lo=-3, hi=3, metric=metric)
+    rows = np.sort(np.random.default_rng(d).choice(n_p, 300, replace=False))
+    x, y = values(dtype, w.P[rows]).astype(np.int64), values(dtype, w.Q).astype(np.int64)
+    s = x @ y.T
+    if metric == "l2":
+        s = (x * x).sum(1)[:, None] + (y * y).sum(1)[None, :] - 2 * s
+    w.threshold = float(np.quantile(s, quantile if metric == "ip" else 1 - quantile,
+                                    method="nearest"))
+    _, g, _ = run_case(w, rows=rows)
+    Pd, Qd = to_device(w.P, dtype), to_device(w.Q, dtype)
+    f = sj.join_ip if metric == "ip" else sj.join_l2
+    a, b = f(Pd, Qd, w.threshold), f(Pd, Qd, w.threshold, recompute=True)
+    assert np.array_equal(a.cpu().numpy(), b.cpu().numpy())
+    h = sorted_pairs(a)
+    assert np.array_equal(g, h[np.isin(h[:, 0], rows)])
+    one = sorted_pairs(f(Pd, Qd, w.threshold, two_pass=False))
+    assert np.array_equal(one, h)
+    assert sj.count(Pd, Qd, w.threshold, metric) == h.shape[0]
+
+
 @pytest.mark.parametrize("dtype,d,metric", [("bf16", 300, "ip"), ("f16", 520, "l2"),
                                              ("i8", 700, "ip"), ("i8", 530, "l2"),
                                              ("bf16", 128, "ip"), ("f16", 256, "l2"),
@@ -344,26 +376,27 @@ def test_two_pass_match_bits_equal_recompute(dtype, d, metric):
 
 
 @pytest.mark.parametrize("dtype,d", [("i8", 64), ("bf16", 96)])
-def test_two_pass_records_every_pair(dtype, d):
+@pytest.mark.parametrize("n_p,n_q", [(300, 768), (3500, 10908)])
+def test_two_pass_records_every_pair(dtype, d, n_p, n_q):
     """Resident kernel, count-then-emit with every pair matching: every 32x32
-    block has a record (the workgroup that sweeps two of the three Q tiles
-    holds the most), and the output is every pair, in the same order as the
-    recomputing second pass."""
+    block has a record, and the output is every pair, in the same order as the
+    recomputing second pass.  300 x 768 takes the small geometry (a workgroup
+    has one tile); at 3500 x 10908 the Q tiles (43 or 86) do not divide by the
+    splits of Q, so some workgroups sweep two tiles and fill their records."""
     import torch
     import paper_2006_12608_amd as sj
-    w = workloads.random_case(23, 300, 768, d, dtype, lo=-3, hi=3)
+    w = workloads.random_case(23, n_p, n_q, d, dtype, lo=-3, hi=3)
     Pd, Qd = to_device(w.P, dtype), to_device(w.Q, dtype)
-    say("records, every pair", dtype, d)
+    say("records, every pair", dtype, d, n_p, n_q)
     ctx = sj.context(0)
     a = sj.join_ip(Pd, Qd, -np.inf, two_pass=True, ctx=ctx)
     st = sj.sj_get_stats(ctx)
     assert st.kernel == 1 and st.emit_from_bits == 1
     b = sj.join_ip(Pd, Qd, -np.inf, two_pass=True, recompute=True, ctx=ctx)
     assert torch.equal(a, b)
-    allp = sorted_pairs(a)
-    assert allp.shape[0] == 300 * 768
-    assert np.array_equal(allp[:, 0], np.repeat(np.arange(300), 768))
-    assert np.array_equal(allp[:, 1], np.tile(np.arange(768), 300))
+    del b
+    key = a[:, 0].long() * n_q + a[:, 1].long()
+    assert torch.equal(key.sort().values, torch.arange(n_p * n_q, device="cuda"))
 
 
 def test_ties_are_inclusive():
