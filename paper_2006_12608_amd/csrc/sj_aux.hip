@@ -21,7 +21,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // for the longest rows.  Must agree with sj_join_kernels.h.
 static const int kResKS16[4] = {2, 4, 8, 16};
 static const int kResKS8[4] = {1, 2, 4, 8};
-static const uint32_t kResNW = 8, kSmallNW = 2, kSmallBN = 64;
+static const uint32_t kResNW = 8, kSmallNW = 2, kSmallNW2 = 4, kSmallBN = 64;
 static uint32_t res_bn(int ks) { return ks <= 2 ? 256 : ks <= 8 ? 128 : 64; }
 static const uint32_t kStBM = ST_BM, kStBN = ST_BN, kStG = ST_G, kStNW = ST_NW;
 
@@ -68,6 +68,15 @@ bool plan_join(int dtype, int metric, uint32_t n_p, uint32_t n_q, uint32_t row_b
             bn = kSmallBN;
             n_pb = (n_p + (uint64_t)bm - 1) / bm;
             n_qt = (n_q + bn - 1) / bn;
+            // More than four workgroups per CU (rows of at most 64 bytes only: each
+            // ordinary tile is up to 16 of these) all end with a reservation on the
+            // one match counter, 7 ns each: twice the waves, half as many (50000 x
+            // 200 x 16 fp16, 1% matches: XXX).
+            if (n_pb * n_qt > 4 * (uint64_t)num_cus && ks <= 2) {
+                nw = kSmallNW2;
+                bm = nw * 32 * wmb;
+                n_pb = (n_p + (uint64_t)bm - 1) / bm;
+            }
         }
         // Enough workgroups to fill every CU twice (with exactly one round,
         // one late workgroup start stretches the whole kernel), down to one Q

@@ -1322,13 +1322,16 @@ constexpr int res_bn()
 // The small geometry (Plan::small): two waves and Q tiles of 64 rows, for joins
 // whose ordinary tiles would leave CUs without a workgroup.  A wave owns the
 // same rows of P as in the ordinary one, so count-then-emit's order (by wave
-// row block, then column) is the same.
-constexpr int SMALL_NW = 2, SMALL_BN = 64;
+// row block, then column) is the same.  With rows of at most 64 bytes, whose ordinary
+// tiles are the largest, four waves where two would make too many workgroups
+// (plan_join).
+constexpr int SMALL_NW = 2, SMALL_NW2 = 4, SMALL_BN = 64;
 
-template <int DT, int MET, int MODE, int V, bool SMALL>
+// SMALL: waves of the small geometry, 0 for the ordinary one.
+template <int DT, int MET, int MODE, int V, int SMALL>
 struct ResidentKernel {
     static constexpr int KS = ResidentCfg<DT>::KS[V];
-    static constexpr int NW = SMALL ? SMALL_NW : RES_NW;
+    static constexpr int NW = SMALL ? SMALL : RES_NW;
     static constexpr auto fn = &join_resident<DT, MET, MODE, KS, res_wmb<DT, KS>(), NW,
                                               SMALL ? SMALL_BN : res_bn<KS>()>;
 };
@@ -1337,13 +1340,20 @@ template <int DT, int MET, int MODE, int V>
 hipError_t launch_resident_v(const Plan &p, const JoinArgs &g, hipStream_t st)
 {
     if constexpr (MODE != MODE_TRI) {
+        if constexpr (ResidentCfg<DT>::KS[V] <= 2) {
+            if (p.small && p.block == SMALL_NW2 * 64) {
+                typedef ResidentKernel<DT, MET, MODE, V, SMALL_NW2> K;
+                hipLaunchKernelGGL(K::fn, dim3(p.grid), dim3(K::NW * 64), 0, st, g);
+                return hipGetLastError();
+            }
+        }
         if (p.small) {
-            typedef ResidentKernel<DT, MET, MODE, V, true> K;
+            typedef ResidentKernel<DT, MET, MODE, V, SMALL_NW> K;
             hipLaunchKernelGGL(K::fn, dim3(p.grid), dim3(K::NW * 64), 0, st, g);
             return hipGetLastError();
         }
     }
-    typedef ResidentKernel<DT, MET, MODE, V, false> K;
+    typedef ResidentKernel<DT, MET, MODE, V, 0> K;
     // the self-join triangle pairs the blocks of P rows (see join_resident)
     const uint32_t grid =
         MODE == MODE_TRI ? (p.grid / p.qsplit + 1) / 2 * p.qsplit : p.grid;
@@ -1355,7 +1365,7 @@ hipError_t launch_resident_v(const Plan &p, const JoinArgs &g, hipStream_t st)
 template <int DT, int MET, int V>
 int resident_occupancy_v()
 {
-    typedef ResidentKernel<DT, MET, MODE_SINGLE, V, false> K;
+    typedef ResidentKernel<DT, MET, MODE_SINGLE, V, 0> K;
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(K::fn),
                                                      K::NW * 64, 0) != hipSuccess)
