@@ -78,21 +78,36 @@ bool plan_join(int dtype, int metric, uint32_t n_p, uint32_t n_q, uint32_t row_b
                 n_pb = (n_p + (uint64_t)bm - 1) / bm;
             }
         }
-        // Enough workgroups to fill every CU twice (with exactly one round,
-        // one late workgroup start stretches the whole kernel), down to one Q
-        // tile each: a few hundred query rows against 262144 rows would
-        // otherwise leave most CUs without a workgroup (256 x 262144 x 256 fp16:
-        // 139 us with at most 64 splits, 43 us with 512).  Splits of Q are powers
-        // of two so that, with workgroups dealt round-robin to the 8 XCDs, each
-        // XCD's workgroups sweep the same Q range (shared in that XCD's L2).
+        // Splits of Q are powers of two so that, with workgroups dealt round-robin to
+        // the 8 XCDs, each XCD's workgroups sweep the same Q range (shared in that XCD's
+        // L2).  Enough workgroups to fill every CU twice (with exactly one round, one late
+        // workgroup start stretches the whole kernel), down to one Q tile each: a few
+        // hundred query rows would otherwise leave most CUs without one (256 x 262144 x
+        // 256 fp16: 152 us a call with at most 64 splits, 58 with 512).  Beyond 64 splits
+        // a workgroup has few tiles, and fewer splits are taken where the busiest CU
+        // then has at least a tenth less to do, counted in tiles of its workgroups plus
+        // 512 / bn for each one's resident rows, which take about as long to load (the
+        // same with 256 splits: 49; 1500 x 9000 x 256, 3 blocks and 141 tiles: 128 splits 46
+        // us, 64 38).  Not below 64: with matches to write the tiles count for more (12000 x
+        // 12000 x 64, 24 and 94, without matches: 32 splits 44 us, 8 38; with 1%: 82 and 93).
         // The small geometry takes one tile per workgroup.
         uint64_t qsplit = 1;
         if (plan->small) {
             qsplit = n_qt;
         } else {
             const int occ = resident_occupancy(dtype, metric, variant);
-            while (n_pb * qsplit < 2ull * (uint64_t)occ * (uint64_t)num_cus && qsplit * 2 <= n_qt)
+            const uint64_t cus = (uint64_t)num_cus;
+            while (n_pb * qsplit < 2ull * (uint64_t)occ * cus && qsplit * 2 <= n_qt)
                 qsplit *= 2;
+            auto busiest = [&](uint64_t q) {
+                return (n_pb * q + cus - 1) / cus * ((n_qt + q - 1) / q + 512 / bn);
+            };
+            uint64_t least = busiest(qsplit);
+            for (uint64_t q = qsplit / 2; q >= 64; q /= 2)
+                if (10 * busiest(q) < 9 * least) {
+                    least = busiest(q);
+                    qsplit = q;
+                }
         }
         plan->family = FAM_RESIDENT;
         plan->variant = variant;
