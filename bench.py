@@ -72,14 +72,15 @@ def _code_only(src: str) -> str:
 
 # Sources of the all-pairs join, its count/emit passes and their launches
 # (the kernels whose counters are recorded); the LSH front end is not among them.
-JOIN_SOURCES = ("sj_api", "sj_aux", "sj_internal", "sj_join")
+JOIN_SOURCES = ("sj_api", "sj_aux", "sj_internal", "sj_join", "sj_tiles")
 
 
 # Sources of the TCU JL transform (its own counter record).
 JL_SOURCES = ("sj_jl", "sj_host")
 
 # Sources of the LSH-bucketed join (it uses the join's MMA helpers too).
-LSH_SOURCES = ("sj_lsh", "sj_sort", "sj_aux", "sj_internal", "sj_host", "sj_join")
+LSH_SOURCES = ("sj_lsh", "sj_sort", "sj_search", "sj_aux", "sj_internal", "sj_host", "sj_join",
+               "sj_tiles")
 
 
 def kernel_source_hash(prefixes=JOIN_SOURCES) -> str:

@@ -155,11 +155,12 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// LDS tile layout: a row of CPR 16-byte chunks is stored with a stride of
-// CPR + 1 chunks.  The LDS has 64 banks of 4 bytes, so a 128-bit access serves
-// 16 lanes per cycle; a B-fragment read has 16 consecutive rows fetch the same
-// chunk c, and their bank groups ((CPR + 1) r + c) mod 16 are all distinct for
-// every CPR used here (2, 4, 8, 16, 32 and the streamed kernel's 8).
+// LDS tile layout of the resident kernel: a row of CPR 16-byte chunks is stored with a
+// stride of CPR + 1 chunks.  The LDS has 64 banks of 4 bytes, so a 128-bit access
+// serves 16 lanes per cycle; a B-fragment read has 16 consecutive rows fetch the same
+// chunk c, and their bank groups ((CPR + 1) r + c) mod 16 are all distinct for every
+// CPR used here (2, 4, 8, 16, 32).  (The K-streamed kernel's rows are unpadded and
+// swizzled, see there.)
 
 // Exact test of one pair.  IP: acc >= thr.  L2: 2 acc >= (N_x + N_y) - r2,
 // i.e. N_x + N_y - 2 <x,y> <= r2 with the fp32 additions rounded in this order

@@ -7,7 +7,7 @@ decisions its fp32 sums make certain and recomputes the rest that way -- so
 the candidate sets agree exactly; the exact test then follows the all-pairs
 join's rules: identical sets for integer-valued inputs, identical outside the
 boundary band for real-valued ones.  Cases cover both hash families, every
-dtype, both metrics, ragged sizes against the 128-row tiles, buckets
+dtype, both metrics, ragged sizes against the 256-row tiles, buckets
 spanning several tiles, unaligned rows, the self-join, k = 0 (the exact
 join), the first-table rule (no duplicates), decisions the fp32 hash cannot
 take, the candidate count, overflow and argument errors.
@@ -96,9 +96,9 @@ def case(seed, n_p, n_q, d, dtype, metric, thr, lo=-4, hi=4, real=False):
     ("i8", "l2", 400.0, 48, 300),
     ("bf16", "l2", 420.0, 96, 400),
     ("f16", "l2", 500.0, 40, 350),
-    ("i8", "l2", 600.0, 96, 400),     # 96-byte rows: the longest that travel as records
+    ("i8", "l2", 600.0, 96, 400),     # 96-byte rows: three 32-byte steps of a stage
     ("f16", "l2", 500.0, 48, 350),
-    ("i8", "l2", 600.0, 97, 400),     # 112-byte padded rows: gathered without records
+    ("i8", "l2", 600.0, 97, 400),     # 112-byte padded rows: a step half filled
 ])
 def test_lsh_parity_integer(dtype, metric, thr, d, wid):
     w = case(700 + d, 333, 290, d, dtype, metric, thr)
