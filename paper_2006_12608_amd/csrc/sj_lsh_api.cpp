@@ -248,13 +248,20 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
     const uint64_t held = lay.held_bytes / sizeof(sjl::Held);
     const uint32_t grid = sjl::join_grid(n_tiles, held, c->num_cus);
     g.held_cap = grid ? (uint32_t)std::min(held / grid, (uint64_t)UINT32_MAX) : 0;
-    // the bucket join into g.pairs, in as many launches as its held records take
-    auto bucket_join = [&](uint64_t *found) -> int {
+    // the bucket join into g.pairs, in as many launches as its held records
+    // take; `end` is recorded after each, ahead of the wait, so that the last
+    // one's time is known when the call reads it
+    auto bucket_join = [&](uint64_t *found, hipEvent_t end) -> int {
         *found = 0;
         g.resume = false;
+        if (!grid) {
+            SJ_HIP(hipEventRecord(end, s));
+            SJ_HIP(hipStreamSynchronize(s));
+        }
         while (grid) {
             SJ_HIP(sjl::launch_join(dtype, metric, g, grid, s));
             SJ_HIP(sjl::launch_join_state(g, grid, c->h_small, s));
+            SJ_HIP(hipEventRecord(end, s));
             SJ_HIP(hipStreamSynchronize(s));
             const uint64_t n_held = c->h_small[1], left = c->h_small[2];
             *found = c->h_small[0];
@@ -262,6 +269,7 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
                 break;
             SJ_HIP(sjl::launch_held(g, grid, n_held, s));
             if (left == 0) {
+                SJ_HIP(hipEventRecord(end, s));
                 SJ_HIP(sjk::launch_publish(c->d_small, c->h_small, s));
                 SJ_HIP(hipStreamSynchronize(s));
                 *found = c->h_small[0];
@@ -273,9 +281,8 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
         return SJ_OK;
     };
     uint64_t total = 0;
-    if ((st = bucket_join(&total)) != SJ_OK)
+    if ((st = bucket_join(&total, c->ev[3])) != SJ_OK)
         return st;
-    SJ_HIP(hipEventRecord(c->ev[3], s));
     if (sized && total > 0) {
         uint32_t *out = (uint32_t *)sized->alloc(sized->user, total);
         if (!out)
@@ -294,7 +301,7 @@ int lsh_join(sj_ctx *c, int metric, int dtype, const void *P, uint32_t n_p, cons
             g.cap = total;
             c->counter_clear = false;
             uint64_t again = 0;
-            if ((st = bucket_join(&again)) != SJ_OK)
+            if ((st = bucket_join(&again, c->ev[4])) != SJ_OK)
                 return st;
         }
         SJ_HIP(hipStreamSynchronize(s));

@@ -513,3 +513,27 @@ def test_lsh_held_records_in_several_rounds():
             sj.join_lsh(Pd, Qd, w.threshold, "ip", L=L, k=0, A=A, out=out[:1000])
         assert e.value.status == sj.SJ_E_OVERFLOW and e.value.n_out == exact.shape[0]
         assert bool((out[exact.shape[0]:] == -1).all())
+
+
+@pytest.mark.parametrize("k,quantile", [(4, 0.999), (0, 0.5)])
+def test_lsh_phase_times_are_measured(k, quantile):
+    """The times of all three phases are there after each call, whether the tiles'
+    matches fit their lists or go through held records, and whether the caller
+    brings the output or has it sized."""
+    import torch
+    import paper_2006_12608_amd as sj
+    w = case(97, 1500, 1300, 64, "i8", "ip", 0.0)
+    x, y = w.P.astype(np.int64), w.Q.astype(np.int64)
+    thr = float(np.quantile(x[:300] @ y.T, quantile, method="nearest"))
+    h = workloads.lsh_params(97, 2, k, w.d, 0)
+    A, B = lsh_device(h)
+    Pd, Qd = to_device(w.P, w.dtype), to_device(w.Q, w.dtype)
+    say("phase times", k, quantile)
+    ctx = sj.context(Pd.device.index)
+    got, _ = sj.join_lsh(Pd, Qd, thr, "ip", L=2, k=k, A=A, B=B)
+    out = torch.empty((got.shape[0] + 1, 2), dtype=torch.int32, device=Pd.device)
+    for o in (None, out, out):
+        again, _ = sj.join_lsh(Pd, Qd, thr, "ip", L=2, k=k, A=A, B=B, out=o)
+        s = sj.sj_get_stats(ctx)
+        assert again.shape[0] == got.shape[0]
+        assert s.ms_norms > 0 and s.ms_scan > 0 and s.ms_join > 0
