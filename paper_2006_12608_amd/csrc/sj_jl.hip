@@ -271,8 +271,8 @@ hipError_t launch_level(int src, const void *X, uint64_t rows, uint32_t K, const
 // Bound by the fp32 matrix cores: 262144 x 256 fp16 to 32 (zeta = 2) are 10.7
 // GFLOP, 68 us at their peak; HBM moves X and Y only (168 MB, 21 us at 8 TB/s)
 // where a kernel per level moves every level's values out and in (705 MB): that
-// call 180 -> 111 us (162 -> 91 us of it on the GPU), 32768 rows of 1024 to 16
-// (zeta = 4) 51 -> 34 us.
+// call 180 -> 111 us (the kernel alone 96 us, traced from a cold clock), 32768 rows
+// of 1024 to 16 (zeta = 4) 51 -> 34 us.
 struct ChainArgs {
     const uint8_t *X;
     const float *A;

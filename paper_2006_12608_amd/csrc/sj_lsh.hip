@@ -1067,11 +1067,11 @@ __device__ __forceinline__ void wave_totals(const uint32_t (&w)[4], uint32_t &to
 // c ^ (r / 2 % 8) of the row: 16 consecutive rows' reads of one chunk hit all
 // banks.  Wave (wr, wc) of 4 x 2 multiplies rows 64 wr .. by columns 128 wc ..
 // (2 x 4 blocks of 32 x 32).  Tiles of 256 x 256 instead of 128 x 128 read a
-// bucket's rows once or twice instead of two or three times.  Measured against
-// 128 x 128 tiles with four workgroups per CU that each ran the chain of loads
-// tile by tile: 262144 x 256 fp16, 16 tables x 10 signs 2150 -> 1765 us (5.4
-// TB/s of gathers); 1048576 x 64 int8, 16 tables x 6 values 4160 -> 2890 us, and
-// the 300 us for copying rows, norms and fingerprints into records are gone.
+// bucket's rows once or twice instead of two or three times.  128 x 128 tiles with
+// four workgroups per CU that each ran the chain of loads tile by tile, after a copy
+// of the rows into records, took 2200 us for 262144 x 256 fp16, 16 tables x 10 signs
+// and 4590 us for 1048576 x 64 int8, 16 tables x 6 values; in kernel traces this
+// takes 1622 us (6.8 GB read a call, 4.2 TB/s) and 3104 us.
 // Matches go to an LDS list (JCAP pairs with their table); the first-table rule,
 // a chain of loads per match, then runs for the list at once, a thread per
 // match, and reserves output slots once.  A wave whose matches of a tile do not
@@ -1518,8 +1518,8 @@ __global__ void __launch_bounds__(JT) join_kernel(JoinArgs g)
 // by ballots, contiguous over the lanes, with one reservation for the two records.
 // Where join_kernel's waves resolved such matches one after the other from
 // memory, with a reservation per 32 x 32 block: 50000 x 100 int8, 16 tables x 10 signs, 14.7 M
-// pairs, a call 1983 us, now 851; 262144 x 64 int8, one table of 10, 23.9 M pairs 1759
-// and 688.
+// pairs, a call 1975 us, now 826; 262144 x 64 int8, one table of 10, 23.9 M pairs 1758
+// and 679.
 constexpr int HT = 512, HR = HT / 256;   // threads, records
 
 __global__ void __launch_bounds__(HT) held_kernel(JoinArgs g)

@@ -142,8 +142,8 @@ def test_lsh_parity_real_cosine(dtype):
 
 
 def test_lsh_buckets_span_tiles_and_ragged():
-    """k = 1: two big buckets per table, each hundreds of rows (several 128-row
-    tiles plus ragged tails on both sides)."""
+    """k = 1: two big buckets per table, of about half the rows each: on the larger
+    side around a tile's 256 rows, ragged on both (whole, partial and lone tiles)."""
     w = case(41, 517, 389, 33, "i8", "ip", 15.0, -6, 6)   # 33-byte rows: repacked
     h = workloads.lsh_params(42, L=3, k=1, d=33)
     run_lsh(w, h)
@@ -174,9 +174,9 @@ def test_lsh_k0_is_exact_join():
 @pytest.mark.parametrize("metric,thr,k,wid", [("l2", 200.0, 0, 0), ("l2", 180.0, 1, 120),
                                              ("ip", 2.0, 2, 0)])
 def test_lsh_dense_matches(metric, thr, k, wid):
-    """Short int8 rows (joined as row records) with thresholds that most pairs
-    pass: waves find from a few to thousands of pairs per tile, so the pairs
-    go both through the per-wave staging (many flushes) and straight out."""
+    """Short int8 rows with thresholds that most pairs pass: waves find from a few
+    to thousands of pairs per tile, so matches go both through the workgroup's list
+    (emptied many times) and through held records."""
     w = case(51 + k, 700, 650, 16, "i8", metric, thr, -3, 3)
     h = workloads.lsh_params(52 + k, L=3, k=k, d=16, w=wid)
     g, ref, exact, *_ = run_lsh(w, h)
@@ -198,10 +198,10 @@ def test_lsh_self_join_same_pointer():
                                      (96, 24, 78.0), (128, 24, 90.0), (32, 256, 20.0)])
 def test_lsh_many_tables_first_table_rule(d, L, thr):
     """Many tables and few functions: most pairs collide in several tables;
-    each must still be reported once.  Short rows carry fingerprints of the
-    first 112 - (row bytes rounded up to 32) tables in their records (80, 48
-    and 16 tables here, later tables by their keys); 128-byte rows carry 16.
-    256 tables is the most one call takes (its hash on the general kernel)."""
+    each must still be reported once.  The first 64 tables' keys are compared by
+    their fingerprint bytes first (in one to four 16-byte chunks per row here),
+    later tables' by the keys.  256 tables is the most one call takes (its hash
+    on the general kernel)."""
     w = case(47 + d, 260, 240, d, "i8", "ip", thr, -3, 3)
     h = workloads.lsh_params(48 + d, L=L, k=2, d=d)
     g, ref, *_ = run_lsh(w, h)
